@@ -158,15 +158,23 @@ class LevelInfo:
     is_dense: bool
 
 
+_current_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream_ptr(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    """The hipStream_t of `stream`, or of torch's current stream.  The latter is asked for as a raw handle: the object
+    torch.cuda.current_stream() builds around it costs 2.5 us, as much as a kernel launch, and a small call needs little more."""
+    if stream is not None:
+        return int(stream.cuda_stream)
+    if not torch.cuda.is_initialized():
+        return int(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
-def _dev(t: torch.Tensor, dtype, shape, name: str) -> int:
+def _dev(t: torch.Tensor, dtype, shape: tuple, name: str) -> int:
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous()):
         raise HashGridError(f"{name} must be a contiguous device tensor")
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape):
+    if t.dtype != dtype or t.shape != shape:
         raise HashGridError(f"{name}: expected {dtype} {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
     return t.data_ptr()
 
@@ -187,6 +195,7 @@ class HashGrid:
         self.io_dtype = _TORCH[self.cfg.io_dtype]
         self.grad_dtype = _TORCH[self.cfg.grad_dtype]
         self.n_entries = int(self._lib.hashgrid_n_entries(self._h))
+        self._batch = (0, False, 0)  # the last batch size asked about: (B, bwd_ws_pays, bwd_workspace_bytes)
         self._ws = {}  # (device, stream) -> scratch buffer kept for calls that pass none
         self._counted = None  # (x pointer, B, workspace pointer, x version, stream) the workspace holds counts for
 
@@ -204,10 +213,10 @@ class HashGrid:
     def levels(self):
         return [self.level_info(l) for l in range(self.L)]
 
-    def _workspace(self, need: int, device, stream) -> torch.Tensor:
+    def _workspace(self, need: int, device, stream, stream_ptr: int) -> torch.Tensor:
         """The scratch buffer this object keeps for calls that pass none: one per (device, stream), because
         calls that overlap in time need separate buffers and calls on one stream never overlap."""
-        key = (device, _stream_ptr(stream))
+        key = (device, stream_ptr)
         ws = self._ws.get(key)
         if ws is None or ws.numel() < need:
             ws = torch.empty(need, dtype=torch.uint8, device=device)
@@ -216,8 +225,16 @@ class HashGrid:
             ws.record_stream(stream)  # allocated on torch's current stream, used on this one
         return ws
 
+    def _of_batch(self, B: int):
+        """(B, bwd_ws_pays, bwd_workspace_bytes): functions of the configuration and B alone, kept for the last B."""
+        known = self._batch
+        if known[0] != B:
+            known = self._batch = (B, bool(self._lib.hashgrid_bwd_ws_pays(self._h, B)),
+                                   int(self._lib.hashgrid_bwd_workspace_bytes(self._h, B)))
+        return known
+
     def bwd_ws_pays(self, B: int) -> bool:
-        return bool(self._lib.hashgrid_bwd_ws_pays(self._h, B))
+        return self._of_batch(B)[1]
 
     def encode_fwd(self, x: torch.Tensor, params: torch.Tensor, y: torch.Tensor | None = None, stream=None,
                    count_for_bwd=False, workspace: torch.Tensor | None = None):
@@ -225,31 +242,27 @@ class HashGrid:
         is served by it and the batch is large enough for the sorted backward pass to pay
         (count_for_bwd="always": whatever the batch): the next encode_bwd on the same, unmodified x and
         the same workspace then skips its counting pass."""
-        B = x.shape[0]
+        B, sp = x.shape[0], _stream_ptr(stream)
         if y is None:
             y = torch.empty((B, self.L * self.F), dtype=self.io_dtype, device=x.device)
         self._counted = None
-        want = bool(count_for_bwd) and B and (count_for_bwd == "always" or self.bwd_ws_pays(B))
-        need = self.bwd_workspace_bytes(B) if want else 0
-        if need:
-            ws = workspace if workspace is not None else self._workspace(need, x.device, stream)
-            st = self._lib.hashgrid_encode_fwd_ws(
-                self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
-                _dev(params, self.param_dtype, (self.n_entries, self.F), "params"),
-                _dev(y, self.io_dtype, (B, self.L * self.F), "y"), ws.data_ptr(), ws.numel() * ws.element_size(),
-                _stream_ptr(stream))
-            if st != HG_ERR_UNSUPPORTED:
-                _check(st, "hashgrid_encode_fwd_ws")
-                self._counted = (x.data_ptr(), B, ws.data_ptr(), x._version, _stream_ptr(stream))  # x unchanged since, as far as torch knows
-                return y
-        _check(self._lib.hashgrid_encode_fwd(
-            self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
-            _dev(params, self.param_dtype, (self.n_entries, self.F), "params"),
-            _dev(y, self.io_dtype, (B, self.L * self.F), "y"), _stream_ptr(stream)), "hashgrid_encode_fwd")
+        arrays = (self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
+                  _dev(params, self.param_dtype, (self.n_entries, self.F), "params"),
+                  _dev(y, self.io_dtype, (B, self.L * self.F), "y"))
+        if count_for_bwd and B and (count_for_bwd == "always" or self.bwd_ws_pays(B)):
+            need = self.bwd_workspace_bytes(B)
+            if need:
+                ws = workspace if workspace is not None else self._workspace(need, x.device, stream, sp)
+                st = self._lib.hashgrid_encode_fwd_ws(*arrays, ws.data_ptr(), ws.numel() * ws.element_size(), sp)
+                if st != HG_ERR_UNSUPPORTED:
+                    _check(st, "hashgrid_encode_fwd_ws")
+                    self._counted = (arrays[2], B, ws.data_ptr(), x._version, sp)  # x unchanged since, as far as torch knows
+                    return y
+        _check(self._lib.hashgrid_encode_fwd(*arrays, sp), "hashgrid_encode_fwd")
         return y
 
     def bwd_workspace_bytes(self, B: int) -> int:
-        return int(self._lib.hashgrid_bwd_workspace_bytes(self._h, B))
+        return self._of_batch(B)[2]
 
     def encode_bwd(self, x: torch.Tensor, dLdy: torch.Tensor, grad_params: torch.Tensor | None = None,
                    stream=None, workspace: torch.Tensor | None = None, use_workspace: bool | None = None,
@@ -259,7 +272,7 @@ class HashGrid:
         by it, False = the latter, None = whichever hashgrid_bwd_ws_pays expects to be faster.
         overwrite: grad_params becomes the gradient of this batch instead of growing by it
         (HG_BWD_OVERWRITE; where the atomic pass runs, the buffer is cleared on the stream first)."""
-        B = x.shape[0]
+        B, sp = x.shape[0], _stream_ptr(stream)
         fresh = grad_params is None
         if fresh:
             grad_params = torch.zeros((self.n_entries, self.F), dtype=self.grad_dtype, device=x.device)
@@ -267,29 +280,27 @@ class HashGrid:
             use_workspace = self._counted is not None or self.bwd_ws_pays(B)
         need = self.bwd_workspace_bytes(B) if use_workspace else 0
         counted, self._counted = self._counted, None  # the pass consumes the counts
+        arrays = (self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
+                  _dev(dLdy, self.io_dtype, (B, self.L * self.F), "dLdy"),
+                  _dev(grad_params, self.grad_dtype, (self.n_entries, self.F), "grad_params"))
         if need:
             if workspace is None:
-                workspace = self._workspace(need, x.device, stream)
+                workspace = self._workspace(need, x.device, stream, sp)
+            at = workspace.data_ptr()
             # the counts are only there for a call ordered after the forward: same stream
-            flags = HG_BWD_COUNTED if counted == (x.data_ptr(), B, workspace.data_ptr(), x._version, _stream_ptr(stream)) else 0
+            flags = HG_BWD_COUNTED if counted == (arrays[2], B, at, x._version, sp) else 0
             if overwrite and not fresh:
                 flags |= HG_BWD_OVERWRITE
-            _check(self._lib.hashgrid_encode_bwd_ws(
-                self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
-                _dev(dLdy, self.io_dtype, (B, self.L * self.F), "dLdy"),
-                _dev(grad_params, self.grad_dtype, (self.n_entries, self.F), "grad_params"),
-                workspace.data_ptr(), workspace.numel() * workspace.element_size(), flags, _stream_ptr(stream)),
-                "hashgrid_encode_bwd_ws")
+            _check(self._lib.hashgrid_encode_bwd_ws(*arrays, at, workspace.numel() * workspace.element_size(), flags, sp),
+                   "hashgrid_encode_bwd_ws")
             return grad_params
         if overwrite and not fresh:  # the atomic pass only adds: clear first, on the same stream
-            _dev(grad_params, self.grad_dtype, (self.n_entries, self.F), "grad_params")
-            with torch.cuda.stream(torch.cuda.current_stream() if stream is None else stream):
+            if stream is None:
                 grad_params.zero_()
-        _check(self._lib.hashgrid_encode_bwd(
-            self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
-            _dev(dLdy, self.io_dtype, (B, self.L * self.F), "dLdy"),
-            _dev(grad_params, self.grad_dtype, (self.n_entries, self.F), "grad_params"), _stream_ptr(stream)),
-            "hashgrid_encode_bwd")
+            else:
+                with torch.cuda.stream(stream):
+                    grad_params.zero_()
+        _check(self._lib.hashgrid_encode_bwd(*arrays, sp), "hashgrid_encode_bwd")
         return grad_params
 
     def encode_bwd_static(self, x: torch.Tensor, dLdy: torch.Tensor, grad_params: torch.Tensor, stream=None,
