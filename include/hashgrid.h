@@ -344,6 +344,53 @@ typedef enum { HG_LOSS_L2 = 0, HG_LOSS_MAPE = 1 } hg_loss;
 hg_status hashgrid_loss_grad(uint64_t n, const float* prediction, const float* target, uint32_t loss, float scale,
                              float* dLdout, double* loss_sum, void* stream);
 
+/* The backward pass of the network without the weight gradients (arguments, precision and errors as
+ * hashgrid_mlp_bwd): dL/dy alone, for gradients with respect to the position.
+ *   dLdout  [B, n_out]  fp32, device, read; NULL stands for all ones */
+hg_status hashgrid_mlp_bwd_input(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1,
+                                 const void* W2, const void* W3, const float* dLdout, void* dLdy, void* stream);
+
+/* What a model keeps between training iterations (device pointers; the arrays tables_zeros and
+ * weights_zeros are all zero before a step, and again after it). */
+#define HG_TRAIN_LOSS_SUMS 513u
+typedef struct {
+  uint32_t n_out;      /* network outputs, 1..32 */
+  uint32_t loss;       /* hg_loss */
+  float loss_scale;    /* dL/dout is the gradient of the summed loss times this factor */
+  hashgrid_adam_config tables_adam;  /* l2_reg must be 0 */
+  hashgrid_adam_config weights_adam; /* l2_reg stands beside the gradient of the summed, scaled loss: a factor
+                                      * that stands beside the mean loss times loss_scale * B * n_out */
+  float* tables;       /* [n_entries, F] fp32 master copy, 16-byte aligned (as the next four) */
+  void* tables_half;   /* [n_entries, F] fp16 working copy */
+  float* tables_m;     /* [n_entries, F] fp32 moments */
+  float* tables_v;
+  float* tables_zeros; /* [n_entries, F] fp32 */
+  float* weights;      /* W1 [64, L*F], W2 [64, 64], W3 [n_out, 64] one after the other, fp32 */
+  void* weights_half;  /* the same, fp16, 8-byte aligned */
+  float* weights_m;
+  float* weights_v;
+  float* weights_zeros;
+  double* loss_sums;   /* [HG_TRAIN_LOSS_SUMS]; [0] = sum of the unscaled loss values of the step's B * n_out
+                        * scalars, before its update; the rest is scratch */
+} hashgrid_train_state;
+
+/* One training iteration (paper Section 4): encoding, network, loss, backward through both, Adam on
+ * tables and weights.  The results are those of hashgrid_encode_mlp_fwd_train, hashgrid_loss_grad,
+ * hashgrid_mlp_bwd, hashgrid_encode_bwd[_ws] and hashgrid_adam_step (twice) in a row, with the same
+ * roundings and the same skip of scalars whose gradient is exactly 0; the table gradient is handed to
+ * the optimiser where it is summed and is not stored.
+ *   target     [B, n_out] fp32, device, read
+ *   y, dLdy    [B, L*F]   fp16, device, 16-byte aligned, scratch that holds the encoded features and their
+ *                         gradient on return
+ *   workspace  as for hashgrid_encode_bwd_ws, or NULL (then, and where hashgrid_bwd_ws_pays says no, the
+ *              gradient is summed with atomic additions into tables_zeros)
+ *   step       1-based, the same for tables and weights
+ * HG_ERR_UNSUPPORTED as hashgrid_encode_mlp_fwd, and unless io_dtype is HG_F16 and grad_dtype HG_F32.
+ * B == 0 is HG_OK and changes nothing. */
+hg_status hashgrid_train_step(const hashgrid_t* hg, const hashgrid_train_state* st, uint32_t B, const float* x,
+                              const float* target, void* y, void* dLdy, void* workspace, uint64_t workspace_bytes,
+                              uint32_t step, void* stream);
+
 /* Static, NUL-terminated description of a status code. */
 const char* hashgrid_strerror(hg_status s);
 

@@ -24,6 +24,7 @@ HG_BWD_OVERWRITE = 2
 HG_ERR_UNSUPPORTED = 2
 HG_STATIC_SCRATCH_BYTES = 64 << 20
 HG_LOSS_L2, HG_LOSS_MAPE = 0, 1
+HG_TRAIN_LOSS_SUMS = 513
 _LOSSES = {"l2": HG_LOSS_L2, "mape": HG_LOSS_MAPE, HG_LOSS_L2: HG_LOSS_L2, HG_LOSS_MAPE: HG_LOSS_MAPE}
 
 _DTYPES = {"f32": HG_F32, "f16": HG_F16, torch.float32: HG_F32, torch.float16: HG_F16}
@@ -34,7 +35,8 @@ EXPORTS = ("hashgrid_create", "hashgrid_destroy", "hashgrid_n_entries", "hashgri
            "hashgrid_debug_indices", "hashgrid_debug_count_outside", "hashgrid_strerror", "hashgrid_bwd_workspace_bytes",
            "hashgrid_encode_bwd_ws", "hashgrid_encode_fwd_ws", "hashgrid_bwd_ws_pays", "hashgrid_adam_step",
            "hashgrid_encode_mlp_fwd", "hashgrid_encode_bwd_static", "hashgrid_encode_mlp_fwd_train", "hashgrid_mlp_bwd",
-           "hashgrid_adam_step_half_grad", "hashgrid_loss_grad", "hashgrid_mlp_fwd")
+           "hashgrid_adam_step_half_grad", "hashgrid_loss_grad", "hashgrid_mlp_fwd",
+           "hashgrid_mlp_bwd_input", "hashgrid_train_step")
 PROBE_EXPORTS = ("hashgrid_probe_copy", "hashgrid_probe_gather", "hashgrid_probe_atomic_add",
                  "hashgrid_probe_gather_lines")
 
@@ -50,6 +52,14 @@ class hashgrid_config(ctypes.Structure):
 
 class hashgrid_adam_config(ctypes.Structure):
     _fields_ = [(n, ctypes.c_float) for n in ("lr", "beta1", "beta2", "eps", "l2_reg")]
+
+
+class hashgrid_train_state(ctypes.Structure):
+    _fields_ = [("n_out", ctypes.c_uint32), ("loss", ctypes.c_uint32), ("loss_scale", ctypes.c_float),
+                ("tables_adam", hashgrid_adam_config), ("weights_adam", hashgrid_adam_config)] + \
+               [(n, ctypes.c_void_p) for n in
+                ("tables", "tables_half", "tables_m", "tables_v", "tables_zeros", "weights", "weights_half", "weights_m",
+                 "weights_v", "weights_zeros", "loss_sums")]
 
 
 _lib = None
@@ -110,6 +120,10 @@ def load_library() -> ctypes.CDLL:
     lib.hashgrid_adam_step_half_grad.restype = ctypes.c_int
     lib.hashgrid_loss_grad.argtypes = [u64, vp, vp, u32, ctypes.c_float, vp, vp, vp]
     lib.hashgrid_loss_grad.restype = ctypes.c_int
+    lib.hashgrid_mlp_bwd_input.argtypes = [u32, u32, u32, vp, vp, vp, vp, vp, vp, vp]
+    lib.hashgrid_mlp_bwd_input.restype = ctypes.c_int
+    lib.hashgrid_train_step.argtypes = [vp, ctypes.POINTER(hashgrid_train_state), u32, vp, vp, vp, vp, vp, u64, u32, vp]
+    lib.hashgrid_train_step.restype = ctypes.c_int
     lib.hashgrid_strerror.argtypes = [ctypes.c_int]
     lib.hashgrid_strerror.restype = ctypes.c_char_p
     _lib = lib
@@ -347,6 +361,20 @@ class HashGrid:
                 "hashgrid_encode_mlp_fwd_train")
         return out
 
+    def train_step(self, state: hashgrid_train_state, x: torch.Tensor, target: torch.Tensor, y: torch.Tensor,
+                   dLdy: torch.Tensor, step: int, stream=None) -> None:
+        """hashgrid_train_step; the scratch of the sorted backward pass is one kept on this object.  The pointers in
+        `state` are the caller's to check (HashGridModel does)."""
+        B, sp = x.shape[0], _stream_ptr(stream)
+        arrays = (_dev(x, torch.float32, (B, self.d), "x"), _dev(target, torch.float32, (B, state.n_out), "target"),
+                  _dev(y, torch.float16, (B, self.L * self.F), "y"), _dev(dLdy, torch.float16, (B, self.L * self.F), "dLdy"))
+        self._counted = None
+        _, pays, need = self._of_batch(B)
+        ws = self._workspace(need, x.device, stream, sp) if pays and need else None
+        _check(self._lib.hashgrid_train_step(self._h, ctypes.byref(state), B, *arrays,
+                                             None if ws is None else ws.data_ptr(), 0 if ws is None else ws.numel(), step, sp),
+               "hashgrid_train_step")
+
     def debug_count_outside(self, x: torch.Tensor, stream=None) -> int:
         """hashgrid_debug_count_outside: coordinates of x that are not in [0,1) (synchronises)."""
         B = x.shape[0]
@@ -484,3 +512,15 @@ def mlp_bwd(y: torch.Tensor, W1: torch.Tensor, W2: torch.Tensor, W3: torch.Tenso
         _dev(dLdout, torch.float32, (B, n_out), "dLdout"), _dev(dLdy, torch.float16, (B, n_in), "dLdy"),
         _dev(dW1, torch.float32, (64, n_in), "dW1"), _dev(dW2, torch.float32, (64, 64), "dW2"),
         _dev(dW3, torch.float32, (n_out, 64), "dW3"), _stream_ptr(stream)), "hashgrid_mlp_bwd")
+
+
+def mlp_bwd_input(y: torch.Tensor, W1: torch.Tensor, W2: torch.Tensor, W3: torch.Tensor, dLdout: torch.Tensor | None,
+                  dLdy: torch.Tensor, stream=None) -> None:
+    """hashgrid_mlp_bwd_input: mlp_bwd without the weight gradients; dLdout None: all ones."""
+    B, n_in = y.shape
+    n_out = W3.shape[0]
+    _check(load_library().hashgrid_mlp_bwd_input(
+        B, n_in, n_out, _dev(y, torch.float16, (B, n_in), "y"), _dev(W1, torch.float16, (64, n_in), "W1"),
+        _dev(W2, torch.float16, (64, 64), "W2"), _dev(W3, torch.float16, (n_out, 64), "W3"),
+        None if dLdout is None else _dev(dLdout, torch.float32, (B, n_out), "dLdout"),
+        _dev(dLdy, torch.float16, (B, n_in), "dLdy"), _stream_ptr(stream)), "hashgrid_mlp_bwd_input")

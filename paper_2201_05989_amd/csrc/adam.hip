@@ -14,21 +14,27 @@
 #include <stdint.h>
 
 #include "hashgrid.h"
+#include "adam_device.hpp"
 
 namespace hg {
 
 constexpr int kAdamThreads = 256;
 
-struct AdamArgs {
-  float lr, beta1, beta2, eps, l2;
-  float inv_c1;       // 1 / (1 - beta1^t)
-  float inv_sqrt_c2;  // 1 / sqrt(1 - beta2^t)
-};
+bool adam_config_ok(const hashgrid_adam_config& c) {
+  return c.beta1 >= 0.0f && c.beta1 < 1.0f && c.beta2 >= 0.0f && c.beta2 < 1.0f && c.eps >= 0.0f && c.l2_reg >= 0.0f &&
+         c.l2_reg < INFINITY;
+}
 
-__device__ __forceinline__ void adam_scalar(const AdamArgs& a, float g, float& m, float& v, float& p) {
-  m = a.beta1 * m + (1.0f - a.beta1) * g;
-  v = a.beta2 * v + (1.0f - a.beta2) * g * g;
-  p -= a.lr * (m * a.inv_c1) / (sqrtf(v) * a.inv_sqrt_c2 + a.eps);
+AdamArgs adam_args(const hashgrid_adam_config& c, const uint32_t step) {
+  AdamArgs a;
+  a.lr = c.lr;
+  a.beta1 = c.beta1;
+  a.beta2 = c.beta2;
+  a.eps = c.eps;
+  a.l2 = c.l2_reg;
+  a.inv_c1 = (float)(1.0 / (1.0 - pow((double)c.beta1, (double)step)));
+  a.inv_sqrt_c2 = (float)(1.0 / sqrt(1.0 - pow((double)c.beta2, (double)step)));
+  return a;
 }
 
 // Four gradient scalars of either type as floats, times grad_scale for the half-precision ones (what
@@ -116,23 +122,14 @@ hg_status adam_launch(uint64_t n_scalars, float* params_master, void* params_hal
   if (!cfg || step == 0) return HG_ERR_INVALID_ARG;
   if (n_scalars == 0) return HG_OK;
   if (!params_master || !grad || !m || !v) return HG_ERR_INVALID_ARG;
-  if (!(cfg->beta1 >= 0.0f && cfg->beta1 < 1.0f && cfg->beta2 >= 0.0f && cfg->beta2 < 1.0f && cfg->eps >= 0.0f &&
-        cfg->l2_reg >= 0.0f && cfg->l2_reg < INFINITY))
-    return HG_ERR_INVALID_ARG;
+  if (!hg::adam_config_ok(*cfg)) return HG_ERR_INVALID_ARG;
   if (!(grad_scale > 0.0f && grad_scale < INFINITY)) return HG_ERR_INVALID_ARG;
   const uintptr_t bits = reinterpret_cast<uintptr_t>(params_master) | reinterpret_cast<uintptr_t>(m) |
                          reinterpret_cast<uintptr_t>(v);
   if ((bits & 15) || (reinterpret_cast<uintptr_t>(params_half) & 7) ||
       (reinterpret_cast<uintptr_t>(grad) & (4 * sizeof(GT) - 1)))
     return HG_ERR_INVALID_ARG;
-  hg::AdamArgs a;
-  a.lr = cfg->lr;
-  a.beta1 = cfg->beta1;
-  a.beta2 = cfg->beta2;
-  a.eps = cfg->eps;
-  a.l2 = cfg->l2_reg;
-  a.inv_c1 = (float)(1.0 / (1.0 - pow((double)cfg->beta1, (double)step)));
-  a.inv_sqrt_c2 = (float)(1.0 / sqrt(1.0 - pow((double)cfg->beta2, (double)step)));
+  const hg::AdamArgs a = hg::adam_args(*cfg, step);
   const uint64_t groups = (n_scalars / 4 + hg::kAdamThreads - 1) / hg::kAdamThreads;
   const uint32_t blocks = (uint32_t)(groups < 1 ? 1 : (groups > 65536 ? 65536 : groups));
   hipStream_t s = static_cast<hipStream_t>(stream);

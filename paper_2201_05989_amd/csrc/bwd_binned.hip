@@ -53,6 +53,7 @@
 #include "hashgrid.h"
 #include "hashgrid_common.hpp"
 #include "hashgrid_internal.hpp"
+#include "adam_device.hpp"
 #include "bwd_bins.hpp"
 #include "bwd_record.hpp"
 
@@ -86,6 +87,7 @@ struct Workspace {
   uint32_t* bin_total;  // [n_bins] records in the bin
   float* tile_max;      // [n_tiles * parts of the scatter grid (at most L)] largest |dL/dy| seen by each scatter workgroup
   uint32_t* item_counter;  // [1] next work item of the accumulate pass
+  uint32_t* chunk_done;    // [n_bins] workgroups that have added their share of a chunk (accumulate pass with the optimiser)
   uint32_t* records;    // [B * L * rec_per_point] records (Record::kWords words each)
   uint32_t n_tiles;
   uint32_t n_bins;
@@ -108,7 +110,7 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     return o;
   };
   const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_start = take((uint64_t)nb * 4),
-                 o_total = take((uint64_t)nb * 4), o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4),
+                 o_total = take((uint64_t)nb * 4), o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4), o_done = take((uint64_t)nb * 4),
                  o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point *
                               (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u));
   if (ws) {
@@ -117,6 +119,7 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     ws->bin_total = reinterpret_cast<uint32_t*>(base + o_total);
     ws->tile_max = reinterpret_cast<float*>(base + o_max);
     ws->item_counter = reinterpret_cast<uint32_t*>(base + o_item);
+    ws->chunk_done = reinterpret_cast<uint32_t*>(base + o_done);
     ws->records = reinterpret_cast<uint32_t*>(base + o_rec);
     ws->n_tiles = nt;
     ws->n_bins = nb;
@@ -360,15 +363,21 @@ constexpr int kScanBins = 32;  // 128-byte rows of the count table per load (16,
 __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles, const uint32_t n_bins,
                                                          uint32_t* __restrict__ counts,
                                                          uint32_t* __restrict__ bin_total,
-                                                         uint32_t* __restrict__ item_counter, const LevelTable lv,
+                                                         uint32_t* __restrict__ item_counter,
+                                                         uint32_t* __restrict__ chunk_done, const LevelTable lv,
                                                          const uint32_t zero_mask, const uint32_t F,
-                                                         void* __restrict__ grad, const bool g16) {
+                                                         void* __restrict__ grad, const bool g16, const SideJob job) {
   __shared__ uint32_t seg_sum[kScanThreads];
+  const uint32_t scan_wgs = gridDim.x - job.blocks;
+  if (blockIdx.x >= scan_wgs) {  // uniform
+    run_side_job(job, blockIdx.x - scan_wgs);
+    return;
+  }
   if (blockIdx.x == 0 && threadIdx.x == 0) item_counter[0] = 0;  // the accumulate pass draws its work items from here
   for (uint32_t l = 0; zero_mask >> l; ++l) {  // uniform
     if (!((zero_mask >> l) & 1u)) continue;
     const uint64_t first = lv.offset[l] * F, n = (uint64_t)lv.size[l] * F;
-    for (uint64_t i = (uint64_t)blockIdx.x * kScanThreads + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kScanThreads) {
+    for (uint64_t i = (uint64_t)blockIdx.x * kScanThreads + threadIdx.x; i < n; i += (uint64_t)scan_wgs * kScanThreads) {
       if (g16) static_cast<_Float16*>(grad)[first + i] = (_Float16)0.0f;
       else static_cast<float*>(grad)[first + i] = 0.0f;
     }
@@ -405,6 +414,7 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
     }
     if (seg == 0) {
       bin_total[gb] = total;
+      chunk_done[gb] = 0;
       col[(uint64_t)n_tiles * n_bins] = total;  // closes the prefix: count of tile t = row t+1 - row t
     }
     uint32_t run = pre;
@@ -742,7 +752,22 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
 // lanes that have just read them.
 // GT: type of the gradient scalars (float, or _Float16: the sums are still exact fixed point and are
 // rounded to half precision once, where they are added to the gradient).
-template <typename IT, int F, bool SMOOTH, typename GT = float>
+//
+// ADAM: a training step has no use for the gradient itself, only for what the optimiser makes of it.  The owner of a
+// chunk then takes its sums straight to Adam on the chunk's entries, instead of writing them for a pass of
+// their own to read back with everything else (the step's largest streams are the two moments and the master copy:
+// 34 bytes a scalar, against 8 for the gradient's round trip), and those streams run beside the
+// LDS work of this kernel.  `grad` is then an array that is zero before and after: the workgroups that share a chunk add their
+// sums into it, and the last one to arrive (chunk_done) takes them out again and applies them, as does the owner of
+// a chunk with what the straddling pairs left there.
+struct NoAdam {};
+struct AdamOut {
+  AdamArgs a;
+  AdamState st;
+  uint32_t* chunk_done;
+  uint32_t cross_mask;  // levels whose straddling pairs were added to grad by the scatter pass
+};
+template <typename IT, int F, bool SMOOTH, typename GT = float, bool ADAM = false>
 __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable lv, const BinPlan bp,
                                                               const uint32_t B, const uint32_t n_items,
                                                               const uint32_t* __restrict__ bin_start,
@@ -751,7 +776,8 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
                                                               const uint32_t n_max,
                                                               const uint32_t* __restrict__ records,
                                                               uint32_t* __restrict__ item_counter,
-                                                              GT* __restrict__ grad, const uint32_t overwrite_mask) {
+                                                              GT* __restrict__ grad, const uint32_t overwrite_mask,
+                                                              const typename std::conditional<ADAM, AdamOut, NoAdam>::type ad) {
   // bit l of overwrite_mask: the owner of a chunk of level l stores its sums (HG_BWD_OVERWRITE, one
   // slice per chunk, no pairs that straddle chunks) instead of adding them to what is there
   __shared__ uint32_t s_ticket;
@@ -782,6 +808,21 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   struct alignas(F * sizeof(GT) > 16 ? 16 : F * sizeof(GT)) Entry {
     GT v[F];
   };
+  // ADAM: one entry of the chunk that starts at entry `first` of the tables, gradient g (not all zero)
+  [[maybe_unused]] auto update_entry = [&](const uint64_t at, const Entry& g, Entry p, Entry m1, Entry m2) {
+    if constexpr (ADAM) {
+      Vec<_Float16, F> h;
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        if (g.v[f] != 0.0f) adam_scalar(ad.a, g.v[f], m1.v[f], m2.v[f], p.v[f]);
+        h.v[f] = (_Float16)p.v[f];
+      }
+      reinterpret_cast<Entry*>(ad.st.m)[at] = m1;
+      reinterpret_cast<Entry*>(ad.st.v)[at] = m2;
+      reinterpret_cast<Entry*>(ad.st.p32)[at] = p;
+      reinterpret_cast<Vec<_Float16, F>*>(ad.st.p16)[at] = h;
+    }
+  };
 
   // item_counter starts at 0 (bin_scan clears it); a ticket is the item it stands for
   auto draw = [&]() {
@@ -806,8 +847,10 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   // gradient chunk, both requested while the previous item is still being flushed.
   struct Item {
     uint32_t l, n_sl, r0, r1, n_e;
+    uint32_t bin, live_slices;  // chunk of the level, and how many of its n_sl slices have records
     GT* gl;
     bool live, dense;
+    bool orphan;  // ADAM: no records, but straddling pairs may have added to the chunk in grad
   };
   using Rec = Record<IT, F>;
   using Stored = typename Rec::Stored;
@@ -820,7 +863,13 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     Item it;
     it.l = l;
     it.n_sl = bp.slices[l];
+    it.bin = bin;
     const uint32_t per = (total + it.n_sl - 1) / it.n_sl;
+    it.orphan = false;
+    if constexpr (ADAM) {
+      it.live_slices = per ? (total + per - 1) / per : 1u;
+      it.orphan = item < n_items && total == 0 && slice == 0 && ((ad.cross_mask >> l) & 1u);
+    }
     it.r0 = start + slice * per;
     it.r1 = (slice * per + per < total) ? it.r0 + per : start + total;
     // true for counts that belong to these points; keeps a caller who passed HG_BWD_COUNTED over
@@ -854,7 +903,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   };
   auto overwrites = [&](const Item& it) { return ((overwrite_mask >> it.l) & 1u) != 0; };  // uniform
   auto request_chunk = [&](const Item& it, Entry (&cur)[kPer]) {
-    if (!kChunkAhead || !it.live || !finite || overwrites(it)) return;
+    if (ADAM || !kChunkAhead || !it.live || !finite || overwrites(it)) return;
     if (it.n_sl == 1) {
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
@@ -887,7 +936,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
       total_n = bin_total[bp.bin_base[l_n] + bin_n];
     }
     Item it_n;
-    it_n.live = false;
+    it_n.live = it_n.orphan = false;
     Entry cur_n[kPer];
     // HG_BWD_OVERWRITE: a chunk that gets no sums stored below is cleared by its owner
     auto clear_chunk = [&](const Item& c) {
@@ -960,6 +1009,23 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
       request_records(it_n, pre, kHalf, kPre);
       request_chunk(it_n, cur_n);
     }
+    // ADAM: the chunk's master values and moments, requested before the barrier that ends the summation.  Where the
+    // chunk's records are few most entries get none, and only those that do are read (and below, written).
+    const uint64_t at0 = ADAM ? (uint64_t)(it.gl - grad) / F : 0;
+    const bool whole = ADAM && kChunkAhead && it.live && finite && it.n_sl == 1 && (it.r1 - it.r0) * 4 >= it.n_e;  // uniform
+    [[maybe_unused]] Entry pp[kPer], m1[kPer], m2[kPer];
+    if constexpr (ADAM) {
+      if (whole) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+          const uint32_t e = threadIdx.x + j * kAccThreads;
+          if (e >= it.n_e) continue;
+          pp[j] = reinterpret_cast<const Entry*>(ad.st.p32)[at0 + e];
+          m1[j] = reinterpret_cast<const Entry*>(ad.st.m)[at0 + e];
+          m2[j] = reinterpret_cast<const Entry*>(ad.st.v)[at0 + e];
+        }
+      }
+    }
     if (threadIdx.x == 0) s_ticket = ticket;
     __syncthreads();
     const uint32_t after_next = s_ticket;  // written before the barrier above, rewritten only after the one below
@@ -975,6 +1041,32 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
             acc[f * cap + e] = 0ull;  // ready for the next item
           }
           if (e >= it.n_e) continue;
+          if constexpr (ADAM) {
+            Entry g;
+            bool any = false;
+            Entry extra;  // what the straddling pairs of this level added for this entry
+            const bool cross = (ad.cross_mask >> it.l) & 1u;  // uniform
+            if (cross) extra = reinterpret_cast<const Entry*>(it.gl)[e];
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+              g.v[f] = a[f] ? (float)((double)a[f] * inv_scale) : 0.0f;
+              if (cross) g.v[f] += extra.v[f];
+              any = any || g.v[f] != 0.0f;
+            }
+            if (cross) {
+              bool put = false;
+#pragma unroll
+              for (int f = 0; f < F; ++f) put = put || extra.v[f] != 0.0f;
+              if (put) reinterpret_cast<Entry*>(it.gl)[e] = Entry{};
+            }
+            if (!any) continue;
+            const uint64_t at = at0 + e;
+            if (whole) update_entry(at, g, pp[j], m1[j], m2[j]);
+            else
+              update_entry(at, g, reinterpret_cast<const Entry*>(ad.st.p32)[at], reinterpret_cast<const Entry*>(ad.st.m)[at],
+                           reinterpret_cast<const Entry*>(ad.st.v)[at]);
+            continue;
+          }
           if (overwrites(it)) {
             // what adding to a cleared entry would leave
 #pragma unroll
@@ -1022,6 +1114,37 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
           const long long a = (long long)*slot;
           *slot = 0ull;
           if (e < it.n_e && a != 0) grad_atomic_add(it.gl, q, (float)((double)a * inv_scale));
+        }
+      }
+    }
+    if constexpr (ADAM) {
+      if ((it.live && (it.n_sl > 1 || !finite)) || it.orphan) {  // uniform: the sums of this chunk meet in grad
+        __shared__ uint32_t s_last;
+        // This workgroup's additions are performed before it is counted: every wave waits for its own.  They, the
+        // counter and the exchanges below are all device-scope atomics, which meet behind the caches, so
+        // nothing else has to be ordered; a device-scope fence would write this XCD's L2 back once per item (the
+        // pass took 502 us with it, 2^18 points at Table 1's sizes).
+        __builtin_amdgcn_s_waitcnt(0);
+        asm volatile("" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0)
+          s_last = __hip_atomic_fetch_add(&ad.chunk_done[bp.bin_base[it.l] + it.bin], 1u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT) + 1u == it.live_slices;
+        __syncthreads();
+        if (s_last) {  // every other workgroup with records of this chunk has been counted
+          for (uint32_t e = threadIdx.x; e < it.n_e; e += kAccThreads) {
+            Entry g;
+            bool any = false;
+#pragma unroll
+            for (int f = 0; f < F; ++f) {  // taken out where the additions were performed, not from a cache
+              g.v[f] = __hip_atomic_exchange(it.gl + (uint64_t)e * F + f, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              any = any || g.v[f] != 0.0f;
+            }
+            const uint64_t at = at0 + e;
+            if (any)
+              update_entry(at, g, reinterpret_cast<const Entry*>(ad.st.p32)[at], reinterpret_cast<const Entry*>(ad.st.m)[at],
+                           reinterpret_cast<const Entry*>(ad.st.v)[at]);
+          }
         }
       }
     }
@@ -1077,9 +1200,17 @@ static hg_status launch_count(const hashgrid* h, uint32_t B, const float* x, con
   return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;
 }
 
+// The optimiser's part of a sorted backward pass (launch_binned_adam)
+struct BinnedAdam {
+  AdamArgs a;
+  AdamState st;
+  SideJob job;
+};
+
 template <int D, typename IT, int F, bool CORNERS>
 static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, const void* dy, void* grad,
-                               const Workspace& ws, const bool counted, const bool overwrite, hipStream_t s) {
+                               const Workspace& ws, const bool counted, const bool overwrite, hipStream_t s,
+                               const BinnedAdam* ba = nullptr) {
   const bool g16 = h->cfg.grad_dtype == HG_F16;
   using Rec = Record<IT, F>;
   constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
@@ -1103,6 +1234,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   // (eight 40-byte records per point do not fit the 160 KiB of a workgroup: such plans scatter unstaged)
   constexpr bool kStaged = kScatterLdsMax <= 160 * 1024;
   constexpr size_t kAccLds = (size_t)F * 8 << chunk_log2_of(F);
+  constexpr bool kAdam = !CORNERS && std::is_same<IT, _Float16>::value;  // what launch_binned_adam serves
   // more dynamic LDS than the default limit of 64 KiB: opt in once per kernel
   static const hipError_t lds_ok = [] {
     hipError_t e = hipSuccess;
@@ -1126,6 +1258,14 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     if (e == hipSuccess && kAccLds > 48 * 1024)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
+    if constexpr (kAdam) {
+      if (e == hipSuccess && kAccLds > 48 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, float, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
+      if (e == hipSuccess && kAccLds > 48 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, float, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
+    }
     return e;
   }();
   if (lds_ok != hipSuccess) return HG_ERR_DEVICE;
@@ -1145,8 +1285,10 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const uint32_t all_levels = L == 32 ? 0xffffffffu : (1u << L) - 1u;
   const uint32_t zero_mask = overwrite ? add_mask : 0u, overwrite_mask = overwrite ? all_levels & ~add_mask : 0u;
   const bool defer_cross = overwrite && cross_mask != 0;  // those atomic adds then follow the accumulate pass
-  hipLaunchKernelGGL(bin_scan, dim3((ws.n_bins + kScanBins - 1) / kScanBins), dim3(kScanThreads), 0, s, ws.n_tiles,
-                     ws.n_bins, ws.counts, ws.bin_total, ws.item_counter, h->lv, zero_mask, (uint32_t)F, grad, g16);
+  const SideJob job = ba ? ba->job : SideJob{};
+  hipLaunchKernelGGL(bin_scan, dim3((ws.n_bins + kScanBins - 1) / kScanBins + job.blocks), dim3(kScanThreads), 0, s,
+                     ws.n_tiles, ws.n_bins, ws.counts, ws.bin_total, ws.item_counter, ws.chunk_done, h->lv, zero_mask,
+                     (uint32_t)F, grad, g16, job);
   auto scatter = [&](auto cross) {
     constexpr bool kCross = decltype(cross)::value;
     constexpr int DS = kCross ? DP : D;  // (the straddling pairs exist with pair records only)
@@ -1179,8 +1321,25 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     using GT = typename std::remove_pointer<decltype(g)>::type;
     hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT>), acc_grid, dim3(kAccThreads), kAccLds, s,
                        h->lv, bp, B, n_items, ws.bin_start, ws.bin_total, ws.tile_max, ws.n_tiles * parts, ws.records,
-                       ws.item_counter, g, overwrite_mask);
+                       ws.item_counter, g, overwrite_mask, NoAdam{});
   };
+  if constexpr (kAdam) {
+    if (ba) {
+      AdamOut out;
+      out.a = ba->a;
+      out.st = ba->st;
+      out.chunk_done = ws.chunk_done;
+      out.cross_mask = cross_mask;
+      auto accumulate_adam = [&](auto smooth_t) {
+        hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, float, true>), acc_grid, dim3(kAccThreads),
+                           kAccLds, s, h->lv, bp, B, n_items, ws.bin_start, ws.bin_total, ws.tile_max, ws.n_tiles * parts,
+                           ws.records, ws.item_counter, static_cast<float*>(grad), 0u, out);
+      };
+      if (smooth) accumulate_adam(std::true_type{});
+      else accumulate_adam(std::false_type{});
+      return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;
+    }
+  }
   if (g16) {
     if (smooth) accumulate(std::true_type{}, static_cast<_Float16*>(grad));
     else accumulate(std::false_type{}, static_cast<_Float16*>(grad));
@@ -1204,6 +1363,30 @@ static hg_status launch_binned_f(const hashgrid* h, uint32_t B, const float* x, 
     case 8: return launch_binned<D, IT, 8, CORNERS>(h, B, x, dy, grad, ws, counted, overwrite, s);
     default: return HG_ERR_UNSUPPORTED;
   }
+}
+
+hg_status launch_binned_adam(const hashgrid* h, uint32_t B, const float* x, const void* dy, float* zeros, void* workspace,
+                             bool counted, const AdamArgs& a, const AdamState& st, const SideJob& job, hipStream_t s) {
+  if (h->bp.corner_records || h->cfg.io_dtype != HG_F16 || h->cfg.grad_dtype != HG_F32) return HG_ERR_UNSUPPORTED;
+  Workspace ws;
+  carve(h, B, static_cast<uint8_t*>(workspace), &ws);
+  BinnedAdam ba;
+  ba.a = a;
+  ba.st = st;
+  ba.job = job;
+#define HG_BA(D, F) launch_binned<D, _Float16, F, false>(h, B, x, dy, zeros, ws, counted, false, s, &ba)
+  switch (h->cfg.d * 16 + h->cfg.F) {
+    case 2 * 16 + 1: return HG_BA(2, 1);
+    case 2 * 16 + 2: return HG_BA(2, 2);
+    case 2 * 16 + 4: return HG_BA(2, 4);
+    case 2 * 16 + 8: return HG_BA(2, 8);
+    case 3 * 16 + 1: return HG_BA(3, 1);
+    case 3 * 16 + 2: return HG_BA(3, 2);
+    case 3 * 16 + 4: return HG_BA(3, 4);
+    case 3 * 16 + 8: return HG_BA(3, 8);
+    default: return HG_ERR_UNSUPPORTED;
+  }
+#undef HG_BA
 }
 
 template <typename IT>

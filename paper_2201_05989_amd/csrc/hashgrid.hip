@@ -15,6 +15,7 @@
 #include "hashgrid.h"
 #include "hashgrid_common.hpp"
 #include "hashgrid_internal.hpp"
+#include "adam_device.hpp"
 #include "bwd_bins.hpp"
 
 namespace hg {
@@ -122,7 +123,7 @@ constexpr int kPmBlock = 1024;
 // in 293 as long as 2^19.  The batch is therefore spread evenly: k = number of rounds the batch
 // needs at full size, then B / (k * CUs) points per workgroup, rounded up to whole waves.  (The
 // counting variant always runs full workgroups: they cover whole tiles of the backward pass.)
-static uint32_t cu_count() {
+uint32_t cu_count() {
   static const uint32_t cus = [] {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -463,6 +464,56 @@ __global__ __launch_bounds__(kBlock) void bwd_general_half(const LevelTable lv, 
   }
 }
 
+// The optimiser's step on what a small batch touched (its gradient, summed by bwd_general into an array of zeros):
+// the lanes visit the batch's corners as bwd_general does and take every gradient scalar out of the array with an
+// exchange for zero, so exactly one of the lanes that reach a scalar holds its gradient and applies it, and the
+// array is zero again.  The streaming pass reads the gradient of every entry to find them: 46 MB at Table 1's sizes,
+// half a gigabyte at T = 2^22, where 2^10 points touch 1 MB.
+// The first look is a plain load: the additions were performed by an earlier kernel, so a zero seen here is one that
+// another lane has taken already (or no gradient at all), and most lanes that come second need no atomic.
+template <int D, int F>
+__global__ __launch_bounds__(kBlock) void adam_touched(const LevelTable lv, const bool smooth, const uint32_t B,
+                                                       const float* __restrict__ x, float* grad, const AdamArgs a,
+                                                       const AdamState st, const SideJob job) {
+  if (blockIdx.y == lv.L) {  // uniform: the last row of workgroups does the work on the side
+    if (blockIdx.x < job.blocks) run_side_job(job, blockIdx.x);
+    return;
+  }
+  constexpr uint32_t G = 2 * F;  // lanes per (point, level)
+  const uint32_t l = blockIdx.y;
+  const uint32_t sub = threadIdx.x % G;
+  const uint32_t xbit = sub / F, f = sub % F;
+  const uint64_t b64 = (uint64_t)blockIdx.x * (kBlock / G) + threadIdx.x / G;
+  if (b64 >= B) return;
+  const uint32_t b = (uint32_t)b64;
+  float xp[D];
+  load_point<D>(x, b, xp);
+  Corners<D> cn;
+  corners_of<D, false>(lv, l, smooth, xp, cn, nullptr);
+  constexpr uint32_t R = 1u << (D - 1);
+  uint64_t at[R];
+  float g[R];
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {  // corners along the other dimensions
+    const uint32_t idx = xbit ? cn.idx[2 * r + 1] : cn.idx[2 * r];
+    at[r] = (lv.offset[l] + idx) * F + f;
+    g[r] = grad[at[r]];
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r)
+    if (g[r] != 0.0f) g[r] = __hip_atomic_exchange(grad + at[r], 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (uint32_t r = 0; r < R; ++r) {
+    if (g[r] == 0.0f) continue;
+    float p = st.p32[at[r]], m = st.m[at[r]], v = st.v[at[r]];
+    adam_scalar(a, g[r], m, v, p);
+    st.m[at[r]] = m;
+    st.v[at[r]] = v;
+    st.p32[at[r]] = p;
+    st.p16[at[r]] = (_Float16)p;
+  }
+}
+
 // Gradient with respect to the position: one thread per point, all levels.
 template <int D, int F, typename PT, typename IT>
 __global__ __launch_bounds__(kBlock) void bwd_input_general(const LevelTable lv, const bool smooth, const uint32_t B,
@@ -715,6 +766,32 @@ hg_status launch_fwd_counting(const hashgrid* h, uint32_t B, const float* x, con
     default: return HG_ERR_UNSUPPORTED;
   }
 #undef HG_FWDC
+}
+
+template <int D, int F>
+static hg_status launch_adam_touched_t(const hashgrid* h, uint32_t B, const float* x, float* grad, const AdamArgs& a,
+                                       const AdamState& st, SideJob job, hipStream_t s) {
+  constexpr uint32_t per_block = kBlock / (2 * F);
+  const dim3 grid((uint32_t)(((uint64_t)B + per_block - 1) / per_block), h->lv.L + 1);
+  if (job.blocks > grid.x) job.blocks = grid.x;
+  hipLaunchKernelGGL((adam_touched<D, F>), grid, dim3(kBlock), 0, s, h->lv, h->cfg.interp == HG_INTERP_SMOOTHSTEP, B, x,
+                     grad, a, st, job);
+  return launched();
+}
+
+hg_status launch_adam_touched(const hashgrid* h, uint32_t B, const float* x, float* grad, const AdamArgs& a,
+                              const AdamState& st, const SideJob& job, hipStream_t s) {
+  switch (h->cfg.d * 16 + h->cfg.F) {
+    case 2 * 16 + 1: return launch_adam_touched_t<2, 1>(h, B, x, grad, a, st, job, s);
+    case 2 * 16 + 2: return launch_adam_touched_t<2, 2>(h, B, x, grad, a, st, job, s);
+    case 2 * 16 + 4: return launch_adam_touched_t<2, 4>(h, B, x, grad, a, st, job, s);
+    case 2 * 16 + 8: return launch_adam_touched_t<2, 8>(h, B, x, grad, a, st, job, s);
+    case 3 * 16 + 1: return launch_adam_touched_t<3, 1>(h, B, x, grad, a, st, job, s);
+    case 3 * 16 + 2: return launch_adam_touched_t<3, 2>(h, B, x, grad, a, st, job, s);
+    case 3 * 16 + 4: return launch_adam_touched_t<3, 4>(h, B, x, grad, a, st, job, s);
+    case 3 * 16 + 8: return launch_adam_touched_t<3, 8>(h, B, x, grad, a, st, job, s);
+    default: return HG_ERR_UNSUPPORTED;
+  }
 }
 
 // Expands `CALL(D, F)` for the runtime (d, F) pair.

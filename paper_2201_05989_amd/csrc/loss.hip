@@ -9,26 +9,11 @@
 #include <stdint.h>
 
 #include "hashgrid.h"
+#include "loss_device.hpp"
 
 namespace hg {
 
 constexpr int kLossThreads = 256;
-constexpr float kMapeOffset = 0.01f;  // Section 4, "Training": the constant in the percentage error's denominator
-
-// value and slope of one scalar's loss; fp32, the sign of p - t is exact (a difference of two floats
-// is zero only if they are equal)
-template <int KIND>
-__device__ __forceinline__ void loss_scalar(float p, float t, float scale, float& slope, float& value) {
-  const float diff = p - t;
-  if (KIND == HG_LOSS_L2) {
-    value = diff * diff;
-    slope = scale * (2.0f * diff);
-  } else {
-    const float inv = 1.0f / (fabsf(t) + kMapeOffset);
-    value = fabsf(diff) * inv;
-    slope = diff > 0.0f ? scale * inv : (diff < 0.0f ? -(scale * inv) : diff);  // diff itself where it is 0 or NaN
-  }
-}
 
 template <int KIND, bool VEC>
 __global__ __launch_bounds__(kLossThreads) void loss_grad(const uint64_t n, const float* __restrict__ p,

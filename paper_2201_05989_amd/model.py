@@ -1,8 +1,7 @@
 """The paper's model as one object (Section 4): the encoding followed by the 64-64 ReLU network, trained with Adam on
-tables and weights.  Bookkeeping only: every step of a training iteration is one call into the C-ABI library
-(hashgrid_encode_mlp_fwd_train, hashgrid_loss_grad, hashgrid_mlp_bwd, hashgrid_encode_bwd[_ws], hashgrid_adam_step
-twice; hashgrid_encode_bwd_input for the gradient with respect to the position); this file allocates the buffers and
-keeps the step counter.
+tables and weights.  Bookkeeping only: a training iteration is one call into the C-ABI library (hashgrid_train_step), the
+gradient with respect to the position three (hashgrid_encode_mlp_fwd_train, hashgrid_mlp_bwd_input,
+hashgrid_encode_bwd_input); this file allocates the buffers and keeps the step counter.
 
 Defaults are the paper's (Section 4, "Initialization" and "Training"): tables U(-1e-4, 1e-4) in half precision behind a
 full-precision master copy, Glorot-uniform weights, Adam with beta1 = 0.9, beta2 = 0.99, eps = 1e-15, an L2 factor
@@ -14,7 +13,8 @@ import math
 
 import torch
 
-from .binding import HashGrid, adam_step, loss_grad, mlp_bwd
+from .binding import (_LOSSES, HG_TRAIN_LOSS_SUMS, HashGrid, HashGridError, _dev, hashgrid_adam_config,
+                      hashgrid_train_state, mlp_bwd_input)
 
 N_HIDDEN = 64
 
@@ -34,15 +34,17 @@ class HashGridModel:
         n = self.grid.n_entries
         self.tables = torch.rand((n, F), device="cuda", generator=gen) * 2e-4 - 1e-4
         self.tables_half = self.tables.half()
-        self._tab_grad, self._tab_m, self._tab_v = (torch.zeros_like(self.tables) for _ in range(3))
+        # _tab_zeros, _net_zeros: zero between steps; where a step sums gradients that several workgroups share
+        self._tab_zeros, self._tab_m, self._tab_v = (torch.zeros_like(self.tables) for _ in range(3))
         self._shapes = [(N_HIDDEN, self.n_in), (N_HIDDEN, N_HIDDEN), (n_out, N_HIDDEN)]
         init = [(torch.rand(s, device="cuda", generator=gen) * 2 - 1) * math.sqrt(6.0 / (s[0] + s[1])) for s in self._shapes]
         self.weights = torch.cat([w.reshape(-1) for w in init]).contiguous()  # W1, W2, W3 in one array: one optimiser call
         self.weights_half = self.weights.half()
-        self._net_grad, self._net_m, self._net_v = (torch.zeros_like(self.weights) for _ in range(3))
-        self._W, self._dW = self._views(self.weights_half), self._views(self._net_grad)
+        self._net_zeros, self._net_m, self._net_v = (torch.zeros_like(self.weights) for _ in range(3))
+        self._W = self._views(self.weights_half)
         self.steps = 0
-        self._loss_sum = torch.zeros(1, dtype=torch.float64, device="cuda")
+        self._loss_sums = torch.zeros(HG_TRAIN_LOSS_SUMS, dtype=torch.float64, device="cuda")
+        self._state, self._state_of = hashgrid_train_state(), None
         self._buf_B = 0
 
     def _views(self, flat):
@@ -55,7 +57,6 @@ class HashGridModel:
     def _buffers(self, B: int):
         if B != self._buf_B:
             self._out = torch.empty((B, self.n_out), device="cuda")
-            self._dout = torch.empty_like(self._out)
             self._y = torch.empty((B, self.n_in), dtype=torch.float16, device="cuda")
             self._dy = torch.empty_like(self._y)
             self._buf_B = B
@@ -68,34 +69,45 @@ class HashGridModel:
         """d(sum_i dLdout_i * out_i) / dx [B, d] fp32: with the default dLdout = 1 and one output, the gradient of the
         output with respect to the position (the normal of a signed distance function, Section 3: the encoding is
         continuous and its derivative piecewise constant).  Three calls: the fused forward keeping y, the network's
-        backward pass (its weight gradients go to a scratch array), hashgrid_encode_bwd_input."""
-        B = x.shape[0]
-        self._buffers(B)
+        backward pass without weight gradients, hashgrid_encode_bwd_input."""
+        self._buffers(x.shape[0])
         self.grid.encode_mlp_fwd(x, self.tables_half, *self._W, self._out, y=self._y)
-        if dLdout is None:
-            dLdout = torch.ones((B, self.n_out), device="cuda")
-        if not hasattr(self, "_dW_scratch"):
-            self._dW_scratch = self._views(torch.zeros_like(self._net_grad))
-        mlp_bwd(self._y, *self._W, dLdout, self._dy, *self._dW_scratch)
+        mlp_bwd_input(self._y, *self._W, dLdout, self._dy)
         return self.grid.encode_bwd_input(x, self.tables_half, self._dy)
+
+    def _train_state(self, B: int) -> hashgrid_train_state:
+        """The library's view of this model: pointers checked when one of the public tensors has moved, and the
+        hyper-parameters as they are now."""
+        st = self._state
+        where = (self.tables.data_ptr(), self.tables_half.data_ptr(), self.weights.data_ptr(), self.weights_half.data_ptr())
+        if where != self._state_of:
+            table, n_w = (self.grid.n_entries, self.grid.F), sum(r * c for r, c in self._shapes)
+            for name, t, kind, shape in (("tables", self.tables, torch.float32, table), ("tables_half", self.tables_half, torch.float16, table),
+                                         ("weights", self.weights, torch.float32, (n_w,)),
+                                         ("weights_half", self.weights_half, torch.float16, (n_w,))):
+                setattr(st, name, _dev(t, kind, shape, name))
+            st.tables_m, st.tables_v, st.tables_zeros = (t.data_ptr() for t in (self._tab_m, self._tab_v, self._tab_zeros))
+            st.weights_m, st.weights_v, st.weights_zeros = (t.data_ptr() for t in (self._net_m, self._net_v, self._net_zeros))
+            st.loss_sums, st.n_out = self._loss_sums.data_ptr(), self.n_out
+            st.tables_adam = hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0)
+            st.weights_adam = hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0)
+            self._state_of = where
+        if self.loss not in _LOSSES:
+            raise HashGridError(f"unknown loss {self.loss!r}")
+        st.loss, st.loss_scale = _LOSSES[self.loss], self.loss_scale
+        st.tables_adam.lr = st.weights_adam.lr = self.lr
+        st.weights_adam.l2_reg = self.l2_reg * self.loss_scale * (B * self.n_out)
+        return st
 
     def step(self, x: torch.Tensor, target: torch.Tensor) -> None:
         """One training iteration on the batch (x [B, d], target [B, n_out], fp32 device tensors).  Nothing here
         synchronises; last_loss() does."""
         B = x.shape[0]
         self._buffers(B)
+        self.grid.train_step(self._train_state(B), x, target, self._y, self._dy, self.steps + 1)
         self.steps += 1
-        self.grid.encode_mlp_fwd(x, self.tables_half, *self._W, self._out, y=self._y)
-        self._loss_sum.zero_()
-        loss_grad(self._out, target, self.loss, self.loss_scale, self._dout, self._loss_sum)
         self._n_last = B * self.n_out
-        mlp_bwd(self._y, *self._W, self._dout, self._dy, *self._dW)
-        self.grid.encode_bwd(x, self._dy, self._tab_grad, overwrite=True)
-        adam_step(self.tables, self._tab_grad, self._tab_m, self._tab_v, self.steps, lr=self.lr,
-                  params_half=self.tables_half, zero_grad=False)
-        adam_step(self.weights, self._net_grad, self._net_m, self._net_v, self.steps, lr=self.lr,
-                  params_half=self.weights_half, zero_grad=True, l2_reg=self.l2_reg * self.loss_scale * self._n_last)
 
     def last_loss(self) -> float:
         """Mean loss over the scalars of the last step's batch, before that step's update (synchronises)."""
-        return float(self._loss_sum.cpu()[0]) / self._n_last
+        return float(self._loss_sums[0].cpu()) / self._n_last

@@ -1,0 +1,132 @@
+"""hashgrid_train_step (one training iteration behind one call, paper Section 4) against the single calls it stands for.
+
+Where nothing rounds the two must agree bit for bit: small integer tables, points at vertices of every level (weights
+0 and 1, or 2^-d with the smoothstep variant's half-voxel shift), sparse integer weights and targets that leave
+dyadic slopes make every half-precision operand and every fp32 sum exact, in any order of summation; the optimiser then
+works on equal gradients.  With random inputs the first moment after one step from zero is (1 - beta1) times the table
+gradient: it is held to the backward bar of the parity suite, 1e-5 of the summand mass (plus the optimiser's own roundings,
+2^-22 of the value), against the plain backward pass on the dL/dy the step itself used.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2201_05989_amd import HashGrid, HashGridModel, adam_step, loss_grad, mlp_bwd
+
+pytestmark = pytest.mark.gpu
+
+
+def exact_model(d, L, F, T, N_min, N_max, n_out, loss, interp, seed):
+    m = HashGridModel(d, n_out, L=L, F=F, T=T, N_min=N_min, N_max=N_max, loss=loss, seed=seed, interp=interp)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    m.tables.copy_(torch.randint(-1, 2, m.tables.shape, device="cuda", generator=gen))
+    m.tables_half.copy_(m.tables)
+    W = torch.randint(-1, 2, m.weights.shape, device="cuda", generator=gen).float()
+    m.weights.copy_(W * (torch.rand(m.weights.shape, device="cuda", generator=gen) < 0.2))
+    m.weights_half.copy_(m.weights)
+    return m, gen
+
+
+def single_calls(m, x, target):
+    """The step as its parts; returns what it leaves (tables, half, moments, weights, half, moments, loss sum, dL/dy)."""
+    B, g = x.shape[0], m.grid
+    tab, tab_h, w, w_h = (t.clone() for t in (m.tables, m.tables_half, m.weights, m.weights_half))
+    y = torch.empty((B, m.n_in), dtype=torch.float16, device="cuda")
+    dy, out = torch.empty_like(y), torch.empty((B, m.n_out), device="cuda")
+    dout, total = torch.empty_like(out), torch.zeros(1, dtype=torch.float64, device="cuda")
+    g.encode_mlp_fwd(x, tab_h, *m._W, out, y=y)
+    loss_grad(out, target, m.loss, m.loss_scale, dout, total)
+    dw = torch.zeros_like(w)
+    mlp_bwd(y, *m._W, dout, dy, *m._views(dw))
+    grad = g.encode_bwd(x, dy, use_workspace=False)
+    tm, tv, wm, wv = torch.zeros_like(tab), torch.zeros_like(tab), torch.zeros_like(w), torch.zeros_like(w)
+    adam_step(tab, grad, tm, tv, 1, lr=m.lr, params_half=tab_h)
+    adam_step(w, dw, wm, wv, 1, lr=m.lr, params_half=w_h, l2_reg=m.l2_reg * m.loss_scale * B * m.n_out)
+    return tab, tab_h, tm, tv, w, w_h, wm, wv, total, dy
+
+
+@pytest.mark.parametrize("d,L,F,T,N_min,N_max,n_out,loss,interp,B", [
+    (3, 8, 2, 1 << 14, 4, 512, 1, "l2", 0, 1),           # atomic additions, one point
+    (3, 8, 4, 1 << 14, 4, 512, 3, "l2", 1, 777),         # atomic additions, 32 features, smoothstep
+    (2, 8, 8, 1 << 19, 4, 512, 9, "mape", 0, 2049),      # eight features, two groups of outputs
+    (2, 16, 1, 1 << 20, 2, 1 << 16, 4, "l2", 0, 300),    # one feature an entry
+    (3, 8, 2, 1 << 12, 4, 512, 1, "mape", 0, 40000),     # sorted, every level shared by several workgroups
+    (3, 8, 2, 1 << 16, 4, 512, 32, "l2", 0, 100003),     # sorted, owned and shared chunks
+    (2, 8, 4, 1 << 15, 64, 8192, 2, "l2", 0, 70001),     # sorted, pairs that straddle two chunks
+    (3, 8, 8, 1 << 15, 4, 512, 17, "l2", 1, 30000),      # sorted, eight features (two blocks of inputs), smoothstep
+])
+def test_equals_the_single_calls_where_nothing_rounds(d, L, F, T, N_min, N_max, n_out, loss, interp, B):
+    m, gen = exact_model(d, L, F, T, N_min, N_max, n_out, loss, interp, seed=B)
+    x = torch.randint(0, N_min, (B, d), device="cuda", generator=gen).float() / N_min
+    if N_max >= 4096:  # vertices of the finest level along dimension 0: carries out of a chunk's index bits among them
+        x[:, 0] = torch.randint(0, 2, (B,), device="cuda", generator=gen) * 0.5 + 0.5 - 1.0 / N_max
+        x[:, 0] = torch.where(torch.rand(B, device="cuda", generator=gen) < 0.5, x[:, 0], torch.zeros_like(x[:, 0]))
+    x = x.contiguous()
+    p = m.infer(x)
+    if loss == "l2":
+        target = (p - torch.randint(-4, 5, p.shape, device="cuda", generator=gen) / 8.0).contiguous()
+    else:  # |t| + 0.01 is 1 in fp32: slopes are plus or minus 1
+        target = torch.where(torch.rand(p.shape, device="cuda", generator=gen) < 0.5, 0.99, -0.99).float().contiguous()
+    *want, total, dy = single_calls(m, x, target)
+    m.step(x, target)
+    torch.cuda.synchronize()
+    if N_max < 4096:
+        assert torch.equal(m._dy, dy)
+    got = (m.tables, m.tables_half, m._tab_m, m._tab_v, m.weights, m.weights_half, m._net_m, m._net_v)
+    for name, g, w in zip(("tables", "tables_half", "m", "v", "weights", "weights_half", "weights m", "weights v"), got, want):
+        assert B == 1 or (w != 0).any()
+        if N_max < 4096:
+            assert torch.equal(g, w), name
+        else:  # 1 - 1 / N_max is no vertex of the coarse levels: sums there are in fp32, either way
+            assert torch.allclose(g.float(), w.float(), rtol=2e-3, atol=1e-5), name
+    assert abs(float(m._loss_sums[0]) - float(total)) <= 1e-9 * abs(float(total))
+    assert not m._tab_zeros.any() and not m._net_zeros.any()
+
+
+@pytest.mark.parametrize("d,L,F,T,N_max,interp,B", [(3, 16, 2, 1 << 19, 2048, 0, 5000), (3, 16, 2, 1 << 17, 2048, 1, 60001),
+                                                    (2, 16, 2, 1 << 20, 32768, 0, 150001), (3, 8, 4, 1 << 15, 512, 0, 50000)])
+def test_first_moments_are_the_gradient(d, L, F, T, N_max, interp, B):
+    m = HashGridModel(d, 2, L=L, F=F, T=T, N_min=16, N_max=N_max, seed=3, interp=interp)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.rand((B, d), device="cuda", generator=gen).clamp_(max=1 - 2.0 ** -24)
+    for k in range(2):
+        m._tab_m.zero_()
+        m._tab_v.zero_()
+        m.step(x, torch.randn((B, 2), device="cuda", generator=gen))
+        g = m.grid.encode_bwd(x, m._dy, use_workspace=False)
+        mass = m.grid.encode_bwd(x, m._dy.abs(), use_workspace=False)
+        floor = float(m._dy.abs().max()) * 2.0 ** (max(d + int(np.ceil(np.log2(B))), 11) - 54)
+        # beta1 m + (1 - beta1) g with m = 0: two roundings, and 0.9 itself is rounded
+        err = (m._tab_m / (1 - torch.tensor(0.9, device="cuda")) - g).abs()
+        assert (err <= 2e-5 * mass + floor + 1e-30).all(), float((err / (mass + 1e-30)).max())
+        assert not m._tab_zeros.any()
+        assert torch.equal(m.tables_half, m.tables.half()) and torch.equal(m.weights_half, m.weights.half())
+
+
+def test_nan_in_the_targets_reaches_the_entries_as_in_the_single_calls():
+    # a gradient that is not finite: the sorted pass falls back to atomic additions inside the kernel
+    m, gen = exact_model(3, 8, 2, 1 << 15, 4, 512, 1, "l2", 0, 11)
+    x = torch.randint(0, 4, (30000, 3), device="cuda", generator=gen).float() / 4
+    target = m.infer(x) - 0.25
+    target[17] = float("nan")
+    want = single_calls(m, x, target)
+    m.step(x, target)
+    assert torch.isnan(m.tables).any()
+    assert torch.equal(torch.isnan(m.tables), torch.isnan(want[0]))
+    ok = ~torch.isnan(want[0])
+    assert torch.equal(m.tables[ok], want[0][ok])
+
+
+@pytest.mark.parametrize("n_in,n_out,B", [(8, 1, 1), (32, 1, 4097), (64, 32, 257), (40, 9, 70001)])
+def test_mlp_bwd_input_is_mlp_bwd_without_the_weight_gradients(n_in, n_out, B):
+    from paper_2201_05989_amd import mlp_bwd_input
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    y = torch.randn((B, n_in), device="cuda", generator=gen).half()
+    W = [torch.randn(s, device="cuda", generator=gen).mul_(0.2).half() for s in ((64, n_in), (64, 64), (n_out, 64))]
+    dout = torch.randn((B, n_out), device="cuda", generator=gen)
+    dW = [torch.zeros(w.shape, device="cuda") for w in W]
+    for given in (dout, None):
+        a, b = torch.empty_like(y), torch.full_like(y, float("nan"))
+        mlp_bwd(y, *W, dout if given is not None else torch.ones_like(dout), a, *dW)
+        mlp_bwd_input(y, *W, given, b)
+        assert torch.equal(a, b)
