@@ -350,9 +350,9 @@ hg_status hashgrid_loss_grad(uint64_t n, const float* prediction, const float* t
 hg_status hashgrid_mlp_bwd_input(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1,
                                  const void* W2, const void* W3, const float* dLdout, void* dLdy, void* stream);
 
-/* What a model keeps between training iterations (device pointers; the arrays tables_zeros and
- * weights_zeros are all zero before a step, and again after it). */
-#define HG_TRAIN_LOSS_SUMS 513u
+/* What a model keeps between training iterations (device pointers; tables_zeros is all zero before a
+ * step, and again after it). */
+#define HG_TRAIN_SCRATCH_BYTES (256u * (8u + 40u * 1024u))
 typedef struct {
   uint32_t n_out;      /* network outputs, 1..32 */
   uint32_t loss;       /* hg_loss */
@@ -369,9 +369,8 @@ typedef struct {
   void* weights_half;  /* the same, fp16, 8-byte aligned */
   float* weights_m;
   float* weights_v;
-  float* weights_zeros;
-  double* loss_sums;   /* [HG_TRAIN_LOSS_SUMS]; [0] = sum of the unscaled loss values of the step's B * n_out
-                        * scalars, before its update; the rest is scratch */
+  double* loss_sum;    /* sum of the unscaled loss values of the step's B * n_out scalars, before its update */
+  void* scratch;       /* HG_TRAIN_SCRATCH_BYTES, 16-byte aligned; the workgroups' sums of loss and weight gradients */
 } hashgrid_train_state;
 
 /* One training iteration (paper Section 4): encoding, network, loss, backward through both, Adam on

@@ -24,7 +24,7 @@ HG_BWD_OVERWRITE = 2
 HG_ERR_UNSUPPORTED = 2
 HG_STATIC_SCRATCH_BYTES = 64 << 20
 HG_LOSS_L2, HG_LOSS_MAPE = 0, 1
-HG_TRAIN_LOSS_SUMS = 513
+HG_TRAIN_SCRATCH_BYTES = 256 * (8 + 40 * 1024)
 _LOSSES = {"l2": HG_LOSS_L2, "mape": HG_LOSS_MAPE, HG_LOSS_L2: HG_LOSS_L2, HG_LOSS_MAPE: HG_LOSS_MAPE}
 
 _DTYPES = {"f32": HG_F32, "f16": HG_F16, torch.float32: HG_F32, torch.float16: HG_F16}
@@ -59,7 +59,7 @@ class hashgrid_train_state(ctypes.Structure):
                 ("tables_adam", hashgrid_adam_config), ("weights_adam", hashgrid_adam_config)] + \
                [(n, ctypes.c_void_p) for n in
                 ("tables", "tables_half", "tables_m", "tables_v", "tables_zeros", "weights", "weights_half", "weights_m",
-                 "weights_v", "weights_zeros", "loss_sums")]
+                 "weights_v", "loss_sum", "scratch")]
 
 
 _lib = None

@@ -35,40 +35,86 @@ struct AdamState {
   float* v;
 };
 
-// Work that a training step's later kernel does on the side, in workgroups of its own: Adam on the network's weights (a
-// few thousand scalars, each gradient cleared as it is read) and the sum of the loss values that the workgroups of the network kernel left.
-// A launch of its own for either costs more than the work.  blocks = 0: nothing to do.
+// How the network's weight-gradient sums lie in a workgroup of mlp_bwd.hip: `quads` runs of four registers of 64 lanes.
+// Quads 0 .. 15 are the four 32 x 32 tiles of dW2 (tile 2 Tm + Tn), then 8 KB quads of dW1 (tile KB Tn + Tk: rows n of
+// tile Tn, columns k of tile Tk), then 2 OS of dW3 (tile Tn: the OS runs of eight rows o that exist); register t of quad q of a
+// tile holds row 8 q + 4 (lane / 32) + t at column lane % 32.
+struct SumLayout {
+  int kb, os, n_in, n_out;
+  __host__ __device__ int quads() const { return 16 + 8 * kb + 2 * os; }
+  // index into W1 [64][n_in], W2 [64][64], W3 [n_out][64] laid one after the other; -1 for padding (k >= n_in, o >= n_out)
+  __device__ int scalar_of(const int i, const int t, const int lane) const {
+    const int c = lane & 31, half_row = 4 * (lane >> 5) + t;
+    if (i < 16) {
+      const int a = i / 4, row = 8 * (i % 4) + half_row;
+      return 64 * n_in + (32 * (a / 2) + row) * 64 + 32 * (a % 2) + c;
+    }
+    if (i < 16 + 8 * kb) {
+      const int a = (i - 16) / 4, row = 8 * ((i - 16) % 4) + half_row, k = 32 * (a % kb) + c;
+      return k < n_in ? (32 * (a / kb) + row) * n_in + k : -1;
+    }
+    const int j = i - 16 - 8 * kb, row = 8 * (j % os) + half_row;
+    return row < n_out ? 64 * n_in + 64 * 64 + row * 64 + 32 * (j / os) + c : -1;
+  }
+};
+
+// Work that a training step's later kernel does on the side, in workgroups of its own: the weight-gradient sums that the
+// workgroups of the network kernel left are added up and taken to Adam on the network's weights, and their loss
+// values are added up.  A launch of its own costs more than the work, and letting the workgroups of
+// the network kernel meet in one array with atomic additions costs them 5 us at its end (every workgroup has all
+// scalars, 100 K requests of 64 bytes).  blocks = 0: nothing to do; else one workgroup for every quad of sums.
 struct SideJob {
-  uint32_t blocks;  // workgroups appended to the grid
-  uint32_t n;
+  uint32_t blocks;
+  SumLayout at;
   AdamArgs a;
-  AdamState w;
-  float* grad;
+  AdamState w;         // the weights, in the order of SumLayout::scalar_of
+  const float4* sums;  // [n_parts][quads][64]
   const double* loss_parts;
   uint32_t n_parts;
   double* loss_sum;
 };
 
-// One workgroup's share (block = 0 .. job.blocks - 1); every thread of the workgroup calls it.
-__device__ __forceinline__ void run_side_job(const SideJob& job, const uint32_t block) {
-  for (uint32_t i = block * blockDim.x + threadIdx.x; i < job.n; i += job.blocks * blockDim.x) {
-    float p = job.w.p32[i], g = job.grad[i];
-    job.grad[i] = 0.0f;
-    g = job.a.l2 != 0.0f ? fmaf(job.a.l2, p, g) : g;
-    if (g == 0.0f) continue;
-    float m = job.w.m[i], v = job.w.v[i];
-    adam_scalar(job.a, g, m, v, p);
-    job.w.m[i] = m;
-    job.w.v[i] = v;
-    job.w.p32[i] = p;
-    job.w.p16[i] = (_Float16)p;
+// Quad `quad` of the job, by all T threads of a workgroup; `part`: T float4 of LDS.
+template <int T>
+__device__ __forceinline__ void run_side_job(const SideJob& job, const uint32_t quad, float4* part) {
+  constexpr uint32_t kSegments = T / 64;
+  const uint32_t lane = threadIdx.x & 63, seg = threadIdx.x >> 6;
+  float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+#pragma unroll 8
+  for (uint32_t p = seg; p < job.n_parts; p += kSegments) {
+    const float4 v = job.sums[((uint64_t)p * job.blocks + quad) * 64 + lane];
+    sum.x += v.x;
+    sum.y += v.y;
+    sum.z += v.z;
+    sum.w += v.w;
   }
-  if (block == 0 && threadIdx.x < 64) {  // one wave
-    double sum = 0.0;
-    for (uint32_t i = threadIdx.x; i < job.n_parts; i += 64) sum += job.loss_parts[i];
+  part[threadIdx.x] = sum;
+  __syncthreads();
+  if (threadIdx.x < 256) {  // lane and register: 64 x 4 scalars
+    const uint32_t t = threadIdx.x >> 6;
+    float g = 0.0f;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
-    if (threadIdx.x == 0) *job.loss_sum = sum;
+    for (uint32_t s = 0; s < kSegments; ++s) g += reinterpret_cast<const float*>(part + s * 64 + lane)[t];
+    const int i = job.at.scalar_of((int)quad, (int)t, (int)lane);
+    if (i >= 0) {
+      float p = job.w.p32[i];
+      g = job.a.l2 != 0.0f ? fmaf(job.a.l2, p, g) : g;
+      if (g != 0.0f) {
+        float m = job.w.m[i], v = job.w.v[i];
+        adam_scalar(job.a, g, m, v, p);
+        job.w.m[i] = m;
+        job.w.v[i] = v;
+        job.w.p32[i] = p;
+        job.w.p16[i] = (_Float16)p;
+      }
+    }
+  }
+  if (quad == 0 && threadIdx.x < 64) {  // one wave
+    double total = 0.0;
+    for (uint32_t i = lane; i < job.n_parts; i += 64) total += job.loss_parts[i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) total += __shfl_down(total, o, 64);
+    if (lane == 0) *job.loss_sum = total;
   }
 }
 

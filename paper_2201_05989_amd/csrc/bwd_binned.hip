@@ -370,7 +370,8 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
   __shared__ uint32_t seg_sum[kScanThreads];
   const uint32_t scan_wgs = gridDim.x - job.blocks;
   if (blockIdx.x >= scan_wgs) {  // uniform
-    run_side_job(job, blockIdx.x - scan_wgs);
+    __shared__ float4 part[kScanThreads];
+    run_side_job<kScanThreads>(job, blockIdx.x - scan_wgs, part);
     return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) item_counter[0] = 0;  // the accumulate pass draws its work items from here

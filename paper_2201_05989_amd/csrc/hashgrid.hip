@@ -476,7 +476,11 @@ __global__ __launch_bounds__(kBlock) void adam_touched(const LevelTable lv, cons
                                                        const float* __restrict__ x, float* grad, const AdamArgs a,
                                                        const AdamState st, const SideJob job) {
   if (blockIdx.y == lv.L) {  // uniform: the last row of workgroups does the work on the side
-    if (blockIdx.x < job.blocks) run_side_job(job, blockIdx.x);
+    __shared__ float4 part[kBlock];
+    for (uint32_t quad = blockIdx.x; quad < job.blocks; quad += gridDim.x) {
+      run_side_job<kBlock>(job, quad, part);
+      __syncthreads();
+    }
     return;
   }
   constexpr uint32_t G = 2 * F;  // lanes per (point, level)
@@ -770,10 +774,9 @@ hg_status launch_fwd_counting(const hashgrid* h, uint32_t B, const float* x, con
 
 template <int D, int F>
 static hg_status launch_adam_touched_t(const hashgrid* h, uint32_t B, const float* x, float* grad, const AdamArgs& a,
-                                       const AdamState& st, SideJob job, hipStream_t s) {
+                                       const AdamState& st, const SideJob& job, hipStream_t s) {
   constexpr uint32_t per_block = kBlock / (2 * F);
   const dim3 grid((uint32_t)(((uint64_t)B + per_block - 1) / per_block), h->lv.L + 1);
-  if (job.blocks > grid.x) job.blocks = grid.x;
   hipLaunchKernelGGL((adam_touched<D, F>), grid, dim3(kBlock), 0, s, h->lv, h->cfg.interp == HG_INTERP_SMOOTHSTEP, B, x,
                      grad, a, st, job);
   return launched();

@@ -41,20 +41,20 @@ uint32_t point_major_block(uint32_t B);
 hg_status launch_fwd_counting(const hashgrid* h, uint32_t B, const float* x, const void* params, void* y,
                               uint32_t* counts, uint32_t n_bins, uint32_t n_tiles, hipStream_t s);
 
+struct AdamArgs;
+struct AdamState;
+struct SideJob;
 // mlp_bwd.hip: the network's part of a training step, forward products, loss and backward products (shapes as
-// hashgrid_mlp_bwd takes them, checked by the caller).  Every workgroup leaves the sum of its loss values in
-// loss_parts; n_groups: their number, kMaxMlpGroups at most.
-constexpr uint32_t kMaxMlpGroups = 512;
+// hashgrid_mlp_bwd takes them, checked by the caller).  Every workgroup (kMaxMlpGroups at most) leaves its loss
+// and weight-gradient sums in scratch (HG_TRAIN_SCRATCH_BYTES); fills in where they are in *job.
+constexpr uint32_t kMaxMlpGroups = 256;
 hg_status launch_mlp_train(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1, const void* W2,
-                           const void* W3, const float* target, uint32_t loss, float scale, void* dLdy, float* dW1, float* dW2,
-                           float* dW3, double* loss_parts, uint32_t* n_groups, hipStream_t s);
+                           const void* W3, const float* target, uint32_t loss, float scale, void* dLdy, SideJob* job,
+                           void* scratch, hipStream_t s);
 
 // bwd_binned.hip: the sorted backward pass that hands every entry's sum to the optimiser instead of to a gradient array
 // (io fp16, gradients fp32, pair records; workspace checked by the caller).  zeros: n_entries * F floats that are all
 // zero, and are again after the call: where several workgroups share a chunk their sums meet there.
-struct AdamArgs;
-struct AdamState;
-struct SideJob;
 hg_status launch_binned_adam(const hashgrid* h, uint32_t B, const float* x, const void* dy, float* zeros, void* workspace,
                              bool counted, const AdamArgs& a, const AdamState& st, const SideJob& job, hipStream_t s);
 // hashgrid.hip: the optimiser's step on the entries that the batch's corners reach (d = 2 or 3); grad is all zeros after it

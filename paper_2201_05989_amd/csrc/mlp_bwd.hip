@@ -27,7 +27,7 @@
 // So a layer costs its products, one rounding of its result, and two more instructions per tile for
 // the second layout; the weight gradients need no memory operand at all.  Weight-gradient sums stay
 // in registers while the wave walks its blocks of points, are then added up across the workgroup's
-// waves in LDS and leave with one atomic add per scalar and workgroup.
+// waves in LDS and leave with one atomic add per scalar and workgroup (training: as they are, for a later kernel).
 //
 // The same kernel is the network's whole part of a training step (MlpMode::kTrainL2, kTrainMape): the output layer's
 // product comes out in layout P, which is where the gradient of the loss is wanted, so prediction, loss and its
@@ -39,6 +39,7 @@
 
 #include "hashgrid.h"
 #include "hashgrid_internal.hpp"
+#include "adam_device.hpp"
 #include "loss_device.hpp"
 
 namespace hg {
@@ -122,32 +123,19 @@ struct MlpBwdShape {
     s.o_end = (s.o_w3 + (train ? 32 * kHidStride : 0) + 7) / 8 * 8;
     return s;
   }
-  // the weights; afterwards the same memory takes the waves' weight-gradient sums, at most 96 registers of
-  // 64 lanes per wave at a time
+  // the weights; afterwards the same memory takes the waves' weight-gradient sums, quads (SumLayout) of 64 lanes per
+  // wave, all of them at a time where they fit 128 KiB
   __host__ __device__ size_t lds_bytes(int waves, bool sums_wanted) const {
-    const size_t weights = (size_t)o_end * 2, sums = sums_wanted ? (size_t)waves * 96 * 64 * 4 : 0;
+    const int quads = 16 + kin_pad / 4 + 2 * ((n_out + 7) / 8);
+    const size_t weights = (size_t)o_end * 2, sums = sums_wanted ? (size_t)waves * quads_per_turn(quads) * 1024 : 0;
     return weights > sums ? weights : sums;
   }
+  __host__ __device__ static constexpr int quads_per_turn(int quads) { return quads <= 32 ? quads : (quads + 1) / 2; }
 };
 
-// Where a weight-gradient sum goes.  A workgroup's sums are numbered by (register g, lane) as they lie
-// in a wave's accumulators: g = 0 .. 63 the four 32 x 32 tiles of dW2 ([2 Tm + Tn]), then 32 KB
-// registers of dW1 ([KB Tn + Tk]: rows n of tile Tn, columns k of tile Tk), then 32 of dW3 ([Tn]: rows
-// o, columns n of tile Tn); register r of a tile holds row 8 (r / 4) + 4 (lane / 32) + r % 4 at
-// column lane % 32.  nullptr for the padding (k >= n_in, o >= n_out).
-__device__ __forceinline__ float* sum_target(const int g, const int lane, const int kb, const int n_in, const int n_out,
-                                             float* dW1, float* dW2, float* dW3) {
-  const int c = lane & 31, r = g % 16, row = 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
-  if (g < 64) return dW2 + (32 * (g / 32) + row) * kHid + 32 * ((g / 16) % 2) + c;
-  if (g < 64 + 32 * kb) {
-    const int a = (g - 64) / 16, k = 32 * (a % kb) + c;
-    return k < n_in ? dW1 + (32 * (a / kb) + row) * n_in + k : nullptr;
-  }
-  const int a = (g - 64 - 32 * kb) / 16;
-  return row < n_out ? dW3 + row * kHid + 32 * a + c : nullptr;
-}
 // KB: 32-column blocks of y (1 for up to 32 encoded features, else 2); OS: groups of eight outputs.
-// dout: dL/dout, or the targets in the training modes; scale and loss_parts (one value per workgroup) are theirs.
+// dout: dL/dout, or the targets in the training modes; scale, loss_parts (one value per workgroup) and sums (the
+// workgroups' weight-gradient sums, instead of dW1, dW2, dW3) are theirs.
 template <int KB, int OS, MlpMode MODE>
 __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, const MlpBwdShape sh,
                                                       const _Float16* __restrict__ y, const _Float16* __restrict__ W1,
@@ -155,7 +143,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
                                                       const float* __restrict__ dout, _Float16* __restrict__ dy,
                                                       float* __restrict__ dW1, float* __restrict__ dW2,
                                                       float* __restrict__ dW3, const float scale,
-                                                      double* __restrict__ loss_parts) {
+                                                      double* __restrict__ loss_parts, float4* __restrict__ sums) {
   constexpr bool TRAIN = MODE == MlpMode::kTrainL2 || MODE == MlpMode::kTrainMape, WGRAD = MODE != MlpMode::kInput;
   constexpr int SUB = blocks_in_flight(KB, OS, TRAIN);
   constexpr int LOSS = MODE == MlpMode::kTrainL2 ? HG_LOSS_L2 : HG_LOSS_MAPE;
@@ -514,48 +502,55 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
     }
   }
 
-  // The weight gradients of the workgroup.  Every wave writes its sums to LDS as they lie in its
-  // registers ([wave][register][lane]; the weights are no longer needed), then every thread adds up
-  // the waves' values of its share of (register, lane) pairs and sends one atomic add per scalar:
-  // the 32 lanes of a half-wave hold 32 consecutive columns of a row.  Two rounds, so that the
-  // area stays below 96 KiB: the second layer's 64 registers, then the first and the output layer's.
-  // (Writing the workgroups' sums to a scratch buffer for a second kernel to add up was measured and is
-  // slower than these atomics: 49 against 40 us at 2^18 points.)
-  float* red = reinterpret_cast<float*>(lds);
-  const int rot = (int)((blockIdx.x * 13u) % 64u);
-  auto reduce = [&](auto&& store_all, const int g0, const int n_regs) {
-    __syncthreads();  // the area is free: every wave is done with the weights (first round) or the round before
-    store_all(red + wave * n_regs * 64 + lane);  // register r to [r * 64]
-    __syncthreads();
-    // (workgroups start at different registers, so that at any time they add to different lines of the gradient)
-    for (int i = wave; i < n_regs; i += waves) {
-      const int r = (i + rot) % n_regs;
-      float v = 0.0f;
-      for (int w = 0; w < waves; ++w) v += red[(w * n_regs + r) * 64 + lane];
-      float* t = sum_target(g0 + r, lane, KB, n_in, n_out, dW1, dW2, dW3);
-      if (t != nullptr && v != 0.0f) __hip_atomic_fetch_add(t, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // The weight gradients of the workgroup.  Every wave writes its sums to LDS as they lie in its registers
+  // ([wave][quad][lane], 16 bytes a lane; the weights are no longer needed), then every wave adds up all waves'
+  // values of every fourth quad.  In training they leave as they are for the kernel that applies them (SideJob);
+  // else with one atomic add per scalar and workgroup, workgroups starting at different quads, so that at any time
+  // they add to different lines.
+  float4* red = reinterpret_cast<float4*>(lds);
+  constexpr int kQuads = 16 + 8 * KB + 2 * OS, kTurn = MlpBwdShape::quads_per_turn(kQuads);
+  const SumLayout layout{KB, OS, n_in, n_out};
+  const int rot = (int)((blockIdx.x * 5u) % (uint32_t)kTurn);
+#pragma unroll
+  for (int q0 = 0; q0 < kQuads; q0 += kTurn) {
+    const int n_q = kQuads - q0 < kTurn ? kQuads - q0 : kTurn;
+    __syncthreads();  // the area is free: every wave is done with the weights, or with the turn before
+#pragma unroll
+    for (int i = q0; i < q0 + n_q; ++i) {
+      const float16v& acc = i < 16 ? aW2[i / 4] : i < 16 + 8 * KB ? aW1[(i - 16) / 4] : aW3[(i - 16 - 8 * KB) / OS];
+      const int r = 4 * (i < 16 + 8 * KB ? i % 4 : (i - 16 - 8 * KB) % OS);
+      red[(wave * kTurn + i - q0) * 64 + lane] = make_float4(acc[r], acc[r + 1], acc[r + 2], acc[r + 3]);
     }
-  };
-  reduce(
-      [&](float* mine) {
+    __syncthreads();
+#pragma unroll 2
+    for (int i = wave; i < n_q; i += kWaves) {
+      int j = i;
+      if constexpr (!TRAIN) {
+        j += rot;
+        j = j < n_q ? j : j - n_q;
+      }
+      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+      for (int w = 0; w < kWaves; ++w) {
+        const float4 o = red[(w * kTurn + j) * 64 + lane];
+        v[0] += o.x;
+        v[1] += o.y;
+        v[2] += o.z;
+        v[3] += o.w;
+      }
+      if constexpr (TRAIN) {
+        sums[((uint64_t)blockIdx.x * kQuads + q0 + j) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+      } else {
 #pragma unroll
-          for (int q = 0; q < 16; ++q) mine[(16 * a + q) * 64] = aW2[a][q];
-      },
-      0, 64);
-  reduce(
-      [&](float* mine) {
-#pragma unroll
-        for (int a = 0; a < 2 * KB; ++a)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) mine[(16 * a + q) * 64] = aW1[a][q];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) mine[(32 * KB + 16 * a + q) * 64] = aW3[a][q];
-      },
-      64, 32 * KB + 32);
+        for (int t = 0; t < 4; ++t) {
+          const int k = layout.scalar_of(q0 + j, t, lane), n1 = kHid * n_in, n2 = n1 + kHid * kHid;
+          if (k < 0 || v[t] == 0.0f) continue;
+          float* to = k < n1 ? dW1 + k : k < n2 ? dW2 + (k - n1) : dW3 + (k - n2);
+          __hip_atomic_fetch_add(to, v[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+    }
+  }
 }
 
 // The launch behind the entry points; `dout` are the targets in the training modes (loss_parts: kMaxMlpGroups doubles).
@@ -563,14 +558,14 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
 template <MlpMode MODE>
 static hg_status launch_mlp_back(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1, const void* W2,
                                  const void* W3, const float* dout, void* dLdy, float* dW1, float* dW2, float* dW3,
-                                 float scale, double* loss_parts, uint32_t* n_groups, hipStream_t s) {
+                                 float scale, double* loss_parts, float4* sums, uint32_t* n_groups, hipStream_t s) {
   constexpr bool TRAIN = MODE == MlpMode::kTrainL2 || MODE == MlpMode::kTrainMape, WGRAD = MODE != MlpMode::kInput;
   const MlpBwdShape sh = MlpBwdShape::make((int)n_in, (int)n_out, TRAIN);
   constexpr size_t kLdsLimit = 160 * 1024;
   const int waves = kWaves;
   if (sh.lds_bytes(waves, WGRAD) > kLdsLimit) return HG_ERR_UNSUPPORTED;
   using Kernel = void (*)(uint32_t, MlpBwdShape, const _Float16*, const _Float16*, const _Float16*, const _Float16*,
-                          const float*, _Float16*, float*, float*, float*, float, double*);
+                          const float*, _Float16*, float*, float*, float*, float, double*, float4*);
   static const Kernel kernels[2][4] = {
       {mlp_bwd_kernel<1, 1, MODE>, mlp_bwd_kernel<1, 2, MODE>, mlp_bwd_kernel<1, 3, MODE>, mlp_bwd_kernel<1, 4, MODE>},
       {mlp_bwd_kernel<2, 1, MODE>, mlp_bwd_kernel<2, 2, MODE>, mlp_bwd_kernel<2, 3, MODE>, mlp_bwd_kernel<2, 4, MODE>}};
@@ -593,17 +588,25 @@ static hg_status launch_mlp_back(uint32_t B, uint32_t n_in, uint32_t n_out, cons
   if (n_groups) *n_groups = grid.x;
   hipLaunchKernelGGL(kernels[sh.kin_pad / 32 - 1][(n_out + 7) / 8 - 1], grid, block, sh.lds_bytes(waves, WGRAD), s, B, sh,
                      static_cast<const _Float16*>(y), static_cast<const _Float16*>(W1), static_cast<const _Float16*>(W2),
-                     static_cast<const _Float16*>(W3), dout, static_cast<_Float16*>(dLdy), dW1, dW2, dW3, scale, loss_parts);
+                     static_cast<const _Float16*>(W3), dout, static_cast<_Float16*>(dLdy), dW1, dW2, dW3, scale, loss_parts,
+                     sums);
   return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;
 }
 
 hg_status launch_mlp_train(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1, const void* W2,
-                           const void* W3, const float* target, uint32_t loss, float scale, void* dLdy, float* dW1, float* dW2,
-                           float* dW3, double* loss_parts, uint32_t* n_groups, hipStream_t s) {
-  return loss == HG_LOSS_L2 ? launch_mlp_back<MlpMode::kTrainL2>(B, n_in, n_out, y, W1, W2, W3, target, dLdy, dW1, dW2, dW3,
-                                                                 scale, loss_parts, n_groups, s)
-                            : launch_mlp_back<MlpMode::kTrainMape>(B, n_in, n_out, y, W1, W2, W3, target, dLdy, dW1, dW2, dW3,
-                                                                   scale, loss_parts, n_groups, s);
+                           const void* W3, const float* target, uint32_t loss, float scale, void* dLdy, SideJob* job,
+                           void* scratch, hipStream_t s) {
+  double* loss_parts = static_cast<double*>(scratch);
+  float4* sums = reinterpret_cast<float4*>(loss_parts + kMaxMlpGroups);
+  job->at = SumLayout{(int)(n_in + 31) / 32, (int)(n_out + 7) / 8, (int)n_in, (int)n_out};
+  job->blocks = (uint32_t)job->at.quads();
+  job->sums = sums;
+  job->loss_parts = loss_parts;
+  return loss == HG_LOSS_L2
+             ? launch_mlp_back<MlpMode::kTrainL2>(B, n_in, n_out, y, W1, W2, W3, target, dLdy, nullptr, nullptr, nullptr,
+                                                  scale, loss_parts, sums, &job->n_parts, s)
+             : launch_mlp_back<MlpMode::kTrainMape>(B, n_in, n_out, y, W1, W2, W3, target, dLdy, nullptr, nullptr, nullptr,
+                                                    scale, loss_parts, sums, &job->n_parts, s);
 }
 
 }  // namespace hg
@@ -629,7 +632,7 @@ extern "C" hg_status hashgrid_mlp_bwd(uint32_t B, uint32_t n_in, uint32_t n_out,
   if ((reinterpret_cast<uintptr_t>(dW1) | reinterpret_cast<uintptr_t>(dW2) | reinterpret_cast<uintptr_t>(dW3)) & 3)
     return HG_ERR_INVALID_ARG;
   return hg::launch_mlp_back<hg::MlpMode::kBackward>(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy, dW1, dW2, dW3, 1.0f,
-                                                     nullptr, nullptr, static_cast<hipStream_t>(stream));
+                                                     nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
 }
 
 extern "C" hg_status hashgrid_mlp_bwd_input(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1,
@@ -639,5 +642,5 @@ extern "C" hg_status hashgrid_mlp_bwd_input(uint32_t B, uint32_t n_in, uint32_t 
   const hg_status ok = check_mlp_back(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy);
   if (ok != HG_OK) return ok;
   return hg::launch_mlp_back<hg::MlpMode::kInput>(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy, nullptr, nullptr, nullptr,
-                                                  1.0f, nullptr, nullptr, static_cast<hipStream_t>(stream));
+                                                  1.0f, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
 }

@@ -32,8 +32,8 @@ extern "C" hg_status hashgrid_train_step(const hashgrid_t* hg, const hashgrid_tr
   auto bad = [](const void* p, uintptr_t a) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; };
   if (bad(x, 4) || bad(target, 4) || bad(y, 16) || bad(dLdy, 16) || bad(st->tables, 16) || bad(st->tables_half, 16) ||
       bad(st->tables_m, 16) || bad(st->tables_v, 16) || bad(st->tables_zeros, 16) || bad(st->weights, 4) ||
-      bad(st->weights_half, 8) || bad(st->weights_m, 4) || bad(st->weights_v, 4) || bad(st->weights_zeros, 4) ||
-      bad(st->loss_sums, 8))
+      bad(st->weights_half, 8) || bad(st->weights_m, 4) || bad(st->weights_v, 4) || bad(st->loss_sum, 8) ||
+      bad(st->scratch, 16))
     return HG_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
 
@@ -49,20 +49,15 @@ extern "C" hg_status hashgrid_train_step(const hashgrid_t* hg, const hashgrid_tr
   if (rc == HG_ERR_UNSUPPORTED) rc = hashgrid_encode_fwd(hg, B, x, st->tables_half, y, stream);
   if (rc != HG_OK) return rc;
 
-  const uint32_t n1 = 64 * n_in, n2 = 64 * 64, n_weights = n1 + n2 + 64 * n_out;
+  const uint32_t n1 = 64 * n_in, n2 = 64 * 64;
   const _Float16* W = static_cast<const _Float16*>(st->weights_half);
   hg::SideJob job{};
-  rc = hg::launch_mlp_train(B, n_in, n_out, y, W, W + n1, W + n1 + n2, target, st->loss, st->loss_scale, dLdy,
-                            st->weights_zeros, st->weights_zeros + n1, st->weights_zeros + n1 + n2, st->loss_sums + 1,
-                            &job.n_parts, s);
+  rc = hg::launch_mlp_train(B, n_in, n_out, y, W, W + n1, W + n1 + n2, target, st->loss, st->loss_scale, dLdy, &job,
+                            st->scratch, s);
   if (rc != HG_OK) return rc;
-  job.blocks = 8;
-  job.n = n_weights;
   job.a = hg::adam_args(st->weights_adam, step);
   job.w = hg::AdamState{st->weights, static_cast<_Float16*>(st->weights_half), st->weights_m, st->weights_v};
-  job.grad = st->weights_zeros;
-  job.loss_parts = st->loss_sums + 1;
-  job.loss_sum = st->loss_sums;
+  job.loss_sum = st->loss_sum;
   const hg::AdamArgs a = hg::adam_args(st->tables_adam, step);
   const hg::AdamState tab{st->tables, static_cast<_Float16*>(st->tables_half), st->tables_m, st->tables_v};
   if (sorted) return hg::launch_binned_adam(hg, B, x, dLdy, st->tables_zeros, workspace, counted, a, tab, job, s);

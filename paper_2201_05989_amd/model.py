@@ -13,7 +13,7 @@ import math
 
 import torch
 
-from .binding import (_LOSSES, HG_TRAIN_LOSS_SUMS, HashGrid, HashGridError, _dev, hashgrid_adam_config,
+from .binding import (_LOSSES, HG_TRAIN_SCRATCH_BYTES, HashGrid, HashGridError, _dev, hashgrid_adam_config,
                       hashgrid_train_state, mlp_bwd_input)
 
 N_HIDDEN = 64
@@ -34,16 +34,17 @@ class HashGridModel:
         n = self.grid.n_entries
         self.tables = torch.rand((n, F), device="cuda", generator=gen) * 2e-4 - 1e-4
         self.tables_half = self.tables.half()
-        # _tab_zeros, _net_zeros: zero between steps; where a step sums gradients that several workgroups share
+        # _tab_zeros: zero between steps; where a step sums gradients that several workgroups share
         self._tab_zeros, self._tab_m, self._tab_v = (torch.zeros_like(self.tables) for _ in range(3))
         self._shapes = [(N_HIDDEN, self.n_in), (N_HIDDEN, N_HIDDEN), (n_out, N_HIDDEN)]
         init = [(torch.rand(s, device="cuda", generator=gen) * 2 - 1) * math.sqrt(6.0 / (s[0] + s[1])) for s in self._shapes]
         self.weights = torch.cat([w.reshape(-1) for w in init]).contiguous()  # W1, W2, W3 in one array: one optimiser call
         self.weights_half = self.weights.half()
-        self._net_zeros, self._net_m, self._net_v = (torch.zeros_like(self.weights) for _ in range(3))
+        self._net_m, self._net_v = torch.zeros_like(self.weights), torch.zeros_like(self.weights)
         self._W = self._views(self.weights_half)
         self.steps = 0
-        self._loss_sums = torch.zeros(HG_TRAIN_LOSS_SUMS, dtype=torch.float64, device="cuda")
+        self._loss_sum = torch.zeros(1, dtype=torch.float64, device="cuda")
+        self._scratch = torch.empty(HG_TRAIN_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
         self._state, self._state_of = hashgrid_train_state(), None
         self._buf_B = 0
 
@@ -87,8 +88,8 @@ class HashGridModel:
                                          ("weights_half", self.weights_half, torch.float16, (n_w,))):
                 setattr(st, name, _dev(t, kind, shape, name))
             st.tables_m, st.tables_v, st.tables_zeros = (t.data_ptr() for t in (self._tab_m, self._tab_v, self._tab_zeros))
-            st.weights_m, st.weights_v, st.weights_zeros = (t.data_ptr() for t in (self._net_m, self._net_v, self._net_zeros))
-            st.loss_sums, st.n_out = self._loss_sums.data_ptr(), self.n_out
+            st.weights_m, st.weights_v = self._net_m.data_ptr(), self._net_v.data_ptr()
+            st.loss_sum, st.scratch, st.n_out = self._loss_sum.data_ptr(), self._scratch.data_ptr(), self.n_out
             st.tables_adam = hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0)
             st.weights_adam = hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0)
             self._state_of = where
@@ -110,4 +111,4 @@ class HashGridModel:
 
     def last_loss(self) -> float:
         """Mean loss over the scalars of the last step's batch, before that step's update (synchronises)."""
-        return float(self._loss_sums[0].cpu()) / self._n_last
+        return float(self._loss_sum.cpu()[0]) / self._n_last
