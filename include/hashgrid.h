@@ -344,11 +344,15 @@ typedef enum { HG_LOSS_L2 = 0, HG_LOSS_MAPE = 1 } hg_loss;
 hg_status hashgrid_loss_grad(uint64_t n, const float* prediction, const float* target, uint32_t loss, float scale,
                              float* dLdout, double* loss_sum, void* stream);
 
-/* The backward pass of the network without the weight gradients (arguments, precision and errors as
- * hashgrid_mlp_bwd): dL/dy alone, for gradients with respect to the position.
- *   dLdout  [B, n_out]  fp32, device, read; NULL stands for all ones */
-hg_status hashgrid_mlp_bwd_input(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1,
-                                 const void* W2, const void* W3, const float* dLdout, void* dLdy, void* stream);
+/* The gradient of the network's output with respect to the position, in one kernel: encoding, network, the
+ * way back through both.  dLdx[b, j] = sum_i dLdout[b, i] * d out[b, i] / d x_j, with the roundings of
+ * hashgrid_encode_mlp_fwd_train, hashgrid_mlp_bwd and hashgrid_encode_bwd_input in a row (arguments and errors
+ * as there); neither features nor their gradient reach memory.
+ *   dLdout  [B, n_out]  fp32, device, read; NULL stands for all ones
+ *   dLdx    [B, d]      fp32, device, written in full */
+hg_status hashgrid_encode_mlp_bwd_input(const hashgrid_t* hg, uint32_t B, const float* x, const void* params,
+                                        const void* W1, const void* W2, const void* W3, uint32_t n_out,
+                                        const float* dLdout, float* dLdx, void* stream);
 
 /* What a model keeps between training iterations (device pointers; tables_zeros is all zero before a
  * step, and again after it). */

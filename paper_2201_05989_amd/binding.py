@@ -36,7 +36,7 @@ EXPORTS = ("hashgrid_create", "hashgrid_destroy", "hashgrid_n_entries", "hashgri
            "hashgrid_encode_bwd_ws", "hashgrid_encode_fwd_ws", "hashgrid_bwd_ws_pays", "hashgrid_adam_step",
            "hashgrid_encode_mlp_fwd", "hashgrid_encode_bwd_static", "hashgrid_encode_mlp_fwd_train", "hashgrid_mlp_bwd",
            "hashgrid_adam_step_half_grad", "hashgrid_loss_grad", "hashgrid_mlp_fwd",
-           "hashgrid_mlp_bwd_input", "hashgrid_train_step")
+           "hashgrid_encode_mlp_bwd_input", "hashgrid_train_step")
 PROBE_EXPORTS = ("hashgrid_probe_copy", "hashgrid_probe_gather", "hashgrid_probe_atomic_add",
                  "hashgrid_probe_gather_lines")
 
@@ -120,8 +120,8 @@ def load_library() -> ctypes.CDLL:
     lib.hashgrid_adam_step_half_grad.restype = ctypes.c_int
     lib.hashgrid_loss_grad.argtypes = [u64, vp, vp, u32, ctypes.c_float, vp, vp, vp]
     lib.hashgrid_loss_grad.restype = ctypes.c_int
-    lib.hashgrid_mlp_bwd_input.argtypes = [u32, u32, u32, vp, vp, vp, vp, vp, vp, vp]
-    lib.hashgrid_mlp_bwd_input.restype = ctypes.c_int
+    lib.hashgrid_encode_mlp_bwd_input.argtypes = [vp, u32, vp, vp, vp, vp, vp, u32, vp, vp, vp]
+    lib.hashgrid_encode_mlp_bwd_input.restype = ctypes.c_int
     lib.hashgrid_train_step.argtypes = [vp, ctypes.POINTER(hashgrid_train_state), u32, vp, vp, vp, vp, vp, u64, u32, vp]
     lib.hashgrid_train_step.restype = ctypes.c_int
     lib.hashgrid_strerror.argtypes = [ctypes.c_int]
@@ -361,6 +361,23 @@ class HashGrid:
                 "hashgrid_encode_mlp_fwd_train")
         return out
 
+    def encode_mlp_bwd_input(self, x: torch.Tensor, params: torch.Tensor, W1: torch.Tensor, W2: torch.Tensor,
+                             W3: torch.Tensor, dLdout: torch.Tensor | None = None, dLdx: torch.Tensor | None = None,
+                             stream=None) -> torch.Tensor:
+        """hashgrid_encode_mlp_bwd_input: d(sum_i dLdout_i * out_i) / dx of the encoding followed by the network; dLdout
+        None: all ones."""
+        B, n_out = x.shape[0], W3.shape[0]
+        if dLdx is None:
+            dLdx = torch.empty((B, self.d), dtype=torch.float32, device=x.device)
+        _check(self._lib.hashgrid_encode_mlp_bwd_input(
+            self._h, B, _dev(x, torch.float32, (B, self.d), "x"),
+            _dev(params, self.param_dtype, (self.n_entries, self.F), "params"),
+            _dev(W1, torch.float16, (64, self.L * self.F), "W1"), _dev(W2, torch.float16, (64, 64), "W2"),
+            _dev(W3, torch.float16, (n_out, 64), "W3"), n_out,
+            None if dLdout is None else _dev(dLdout, torch.float32, (B, n_out), "dLdout"),
+            _dev(dLdx, torch.float32, (B, self.d), "dLdx"), _stream_ptr(stream)), "hashgrid_encode_mlp_bwd_input")
+        return dLdx
+
     def train_step(self, state: hashgrid_train_state, x: torch.Tensor, target: torch.Tensor, y: torch.Tensor,
                    dLdy: torch.Tensor, step: int, stream=None) -> None:
         """hashgrid_train_step; the scratch of the sorted backward pass is one kept on this object.  The pointers in
@@ -512,15 +529,3 @@ def mlp_bwd(y: torch.Tensor, W1: torch.Tensor, W2: torch.Tensor, W3: torch.Tenso
         _dev(dLdout, torch.float32, (B, n_out), "dLdout"), _dev(dLdy, torch.float16, (B, n_in), "dLdy"),
         _dev(dW1, torch.float32, (64, n_in), "dW1"), _dev(dW2, torch.float32, (64, 64), "dW2"),
         _dev(dW3, torch.float32, (n_out, 64), "dW3"), _stream_ptr(stream)), "hashgrid_mlp_bwd")
-
-
-def mlp_bwd_input(y: torch.Tensor, W1: torch.Tensor, W2: torch.Tensor, W3: torch.Tensor, dLdout: torch.Tensor | None,
-                  dLdy: torch.Tensor, stream=None) -> None:
-    """hashgrid_mlp_bwd_input: mlp_bwd without the weight gradients; dLdout None: all ones."""
-    B, n_in = y.shape
-    n_out = W3.shape[0]
-    _check(load_library().hashgrid_mlp_bwd_input(
-        B, n_in, n_out, _dev(y, torch.float16, (B, n_in), "y"), _dev(W1, torch.float16, (64, n_in), "W1"),
-        _dev(W2, torch.float16, (64, 64), "W2"), _dev(W3, torch.float16, (n_out, 64), "W3"),
-        None if dLdout is None else _dev(dLdout, torch.float32, (B, n_out), "dLdout"),
-        _dev(dLdy, torch.float16, (B, n_in), "dLdy"), _stream_ptr(stream)), "hashgrid_mlp_bwd_input")

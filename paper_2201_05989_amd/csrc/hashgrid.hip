@@ -357,8 +357,7 @@ __global__ __launch_bounds__(kPmBlock) void bwd_input_point_major(const LevelTab
       }
 #pragma unroll
       for (int q = 0; q < SB; ++q) {
-        // val[m]: blend over the dimensions folded so far; der[i][m]: its derivative along dimension i
-        float val[1 << D], der[D][1 << D];
+        float val[1 << D];
 #pragma unroll
         for (uint32_t m = 0; m < (1u << D); ++m) {
           float sm = 0.0f;
@@ -366,20 +365,7 @@ __global__ __launch_bounds__(kPmBlock) void bwd_input_point_major(const LevelTab
           for (int f = 0; f < F; ++f) sm = fmaf((float)g[q].v[F * j + f], (float)e[q][m].v[f], sm);
           val[m] = sm;
         }
-#pragma unroll
-        for (int i = 0; i < D; ++i) {        // fold dimension i: corners m (bit i clear) and m | 1<<i
-#pragma unroll
-          for (uint32_t m = 0; m < (1u << D); ++m) {
-            if (m & ((2u << i) - 1u)) continue;  // representatives: bits 0..i clear
-            const uint32_t hi = m | (1u << i);
-#pragma unroll
-            for (int k = 0; k < i; ++k) der[k][m] = u[q][i] * der[k][m] + w[q][i] * der[k][hi];
-            der[i][m] = dw[q][i] * (val[hi] - val[m]);
-            val[m] = u[q][i] * val[m] + w[q][i] * val[hi];
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < D; ++i) gx[q][i] += der[i][0];
+        add_blend_derivative<D>(val, w[q], u[q], dw[q], gx[q]);
       }
       asm volatile("" ::: "memory");
       __syncthreads();

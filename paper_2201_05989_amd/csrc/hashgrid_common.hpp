@@ -176,6 +176,55 @@ __device__ __forceinline__ void level_corners(const LevelTable& lv, uint32_t l, 
   u0 = u[0];
 }
 
+// Derivative of the d-linear blend of the corner values val[m] along every dimension, added to gx: dimension by
+// dimension, a pair (lower a, upper b) along one with weights (u, w) and slope dw becomes value u a + w b and derivative
+// dw (b - a).
+template <int D>
+__device__ __forceinline__ void add_blend_derivative(float (&val)[1 << D], const float (&w)[D], const float (&u)[D],
+                                                     const float (&dw)[D], float (&gx)[D]) {
+  float der[D][1 << D];  // der[i][m]: derivative along dimension i of the blend over the dimensions folded so far
+#pragma unroll
+  for (int i = 0; i < D; ++i) {  // fold dimension i: corners m (bit i clear) and m | 1<<i
+#pragma unroll
+    for (uint32_t m = 0; m < (1u << D); ++m) {
+      if (m & ((2u << i) - 1u)) continue;  // representatives: bits 0..i clear
+      const uint32_t hi = m | (1u << i);
+#pragma unroll
+      for (int k = 0; k < i; ++k) der[k][m] = u[i] * der[k][m] + w[i] * der[k][hi];
+      der[i][m] = dw[i] * (val[hi] - val[m]);
+      val[m] = u[i] * val[m] + w[i] * val[hi];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < D; ++i) gx[i] += der[i][0];
+}
+
+// Level l's part of the gradient with respect to the position, from its corner entries e and its features' gradient g
+template <int D, int F>
+__device__ __forceinline__ void add_position_gradient(const LevelTable& lv, uint32_t l, bool smooth, const float (&xp)[D],
+                                                      const Vec<_Float16, F> (&e)[1 << D], const float (&g)[F],
+                                                      float (&gx)[D]) {
+  const float Nf = (float)lv.N[l];
+  float w[D], u[D], dw[D], val[1 << D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    float wf;
+    uint32_t c0;
+    split(xp[i], Nf, smooth ? 0.5f : 0.0f, smooth ? Nf : Nf - 1.0f, c0, wf);
+    w[i] = smooth ? smoothstep(wf) : wf;
+    u[i] = smooth ? smoothstep(1.0f - wf) : 1.0f - wf;
+    dw[i] = smooth ? dsmoothstep(wf) * Nf : Nf;
+  }
+#pragma unroll
+  for (uint32_t m = 0; m < (1u << D); ++m) {
+    float sm = 0.0f;
+#pragma unroll
+    for (int f = 0; f < F; ++f) sm = fmaf(g[f], (float)e[m].v[f], sm);
+    val[m] = sm;
+  }
+  add_blend_derivative<D>(val, w, u, dw, gx);
+}
+
 template <int D, bool POW2>
 __device__ __forceinline__ void level_corners(const LevelTable& lv, uint32_t l, bool smooth, const float (&xp)[D],
                                               uint32_t (&idx)[1 << D], float (&wr)[1 << (D - 1)], float& w0,

@@ -6,16 +6,8 @@
 // has to be kept from the forward pass.
 //
 // Work unit: one wave and 32 points.  Activations and gradients of a block never leave the wave's
-// registers; LDS holds the weights only.  Every product is v_mfma_f32_32x32x16_f16 (fp16 operands,
-// fp32 accumulation), D[i][j] = sum_k A[i][k] B[k][j] over 16 values of k, with, per lane l
-// (c = l % 32, h = l / 32):
-//   A: row i = c, eight values of k in registers;   B: column j = c, eight values of k;
-//   D: column j = c, rows i = 8 q + 4 h + t in register 4 q + t (q, t = 0 .. 3).
-// Which eight k a lane holds is the instruction's business only in that A and B must agree, so k is
-// numbered here the way D comes out: slot s = 0 .. 7 of lane half h in step j stands for
-// k = 16 j + 8 (s / 4) + 4 h + s % 4.  Then a lane's part of D, rounded to half, register groups
-// 2 j and 2 j + 1, is already its part of the B (or A) operand of step j of a product that contracts
-// over D's rows, and the matching fragment of a weight row is two 8-byte pieces 16 bytes apart.
+// registers; LDS holds the weights only.  The products, and how results
+// of one are operands of the next without leaving their lanes, are in mlp_device.hpp.
 // Two layouts of a matrix z[point][neuron] of a block follow:
 //   "P": lane = point c, registers = neurons 32 T + 8 q + 4 h + t of tile T.  It is the B operand of
 //        W z (A = rows of the weights from LDS), whose result is again in layout P: the chain
@@ -31,8 +23,7 @@
 //
 // The same kernel is the network's whole part of a training step (MlpMode::kTrainL2, kTrainMape): the output layer's
 // product comes out in layout P, which is where the gradient of the loss is wanted, so prediction, loss and its
-// slope exist in registers only; and, without the weight gradients and what only they need, the way back from
-// dL/dout to dL/dy alone (MlpMode::kInput), a third of the products.
+// slope exist in registers only.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -41,62 +32,18 @@
 #include "hashgrid_internal.hpp"
 #include "adam_device.hpp"
 #include "loss_device.hpp"
+#include "mlp_device.hpp"
 
 namespace hg {
 
-constexpr int kHid = 64;      // neurons of a hidden layer
-constexpr int kPad = 4;       // halves of padding per LDS row: the 8-byte reads of 32 lanes a row apart cover all banks
-constexpr int kHidStride = kHid + kPad;
-constexpr int kPts = 32;      // points of a wave's block
 constexpr int kWaves = 4;     // waves of a workgroup: one per SIMD, which leaves a wave all 512 registers
 // Blocks of 32 points a wave has in flight: two, and one where two with their targets do not fit a wave's 512 registers.
 constexpr int blocks_in_flight(int KB, int OS, bool train) { return train && (KB == 2 || OS > 2) ? 1 : 2; }
 
-using half4 = _Float16 __attribute__((ext_vector_type(4)));
-using half8 = _Float16 __attribute__((ext_vector_type(8)));
-using short8v = short __attribute__((ext_vector_type(8)));
-using float8v = float __attribute__((ext_vector_type(8)));
-using float16v = float __attribute__((ext_vector_type(16)));
-
-__device__ __forceinline__ float16v zero16() {
-  float16v z;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) z[i] = 0.0f;
-  return z;
-}
-__device__ __forceinline__ float16v mfma(const half8 a, const half8 b, const float16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-}
-// register groups 2 j and 2 j + 1 of a result, rounded to half (nearest even): step j of an operand
-__device__ __forceinline__ half8 to_half(const float16v& acc, const int j) {
-  float8v v;
-#pragma unroll
-  for (int s = 0; s < 8; ++s) v[s] = acc[8 * j + s];
-  return __builtin_convertvector(v, half8);
-}
-// ReLU on halves: as 16-bit integers the negative halves (and -0) are the negative numbers
-__device__ __forceinline__ half8 relu(const half8 v) {
-  return __builtin_bit_cast(half8, __builtin_elementwise_max(__builtin_bit_cast(short8v, v), (short8v)0));
-}
-// g where the activation act (not negative: it went through relu) is positive, else 0: all ones
-// where the bits of act are not zero, two packed instructions for two halves (written out: the
-// compiler would turn the C expression into a compare and a select per half)
-__device__ __forceinline__ half8 where_positive(const half8 g, const half8 act) {
-  uint4 a = __builtin_bit_cast(uint4, act);
-  const uint4 gb = __builtin_bit_cast(uint4, g);
-  // (op_sel_hi: the upper half of the instruction takes the shift count from the constant's lower 16 bits too)
-  asm("v_pk_sub_i16 %0, 0, %0\n\tv_pk_ashrrev_i16 %0, 15, %0 op_sel_hi:[0,1]" : "+v"(a.x));
-  asm("v_pk_sub_i16 %0, 0, %0\n\tv_pk_ashrrev_i16 %0, 15, %0 op_sel_hi:[0,1]" : "+v"(a.y));
-  asm("v_pk_sub_i16 %0, 0, %0\n\tv_pk_ashrrev_i16 %0, 15, %0 op_sel_hi:[0,1]" : "+v"(a.z));
-  asm("v_pk_sub_i16 %0, 0, %0\n\tv_pk_ashrrev_i16 %0, 15, %0 op_sel_hi:[0,1]" : "+v"(a.w));
-  return __builtin_bit_cast(half8, uint4{gb.x & a.x, gb.y & a.y, gb.z & a.z, gb.w & a.w});
-}
-
 enum class MlpMode {
   kBackward,   // dL/dout given: dL/dy and the weight gradients
   kTrainL2,    // targets given: the output layer and the loss between forward and backward
-  kTrainMape,
-  kInput       // dL/dout given, or all ones: dL/dy only
+  kTrainMape
 };
 
 struct MlpBwdShape {
@@ -125,9 +72,9 @@ struct MlpBwdShape {
   }
   // the weights; afterwards the same memory takes the waves' weight-gradient sums, quads (SumLayout) of 64 lanes per
   // wave, all of them at a time where they fit 128 KiB
-  __host__ __device__ size_t lds_bytes(int waves, bool sums_wanted) const {
+  __host__ __device__ size_t lds_bytes(int waves) const {
     const int quads = 16 + kin_pad / 4 + 2 * ((n_out + 7) / 8);
-    const size_t weights = (size_t)o_end * 2, sums = sums_wanted ? (size_t)waves * quads_per_turn(quads) * 1024 : 0;
+    const size_t weights = (size_t)o_end * 2, sums = (size_t)waves * quads_per_turn(quads) * 1024;
     return weights > sums ? weights : sums;
   }
   __host__ __device__ static constexpr int quads_per_turn(int quads) { return quads <= 32 ? quads : (quads + 1) / 2; }
@@ -144,7 +91,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
                                                       float* __restrict__ dW1, float* __restrict__ dW2,
                                                       float* __restrict__ dW3, const float scale,
                                                       double* __restrict__ loss_parts, float4* __restrict__ sums) {
-  constexpr bool TRAIN = MODE == MlpMode::kTrainL2 || MODE == MlpMode::kTrainMape, WGRAD = MODE != MlpMode::kInput;
+  constexpr bool TRAIN = MODE == MlpMode::kTrainL2 || MODE == MlpMode::kTrainMape;
   constexpr int SUB = blocks_in_flight(KB, OS, TRAIN);
   constexpr int LOSS = MODE == MlpMode::kTrainL2 ? HG_LOSS_L2 : HG_LOSS_MAPE;
   extern __shared__ _Float16 lds[];
@@ -187,7 +134,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int o = 8 * ks + 4 * h + t;
-          const float v = !WGRAD && dout == nullptr ? 1.0f : dout[pr * n_out + (o < n_out ? o : n_out - 1)];
+          const float v = dout[pr * n_out + (o < n_out ? o : n_out - 1)];
           d_next[u][ks][t] = (inside && o < n_out) ? v : 0.0f;
         }
     }
@@ -240,13 +187,6 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
   __syncthreads();
 
   constexpr int OJ = (OS + 1) / 2;  // steps of 16 outputs
-  // this lane's fragment of row 32 T + c of a weight array for step j: columns 16 j + 4 h .. + 3 and 16 j + 8 + 4 h .. + 3
-  auto frag = [&](const _Float16* w, const int stride, const int T, const int j) {
-    const _Float16* at = w + (32 * T + c) * stride + 16 * j + 4 * h;
-    const half4 lo = *reinterpret_cast<const half4*>(at), hi = *reinterpret_cast<const half4*>(at + 8);
-    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  };
-
   float16v aW2[4], aW1[2 * KB], aW3[2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) aW2[i] = zero16();
@@ -310,7 +250,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) aP[u] = zero16();
 #pragma unroll
       for (int j = 0; j < 2 * KB; ++j) {
-        const half8 w = frag(w1, sh.w1_stride, T, j);
+        const half8 w = weight_frag(w1, sh.w1_stride, T, j);
 #pragma unroll
         for (int u = 0; u < SUB; ++u) aP[u] = mfma(w, yP[u][j], aP[u]);
       }
@@ -318,7 +258,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) h1P[u][2 * T + j] = relu(to_half(aP[u], j));
-        if constexpr (WGRAD) exchange(&h1P[u][2 * T], 2, &h1N[u][2 * T]);
+        exchange(&h1P[u][2 * T], 2, &h1N[u][2 * T]);
       }
     }
 #pragma unroll
@@ -328,7 +268,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) aP[u] = zero16();
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const half8 w = frag(w2, kHidStride, T, j);
+        const half8 w = weight_frag(w2, kHidStride, T, j);
 #pragma unroll
         for (int u = 0; u < SUB; ++u) aP[u] = mfma(w, h1P[u][j], aP[u]);
       }
@@ -336,7 +276,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) h2P[u][2 * T + j] = relu(to_half(aP[u], j));
-        if constexpr (WGRAD) exchange(&h2P[u][2 * T], 2, &h2N[u][2 * T]);
+        exchange(&h2P[u][2 * T], 2, &h2N[u][2 * T]);
       }
     }
     if constexpr (TRAIN) {
@@ -346,7 +286,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) o[u] = zero16();
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const half8 w = frag(w3, kHidStride, 0, j);
+        const half8 w = weight_frag(w3, kHidStride, 0, j);
 #pragma unroll
         for (int u = 0; u < SUB; ++u) o[u] = mfma(w, h2P[u][j], o[u]);
       }
@@ -370,19 +310,15 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
     }
     // dL/dout in layout N (lane = output, registers = points)
     half8 g3N[SUB][2];
-    if constexpr (WGRAD) {
 #pragma unroll
-      for (int u = 0; u < SUB; ++u) exchange(g3P[u], OJ, g3N[u]);
-    }
+    for (int u = 0; u < SUB; ++u) exchange(g3P[u], OJ, g3N[u]);
     // output layer: dW3[o][n] += sum_p dout[p][o] h2[p][n];  g2 = (W3^T dout) through the ReLU of layer 2
-    if constexpr (WGRAD) {
 #pragma unroll
-      for (int u = 0; u < SUB; ++u)
+    for (int u = 0; u < SUB; ++u)
 #pragma unroll
-        for (int T = 0; T < 2; ++T)
+      for (int T = 0; T < 2; ++T)
 #pragma unroll
-          for (int j = 0; j < 2; ++j) aW3[T] = mfma(g3N[u][j], h2N[u][2 * T + j], aW3[T]);
-    }
+        for (int j = 0; j < 2; ++j) aW3[T] = mfma(g3N[u][j], h2N[u][2 * T + j], aW3[T]);
     half8 g2P[SUB][4], g2N[SUB][4];
 #pragma unroll
     for (int T = 0; T < 2; ++T) {
@@ -391,7 +327,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) aP[u] = zero16();
 #pragma unroll
       for (int j = 0; j < OJ; ++j) {
-        const half8 w = frag(w3t, sh.w3t_stride, T, j);
+        const half8 w = weight_frag(w3t, sh.w3t_stride, T, j);
 #pragma unroll
         for (int u = 0; u < SUB; ++u) aP[u] = mfma(w, g3P[u][j], aP[u]);
       }
@@ -399,21 +335,19 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) g2P[u][2 * T + j] = where_positive(to_half(aP[u], j), h2P[u][2 * T + j]);
-        if constexpr (WGRAD) exchange(&g2P[u][2 * T], 2, &g2N[u][2 * T]);
+        exchange(&g2P[u][2 * T], 2, &g2N[u][2 * T]);
       }
     }
     // second layer: dW2[m][n] += sum_p g2[p][m] h1[p][n];  g1 = (W2^T g2) through the ReLU of layer 1
-    if constexpr (WGRAD) {
 #pragma unroll
-      for (int u = 0; u < SUB; ++u)
+    for (int u = 0; u < SUB; ++u)
 #pragma unroll
-        for (int Tm = 0; Tm < 2; ++Tm)
+      for (int Tm = 0; Tm < 2; ++Tm)
 #pragma unroll
-          for (int Tn = 0; Tn < 2; ++Tn)
+        for (int Tn = 0; Tn < 2; ++Tn)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-              aW2[2 * Tm + Tn] = mfma(g2N[u][2 * Tm + j], h1N[u][2 * Tn + j], aW2[2 * Tm + Tn]);
-    }
+          for (int j = 0; j < 2; ++j)
+            aW2[2 * Tm + Tn] = mfma(g2N[u][2 * Tm + j], h1N[u][2 * Tn + j], aW2[2 * Tm + Tn]);
     half8 g1P[SUB][4], g1N[SUB][4];
 #pragma unroll
     for (int T = 0; T < 2; ++T) {
@@ -422,7 +356,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) aP[u] = zero16();
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const half8 w = frag(w2t, kHidStride, T, j);
+        const half8 w = weight_frag(w2t, kHidStride, T, j);
 #pragma unroll
         for (int u = 0; u < SUB; ++u) aP[u] = mfma(w, g2P[u][j], aP[u]);
       }
@@ -430,23 +364,21 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) g1P[u][2 * T + j] = where_positive(to_half(aP[u], j), h1P[u][2 * T + j]);
-        if constexpr (WGRAD) exchange(&g1P[u][2 * T], 2, &g1N[u][2 * T]);
+        exchange(&g1P[u][2 * T], 2, &g1N[u][2 * T]);
       }
     }
     // first layer: dW1[n][k] += sum_p g1[p][n] y[p][k]
-    if constexpr (WGRAD) {
 #pragma unroll
-      for (int u = 0; u < SUB; ++u)
+    for (int u = 0; u < SUB; ++u)
 #pragma unroll
-        for (int Tk = 0; Tk < KB; ++Tk) {
-          half8 yN[2];
-          exchange(&yP[u][2 * Tk], 2, yN);
+      for (int Tk = 0; Tk < KB; ++Tk) {
+        half8 yN[2];
+        exchange(&yP[u][2 * Tk], 2, yN);
 #pragma unroll
-          for (int Tn = 0; Tn < 2; ++Tn)
+        for (int Tn = 0; Tn < 2; ++Tn)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) aW1[KB * Tn + Tk] = mfma(g1N[u][2 * Tn + j], yN[j], aW1[KB * Tn + Tk]);
-        }
-    }
+          for (int j = 0; j < 2; ++j) aW1[KB * Tn + Tk] = mfma(g1N[u][2 * Tn + j], yN[j], aW1[KB * Tn + Tk]);
+      }
     // dL/dy = W1^T g1, layout P: four features per register group, straight to memory
 #pragma unroll
     for (int Tk = 0; Tk < KB; ++Tk) {
@@ -455,7 +387,7 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
       for (int u = 0; u < SUB; ++u) d[u] = zero16();
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const half8 w = frag(w1t, kHidStride, Tk, j);
+        const half8 w = weight_frag(w1t, kHidStride, Tk, j);
 #pragma unroll
         for (int u = 0; u < SUB; ++u) d[u] = mfma(w, g1P[u][j], d[u]);
       }
@@ -487,7 +419,6 @@ __global__ __launch_bounds__(64 * kWaves) void mlp_bwd_kernel(const uint32_t B, 
     else blocks(p0, p0_next, std::false_type{});
   }
 
-  if constexpr (!WGRAD) return;
   if constexpr (TRAIN) {  // the workgroup's loss values: lanes, then waves; whoever runs next adds the workgroups up
     double* wave_sum = reinterpret_cast<double*>(lds);
     __syncthreads();  // every wave is done with the weights
@@ -559,11 +490,11 @@ template <MlpMode MODE>
 static hg_status launch_mlp_back(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1, const void* W2,
                                  const void* W3, const float* dout, void* dLdy, float* dW1, float* dW2, float* dW3,
                                  float scale, double* loss_parts, float4* sums, uint32_t* n_groups, hipStream_t s) {
-  constexpr bool TRAIN = MODE == MlpMode::kTrainL2 || MODE == MlpMode::kTrainMape, WGRAD = MODE != MlpMode::kInput;
+  constexpr bool TRAIN = MODE == MlpMode::kTrainL2 || MODE == MlpMode::kTrainMape;
   const MlpBwdShape sh = MlpBwdShape::make((int)n_in, (int)n_out, TRAIN);
   constexpr size_t kLdsLimit = 160 * 1024;
   const int waves = kWaves;
-  if (sh.lds_bytes(waves, WGRAD) > kLdsLimit) return HG_ERR_UNSUPPORTED;
+  if (sh.lds_bytes(waves) > kLdsLimit) return HG_ERR_UNSUPPORTED;
   using Kernel = void (*)(uint32_t, MlpBwdShape, const _Float16*, const _Float16*, const _Float16*, const _Float16*,
                           const float*, _Float16*, float*, float*, float*, float, double*, float4*);
   static const Kernel kernels[2][4] = {
@@ -583,10 +514,9 @@ static hg_status launch_mlp_back(uint32_t B, uint32_t n_in, uint32_t n_out, cons
   const uint32_t per_round = blocks_in_flight(sh.kin_pad / 32, (int)(n_out + 7) / 8, TRAIN) * kPts;
   const uint32_t n_rounds = (B + per_round - 1) / per_round;
   const uint32_t want = (n_rounds + waves - 1) / waves;
-  const uint32_t slots = WGRAD ? cus : 2 * cus;  // (without the sums two workgroups fit a compute unit)
-  const dim3 grid(want < slots ? want : slots), block(64 * waves);
+  const dim3 grid(want < cus ? want : cus), block(64 * waves);
   if (n_groups) *n_groups = grid.x;
-  hipLaunchKernelGGL(kernels[sh.kin_pad / 32 - 1][(n_out + 7) / 8 - 1], grid, block, sh.lds_bytes(waves, WGRAD), s, B, sh,
+  hipLaunchKernelGGL(kernels[sh.kin_pad / 32 - 1][(n_out + 7) / 8 - 1], grid, block, sh.lds_bytes(waves), s, B, sh,
                      static_cast<const _Float16*>(y), static_cast<const _Float16*>(W1), static_cast<const _Float16*>(W2),
                      static_cast<const _Float16*>(W3), dout, static_cast<_Float16*>(dLdy), dW1, dW2, dW3, scale, loss_parts,
                      sums);
@@ -611,36 +541,18 @@ hg_status launch_mlp_train(uint32_t B, uint32_t n_in, uint32_t n_out, const void
 
 }  // namespace hg
 
-// shared argument checks (W1, W2, W3 and what every caller of the backward products passes)
-static hg_status check_mlp_back(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1, const void* W2,
-                                const void* W3, const float* dLdout, void* dLdy) {
-  if (B > HG_MAX_BATCH) return HG_ERR_UNSUPPORTED;
-  if (!y || !W1 || !W2 || !W3 || !dLdy || n_out == 0 || n_in == 0) return HG_ERR_INVALID_ARG;
-  if (n_in % 8 != 0 || n_in > 64 || n_out > 32) return HG_ERR_UNSUPPORTED;
-  auto bad = [](const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; };
-  if (bad(y, 16) || bad(dLdy, 8) || bad(W1, 2) || bad(W2, 2) || bad(W3, 2) || bad(dLdout, 4)) return HG_ERR_INVALID_ARG;
-  return HG_OK;
-}
-
 extern "C" hg_status hashgrid_mlp_bwd(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1,
                                       const void* W2, const void* W3, const float* dLdout, void* dLdy, float* dW1,
                                       float* dW2, float* dW3, void* stream) {
   if (B == 0) return HG_OK;
-  if (B <= HG_MAX_BATCH && (!dLdout || !dW1 || !dW2 || !dW3)) return HG_ERR_INVALID_ARG;
-  const hg_status ok = check_mlp_back(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy);
-  if (ok != HG_OK) return ok;
-  if ((reinterpret_cast<uintptr_t>(dW1) | reinterpret_cast<uintptr_t>(dW2) | reinterpret_cast<uintptr_t>(dW3)) & 3)
+  if (B > HG_MAX_BATCH) return HG_ERR_UNSUPPORTED;
+  if (!y || !W1 || !W2 || !W3 || !dLdout || !dLdy || !dW1 || !dW2 || !dW3 || n_out == 0 || n_in == 0)
+    return HG_ERR_INVALID_ARG;
+  if (n_in % 8 != 0 || n_in > 64 || n_out > 32) return HG_ERR_UNSUPPORTED;
+  auto bad = [](const void* p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; };
+  if (bad(y, 16) || bad(dLdy, 8) || bad(W1, 2) || bad(W2, 2) || bad(W3, 2) || bad(dLdout, 4) || bad(dW1, 4) ||
+      bad(dW2, 4) || bad(dW3, 4))
     return HG_ERR_INVALID_ARG;
   return hg::launch_mlp_back<hg::MlpMode::kBackward>(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy, dW1, dW2, dW3, 1.0f,
                                                      nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
-}
-
-extern "C" hg_status hashgrid_mlp_bwd_input(uint32_t B, uint32_t n_in, uint32_t n_out, const void* y, const void* W1,
-                                            const void* W2, const void* W3, const float* dLdout, void* dLdy,
-                                            void* stream) {
-  if (B == 0) return HG_OK;
-  const hg_status ok = check_mlp_back(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy);
-  if (ok != HG_OK) return ok;
-  return hg::launch_mlp_back<hg::MlpMode::kInput>(B, n_in, n_out, y, W1, W2, W3, dLdout, dLdy, nullptr, nullptr, nullptr,
-                                                  1.0f, nullptr, nullptr, nullptr, static_cast<hipStream_t>(stream));
 }

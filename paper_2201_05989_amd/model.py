@@ -1,7 +1,7 @@
 """The paper's model as one object (Section 4): the encoding followed by the 64-64 ReLU network, trained with Adam on
-tables and weights.  Bookkeeping only: a training iteration is one call into the C-ABI library (hashgrid_train_step), the
-gradient with respect to the position three (hashgrid_encode_mlp_fwd_train, hashgrid_mlp_bwd_input,
-hashgrid_encode_bwd_input); this file allocates the buffers and keeps the step counter.
+tables and weights.  Bookkeeping only: a training iteration is one call into the C-ABI library (hashgrid_train_step), and so are the
+output at a batch of points and its gradient with respect to the position; this file allocates the buffers and keeps the
+step counter.
 
 Defaults are the paper's (Section 4, "Initialization" and "Training"): tables U(-1e-4, 1e-4) in half precision behind a
 full-precision master copy, Glorot-uniform weights, Adam with beta1 = 0.9, beta2 = 0.99, eps = 1e-15, an L2 factor
@@ -14,7 +14,7 @@ import math
 import torch
 
 from .binding import (_LOSSES, HG_TRAIN_SCRATCH_BYTES, HashGrid, HashGridError, _dev, hashgrid_adam_config,
-                      hashgrid_train_state, mlp_bwd_input)
+                      hashgrid_train_state)
 
 N_HIDDEN = 64
 
@@ -57,7 +57,6 @@ class HashGridModel:
 
     def _buffers(self, B: int):
         if B != self._buf_B:
-            self._out = torch.empty((B, self.n_out), device="cuda")
             self._y = torch.empty((B, self.n_in), dtype=torch.float16, device="cuda")
             self._dy = torch.empty_like(self._y)
             self._buf_B = B
@@ -69,12 +68,8 @@ class HashGridModel:
     def input_gradient(self, x: torch.Tensor, dLdout: torch.Tensor | None = None) -> torch.Tensor:
         """d(sum_i dLdout_i * out_i) / dx [B, d] fp32: with the default dLdout = 1 and one output, the gradient of the
         output with respect to the position (the normal of a signed distance function, Section 3: the encoding is
-        continuous and its derivative piecewise constant).  Three calls: the fused forward keeping y, the network's
-        backward pass without weight gradients, hashgrid_encode_bwd_input."""
-        self._buffers(x.shape[0])
-        self.grid.encode_mlp_fwd(x, self.tables_half, *self._W, self._out, y=self._y)
-        mlp_bwd_input(self._y, *self._W, dLdout, self._dy)
-        return self.grid.encode_bwd_input(x, self.tables_half, self._dy)
+        continuous and its derivative piecewise constant)."""
+        return self.grid.encode_mlp_bwd_input(x, self.tables_half, *self._W, dLdout)
 
     def _train_state(self, B: int) -> hashgrid_train_state:
         """The library's view of this model: pointers checked when one of the public tensors has moved, and the

@@ -1,0 +1,80 @@
+"""The encoding with the network behind it, at the sizes where its kernels change: batches below and above what the split
+kernel takes (40 000 points, 100 000), paced and free-running workgroups (d = 3 or 2, narrow or wide entries, tables within
+or beyond an L2), points in raster and in random order, one to four levels a wave, ragged last blocks.
+
+The fused output must equal the network alone on the features the call keeps, bit for bit (the same instructions on the
+same halves), and the kept features are the encoding's (one rounding to half; ties may fall either way: 2^-10 of the
+value).  The gradient with respect to the position is held to the three calls it stands for where nothing rounds
+(integer tables and weights, points whose fractional positions are 0 and 1/2: every product and sum is exact)."""
+import pytest
+import torch
+
+from paper_2201_05989_amd import HashGrid, mlp_bwd, mlp_fwd
+
+pytestmark = pytest.mark.gpu
+
+
+def network(n_in, n_out, gen, integers):
+    shapes = ((64, n_in), (64, 64), (n_out, 64))
+    if not integers:
+        return [torch.randn(s, device="cuda", generator=gen).mul_(0.2).half() for s in shapes]
+    return [(torch.randint(-1, 2, s, device="cuda", generator=gen) * (torch.rand(s, device="cuda", generator=gen) < 0.2)).half()
+            for s in shapes]
+
+
+@pytest.mark.parametrize("d,L,F,T,N_max,n_out,B,order,interp", [
+    (3, 16, 2, 1 << 19, 2048, 3, 1, "random", 0),
+    (3, 16, 2, 1 << 19, 2048, 3, 39999, "random", 0),
+    (3, 16, 2, 1 << 19, 2048, 4, 40001, "random", 0),      # paced, workgroups of a few waves
+    (3, 16, 2, 1 << 14, 512, 1, 300007, "random", 1),      # paced, full workgroups, several blocks each
+    (3, 16, 4, 1 << 14, 512, 17, 100001, "random", 0),     # free-running, 64 features
+    (3, 8, 8, 1 << 18, 512, 32, 70001, "random", 0),       # paced, eight features an entry, 64 features
+    (3, 32, 1, 1 << 12, 256, 2, 70003, "random", 0),       # split, four levels a wave
+    (3, 32, 2, 1 << 12, 256, 2, 5, "random", 0),
+    (2, 16, 2, 1 << 18, 4096, 3, 100000, "raster", 0),     # split at the last batch it takes
+    (2, 16, 2, 1 << 18, 4096, 3, 262145, "raster", 0),     # free-running
+    (2, 16, 2, 1 << 18, 4096, 16, 262145, "random", 1),    # paced by the order of the points
+    (2, 12, 2, 1 << 14, 300, 4, 150001, "raster", 1),      # 24 features: a ragged operand
+    (2, 8, 8, 1 << 14, 300, 9, 130001, "raster", 0),
+    (2, 8, 1, 1 << 10, 64, 1, 110001, "random", 0),        # eight features in all
+])
+def test_fused_output_is_the_network_on_the_kept_features(d, L, F, T, N_max, n_out, B, order, interp):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    grid = HashGrid(d, L, F, T, 16, N_max, "f16", "f16", interp)
+    theta = torch.randn((grid.n_entries, F), device="cuda", generator=gen).half()
+    x = torch.rand((B, d), device="cuda", generator=gen)
+    if order == "raster":
+        i = torch.arange(B, device="cuda")
+        x = torch.stack([(i % 640) / 640.0, (i // 640) / (B // 640 + 1.0)], dim=1).contiguous()
+    W = network(L * F, n_out, gen, False)
+    y = torch.full((B, L * F), float("nan"), dtype=torch.float16, device="cuda")
+    out = grid.encode_mlp_fwd(x, theta, *W, torch.full((B, n_out), float("nan"), device="cuda"), y=y)
+    assert torch.equal(out, mlp_fwd(y, *W))
+    assert torch.equal(out, grid.encode_mlp_fwd(x, theta, *W))
+    ref = grid.encode_fwd(x, theta).float()
+    assert ((y.float() - ref).abs() <= 2.0 ** -10 * ref.abs() + 1e-7).all()
+
+
+@pytest.mark.parametrize("d,L,F,T,n_out,B,interp", [(3, 8, 2, 1 << 14, 1, 1, 0), (3, 8, 4, 1 << 14, 1, 65, 0), (2, 8, 8, 1 << 12, 3, 1000, 0),
+                                                    (3, 7, 8, 1 << 14, 32, 777, 0), (2, 12, 2, 1 << 20, 17, 40001, 0),
+                                                    (3, 16, 1, 1 << 12, 9, 3001, 1), (2, 24, 1, 1 << 12, 2, 130, 0)])
+def test_position_gradient_equals_the_three_calls_where_nothing_rounds(d, L, F, T, n_out, B, interp):
+    gen = torch.Generator(device="cuda").manual_seed(100 + B)
+    grid = HashGrid(d, L, F, T, 4, 4 << (min(L, 12) - 1), "f16", "f16", interp)
+    exact = all(l.N & (l.N - 1) == 0 for l in grid.levels())  # else fractional positions round: compared with a tolerance
+    theta = torch.randint(-1, 2, (grid.n_entries, F), device="cuda", generator=gen).half()
+    x = ((2 * torch.randint(0, 4, (B, d), device="cuda", generator=gen) + 1).float() / 8).contiguous()
+    W = network(L * F, n_out, gen, True)
+    for dout in (None, torch.randint(-4, 5, (B, n_out), device="cuda", generator=gen) / 4.0):
+        y = torch.empty((B, L * F), dtype=torch.float16, device="cuda")
+        dy = torch.empty_like(y)
+        grid.encode_mlp_fwd(x, theta, *W, y=y)
+        dW = [torch.zeros(w.shape, device="cuda") for w in W]
+        mlp_bwd(y, *W, torch.ones((B, n_out), device="cuda") if dout is None else dout, dy, *dW)
+        want = grid.encode_bwd_input(x, theta, dy)
+        got = grid.encode_mlp_bwd_input(x, theta, *W, dout, torch.full((B, d), float("nan"), device="cuda"))
+        assert B == 1 or want.abs().max() > 1
+        if exact:
+            assert torch.equal(got, want)
+        else:  # fp32 sums over the levels in two orders; a half that rounds the other way moves the sum by 2^-11 of a level
+            assert ((got - want).abs() <= 2.0 ** -9 * want.abs().max()).all()

@@ -115,18 +115,3 @@ def test_nan_in_the_targets_reaches_the_entries_as_in_the_single_calls():
     assert torch.equal(torch.isnan(m.tables), torch.isnan(want[0]))
     ok = ~torch.isnan(want[0])
     assert torch.equal(m.tables[ok], want[0][ok])
-
-
-@pytest.mark.parametrize("n_in,n_out,B", [(8, 1, 1), (32, 1, 4097), (64, 32, 257), (40, 9, 70001)])
-def test_mlp_bwd_input_is_mlp_bwd_without_the_weight_gradients(n_in, n_out, B):
-    from paper_2201_05989_amd import mlp_bwd_input
-    gen = torch.Generator(device="cuda").manual_seed(B)
-    y = torch.randn((B, n_in), device="cuda", generator=gen).half()
-    W = [torch.randn(s, device="cuda", generator=gen).mul_(0.2).half() for s in ((64, n_in), (64, 64), (n_out, 64))]
-    dout = torch.randn((B, n_out), device="cuda", generator=gen)
-    dW = [torch.zeros(w.shape, device="cuda") for w in W]
-    for given in (dout, None):
-        a, b = torch.empty_like(y), torch.full_like(y, float("nan"))
-        mlp_bwd(y, *W, dout if given is not None else torch.ones_like(dout), a, *dW)
-        mlp_bwd_input(y, *W, given, b)
-        assert torch.equal(a, b)
