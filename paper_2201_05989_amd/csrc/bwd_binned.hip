@@ -83,11 +83,11 @@ static_assert(kChunkLog2 <= 12, "a record holds a 12-bit local index");
 
 struct Workspace {
   uint32_t* counts;     // [n_tiles + 1][n_bins] counts, then exclusive prefix over tiles (last row: totals)
-  uint32_t* bin_start;  // [n_bins] first record of the bin
+  uint4* items;         // [accumulate work items] what a workgroup of that pass needs to know of each (Item)
   uint32_t* bin_total;  // [n_bins] records in the bin
   float* tile_max;      // [n_tiles * parts of the scatter grid (at most L)] largest |dL/dy| seen by each scatter workgroup
   uint32_t* item_counter;  // [1] next work item of the accumulate pass
-  uint32_t* chunk_done;    // [n_bins] workgroups that have added their share of a chunk (accumulate pass with the optimiser)
+  uint32_t* chunk_open;    // [n_bins] workgroups that have yet to add their share of a chunk (accumulate pass with the optimiser)
   uint32_t* records;    // [B * L * rec_per_point] records (Record::kWords words each)
   uint32_t n_tiles;
   uint32_t n_bins;
@@ -101,6 +101,30 @@ static uint32_t tiles_for(const BinPlan& bp, uint32_t B) {
   return (uint32_t)(((uint64_t)B + points - 1) / points);
 }
 
+// Slices per bin of each level for a batch of B points: coarse 1:1 levels have
+// few bins and receive B * 2^(d-1) records, so their bins are shared by several
+// accumulate-workgroups.
+static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B) {
+  uint32_t wgs = 0;
+  for (uint32_t l = 0; l < lv.L; ++l) {
+    const uint32_t nb = bp.bin_base[l + 1] - bp.bin_base[l];
+    const uint64_t per_bin = ((uint64_t)B * bp.rec_per_point + nb - 1) / nb;
+    uint64_t s = (per_bin + kTargetRecordsPerAccWg - 1) / kTargetRecordsPerAccWg;
+    if (!((lv.dense_mask >> l) & 1u) && s < 4) s = 1;  // hashed bins are evenly filled
+    if (s > 256) s = 256;
+    bp.slices[l] = (uint32_t)(s < 1 ? 1 : s);
+    bp.wg_base[l] = wgs;
+    wgs += nb * bp.slices[l];
+  }
+  bp.wg_base[lv.L] = wgs;
+}
+
+static uint64_t max_items(const hashgrid* h, uint32_t B) {
+  BinPlan bp = h->bp;
+  plan_slices(bp, h->lv, B);
+  return bp.wg_base[h->lv.L];
+}
+
 static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* ws) {
   const uint32_t nt = tiles_for(h->bp, B), nb = h->bp.bin_base[h->lv.L];
   uint64_t off = 0;
@@ -109,17 +133,17 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     off = align_up(off + bytes, 256);
     return o;
   };
-  const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_start = take((uint64_t)nb * 4),
-                 o_total = take((uint64_t)nb * 4), o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4), o_done = take((uint64_t)nb * 4),
+  const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_items = take(max_items(h, B) * 16),
+                 o_total = take((uint64_t)nb * 4), o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4), o_open = take((uint64_t)nb * 4),
                  o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point *
                               (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u));
   if (ws) {
     ws->counts = reinterpret_cast<uint32_t*>(base + o_counts);
-    ws->bin_start = reinterpret_cast<uint32_t*>(base + o_start);
+    ws->items = reinterpret_cast<uint4*>(base + o_items);
     ws->bin_total = reinterpret_cast<uint32_t*>(base + o_total);
     ws->tile_max = reinterpret_cast<float*>(base + o_max);
     ws->item_counter = reinterpret_cast<uint32_t*>(base + o_item);
-    ws->chunk_done = reinterpret_cast<uint32_t*>(base + o_done);
+    ws->chunk_open = reinterpret_cast<uint32_t*>(base + o_open);
     ws->records = reinterpret_cast<uint32_t*>(base + o_rec);
     ws->n_tiles = nt;
     ws->n_bins = nb;
@@ -190,24 +214,6 @@ void build_bin_plan(hashgrid* h) {
   bp.scatter_parts = bp.tile_mult > 1 ? parts_for(kMaxParts, kMaxDirectPartBins) : parts_for(kMaxParts, kMaxScatterPartBins);
   if (!bp.count_parts || !bp.scatter_parts) return;
   bp.supported = 1;
-}
-
-// Slices per bin of each level for a batch of B points: coarse 1:1 levels have
-// few bins and receive B * 2^(d-1) records, so their bins are shared by several
-// accumulate-workgroups.
-static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B) {
-  uint32_t wgs = 0;
-  for (uint32_t l = 0; l < lv.L; ++l) {
-    const uint32_t nb = bp.bin_base[l + 1] - bp.bin_base[l];
-    const uint64_t per_bin = ((uint64_t)B * bp.rec_per_point + nb - 1) / nb;
-    uint64_t s = (per_bin + kTargetRecordsPerAccWg - 1) / kTargetRecordsPerAccWg;
-    if (!((lv.dense_mask >> l) & 1u) && s < 4) s = 1;  // hashed bins are evenly filled
-    if (s > 256) s = 256;
-    bp.slices[l] = (uint32_t)(s < 1 ? 1 : s);
-    bp.wg_base[l] = wgs;
-    wgs += nb * bp.slices[l];
-  }
-  bp.wg_base[lv.L] = wgs;
 }
 
 // ------------------------------------------------------------------ device
@@ -364,7 +370,7 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
                                                          uint32_t* __restrict__ counts,
                                                          uint32_t* __restrict__ bin_total,
                                                          uint32_t* __restrict__ item_counter,
-                                                         uint32_t* __restrict__ chunk_done, const LevelTable lv,
+                                                         const LevelTable lv,
                                                          const uint32_t zero_mask, const uint32_t F,
                                                          void* __restrict__ grad, const bool g16, const SideJob job) {
   __shared__ uint32_t seg_sum[kScanThreads];
@@ -415,7 +421,6 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
     }
     if (seg == 0) {
       bin_total[gb] = total;
-      chunk_done[gb] = 0;
       col[(uint64_t)n_tiles * n_bins] = total;  // closes the prefix: count of tile t = row t+1 - row t
     }
     uint32_t run = pre;
@@ -438,6 +443,39 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
   }
 }
 
+// A work item of the accumulate pass, written by the scatter workgroups of the first tile (they know where the bins
+// start) so that the accumulate pass reads 16 bytes an item instead of searching the plan's level table and chasing the
+// bin's start and count: with a table of 2^22 entries a level an item is 1100 records, and that chain was most of its 5 us.
+//   .x, .y  first record, one past the last;  .z  first entry of the chunk in the tables
+//   .w      bits 0-11 entries of the chunk minus 1, 12-16 level, 17 1:1 index map (lb = la + 1), 18 the chunk is
+//           shared by several workgroups (not set for the first share of an empty one), 19 it has records, 20-31 chunk of the level
+constexpr uint32_t kItemDense = 1u << 17, kItemShared = 1u << 18, kItemLive = 1u << 19;
+static_assert(kMaxLevelBins <= 1u << 12 && HG_MAX_LEVELS <= 32, "an item's last word");
+__device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan& bp, const uint32_t l0, const uint32_t l1,
+                                            const uint32_t gb, const uint32_t start, const uint32_t total,
+                                            uint4* __restrict__ items, uint32_t* __restrict__ chunk_open) {
+  uint32_t l = l0;
+  while (l + 1 < l1 && gb >= bp.bin_base[l + 1]) ++l;
+  const uint32_t bin = gb - bp.bin_base[l], n_sl = bp.slices[l], per = (total + n_sl - 1) / n_sl;
+  const bool dense = ((lv.dense_mask >> l) & 1u) && !bp.corner_records;  // (corner records: every level in aligned blocks)
+  uint32_t e0, e1;
+  if (dense) {
+    e0 = (bin << bp.row_shift[l]) * lv.verts[l];
+    e1 = e0 + (lv.verts[l] << bp.row_shift[l]);
+  } else {
+    e0 = bin << bp.chunk_log2;
+    e1 = e0 + (1u << bp.chunk_log2);
+  }
+  if (e1 > lv.size[l]) e1 = lv.size[l];
+  chunk_open[gb] = per ? (total + per - 1) / per : 1u;
+  const uint32_t w = (e1 - e0 - 1u) | (l << 12) | (dense ? kItemDense : 0u) | (bin << 20);
+  for (uint32_t k = 0; k < n_sl; ++k) {
+    const uint32_t r0 = k * per < total ? k * per : total, r1 = r0 + per < total ? r0 + per : total;
+    items[bp.wg_base[l] + bin * n_sl + k] =
+        make_uint4(start + r0, start + r1, (uint32_t)lv.offset[l] + e0, w | (r0 < r1 ? kItemLive : 0u) | (n_sl > 1 && (k || total) ? kItemShared : 0u));
+  }
+}
+
 // scatter: writes every record to its slot.  A bin's first record is the sum of
 // the record counts of all bins before it (every level holds exactly
 // B * rec_per_point records, so this is also level-major); inside a bin the
@@ -457,7 +495,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
                                                            const IT* __restrict__ dy,
                                                            const uint32_t* __restrict__ counts,
                                                            const uint32_t* __restrict__ bin_total,
-                                                           uint32_t* __restrict__ bin_start,
+                                                           uint4* __restrict__ items, uint32_t* __restrict__ chunk_open,
                                                            uint32_t* __restrict__ records, const uint32_t n_bins,
                                                            const uint32_t n_records, const uint32_t n_tiles,
                                                            float* __restrict__ tile_max, void* __restrict__ grad, const bool g16) {
@@ -503,7 +541,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   block_exclusive_scan<kBinThreads>(local, nbp + 1, scan_tmp);
   for (uint32_t i = threadIdx.x; i < nbp; i += kBinThreads) {
     const uint32_t f = before + delta[i];  // first record of the bin
-    if (tile == 0) bin_start[gb_a + i] = f;
+    if (tile == 0) write_items(lv, bp, l0, l1, gb_a + i, f, bin_total[gb_a + i], items, chunk_open);
     cur[i] = local[i];
     delta[i] = f + row0[i] - local[i];  // wrap-around arithmetic; undone when a position is added
   }
@@ -626,7 +664,7 @@ template <int D, typename IT, int F, bool CROSS, bool CORNERS = false>
 __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
     const LevelTable lv, const BinPlan bp, const bool smooth, const uint32_t B, const float* __restrict__ x,
     const IT* __restrict__ dy, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ bin_total,
-    uint32_t* __restrict__ bin_start, uint32_t* __restrict__ records, const uint32_t n_bins, const uint32_t n_records,
+    uint4* __restrict__ items, uint32_t* __restrict__ chunk_open, uint32_t* __restrict__ records, const uint32_t n_bins, const uint32_t n_records,
     const uint32_t n_tiles, float* __restrict__ tile_max, void* __restrict__ grad, const bool g16) {
   constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
   using Rec = Record<IT, F>;
@@ -656,7 +694,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
   const uint32_t* row0 = counts + (uint64_t)tile * n_bins + gb_a;  // prefix over the tiles before this one
   for (uint32_t i = threadIdx.x; i < nbp; i += kBinThreads) {
     const uint32_t f = before + slot[i];
-    if (tile == 0) bin_start[gb_a + i] = f;
+    if (tile == 0) write_items(lv, bp, l0, l1, gb_a + i, f, bin_total[gb_a + i], items, chunk_open);
     slot[i] = f + row0[i];
   }
   __syncthreads();
@@ -759,20 +797,19 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
 // their own to read back with everything else (the step's largest streams are the two moments and the master copy:
 // 34 bytes a scalar, against 8 for the gradient's round trip), and those streams run beside the
 // LDS work of this kernel.  `grad` is then an array that is zero before and after: the workgroups that share a chunk add their
-// sums into it, and the last one to arrive (chunk_done) takes them out again and applies them, as does the owner of
+// sums into it, and the last one to arrive (chunk_open) takes them out again and applies them, as does the owner of
 // a chunk with what the straddling pairs left there.
 struct NoAdam {};
 struct AdamOut {
   AdamArgs a;
   AdamState st;
-  uint32_t* chunk_done;
+  uint32_t* chunk_open;
   uint32_t cross_mask;  // levels whose straddling pairs were added to grad by the scatter pass
 };
 template <typename IT, int F, bool SMOOTH, typename GT = float, bool ADAM = false>
 __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable lv, const BinPlan bp,
                                                               const uint32_t B, const uint32_t n_items,
-                                                              const uint32_t* __restrict__ bin_start,
-                                                              const uint32_t* __restrict__ bin_total,
+                                                              const uint4* __restrict__ items,
                                                               const float* __restrict__ tile_max,
                                                               const uint32_t n_max,
                                                               const uint32_t* __restrict__ records,
@@ -834,23 +871,13 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   __syncthreads();
   uint32_t next = s_ticket;  // every item number of n_items or more ends the loop, and tickets only grow
 
-  // which level, bin and slice an item is
-  auto decode = [&](uint32_t item, uint32_t& l, uint32_t& bin, uint32_t& slice) {
-    l = 0;
-    while (l + 1 < lv.L && item >= bp.wg_base[l + 1]) ++l;
-    const uint32_t k = item - bp.wg_base[l];
-    bin = k / bp.slices[l];
-    slice = k - bin * bp.slices[l];
-  };
-
   // Everything an item needs before its records can be used: where they are, which chunk of
   // the gradient it owns, and (software pipeline) its first kPre records per lane and its
   // gradient chunk, both requested while the previous item is still being flushed.
   struct Item {
-    uint32_t l, n_sl, r0, r1, n_e;
-    uint32_t bin, live_slices;  // chunk of the level, and how many of its n_sl slices have records
+    uint32_t l, r0, r1, n_e, bin;
     GT* gl;
-    bool live, dense;
+    bool live, dense, shared;
     bool orphan;  // ADAM: no records, but straddling pairs may have added to the chunk in grad
   };
   using Rec = Record<IT, F>;
@@ -860,36 +887,21 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   // flight as well, so the chunk is read when it is flushed and fewer records are unrolled
   constexpr bool kChunkAhead = F <= 2;
   constexpr int kUnroll = F <= 2 ? kAccUnroll : 2;
-  auto describe = [&](uint32_t item, uint32_t start, uint32_t total, uint32_t l, uint32_t bin, uint32_t slice) {
+  auto describe = [&](const uint4 d, const bool exists) {
     Item it;
-    it.l = l;
-    it.n_sl = bp.slices[l];
-    it.bin = bin;
-    const uint32_t per = (total + it.n_sl - 1) / it.n_sl;
+    it.l = (d.w >> 12) & 31u;
+    it.bin = d.w >> 20;
+    it.live = exists && (d.w & kItemLive);
+    it.dense = d.w & kItemDense;
+    it.shared = d.w & kItemShared;
+    // (within the records for counts that belong to these points; the bound keeps a caller who passed HG_BWD_COUNTED over
+    // the counts of another batch from reading outside them)
+    it.r0 = d.x < n_records ? d.x : n_records;
+    it.r1 = d.y < n_records ? d.y : n_records;
+    it.n_e = (d.w & 0xfffu) + 1u;
+    it.gl = grad + (uint64_t)d.z * F;
     it.orphan = false;
-    if constexpr (ADAM) {
-      it.live_slices = per ? (total + per - 1) / per : 1u;
-      it.orphan = item < n_items && total == 0 && slice == 0 && ((ad.cross_mask >> l) & 1u);
-    }
-    it.r0 = start + slice * per;
-    it.r1 = (slice * per + per < total) ? it.r0 + per : start + total;
-    // true for counts that belong to these points; keeps a caller who passed HG_BWD_COUNTED over
-    // the counts of another batch from reading outside the records
-    it.r0 = it.r0 < n_records ? it.r0 : n_records;
-    it.r1 = it.r1 < n_records ? it.r1 : n_records;
-    it.live = item < n_items && slice * per < total;
-    uint32_t e0, e1;  // entries of this chunk in the level's slice
-    it.dense = ((lv.dense_mask >> l) & 1u) && !bp.corner_records;  // (corner records: every level in aligned blocks)
-    if (it.dense) {
-      e0 = (bin << bp.row_shift[l]) * lv.verts[l];
-      e1 = e0 + (lv.verts[l] << bp.row_shift[l]);
-    } else {
-      e0 = bin << cl;
-      e1 = e0 + cap;
-    }
-    if (e1 > lv.size[l]) e1 = lv.size[l];
-    it.n_e = e1 - e0;
-    it.gl = grad + (lv.offset[l] + e0) * F;
+    if constexpr (ADAM) it.orphan = exists && !(d.w & (kItemLive | kItemShared)) && ((ad.cross_mask >> it.l) & 1u);
     return it;
   };
   // records j0..j1-1 of each lane's share of the item
@@ -905,7 +917,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   auto overwrites = [&](const Item& it) { return ((overwrite_mask >> it.l) & 1u) != 0; };  // uniform
   auto request_chunk = [&](const Item& it, Entry (&cur)[kPer]) {
     if (ADAM || !kChunkAhead || !it.live || !finite || overwrites(it)) return;
-    if (it.n_sl == 1) {
+    if (!it.shared) {
 #pragma unroll
       for (int j = 0; j < kPer; ++j) {
         const uint32_t e = threadIdx.x + j * kAccThreads;
@@ -915,13 +927,8 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   };
 
   uint32_t item = blockIdx.x;
-  uint32_t l = 0, bin = 0, slice = 0, start = 0, total = 0;
-  if (item < n_items) {
-    decode(item, l, bin, slice);
-    start = bin_start[bp.bin_base[l] + bin];
-    total = bin_total[bp.bin_base[l] + bin];
-  }
-  Item it = describe(item, start, total, l, bin, slice);
+  auto item_at = [&](const uint32_t i) { return i < n_items ? items[i] : make_uint4(0u, 0u, 0u, 0u); };  // uniform
+  Item it = describe(item_at(item), item < n_items);
   Stored pre[kPre];
   Entry cur[kPer];
   request_records(it, pre, 0, kPre);
@@ -930,12 +937,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     // the item after the next one, and the offsets of the next one: in flight while this one is processed
     uint32_t ticket = 0;
     if (threadIdx.x == 0) ticket = draw();
-    uint32_t l_n = 0, bin_n = 0, slice_n = 0, start_n = 0, total_n = 0;
-    if (next < n_items) {
-      decode(next, l_n, bin_n, slice_n);
-      start_n = bin_start[bp.bin_base[l_n] + bin_n];
-      total_n = bin_total[bp.bin_base[l_n] + bin_n];
-    }
+    const uint4 desc_n = item_at(next);
     Item it_n;
     it_n.live = it_n.orphan = false;
     Entry cur_n[kPer];
@@ -963,10 +965,10 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
           if (lb < it.n_e) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
         }
       }
-      it_n = describe(next, start_n, total_n, l_n, bin_n, slice_n);
+      it_n = describe(desc_n, next < n_items);
     } else if (!it.live) {
       if (overwrites(it)) clear_chunk(it);  // no records for this chunk (item < n_items inside the loop)
-      it_n = describe(next, start_n, total_n, l_n, bin_n, slice_n);
+      it_n = describe(desc_n, next < n_items);
       request_records(it_n, pre, 0, kPre);
       request_chunk(it_n, cur_n);
     } else {
@@ -991,7 +993,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
 #pragma unroll
       for (int j = 0; j < kHalf; ++j)
         if (it.r0 + threadIdx.x + j * kAccThreads < it.r1) add_record(pre[j]);
-      it_n = describe(next, start_n, total_n, l_n, bin_n, slice_n);
+      it_n = describe(desc_n, next < n_items);
       request_records(it_n, pre, 0, kHalf);
 #pragma unroll
       for (int j = kHalf; j < kPre; ++j)
@@ -1013,7 +1015,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     // ADAM: the chunk's master values and moments, requested before the barrier that ends the summation.  Where the
     // chunk's records are few most entries get none, and only those that do are read (and below, written).
     const uint64_t at0 = ADAM ? (uint64_t)(it.gl - grad) / F : 0;
-    const bool whole = ADAM && kChunkAhead && it.live && finite && it.n_sl == 1 && (it.r1 - it.r0) * 4 >= it.n_e;  // uniform
+    const bool whole = ADAM && kChunkAhead && it.live && finite && !it.shared && (it.r1 - it.r0) * 4 >= it.n_e;  // uniform
     [[maybe_unused]] Entry pp[kPer], m1[kPer], m2[kPer];
     if constexpr (ADAM) {
       if (whole) {
@@ -1031,7 +1033,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     __syncthreads();
     const uint32_t after_next = s_ticket;  // written before the barrier above, rewritten only after the one below
     if (it.live && finite) {
-      if (it.n_sl == 1) {
+      if (!it.shared) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           const uint32_t e = threadIdx.x + j * kAccThreads;
@@ -1119,7 +1121,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
       }
     }
     if constexpr (ADAM) {
-      if ((it.live && (it.n_sl > 1 || !finite)) || it.orphan) {  // uniform: the sums of this chunk meet in grad
+      if ((it.live && (it.shared || !finite)) || it.orphan) {  // uniform: the sums of this chunk meet in grad
         __shared__ uint32_t s_last;
         // This workgroup's additions are performed before it is counted: every wave waits for its own.  They, the
         // counter and the exchanges below are all device-scope atomics, which meet behind the caches, so
@@ -1129,8 +1131,8 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         asm volatile("" ::: "memory");
         __syncthreads();
         if (threadIdx.x == 0)
-          s_last = __hip_atomic_fetch_add(&ad.chunk_done[bp.bin_base[it.l] + it.bin], 1u, __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_AGENT) + 1u == it.live_slices;
+          s_last = __hip_atomic_fetch_sub(&ad.chunk_open[bp.bin_base[it.l] + it.bin], 1u, __ATOMIC_RELAXED,
+                                          __HIP_MEMORY_SCOPE_AGENT) == 1u;
         __syncthreads();
         if (s_last) {  // every other workgroup with records of this chunk has been counted
           for (uint32_t e = threadIdx.x; e < it.n_e; e += kAccThreads) {
@@ -1288,7 +1290,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const bool defer_cross = overwrite && cross_mask != 0;  // those atomic adds then follow the accumulate pass
   const SideJob job = ba ? ba->job : SideJob{};
   hipLaunchKernelGGL(bin_scan, dim3((ws.n_bins + kScanBins - 1) / kScanBins + job.blocks), dim3(kScanThreads), 0, s,
-                     ws.n_tiles, ws.n_bins, ws.counts, ws.bin_total, ws.item_counter, ws.chunk_done, h->lv, zero_mask,
+                     ws.n_tiles, ws.n_bins, ws.counts, ws.bin_total, ws.item_counter, h->lv, zero_mask,
                      (uint32_t)F, grad, g16, job);
   auto scatter = [&](auto cross) {
     constexpr bool kCross = decltype(cross)::value;
@@ -1296,12 +1298,12 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     if (bp.tile_mult > 1 || !kStaged) {
       hipLaunchKernelGGL((bin_scatter_direct<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
                          dim3(kBinThreads), (size_t)max_part_bins(parts) * 4, s, h->lv, bp, smooth, B, x,
-                         static_cast<const IT*>(dy), ws.counts, ws.bin_total, ws.bin_start, ws.records, ws.n_bins,
+                         static_cast<const IT*>(dy), ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins,
                          n_records, ws.n_tiles, ws.tile_max, grad, g16);
     } else if constexpr (kStaged) {
       hipLaunchKernelGGL((bin_scatter<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
                          dim3(kBinThreads), lds_scatter, s, h->lv, bp, smooth, B, x, static_cast<const IT*>(dy),
-                         ws.counts, ws.bin_total, ws.bin_start, ws.records, ws.n_bins, n_records, ws.n_tiles,
+                         ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins, n_records, ws.n_tiles,
                          ws.tile_max, grad, g16);
     }
   };
@@ -1321,7 +1323,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   auto accumulate = [&](auto smooth_t, auto* g) {
     using GT = typename std::remove_pointer<decltype(g)>::type;
     hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT>), acc_grid, dim3(kAccThreads), kAccLds, s,
-                       h->lv, bp, B, n_items, ws.bin_start, ws.bin_total, ws.tile_max, ws.n_tiles * parts, ws.records,
+                       h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts, ws.records,
                        ws.item_counter, g, overwrite_mask, NoAdam{});
   };
   if constexpr (kAdam) {
@@ -1329,12 +1331,11 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
       AdamOut out;
       out.a = ba->a;
       out.st = ba->st;
-      out.chunk_done = ws.chunk_done;
+      out.chunk_open = ws.chunk_open;
       out.cross_mask = cross_mask;
       auto accumulate_adam = [&](auto smooth_t) {
         hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, float, true>), acc_grid, dim3(kAccThreads),
-                           kAccLds, s, h->lv, bp, B, n_items, ws.bin_start, ws.bin_total, ws.tile_max, ws.n_tiles * parts,
-                           ws.records, ws.item_counter, static_cast<float*>(grad), 0u, out);
+                           kAccLds, s, h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts, ws.records, ws.item_counter, static_cast<float*>(grad), 0u, out);
       };
       if (smooth) accumulate_adam(std::true_type{});
       else accumulate_adam(std::false_type{});
