@@ -83,12 +83,12 @@ static_assert(kChunkLog2 <= 12, "a record holds a 12-bit local index");
 
 struct Workspace {
   uint32_t* counts;     // [n_tiles + 1][n_bins] counts, then exclusive prefix over tiles (last row: totals)
-  uint4* items;         // [accumulate work items] what a workgroup of that pass needs to know of each (Item)
   uint32_t* bin_total;  // [n_bins] records in the bin
   float* tile_max;      // [n_tiles * parts of the scatter grid (at most L)] largest |dL/dy| seen by each scatter workgroup
   uint32_t* item_counter;  // [1] next work item of the accumulate pass
   uint32_t* chunk_open;    // [n_bins] workgroups that have yet to add their share of a chunk (accumulate pass with the optimiser)
   uint32_t* records;    // [B * L * rec_per_point] records (Record::kWords words each)
+  uint4* items;         // [accumulate work items] what a workgroup of that pass needs to know of each (write_items)
   uint32_t n_tiles;
   uint32_t n_bins;
 };
@@ -125,7 +125,8 @@ static uint64_t max_items(const hashgrid* h, uint32_t B) {
   return bp.wg_base[h->lv.L];
 }
 
-static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* ws) {
+// Bytes of the workspace; before_items: those in front of the item list, which is last.
+static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* ws, uint64_t* before_items = nullptr) {
   const uint32_t nt = tiles_for(h->bp, B), nb = h->bp.bin_base[h->lv.L];
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
@@ -133,18 +134,20 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     off = align_up(off + bytes, 256);
     return o;
   };
-  const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_items = take(max_items(h, B) * 16),
-                 o_total = take((uint64_t)nb * 4), o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4), o_open = take((uint64_t)nb * 4),
+  const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_total = take((uint64_t)nb * 4),
+                 o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4), o_open = take((uint64_t)nb * 4),
                  o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point *
-                              (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u));
+                              (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u)),
+                 o_items = take(max_items(h, B) * sizeof(uint4));
+  if (before_items) *before_items = o_items;
   if (ws) {
     ws->counts = reinterpret_cast<uint32_t*>(base + o_counts);
-    ws->items = reinterpret_cast<uint4*>(base + o_items);
     ws->bin_total = reinterpret_cast<uint32_t*>(base + o_total);
     ws->tile_max = reinterpret_cast<float*>(base + o_max);
     ws->item_counter = reinterpret_cast<uint32_t*>(base + o_item);
     ws->chunk_open = reinterpret_cast<uint32_t*>(base + o_open);
     ws->records = reinterpret_cast<uint32_t*>(base + o_rec);
+    ws->items = reinterpret_cast<uint4*>(base + o_items);
     ws->n_tiles = nt;
     ws->n_bins = nb;
   }
@@ -1497,7 +1500,15 @@ hg_status hashgrid_encode_bwd_ws(const hashgrid_t* hg, uint32_t B, const float* 
 // For callers that cannot allocate (code under HIP graph capture, tight serving loops, harnesses that
 // forbid hipMalloc) and have no workspace to hand over: the scratch of the sorted pass lives in a
 // fixed device array that every GPU holds from the moment the library is loaded.
-static __device__ __align__(256) unsigned char scratch[HG_STATIC_SCRATCH_BYTES];
+//
+// HG_STATIC_SCRATCH_BYTES is what counts and records may take; the item list has room of its own behind them.  A level
+// of n chunks has n * ceil(ceil(B R / n) / kTargetRecordsPerAccWg) items at most (plan_slices), which is below
+// n + n / target + B R / target; 32 levels of 4096 chunks and records of 12 bytes and more make that the bound below.
+constexpr uint64_t kMostBins = (uint64_t)HG_MAX_LEVELS * hg::kMaxLevelBins;
+constexpr uint64_t kMostItems = kMostBins + kMostBins / hg::kTargetRecordsPerAccWg + 1 +
+                                HG_STATIC_SCRATCH_BYTES / 12 / hg::kTargetRecordsPerAccWg + 1;
+constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256;
+static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 namespace hg {
 constexpr int kMaxDevices = 64;
@@ -1527,13 +1538,16 @@ hg_status hashgrid_encode_bwd_static(const hashgrid_t* hg, uint32_t B, const flo
   if (!hg || (flags & ~(uint32_t)HG_BWD_OVERWRITE)) return HG_ERR_INVALID_ARG;
   if (B == 0) return HG_OK;
   const uint64_t need = hashgrid_bwd_workspace_bytes(hg, B);
-  if (need == 0 || need > HG_STATIC_SCRATCH_BYTES) return HG_ERR_UNSUPPORTED;  // batch too large for the fixed array
+  if (need == 0) return HG_ERR_UNSUPPORTED;
+  uint64_t before_items = 0;
+  (void)hg::carve(hg, B, nullptr, nullptr, &before_items);
+  if (before_items > HG_STATIC_SCRATCH_BYTES || need > kStaticBytes) return HG_ERR_UNSUPPORTED;  // batch too large for the fixed array
   void* ws = hg::static_scratch_of_current_device();
   if (!ws) return HG_ERR_DEVICE;
   // every word of the scratch that a kernel reads is written earlier in the same call (counts by
   // bin_count, totals and the work counter by bin_scan, offsets, records and maxima by bin_scatter),
   // so what the previous call left behind needs no clearing
-  return hashgrid_encode_bwd_ws(hg, B, x, dLdy, grad_params, ws, HG_STATIC_SCRATCH_BYTES, flags, stream);
+  return hashgrid_encode_bwd_ws(hg, B, x, dLdy, grad_params, ws, kStaticBytes, flags, stream);
 }
 
 }  // extern "C"

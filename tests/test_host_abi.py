@@ -200,3 +200,17 @@ def test_workspace_size_of_the_sorted_backward_needs_no_device():
     assert binding.HashGrid(3, 2, 2, 1 << 25, 16, 2048).bwd_workspace_bytes(1000) == 0
     assert table1.bwd_workspace_bytes(1 << 27) == 0
     assert table1.bwd_workspace_bytes(0) == 0
+
+
+# the largest batches whose counts and records fit HG_STATIC_SCRATCH_BYTES, from counts (tiles + 1, chunks), totals, open
+# chunks, maxima and records: the list of work items has room of its own and does not lower them
+@pytest.mark.parametrize("d,L,F,T,N_min,N_max,dtype,most", [
+    (3, 16, 2, 1 << 19, 16, 2048, "f16", 86016), (2, 16, 2, 1 << 22, 16, 32768, "f16", 151704),
+    (3, 16, 2, 1 << 24, 16, 1 << 19, "f16", 81347), (3, 16, 2, 1000003, 16, 2048, "f32", 32417),
+    (1, 7, 8, 100, 3, 999, "f32", 119812), (3, 32, 1, 1 << 24, 16, 1 << 19, "f16", 40296)])
+def test_largest_batch_of_the_fixed_scratch(d, L, F, T, N_min, N_max, dtype, most):
+    g = binding.HashGrid(d, L, F, T, N_min, N_max, dtype, dtype)
+    lib = binding.load_library()
+    taken = [lib.hashgrid_encode_bwd_static(g._h, B, None, None, None, 0, None) != binding.HG_ERR_UNSUPPORTED
+             for B in (most, most + 1)]  # (no arrays, perhaps no device: another error, after the size)
+    assert taken == [True, False]
