@@ -45,7 +45,10 @@ class HashGridModel:
         self.steps = 0
         self._loss_sum = torch.zeros(1, dtype=torch.float64, device="cuda")
         self._scratch = torch.empty(HG_TRAIN_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
-        self._state, self._state_of = hashgrid_train_state(), None
+        self._state = hashgrid_train_state(
+            n_out=n_out, tables_adam=hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0),
+            weights_adam=hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0), loss_sum=self._loss_sum.data_ptr(),
+            scratch=self._scratch.data_ptr())
         self._buf_B = 0
 
     def _views(self, flat):
@@ -72,22 +75,19 @@ class HashGridModel:
         return self.grid.encode_mlp_bwd_input(x, self.tables_half, *self._W, dLdout)
 
     def _train_state(self, B: int) -> hashgrid_train_state:
-        """The library's view of this model: pointers checked when one of the public tensors has moved, and the
-        hyper-parameters as they are now."""
-        st = self._state
-        where = (self.tables.data_ptr(), self.tables_half.data_ptr(), self.weights.data_ptr(), self.weights_half.data_ptr())
-        if where != self._state_of:
-            table, n_w = (self.grid.n_entries, self.grid.F), sum(r * c for r, c in self._shapes)
-            for name, t, kind, shape in (("tables", self.tables, torch.float32, table), ("tables_half", self.tables_half, torch.float16, table),
-                                         ("weights", self.weights, torch.float32, (n_w,)),
-                                         ("weights_half", self.weights_half, torch.float16, (n_w,))):
-                setattr(st, name, _dev(t, kind, shape, name))
-            st.tables_m, st.tables_v, st.tables_zeros = (t.data_ptr() for t in (self._tab_m, self._tab_v, self._tab_zeros))
-            st.weights_m, st.weights_v = self._net_m.data_ptr(), self._net_v.data_ptr()
-            st.loss_sum, st.scratch, st.n_out = self._loss_sum.data_ptr(), self._scratch.data_ptr(), self.n_out
-            st.tables_adam = hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0)
-            st.weights_adam = hashgrid_adam_config(0.0, 0.9, 0.99, 1e-15, 0.0)
-            self._state_of = where
+        """The library's view of this model as it is now: tensors that the caller has replaced or loaded count, and are
+        checked, from this call on (3 us of a call; nothing is kept by a tensor's address)."""
+        st, f32, f16 = self._state, torch.float32, torch.float16
+        table, flat = (self.grid.n_entries, self.grid.F), (sum(r * c for r, c in self._shapes),)
+        st.tables = _dev(self.tables, f32, table, "tables")
+        st.tables_half = _dev(self.tables_half, f16, table, "tables_half")
+        st.tables_m = _dev(self._tab_m, f32, table, "first moment of the tables")
+        st.tables_v = _dev(self._tab_v, f32, table, "second moment of the tables")
+        st.tables_zeros = _dev(self._tab_zeros, f32, table, "shared table sums")
+        st.weights = _dev(self.weights, f32, flat, "weights")
+        st.weights_half = _dev(self.weights_half, f16, flat, "weights_half")
+        st.weights_m = _dev(self._net_m, f32, flat, "first moment of the weights")
+        st.weights_v = _dev(self._net_v, f32, flat, "second moment of the weights")
         if self.loss not in _LOSSES:
             raise HashGridError(f"unknown loss {self.loss!r}")
         st.loss, st.loss_scale = _LOSSES[self.loss], self.loss_scale

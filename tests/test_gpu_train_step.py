@@ -11,7 +11,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2201_05989_amd import HashGrid, HashGridModel, adam_step, loss_grad, mlp_bwd
+from paper_2201_05989_amd import HashGridError, HashGridModel, adam_step, loss_grad, mlp_bwd
 
 pytestmark = pytest.mark.gpu
 
@@ -115,3 +115,25 @@ def test_nan_in_the_targets_reaches_the_entries_as_in_the_single_calls():
     assert torch.equal(torch.isnan(m.tables), torch.isnan(want[0]))
     ok = ~torch.isnan(want[0])
     assert torch.equal(m.tables[ok], want[0][ok])
+
+
+def test_tensors_replaced_between_steps_are_checked_and_used():
+    B = 1000
+    m, gen = exact_model(3, 8, 2, 1 << 14, 4, 512, 1, "l2", 0, 5)
+    x, target = torch.rand((B, 3), device="cuda", generator=gen), torch.rand((B, 1), device="cuda", generator=gen)
+    m.step(x, target)
+    moments = [torch.full_like(t, 0.5) for t in (m._tab_m, m._tab_v, m._net_m, m._net_v)]  # a checkpoint's
+    before = [t.clone() for t in moments]
+    old = m._tab_m.clone()
+    kept, (m._tab_m, m._tab_v, m._net_m, m._net_v) = m._tab_m, moments
+    m.step(x, target)
+    assert torch.equal(kept, old)
+    assert all((a != b).any() for a, b in zip(moments, before))
+    for name, bad in (("tables", m.tables[:-1]), ("tables_half", m.tables_half.float()), ("weights", m.weights[:-1]),
+                      ("weights_half", m.weights_half[None])):  # (two of them at the address of the good ones)
+        good = getattr(m, name)
+        setattr(m, name, bad)
+        with pytest.raises(HashGridError):
+            m.step(x, target)
+        setattr(m, name, good)
+    m.step(x, target)
