@@ -360,12 +360,12 @@ hg_status hashgrid_encode_mlp_bwd_input(const hashgrid_t* hg, uint32_t B, const 
 typedef struct {
   uint32_t n_out;      /* network outputs, 1..32 */
   uint32_t loss;       /* hg_loss */
-  float loss_scale;    /* dL/dout is the gradient of the summed loss times this factor */
+  float loss_scale;    /* finite; dL/dout is the gradient of the summed loss times this factor */
   hashgrid_adam_config tables_adam;  /* l2_reg must be 0 */
   hashgrid_adam_config weights_adam; /* l2_reg stands beside the gradient of the summed, scaled loss: a factor
                                       * that stands beside the mean loss times loss_scale * B * n_out */
-  float* tables;       /* [n_entries, F] fp32 master copy, 16-byte aligned (as the next four) */
-  void* tables_half;   /* [n_entries, F] fp16 working copy */
+  float* tables;       /* [n_entries, F] fp32 master copy, 16-byte aligned (as the moments and zeros) */
+  void* tables_half;   /* [n_entries, F] fp16 working copy, 8-byte aligned (F = 8: 16) */
   float* tables_m;     /* [n_entries, F] fp32 moments */
   float* tables_v;
   float* tables_zeros; /* [n_entries, F] fp32 */

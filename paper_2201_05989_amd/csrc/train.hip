@@ -8,6 +8,7 @@
 // Five and four launches of dependent kernels, each 2.6 us after the one before at the earliest and 3 us of the
 // caller's time: one call per pass of the method took eleven and ten, and read and wrote the gradient of every table entry.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "hashgrid.h"
@@ -27,10 +28,11 @@ extern "C" hg_status hashgrid_train_step(const hashgrid_t* hg, const hashgrid_tr
       n_in % 8 != 0 || n_in > 64 || n_out > 32)
     return HG_ERR_UNSUPPORTED;
   if (st->loss != HG_LOSS_L2 && st->loss != HG_LOSS_MAPE) return HG_ERR_INVALID_ARG;
+  if (!(fabsf(st->loss_scale) < INFINITY)) return HG_ERR_INVALID_ARG;
   if (!hg::adam_config_ok(st->tables_adam) || !hg::adam_config_ok(st->weights_adam) || st->tables_adam.l2_reg != 0.0f)
     return HG_ERR_INVALID_ARG;
   auto bad = [](const void* p, uintptr_t a) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & (a - 1)) != 0; };
-  if (bad(x, 4) || bad(target, 4) || bad(y, 16) || bad(dLdy, 16) || bad(st->tables, 16) || bad(st->tables_half, 16) ||
+  if (bad(x, 4) || bad(target, 4) || bad(y, 16) || bad(dLdy, 16) || bad(st->tables, 16) || bad(st->tables_half, c.F * 2 > 8 ? c.F * 2 : 8) ||
       bad(st->tables_m, 16) || bad(st->tables_v, 16) || bad(st->tables_zeros, 16) || bad(st->weights, 4) ||
       bad(st->weights_half, 8) || bad(st->weights_m, 4) || bad(st->weights_v, 4) || bad(st->loss_sum, 8) ||
       bad(st->scratch, 16))

@@ -137,3 +137,18 @@ def test_tensors_replaced_between_steps_are_checked_and_used():
             m.step(x, target)
         setattr(m, name, good)
     m.step(x, target)
+
+
+@pytest.mark.parametrize("F", [1, 2, 4])
+def test_step_takes_and_refuses_what_the_single_calls_do(F):
+    m = HashGridModel(3, 1, L=8, F=F, T=1 << 14, N_min=4, N_max=512, seed=F)
+    x, target = torch.rand((40000, 3), device="cuda"), torch.rand((40000, 1), device="cuda")
+    for n in (100, 40000):  # atomic additions, sorted
+        flat = torch.zeros(m.tables_half.numel() + 4, dtype=torch.float16, device="cuda")
+        m.tables_half = flat[4:].view(m.tables_half.shape).copy_(m.tables)  # 8 bytes past a 16-byte boundary
+        m.step(x[:n], target[:n])
+        assert torch.equal(m.tables_half, m.tables.half()) and not flat[:4].any()
+    for scale in (float("inf"), float("nan")):
+        m.loss_scale = scale
+        with pytest.raises(HashGridError):
+            m.step(x, target)
