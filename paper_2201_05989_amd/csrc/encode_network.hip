@@ -131,11 +131,13 @@ __device__ __forceinline__ void layer(const _Float16* w, const int stride, const
   }
 }
 
-template <int U>
+// BACK: the activations as the way back needs them (relu: zeros are +0, a NaN stays one where its sign is clear), the
+// network's backward pass has the same; the output takes a NaN to 0.
+template <int U, bool BACK>
 __device__ __forceinline__ void hidden_layers(const _Float16* lds, const NetShape& sh, const half8 (&y)[U][2],
                                               half8 (&h1)[U][2], half8 (&h2)[U][2]) {
-  layer<U>(lds, sh.w1_stride, y, sh.k32 / 32, [&](int u, int j, half8 v) { h1[u][j] = relu(v); });
-  layer<U>(lds + sh.o_w2, kHidStride, h1, 2, [&](int u, int j, half8 v) { h2[u][j] = relu(v); });
+  layer<U>(lds, sh.w1_stride, y, sh.k32 / 32, [&](int u, int j, half8 v) { h1[u][j] = BACK ? relu(v) : relu_max(v); });
+  layer<U>(lds + sh.o_w2, kHidStride, h1, 2, [&](int u, int j, half8 v) { h2[u][j] = BACK ? relu(v) : relu_max(v); });
 }
 
 // The network on U times 16 points of a wave, p + 16 u being this lane's (p: the first block's point of lane % 16), row[u] its row
@@ -145,7 +147,7 @@ __device__ __forceinline__ void network(const _Float16* lds, const NetShape& sh,
   half8 y[U][2], h1[U][2], h2[U][2];
 #pragma unroll
   for (int u = 0; u < U; ++u) load_features(row[u], sh, y[u]);
-  hidden_layers<U>(lds, sh, y, h1, h2);
+  hidden_layers<U, false>(lds, sh, y, h1, h2);
   const int g = ((int)threadIdx.x & 63) >> 4;
 #pragma unroll
   for (int T = 0; T < 2; ++T) {
@@ -371,7 +373,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
       } else {
         half8 y[1][2], h1[1][2], h2[1][2], z[1][2];
         load_features(rows + r * stride, sh, y[0]);
-        hidden_layers<1>(lds, sh, y, h1, h2);
+        hidden_layers<1, true>(lds, sh, y, h1, h2);
         // dL/dout, rounded to half as the backward pass of the network rounds it
         const float* d = dout != nullptr ? dout + (p < B ? p : B - 1) * (uint64_t)sh.n_out : nullptr;
 #pragma unroll

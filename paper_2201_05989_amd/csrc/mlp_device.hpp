@@ -57,6 +57,8 @@ __device__ __forceinline__ half8 to_half(const float16v& acc, const int j) {
 __device__ __forceinline__ half8 relu(const half8 v) {
   return __builtin_bit_cast(half8, __builtin_elementwise_max(__builtin_bit_cast(short8v, v), (short8v)0));
 }
+// ReLU for an output that nothing is propagated back from: max(v, 0) as the floating-point maximum has it, NaN to 0
+__device__ __forceinline__ half8 relu_max(const half8 v) { return __builtin_elementwise_max(v, (half8)(_Float16)0.0f); }
 // g where the activation act (not negative: it went through relu) is positive, else 0: all ones
 // where the bits of act are not zero, two packed instructions for two halves (written out: the
 // compiler would turn the C expression into a compare and a select per half)

@@ -78,3 +78,22 @@ def test_position_gradient_equals_the_three_calls_where_nothing_rounds(d, L, F, 
             assert torch.equal(got, want)
         else:  # fp32 sums over the levels in two orders; a half that rounds the other way moves the sum by 2^-11 of a level
             assert ((got - want).abs() <= 2.0 ** -9 * want.abs().max()).all()
+
+
+@pytest.mark.parametrize("d,T,B", [(3, 1 << 19, 1000), (3, 1 << 19, 50000), (2, 1 << 14, 120000)])  # split, paced, free-running
+def test_not_a_number_in_a_hidden_layer_is_zero_behind_the_relu(d, T, B):
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    grid = HashGrid(d, 16, 2, T, 16, 512, "f16", "f16")
+    theta = torch.full((grid.n_entries, 2), 1e4, device="cuda").half()
+    theta[:, 1] = float("nan")
+    x = torch.rand((B, d), device="cuda", generator=gen)
+    W = network(32, 3, gen, True)
+    W[0][:, 1::2] = 0  # NaN * 0: every neuron of the first layer
+    assert torch.equal(grid.encode_mlp_fwd(x, theta, *W), torch.zeros((B, 3), device="cuda"))
+    theta[:, 1] = 0
+    W[0][:, ::2] = 1  # 16 x 1e4, beyond a half: infinity in every neuron of the first layer
+    assert (W[1] == 0).any(dim=1).all()  # and infinity * 0 in every one of the second
+    y = torch.empty((B, 32), dtype=torch.float16, device="cuda")
+    out = grid.encode_mlp_fwd(x, theta, *W, y=y)
+    assert torch.isfinite(y).all()
+    assert torch.equal(out, torch.zeros_like(out)) and torch.equal(mlp_fwd(y, *W), out)
