@@ -67,6 +67,15 @@ constexpr int kAccUnroll = 4;                    // record loads in flight per l
 constexpr int kAccPreWords = 24;                 // registers per lane for records requested one item ahead
 constexpr uint32_t kAccWgsPerCu = 1;             // its registers let one accumulate workgroup run per CU
 constexpr uint32_t kTargetRecordsPerAccWg = 16384;
+// Wide entries: a record is 2 F additions in LDS, so 16384 records of 8 features keep a compute unit busy for 30 us, however
+// little the others have to do.  Items of more than kGroupedShare times a compute unit's share of the batch are shared out by
+// features, kGroupFeatures to a work item: every sum is formed from the same records in one place as before, where a finer
+// cut of the records would add partial sums that are rounded (to half, with half-precision gradients).  Each part reads the
+// records again: 30011 points, 8 levels of 8 features, half-precision gradients 48.7 -> 36.0 us; with every item of 8192
+// records or more shared out 71913 points in two dimensions, 16 levels of 4 features, took 98.7 us instead of 96.7 for both passes.
+constexpr int kGroupFeatures = 2;
+constexpr uint32_t kGroupedShare = 2, kShares = 256;  // shares: compute units of the chip
+constexpr uint32_t kMinGroupedAdds = 1u << 15;        // records * F below which an item is short anyway (4 us)
 constexpr uint32_t kMaxParts = 4;                // level parts of the scatter grid (1, 2, 8: slower)
 constexpr uint32_t kCountParts = 2;              // ... of the count grid (its workgroups are lighter)
 // Level parts are doubled (up to one level per part) until one part's bins fit these bounds: a count
@@ -103,9 +112,12 @@ static uint32_t tiles_for(const BinPlan& bp, uint32_t B) {
 
 // Slices per bin of each level for a batch of B points: coarse 1:1 levels have
 // few bins and receive B * 2^(d-1) records, so their bins are shared by several
-// accumulate-workgroups.
-static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B) {
+// accumulate-workgroups.  Levels in group_mask: every share once for each kGroupFeatures features (adam: only where a chunk
+// has several shares, whose sums meet in memory; the owner of a chunk updates whole entries).
+static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool adam) {
   uint32_t wgs = 0;
+  bp.group_mask = 0;
+  const uint64_t share = (uint64_t)B * lv.L * bp.rec_per_point / kShares;
   for (uint32_t l = 0; l < lv.L; ++l) {
     const uint32_t nb = bp.bin_base[l + 1] - bp.bin_base[l];
     const uint64_t per_bin = ((uint64_t)B * bp.rec_per_point + nb - 1) / nb;
@@ -114,14 +126,17 @@ static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B) {
     if (s > 256) s = 256;
     bp.slices[l] = (uint32_t)(s < 1 ? 1 : s);
     bp.wg_base[l] = wgs;
-    wgs += nb * bp.slices[l];
+    const bool grouped = F > kGroupFeatures && per_bin > kGroupedShare * share * bp.slices[l] &&
+                         per_bin * F >= (uint64_t)kMinGroupedAdds * bp.slices[l] && (bp.slices[l] > 1 || !adam);
+    if (grouped) bp.group_mask |= 1u << l;
+    wgs += nb * bp.slices[l] * (grouped ? F / kGroupFeatures : 1u);
   }
   bp.wg_base[lv.L] = wgs;
 }
 
 static uint64_t max_items(const hashgrid* h, uint32_t B) {
   BinPlan bp = h->bp;
-  plan_slices(bp, h->lv, B);
+  plan_slices(bp, h->lv, B, h->cfg.F, false);
   return bp.wg_base[h->lv.L];
 }
 
@@ -449,11 +464,12 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
 // A work item of the accumulate pass, written by the scatter workgroups of the first tile (they know where the bins
 // start) so that the accumulate pass reads 16 bytes an item instead of searching the plan's level table and chasing the
 // bin's start and count: with a table of 2^22 entries a level an item is 1100 records, and that chain was most of its 5 us.
-//   .x, .y  first record, one past the last;  .z  first entry of the chunk in the tables
+//   .x, .y  first record, one past the last;  .z  first entry of the chunk in the tables (below 2^30), bits 30-31 group of features
 //   .w      bits 0-11 entries of the chunk minus 1, 12-16 level, 17 1:1 index map (lb = la + 1), 18 the chunk is
 //           shared by several workgroups (not set for the first share of an empty one), 19 it has records, 20-31 chunk of the level
 constexpr uint32_t kItemDense = 1u << 17, kItemShared = 1u << 18, kItemLive = 1u << 19;
 static_assert(kMaxLevelBins <= 1u << 12 && HG_MAX_LEVELS <= 32, "an item's last word");
+template <int F>
 __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan& bp, const uint32_t l0, const uint32_t l1,
                                             const uint32_t gb, const uint32_t start, const uint32_t total,
                                             uint4* __restrict__ items, uint32_t* __restrict__ chunk_open) {
@@ -470,12 +486,16 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
     e1 = e0 + (1u << bp.chunk_log2);
   }
   if (e1 > lv.size[l]) e1 = lv.size[l];
-  chunk_open[gb] = per ? (total + per - 1) / per : 1u;
+  uint32_t groups = 1;
+  if constexpr (F > kGroupFeatures) groups = (bp.group_mask >> l) & 1u ? F / kGroupFeatures : 1u;
+  chunk_open[gb] = per ? (total + per - 1) / per * groups : 1u;
   const uint32_t w = (e1 - e0 - 1u) | (l << 12) | (dense ? kItemDense : 0u) | (bin << 20);
   for (uint32_t k = 0; k < n_sl; ++k) {
     const uint32_t r0 = k * per < total ? k * per : total, r1 = r0 + per < total ? r0 + per : total;
-    items[bp.wg_base[l] + bin * n_sl + k] =
-        make_uint4(start + r0, start + r1, (uint32_t)lv.offset[l] + e0, w | (r0 < r1 ? kItemLive : 0u) | (n_sl > 1 && (k || total) ? kItemShared : 0u));
+    for (uint32_t q = 0; q < groups; ++q)
+      items[bp.wg_base[l] + (bin * n_sl + k) * groups + q] =
+          make_uint4(start + r0, start + r1, ((uint32_t)lv.offset[l] + e0) | (q << 30),
+                     w | (r0 < r1 ? kItemLive : 0u) | (n_sl > 1 && (k || total) ? kItemShared : 0u));
   }
 }
 
@@ -544,7 +564,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   block_exclusive_scan<kBinThreads>(local, nbp + 1, scan_tmp);
   for (uint32_t i = threadIdx.x; i < nbp; i += kBinThreads) {
     const uint32_t f = before + delta[i];  // first record of the bin
-    if (tile == 0) write_items(lv, bp, l0, l1, gb_a + i, f, bin_total[gb_a + i], items, chunk_open);
+    if (tile == 0) write_items<F>(lv, bp, l0, l1, gb_a + i, f, bin_total[gb_a + i], items, chunk_open);
     cur[i] = local[i];
     delta[i] = f + row0[i] - local[i];  // wrap-around arithmetic; undone when a position is added
   }
@@ -697,7 +717,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
   const uint32_t* row0 = counts + (uint64_t)tile * n_bins + gb_a;  // prefix over the tiles before this one
   for (uint32_t i = threadIdx.x; i < nbp; i += kBinThreads) {
     const uint32_t f = before + slot[i];
-    if (tile == 0) write_items(lv, bp, l0, l1, gb_a + i, f, bin_total[gb_a + i], items, chunk_open);
+    if (tile == 0) write_items<F>(lv, bp, l0, l1, gb_a + i, f, bin_total[gb_a + i], items, chunk_open);
     slot[i] = f + row0[i];
   }
   __syncthreads();
@@ -880,7 +900,8 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   struct Item {
     uint32_t l, r0, r1, n_e, bin;
     GT* gl;
-    bool live, dense, shared;
+    int f0;  // grouped: this item's features are f0 .. f0 + kGroupFeatures - 1
+    bool live, dense, shared, grouped;
     bool orphan;  // ADAM: no records, but straddling pairs may have added to the chunk in grad
   };
   using Rec = Record<IT, F>;
@@ -889,6 +910,11 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   // wide entries: the registers do not hold the next item's gradient chunk and several records in
   // flight as well, so the chunk is read when it is flushed and fewer records are unrolled
   constexpr bool kChunkAhead = F <= 2;
+  constexpr bool kGroups = F > kGroupFeatures;
+  // is feature f the item's business
+  auto takes = [&](const Item& c, const int f) {
+    return !kGroups || !c.grouped || (f >= c.f0 && f < c.f0 + kGroupFeatures);
+  };
   constexpr int kUnroll = F <= 2 ? kAccUnroll : 2;
   auto describe = [&](const uint4 d, const bool exists) {
     Item it;
@@ -902,7 +928,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     it.r0 = d.x < n_records ? d.x : n_records;
     it.r1 = d.y < n_records ? d.y : n_records;
     it.n_e = (d.w & 0xfffu) + 1u;
-    it.gl = grad + (uint64_t)d.z * F;
+    it.gl = grad + (uint64_t)(d.z & 0x3fffffffu) * F;
+    it.grouped = kGroups && ((bp.group_mask >> it.l) & 1u);
+    it.f0 = it.grouped ? __builtin_amdgcn_readfirstlane((int)(d.z >> 30)) * kGroupFeatures : 0;
     it.orphan = false;
     if constexpr (ADAM) it.orphan = exists && !(d.w & (kItemLive | kItemShared)) && ((ad.cross_mask >> it.l) & 1u);
     return it;
@@ -946,7 +974,8 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     Entry cur_n[kPer];
     // HG_BWD_OVERWRITE: a chunk that gets no sums stored below is cleared by its owner
     auto clear_chunk = [&](const Item& c) {
-      for (uint32_t q = threadIdx.x; q < c.n_e * F; q += kAccThreads) c.gl[q] = (GT)0.0f;
+      for (uint32_t q = threadIdx.x; q < c.n_e * F; q += kAccThreads)
+        if (takes(c, (int)(q % F))) c.gl[q] = (GT)0.0f;
     };
     if (it.live && !finite) {
       if (overwrites(it)) {  // uniform
@@ -964,6 +993,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         const float wu = SMOOTH && !first ? smoothstep(w_up) : w_up, wl = SMOOTH && !first ? smoothstep(w_lo) : w_lo;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
+          if (!takes(it, f)) continue;  // uniform
           if (la < it.n_e) grad_atomic_add(it.gl, F * la + f, wl * (float)G[f]);
           if (lb < it.n_e) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
         }
@@ -984,6 +1014,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         const float wu = SMOOTH && !first ? smoothstep(w_up) : w_up, wl = SMOOTH && !first ? smoothstep(w_lo) : w_lo;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
+          if (!takes(it, f)) continue;  // uniform
           __hip_atomic_fetch_add(&acc[f * cap + la], fixed_product(wl, G[f]), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
           __hip_atomic_fetch_add(&acc[f * cap + lb], fixed_product(wu, G[f]), __ATOMIC_RELAXED,
@@ -1036,7 +1067,19 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     __syncthreads();
     const uint32_t after_next = s_ticket;  // written before the barrier above, rewritten only after the one below
     if (it.live && finite) {
-      if (!it.shared) {
+      if (kGroups && !ADAM && it.grouped && !it.shared) {
+        // the owner of some features of a chunk, each sum put where it belongs as below
+#pragma unroll
+        for (int j = 0; j < kPer * kGroupFeatures; ++j) {
+          const uint32_t q = threadIdx.x + j * kAccThreads, e = q / kGroupFeatures, f = it.f0 + q % kGroupFeatures;
+          const long long a = (long long)acc[f * cap + e];
+          acc[f * cap + e] = 0ull;
+          if (e >= it.n_e) continue;
+          GT* at = it.gl + (uint64_t)e * F + f;
+          if (overwrites(it)) *at = (GT)(0.0f + (a ? (float)((double)a * inv_scale) : 0.0f));
+          else *at = (GT)((float)*at + (a ? (float)((double)a * inv_scale) : -0.0f));
+        }
+      } else if (!it.shared) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
           const uint32_t e = threadIdx.x + j * kAccThreads;
@@ -1101,7 +1144,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
 #pragma unroll
           for (int t = 0; t < 2; ++t) {
             const int q = q0 + t;
-            if (q < 0 || q >= F * (int)cap) continue;
+            if (q < 0 || q >= F * (int)cap || !takes(it, q % F)) continue;
             unsigned long long* slot = &acc[(q % F) * cap + q / F];
             const long long a = (long long)*slot;
             *slot = 0ull;
@@ -1116,6 +1159,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         for (int j = 0; j < F * kPer; ++j) {
           const uint32_t q = threadIdx.x + j * kAccThreads;  // float index in the chunk
           const uint32_t e = q / F;
+          if (!takes(it, (int)(q % F))) continue;
           unsigned long long* slot = &acc[(q % F) * cap + e];
           const long long a = (long long)*slot;
           *slot = 0ull;
@@ -1222,7 +1266,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
   constexpr int DP = CORNERS ? 2 : D;  // (dimension of the kernels that only the pair records use: never D = 1)
   BinPlan bp = h->bp;
-  plan_slices(bp, h->lv, B);
+  plan_slices(bp, h->lv, B, F, ba != nullptr);
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const uint32_t n_records = B * h->lv.L * bp.rec_per_point;
   const uint32_t L = h->lv.L, parts = parts_for_batch(bp.scatter_parts, L, ws.n_tiles);
@@ -1504,9 +1548,11 @@ hg_status hashgrid_encode_bwd_ws(const hashgrid_t* hg, uint32_t B, const float* 
 // HG_STATIC_SCRATCH_BYTES is what counts and records may take; the item list has room of its own behind them.  A level
 // of n chunks has n * ceil(ceil(B R / n) / kTargetRecordsPerAccWg) items at most (plan_slices), which is below
 // n + n / target + B R / target; 32 levels of 4096 chunks and records of 12 bytes and more make that the bound below.
+// Items shared out by features have 4096 records or more and twice the 256th part of all: fewer than 256 of them.
 constexpr uint64_t kMostBins = (uint64_t)HG_MAX_LEVELS * hg::kMaxLevelBins;
 constexpr uint64_t kMostItems = kMostBins + kMostBins / hg::kTargetRecordsPerAccWg + 1 +
-                                HG_STATIC_SCRATCH_BYTES / 12 / hg::kTargetRecordsPerAccWg + 1;
+                                HG_STATIC_SCRATCH_BYTES / 12 / hg::kTargetRecordsPerAccWg + 1 +
+                                (8u / hg::kGroupFeatures - 1) * hg::kShares;
 constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 

@@ -12,6 +12,7 @@ struct BinPlan {
   uint32_t bin_base[HG_MAX_LEVELS + 1];  // first global bin of the level; [L] = number of bins
   uint32_t wg_base[HG_MAX_LEVELS + 1];   // first accumulate-workgroup of the level; [L] = their number
   uint32_t slices[HG_MAX_LEVELS];        // workgroups that share one bin of the level
+  uint32_t group_mask;                   // levels whose work items are shared out by features as well (accumulate pass)
   uint8_t row_shift[HG_MAX_LEVELS];      // 1:1 levels: log2 of grid rows per chunk
   uint32_t chunk_log2;                   // log2 of the entries a chunk can hold
   uint32_t rec_per_point;                // records per (point, level): 2^(d-1) pairs of corners, or 2^d corners
