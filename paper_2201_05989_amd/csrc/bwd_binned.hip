@@ -72,7 +72,7 @@ constexpr uint32_t kTargetRecordsPerAccWg = 16384;
 // features, kGroupFeatures to a work item: every sum is formed from the same records in one place as before, where a finer
 // cut of the records would add partial sums that are rounded (to half, with half-precision gradients).  Each part reads the
 // records again: 30011 points, 8 levels of 8 features, half-precision gradients 48.7 -> 36.0 us; with every item of 8192
-// records or more shared out 71913 points in two dimensions, 16 levels of 4 features, took 98.7 us instead of 96.7 for both passes.
+// records or more shared out 71913 points in two dimensions, 16 levels of 4 features, took 98.7 us instead of 96.9 for both passes.
 constexpr int kGroupFeatures = 2;
 constexpr uint32_t kGroupedShare = 2, kShares = 256;  // shares: compute units of the chip
 constexpr uint32_t kMinGroupedAdds = 1u << 15;        // records * F below which an item is short anyway (4 us)
