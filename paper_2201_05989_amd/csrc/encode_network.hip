@@ -25,7 +25,8 @@ constexpr int kOutStride = kMaxOut + kPad;
 
 // The weights in LDS, rows padded by kPad halves: w1 [64][n_in up to a multiple of 32, zeros beyond n_in], w2 [64][64],
 // w3 [32][64] (zero rows from n_out on); for the way back, instead of w3, the transposed ones: w3t [64][32] (zero columns
-// from n_out on), w2t [64][64], w1t [n_in up to a multiple of 32][64] (zero rows beyond n_in).
+// from n_out on), w2t [64][64], w1t [n_in up to a multiple of 32][64] (zero rows beyond n_in).  What a product contracts
+// over, and the rows that become the next product's operand, are in the order of place16.
 struct NetShape {
   int n_in, n_out, k32;
   int w1_stride;
@@ -56,20 +57,20 @@ __device__ __forceinline__ void stage_weights(_Float16* lds, const NetShape& sh,
   for (int i = threadIdx.x; i < kHid * q1; i += block) {
     const int n = i / q1, k = 4 * (i % q1);
     const half4 v = k < sh.n_in ? *reinterpret_cast<const half4*>(W1 + n * sh.n_in + k) : zero;
-    *reinterpret_cast<half4*>(lds + n * sh.w1_stride + k) = v;
+    *reinterpret_cast<half4*>(lds + place16(n) * sh.w1_stride + place16(k)) = v;
     if (BACK) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) lds[sh.o_w1t + (k + t) * kHidStride + n] = v[t];
+      for (int t = 0; t < 4; ++t) lds[sh.o_w1t + (k + t) * kHidStride + place16(n)] = v[t];
     }
   }
   constexpr int q2 = kHid / 4;
   for (int i = threadIdx.x; i < kHid * q2; i += block) {
     const int m = i / q2, n = 4 * (i % q2);
     const half4 v = *reinterpret_cast<const half4*>(W2 + 4 * i);
-    *reinterpret_cast<half4*>(lds + sh.o_w2 + m * kHidStride + n) = v;
+    *reinterpret_cast<half4*>(lds + sh.o_w2 + place16(m) * kHidStride + place16(n)) = v;
     if (BACK) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) lds[sh.o_w2t + (n + t) * kHidStride + m] = v[t];
+      for (int t = 0; t < 4; ++t) lds[sh.o_w2t + (place16(n) + t) * kHidStride + place16(m)] = v[t];
     }
   }
   for (int i = threadIdx.x; i < kMaxOut * q2; i += block) {
@@ -77,15 +78,36 @@ __device__ __forceinline__ void stage_weights(_Float16* lds, const NetShape& sh,
     const half4 v = o < sh.n_out ? *reinterpret_cast<const half4*>(W3 + 4 * i) : zero;
     if (BACK) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) lds[sh.o_w3t + (n + t) * kOutStride + o] = v[t];
+      for (int t = 0; t < 4; ++t) lds[sh.o_w3t + (place16(n) + t) * kOutStride + place16(o)] = v[t];
     } else {
-      *reinterpret_cast<half4*>(lds + sh.o_w3 + o * kHidStride + n) = v;
+      *reinterpret_cast<half4*>(lds + sh.o_w3 + o * kHidStride + place16(n)) = v;
     }
   }
 }
 
 // Rows of encoded features in LDS: n_in halves and kPad of padding, 8-byte aligned
 __device__ __forceinline__ int row_stride(const NetShape& sh) { return sh.n_in + kPad; }
+
+// A level's features of a point into its row.  A feature is the fp32 sum, rounded to half: the compiler otherwise makes one
+// instruction with one rounding (v_fma_mixlo_f16) of the last multiply-add and the conversion in some kernels and not in
+// others, and a feature that the forward call keeps is then now and then not the one that the way back has.  (F = 1: it does
+// so in all of them, the forward kernel included.)
+template <int F>
+__device__ __forceinline__ void put_features(float (&acc)[F], _Float16* at) {
+  if constexpr (F == 1) {
+    at[0] = (_Float16)acc[0];
+  } else {
+#pragma unroll
+    for (int f = 0; f < F; ++f) asm("" : "+v"(acc[f]));
+    _Float16* to = static_cast<_Float16*>(__builtin_assume_aligned(at, F == 2 ? 4 : 8));
+#pragma unroll
+    for (int f = 0; f < F; f += 2) {
+      const half2v h = __builtin_convertvector((float2v{acc[f], acc[f + 1]}), half2v);
+      to[f] = h[0];
+      to[f + 1] = h[1];
+    }
+  }
+}
 
 // A lane's part of the features of 16 points as an operand: `row` is its point's row (lane % 16), in LDS or memory, 8-byte aligned
 __device__ __forceinline__ void load_features(const _Float16* row, const NetShape& sh, half8 (&y)[2]) {
@@ -94,7 +116,7 @@ __device__ __forceinline__ void load_features(const _Float16* row, const NetShap
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     if (32 * j >= sh.n_in) break;  // uniform
-    const int k0 = 32 * j + 4 * g, k1 = k0 + 16;  // (a column beyond the row reads its first ones, and is replaced by zero)
+    const int k0 = 32 * j + 16 * (g / 2) + 4 * (g % 2), k1 = k0 + 8;  // (a column beyond the row reads its first ones, and is replaced by zero)
     const half4 lo = *reinterpret_cast<const half4*>(row + (k0 < sh.n_in ? k0 : 0));
     const half4 hi = *reinterpret_cast<const half4*>(row + (k1 < sh.n_in ? k1 : 0));
     y[j] = __builtin_shufflevector(k0 < sh.n_in ? lo : zero, k1 < sh.n_in ? hi : zero, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -240,8 +262,7 @@ __global__ __launch_bounds__(PACED ? kPacedBlock : kNetBlock, 4) void encode_net
 #pragma unroll
           for (int f = 0; f < F; ++f) acc[f] = fmaf(wt, (float)e[set][m].v[f], acc[f]);
         }
-#pragma unroll
-        for (int f = 0; f < F; ++f) my_row[l * F + f] = (_Float16)acc[f];
+        put_features<F>(acc, my_row + l * F);
         asm volatile("" ::: "memory");  // keep the gathers of one level together
         if constexpr (decltype(pace)::value) __syncthreads();
       };
@@ -294,7 +315,8 @@ __global__ __launch_bounds__(PACED ? kPacedBlock : kNetBlock, 4) void encode_net
 // A block of 64 points and eight waves; wave w has the levels w, w + 8, ...: LPW of them at most, all their gathers in
 // flight at once.  Four of the waves then run the network, 16 points each.
 // GRAD: not the output but its gradient with respect to the position.  The four waves go on from the hidden
-// activations back to the gradient of the features, which all waves contract with the entries they still hold.
+// activations back to the gradient of the features, which all waves contract with the entries they still hold.  The levels'
+// parts are added up in the order of the levels: the bits are those of the three calls that the kernel stands for.
 template <int F>
 __device__ __forceinline__ void keep_packed(Vec<_Float16, F>& v) {
   if constexpr (F == 1) {
@@ -317,7 +339,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
   extern __shared__ _Float16 lds[];
   const int stride = row_stride(sh);
   _Float16* rows = lds + sh.o_end;  // [kSplitPoints][stride]
-  float* part = reinterpret_cast<float*>(rows + (kSplitPoints * stride + 7) / 8 * 8);  // GRAD: [kSplitWaves][D][kSplitPoints]
+  float* part = reinterpret_cast<float*>(rows + (kSplitPoints * stride + 7) / 8 * 8);  // GRAD: [L][D][kSplitPoints]
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   stage_weights<GRAD>(lds, sh, W1, W2, W3);
   for (uint64_t p0 = (uint64_t)blockIdx.x * kSplitPoints; p0 < B; p0 += (uint64_t)gridDim.x * kSplitPoints) {
@@ -352,8 +374,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
 #pragma unroll
         for (int f = 0; f < F; ++f) acc[f] = fmaf(wt, (float)e[q][m].v[f], acc[f]);
       }
-#pragma unroll
-      for (int f = 0; f < F; ++f) rows[lane * stride + l * F + f] = (_Float16)acc[f];
+      put_features<F>(acc, rows + lane * stride + l * F);
     }
     __syncthreads();  // the rows are complete (and, the first time, the weights)
     if (!GRAD && y_out != nullptr) {
@@ -378,7 +399,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
         const float* d = dout != nullptr ? dout + (p < B ? p : B - 1) * (uint64_t)sh.n_out : nullptr;
 #pragma unroll
         for (int s8 = 0; s8 < 8; ++s8) {
-          const int o = 16 * (s8 / 4) + 4 * g + s8 % 4;
+          const int o = 16 * (g / 2) + 8 * (s8 / 4) + 4 * (g % 2) + s8 % 4;
           z[0][0][s8] = (_Float16)0.0f;
           if (o < sh.n_out) z[0][0][s8] = d != nullptr ? (_Float16)d[o] : (_Float16)1.0f;
         }
@@ -398,31 +419,28 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
     }
     __syncthreads();  // every reader of the rows is done (GRAD: dL/dy is in them)
     if constexpr (GRAD) {
-      float gx[D];
 #pragma unroll
-      for (int i = 0; i < D; ++i) {
-        gx[i] = 0.0f;
-        asm volatile("" : "+v"(xp[i]));  // the weights are computed again, not kept in registers across the network,
-      }
+      for (int i = 0; i < D; ++i) asm volatile("" : "+v"(xp[i]));  // the weights are computed again, not kept in registers across the network,
 #pragma unroll
       for (int q = 0; q < LPW; ++q) {
         const uint32_t l = wave + kSplitWaves * q;
         if (l >= lv.L) break;  // uniform
-        float g[F];
+        float g[F], gx[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i) gx[i] = 0.0f;
 #pragma unroll
         for (uint32_t m = 0; m < (1u << D); ++m) keep_packed(e[q][m]);  // ... and the entries stay halves across it
 #pragma unroll
         for (int f = 0; f < F; ++f) g[f] = (float)rows[lane * stride + l * F + f];
         add_position_gradient<D, F>(lv, l, smooth, xp, e[q], g, gx);
-      }
 #pragma unroll
-      for (int i = 0; i < D; ++i) part[(wave * D + i) * kSplitPoints + lane] = gx[i];
+        for (int i = 0; i < D; ++i) part[(l * D + i) * kSplitPoints + lane] = gx[i];
+      }
       __syncthreads();
       const int t = (int)threadIdx.x;
       if (t < kSplitPoints * D && p0 + t / D < B) {
         float sum = 0.0f;
-#pragma unroll
-        for (int w = 0; w < kSplitWaves; ++w) sum += part[(w * D + t % D) * kSplitPoints + t / D];
+        for (uint32_t l = 0; l < lv.L; ++l) sum += part[(l * D + t % D) * kSplitPoints + t / D];
         out[p0 * D + t] = sum;
       }
     }
@@ -494,7 +512,7 @@ static hg_status launch_network_grad(const hashgrid* h, uint32_t B, const float*
   const int n_in = (int)h->lv.L * F;
   const NetShape sh = NetShape::make(n_in, (int)n_out, true);
   const size_t lds = ((size_t)sh.o_end + (kSplitPoints * (n_in + kPad) + 7) / 8 * 8) * sizeof(_Float16) +
-                     (size_t)kSplitWaves * D * kSplitPoints * sizeof(float);  // 64 KB at most
+                     (size_t)h->lv.L * D * kSplitPoints * sizeof(float);  // 59 KB at most up to 16 levels, then 71
   const uint32_t blocks = (B + kSplitPoints - 1) / kSplitPoints, slots = 2 * cu_count();
   const dim3 grid(blocks < slots ? blocks : slots), block(64 * kSplitWaves);
 #define HG_SPLIT(LPW)                                                                                                  \
@@ -507,7 +525,12 @@ static hg_status launch_network_grad(const hashgrid* h, uint32_t B, const float*
   } else if (h->lv.L <= 16) {
     if constexpr (F <= 4) HG_SPLIT(2);  // (L * F is 64 at most)
   } else {
-    if constexpr (F <= 2) HG_SPLIT(4);
+    if constexpr (F <= 2) {
+      static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(encode_network_split<D, F, 4, true>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+      if (lds_ok != hipSuccess) return HG_ERR_DEVICE;
+      HG_SPLIT(4);
+    }
   }
 #undef HG_SPLIT
   return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;

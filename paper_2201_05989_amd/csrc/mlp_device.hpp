@@ -14,8 +14,13 @@
 // tile T.  It is the B operand of W z (A = rows of the weights from LDS), whose result is again in layout P.
 //
 // v_mfma_f32_16x16x32_f16 works the same way on 16 points (functions that end in 16): c = l % 16, g = l / 16, D rows
-// 4 g + t in register t, slot s of step j for k = 32 j + 16 (s / 4) + 4 g + s % 4, weight pieces 32 bytes apart.  A quarter of
-// the registers and half of the latency of a block, for twice the weight reads a point.
+// 4 g + t in register t.  A quarter of the registers and half of the latency of a block, for twice the weight reads a
+// point.  It adds the products of lane groups 0 and 1 to the accumulator and then those of 2 and 3, so its slots stand for
+// what two steps of the instruction above have in theirs, k = 32 j + 16 (g / 2) + 8 (s / 4) + 4 (g % 2) + s % 4, and its
+// sums are the same bits (2^16 sums of 64 random products on an MI355X: all equal; with k = 32 j + 16 (s / 4) + 4 g + s % 4
+// 62 % differ in the last bit, which now and then takes a half or a ReLU the other way).  In that order D's rows are what the
+// next operand needs if the weight arrays have index n of a contracted (or next) dimension at place16(n); a lane's piece of a
+// row is then 32 bytes from its other one.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -30,11 +35,13 @@ constexpr int kPad = 4;       // halves of padding per LDS row: the 8-byte reads
 constexpr int kHidStride = kHid + kPad;
 constexpr int kPts = 32;      // points of a wave's block
 
+using half2v = _Float16 __attribute__((ext_vector_type(2)));
 using half4 = _Float16 __attribute__((ext_vector_type(4)));
 using half8 = _Float16 __attribute__((ext_vector_type(8)));
 using short8v = short __attribute__((ext_vector_type(8)));
 using float8v = float __attribute__((ext_vector_type(8)));
 using float16v = float __attribute__((ext_vector_type(16)));
+using float2v = float __attribute__((ext_vector_type(2)));
 using float4v = float __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float16v zero16() {
@@ -80,6 +87,8 @@ __device__ __forceinline__ float4v mfma16(const half8 a, const half8 b, const fl
 __device__ __forceinline__ half8 to_half16(const float4v lo, const float4v hi) {
   return __builtin_convertvector(__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7), half8);
 }
+// Where a weight array has neuron (or input) n: bits 3 and 4 change places
+__device__ __forceinline__ constexpr int place16(const int n) { return (n & ~24) | ((n & 8) << 1) | ((n & 16) >> 1); }
 // A lane's fragment of row 16 T + c of a weight array in LDS for step j: columns 32 j + 4 g .. + 3 and 32 j + 16 + 4 g .. + 3
 __device__ __forceinline__ half8 weight_frag16(const _Float16* w, const int stride, const int T, const int j) {
   const int lane = (int)threadIdx.x & 63;

@@ -4,8 +4,9 @@ or beyond an L2), points in raster and in random order, one to four levels a wav
 
 The fused output must equal the network alone on the features the call keeps, bit for bit (the same instructions on the
 same halves), and the kept features are the encoding's (one rounding to half; ties may fall either way: 2^-10 of the
-value).  The gradient with respect to the position is held to the three calls it stands for where nothing rounds
-(integer tables and weights, points whose fractional positions are 0 and 1/2: every product and sum is exact)."""
+value).  The gradient with respect to the position is held to the three calls it stands for, each of which is held to the
+oracle in a module of its own: bit for bit, with random tables and weights too (the same products, summed and rounded in the same
+order)."""
 import pytest
 import torch
 
@@ -78,6 +79,26 @@ def test_position_gradient_equals_the_three_calls_where_nothing_rounds(d, L, F, 
             assert torch.equal(got, want)
         else:  # fp32 sums over the levels in two orders; a half that rounds the other way moves the sum by 2^-11 of a level
             assert ((got - want).abs() <= 2.0 ** -9 * want.abs().max()).all()
+
+
+@pytest.mark.parametrize("d,L,F,T,n_out,B,interp", [(3, 8, 4, 1 << 15, 1, 30001, 1), (3, 16, 2, 1 << 19, 4, 20000, 0), (2, 8, 1, 1 << 12, 8, 777, 0),
+                                                    (3, 12, 2, 1 << 14, 17, 5001, 0), (3, 32, 2, 1 << 12, 32, 3001, 0), (2, 8, 8, 1 << 14, 9, 5000, 1),
+                                                    (3, 16, 4, 1 << 14, 16, 2049, 0), (2, 24, 1, 1 << 12, 2, 130, 0)])
+def test_position_gradient_has_the_bits_of_the_three_calls(d, L, F, T, n_out, B, interp):
+    gen = torch.Generator(device="cuda").manual_seed(200 + B)
+    grid = HashGrid(d, L, F, T, 16, 512, "f16", "f16", interp)
+    theta = torch.randn((grid.n_entries, F), device="cuda", generator=gen).mul_(0.5).half()
+    x = torch.rand((B, d), device="cuda", generator=gen).clamp_(max=1 - 2.0 ** -24)
+    W = network(L * F, n_out, gen, False)
+    y = torch.empty((B, L * F), dtype=torch.float16, device="cuda")
+    grid.encode_mlp_fwd(x, theta, *W, y=y)
+    for dout in (None, torch.randn((B, n_out), device="cuda", generator=gen)):
+        dy = torch.empty_like(y)
+        mlp_bwd(y, *W, torch.ones((B, n_out), device="cuda") if dout is None else dout, dy, *[torch.zeros(w.shape, device="cuda") for w in W])
+        want = grid.encode_bwd_input(x, theta, dy)
+        got = grid.encode_mlp_bwd_input(x, theta, *W, dout, torch.full((B, d), float("nan"), device="cuda"))
+        assert want.abs().max() > 1
+        assert torch.equal(got, want), float((got - want).abs().max() / want.abs().max())
 
 
 @pytest.mark.parametrize("d,T,B", [(3, 1 << 19, 1000), (3, 1 << 19, 50000), (2, 1 << 14, 120000)])  # split, paced, free-running
