@@ -399,7 +399,7 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
     return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) item_counter[0] = 0;  // the accumulate pass draws its work items from here
-  for (uint32_t l = 0; zero_mask >> l; ++l) {  // uniform
+  for (uint32_t l = 0; l < lv.L; ++l) {  // uniform; bounded by L, not by the mask: with level 31 in it the shifts would go on to 32
     if (!((zero_mask >> l) & 1u)) continue;
     const uint64_t first = lv.offset[l] * F, n = (uint64_t)lv.size[l] * F;
     for (uint64_t i = (uint64_t)blockIdx.x * kScanThreads + threadIdx.x; i < n; i += (uint64_t)scan_wgs * kScanThreads) {
@@ -792,7 +792,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
   const uint32_t b = (uint32_t)b64;
   float xp[D];
   load_x<D>(x, b, xp);
-  for (uint32_t l = 0; level_mask >> l; ++l) {  // uniform
+  for (uint32_t l = 0; l < lv.L; ++l) {  // uniform; bounded by L, as in bin_scan
     if (!((level_mask >> l) & 1u)) continue;
     Rows<D> rw;
     rows_of<D, true>(lv, bp, l, smooth, xp, rw);

@@ -419,6 +419,23 @@ def test_workspace_backward_when_pairs_straddle_two_chunks(d, iot):
     assert grid.bwd_workspace_bytes(B) > 0
 
 
+@pytest.mark.parametrize("d,F,T,N_max,B", [(3, 1, 1 << 12, 256, 32768), (2, 2, 1 << 14, 8192, 6000)])
+def test_workspace_backward_with_all_32_levels(d, F, T, N_max, B):
+    # the last of 32 levels in the sets of levels that the passes walk: one chunk that several workgroups share (cleared
+    # first when the gradient is overwritten), and pairs that straddle two chunks there (added after the owners' stores)
+    L = 32
+    lv = orc.levels(orc.OracleConfig(d, L, F, T, 16, N_max))
+    assert not lv.dense[31] and lv.N[31] == N_max
+    rng = np.random.default_rng(79)
+    x = synth.points_uniform(rng, B, d)
+    if N_max > 4096:
+        x[: B // 2, 0] = np.float32(4095.75 / N_max)
+    theta = synth.make_tables(rng, lv.total, F, "f16", 1.0)
+    dy = synth.make_dy(rng, B, L * F, "f16")
+    grid = run_case(d, L, F, T, 16, N_max, "f16", "f16", 0, x, theta, dy, do_indices=False, do_dx=False)
+    assert grid.bwd_workspace_bytes(B) > 0
+
+
 @pytest.mark.parametrize("d,F,iot,interp,B", [(2, 1, "f32", 1, 9000), (3, 2, "f16", 0, 4096 + 513)])
 def test_workspace_backward_with_very_many_chunks(d, F, iot, interp, B):
     # more than 16 K chunks in all: the sorted pass takes tiles of 4096 points and writes its records
