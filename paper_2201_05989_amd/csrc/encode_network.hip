@@ -153,8 +153,8 @@ __device__ __forceinline__ void layer(const _Float16* w, const int stride, const
   }
 }
 
-// BACK: the activations as the way back needs them (relu: zeros are +0, a NaN stays one where its sign is clear), the
-// network's backward pass has the same; the output takes a NaN to 0.
+// BACK: the activations as the way back needs them (relu: zeros are +0), the network's backward pass has the same.  A NaN is 0
+// to both forms, see relu.
 template <int U, bool BACK>
 __device__ __forceinline__ void hidden_layers(const _Float16* lds, const NetShape& sh, const half8 (&y)[U][2],
                                               half8 (&h1)[U][2], half8 (&h2)[U][2]) {

@@ -60,7 +60,9 @@ __device__ __forceinline__ half8 to_half(const float16v& acc, const int j) {
   for (int s = 0; s < 8; ++s) v[s] = acc[8 * j + s];
   return __builtin_convertvector(v, half8);
 }
-// ReLU on halves: as 16-bit integers the negative halves (and -0) are the negative numbers
+// ReLU on halves: as 16-bit integers the negative halves (and -0) are the negative numbers.  So is a NaN that a matrix
+// instruction made, the only ones that come here: it is 0xffc00000 for every pair of zeros, ones, largest, infinite and NaN
+// operands of either sign, in both instructions (tried on an MI355X), and 0xfe00 as a half.
 __device__ __forceinline__ half8 relu(const half8 v) {
   return __builtin_bit_cast(half8, __builtin_elementwise_max(__builtin_bit_cast(short8v, v), (short8v)0));
 }

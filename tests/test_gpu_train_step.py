@@ -117,6 +117,45 @@ def test_nan_in_the_targets_reaches_the_entries_as_in_the_single_calls():
     assert torch.equal(m.tables[ok], want[0][ok])
 
 
+def same(a, b):
+    return torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(a.nan_to_num(7.0, 8.0, -8.0), b.nan_to_num(7.0, 8.0, -8.0))
+
+
+@pytest.mark.parametrize("n_out,F,loss,B", [(1, 2, "l2", 300), (3, 2, "mape", 40000), (1, 4, "l2", 40000), (9, 8, "mape", 300), (16, 4, "mape", 40000)])
+@pytest.mark.parametrize("infinite", [False, True])
+def test_hidden_layers_beyond_a_half_as_in_the_single_calls(n_out, F, loss, B, infinite):
+    # A NaN in a hidden layer is 0 behind the ReLU, in the step as in the single calls (it comes out of a matrix instruction, whose
+    # NaN has its sign set: 0 to an integer maximum too).  Some points have features whose sum overflows in every neuron of the
+    # first layer (infinity * 0 = NaN in the second), or an infinite feature (NaN in some neurons of the first layer, infinity in
+    # others; no zeros after it).  Loss, dL/dy and the tables' update are those of the single calls (the weight gradients
+    # are NaN either way).  Points are centres of the finest voxels: features are exact sums rounded once.
+    m, gen = exact_model(3, 8, F, 1 << 14, 4, 512, n_out, loss, 0, seed=B)
+    upper = m.tables_half[75:125]  # entries of the coarsest level (five vertices a side) in the upper part of the cube
+    if infinite:
+        m.weights_half[64 * m.n_in:] = 1
+        upper[:, 0] = float("inf")
+    else:
+        m._W[0][:, :2] = 1
+        upper[:, :2] = 60000
+    x = ((2 * torch.randint(0, 512, (B, 3), device="cuda", generator=gen) + 1).float() / 1024).contiguous()
+    x[:, 2] = x[:, 2] / 4 + 0.75 * (torch.rand(B, device="cuda", generator=gen) < 0.5)  # the lowest or the highest voxels
+    target = (m.infer(x) - 0.25).nan_to_num(0.0, 0.0, 0.0) if loss == "l2" else torch.full((B, n_out), 0.99, device="cuda")
+    y = torch.empty((B, m.n_in), dtype=torch.float16, device="cuda")
+    m.grid.encode_mlp_fwd(x, m.tables_half, *m._W, y=y)
+    first = y.float() @ m._W[0].float().T
+    odd = (first.isnan().any(dim=1) & (first == float("inf")).any(dim=1)) if infinite else (first > 65520).all(dim=1)
+    assert 0.05 < odd.float().mean() < 0.95
+    *want, total, dy = single_calls(m, x, target)
+    assert bool(total.isfinite()) != infinite
+    m.step(x, target)
+    assert float(m._loss_sum) == float(total) if infinite else abs(float(m._loss_sum - total)) <= 1e-9 * float(total)
+    assert same(m._dy, dy)
+    for got, single in ((m.tables, want[0]), (m._tab_m, want[2])):
+        assert torch.equal(got.isnan(), single.isnan())
+        ok = single.isfinite()
+        assert torch.allclose(got[ok], single[ok], rtol=1e-3, atol=1e-5 * float(single[ok].abs().max()))
+
+
 def test_tensors_replaced_between_steps_are_checked_and_used():
     B = 1000
     m, gen = exact_model(3, 8, 2, 1 << 14, 4, 512, 1, "l2", 0, 5)
