@@ -41,7 +41,7 @@ class HashGridModel:
         self.weights = torch.cat([w.reshape(-1) for w in init]).contiguous()  # W1, W2, W3 in one array: one optimiser call
         self.weights_half = self.weights.half()
         self._net_m, self._net_v = torch.zeros_like(self.weights), torch.zeros_like(self.weights)
-        self._W = self._views(self.weights_half)
+        self._W, self._n_weights = self._views(self.weights_half), self.weights.numel()
         self.steps = 0
         self._loss_sum = torch.zeros(1, dtype=torch.float64, device="cuda")
         self._scratch = torch.empty(HG_TRAIN_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
@@ -64,21 +64,29 @@ class HashGridModel:
             self._dy = torch.empty_like(self._y)
             self._buf_B = B
 
+    def _network(self):
+        """W1, W2, W3 of weights_half as it is now.  The views are made again where it lies elsewhere than they do (they keep
+        their memory, so what lies where they do is theirs); making them costs a small call as much as its kernel."""
+        if self.weights_half.data_ptr() != self._W[0].data_ptr():
+            _dev(self.weights_half, torch.float16, (self._n_weights,), "weights_half")
+            self._W = self._views(self.weights_half)
+        return self._W
+
     def infer(self, x: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
         """The network's output [B, n_out] fp32 for points x [B, d] in [0,1)^d."""
-        return self.grid.encode_mlp_fwd(x, self.tables_half, *self._W, out)
+        return self.grid.encode_mlp_fwd(x, self.tables_half, *self._network(), out)
 
     def input_gradient(self, x: torch.Tensor, dLdout: torch.Tensor | None = None) -> torch.Tensor:
         """d(sum_i dLdout_i * out_i) / dx [B, d] fp32: with the default dLdout = 1 and one output, the gradient of the
         output with respect to the position (the normal of a signed distance function, Section 3: the encoding is
         continuous and its derivative piecewise constant)."""
-        return self.grid.encode_mlp_bwd_input(x, self.tables_half, *self._W, dLdout)
+        return self.grid.encode_mlp_bwd_input(x, self.tables_half, *self._network(), dLdout)
 
     def _train_state(self, B: int) -> hashgrid_train_state:
         """The library's view of this model as it is now: tensors that the caller has replaced or loaded count, and are
         checked, from this call on (3 us of a call; nothing is kept by a tensor's address)."""
         st, f32, f16 = self._state, torch.float32, torch.float16
-        table, flat = (self.grid.n_entries, self.grid.F), (sum(r * c for r, c in self._shapes),)
+        table, flat = (self.grid.n_entries, self.grid.F), (self._n_weights,)
         st.tables = _dev(self.tables, f32, table, "tables")
         st.tables_half = _dev(self.tables_half, f16, table, "tables_half")
         st.tables_m = _dev(self._tab_m, f32, table, "first moment of the tables")

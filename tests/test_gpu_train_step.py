@@ -178,6 +178,25 @@ def test_tensors_replaced_between_steps_are_checked_and_used():
     m.step(x, target)
 
 
+def test_output_and_its_gradient_follow_replaced_weights():
+    m, gen = exact_model(3, 8, 2, 1 << 14, 4, 512, 3, "l2", 0, 6)
+    x = torch.rand((500, 3), device="cuda", generator=gen)
+    first, grad = m.infer(x), m.input_gradient(x)
+    assert first.any() and grad.any()
+    m.weights_half = -m.weights_half  # a loaded network
+    m.weights_half[:64 * m.n_in] *= -1
+    m.weights_half[64 * m.n_in:64 * m.n_in + 4096] *= -1  # its last layer has the other sign
+    assert torch.equal(m.infer(x), -first) and torch.equal(m.input_gradient(x), -grad)
+    m.weights_half.zero_()  # in place
+    assert not m.infer(x).any()
+    for bad in (m.weights_half[1:], m.weights_half.float(), m.weights_half.cpu()):
+        good, m.weights_half = m.weights_half, bad
+        for call in (m.infer, m.input_gradient):
+            with pytest.raises(HashGridError):
+                call(x)
+        m.weights_half = good
+
+
 @pytest.mark.parametrize("F", [1, 2, 4])
 def test_step_takes_and_refuses_what_the_single_calls_do(F):
     m = HashGridModel(3, 1, L=8, F=F, T=1 << 14, N_min=4, N_max=512, seed=F)
