@@ -385,8 +385,8 @@ typedef struct {
  *   target     [B, n_out] fp32, device, read
  *   y, dLdy    [B, L*F]   fp16, device, 16-byte aligned, scratch that holds the encoded features and their
  *                         gradient on return
- *   workspace  as for hashgrid_encode_bwd_ws, or NULL (then, and where hashgrid_bwd_ws_pays says no, the
- *              gradient is summed with atomic additions into tables_zeros)
+ *   workspace  as for hashgrid_encode_bwd_ws (size and alignment are checked where it is used), or NULL (then, and
+ *              where hashgrid_bwd_ws_pays says no, the gradient is summed with atomic additions into tables_zeros)
  *   step       1-based, the same for tables and weights
  * HG_ERR_UNSUPPORTED as hashgrid_encode_mlp_fwd, and unless io_dtype is HG_F16 and grad_dtype HG_F32.
  * B == 0 is HG_OK and changes nothing. */

@@ -40,8 +40,8 @@ extern "C" hg_status hashgrid_train_step(const hashgrid_t* hg, const hashgrid_tr
   hipStream_t s = static_cast<hipStream_t>(stream);
 
   const uint64_t need = hashgrid_bwd_workspace_bytes(hg, B);
-  const bool sorted = need != 0 && hashgrid_bwd_ws_pays(hg, B) && workspace && workspace_bytes >= need &&
-                      (reinterpret_cast<uintptr_t>(workspace) & 255) == 0;
+  const bool sorted = need != 0 && workspace && hashgrid_bwd_ws_pays(hg, B);
+  if (sorted && (workspace_bytes < need || bad(workspace, 256))) return HG_ERR_INVALID_ARG;
   bool counted = false;
   hg_status rc = HG_ERR_UNSUPPORTED;
   if (sorted) {
