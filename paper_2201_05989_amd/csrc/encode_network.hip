@@ -212,28 +212,38 @@ __global__ __launch_bounds__(kMlpOnlyBlock) void mlp_fwd_from_features(const uin
 }
 
 // One thread per point, level by level, as the forward kernel (hashgrid.hip) with the gathers of later levels issued before
-// a level is blended.
+// a level is blended.  The levels whose gathers look ahead to a level that exists have a loop without a condition: behind one
+// the compiler counts loads in flight as if the later level's were not there, and waits for them too (d = 3, 16 levels of
+// one feature, T = 2^19, 33000 points in random order: 31.4 us with the condition, 25.4 without).
 // PACED: a barrier per level keeps the waves of a workgroup on the same slice of the tables, as there: 2^20 points at T = 2^19,
-// d = 3, take 332 us in 1024-thread workgroups with it and 625 us without.  Otherwise the waves run free in 512-thread
-// workgroups, two a compute unit, and one wave's products run under another's gathers: 2^20 pixels of a raster at
-// T = 2^22 75 us, 89 with the barrier.  That is for tables that stay in an XCD's L2 and are too wide for the L1 to gain from the
-// order either (d = 3, F of 4 or 8: 91 against 105 us), and for d = 2 as long as neighbouring lanes have neighbouring
-// points: a workgroup whose first block of points is in no such order (kNear) paces itself all the same.
+// d = 3, take 332 us in 1024-thread workgroups with it and 625 us without.  Otherwise the waves run free and one wave's
+// products run under another's gathers: 2^20 pixels of a raster at T = 2^22 75 us, 89 with the barrier.  That is for tables that
+// stay in an XCD's L2 and are too wide for the L1 to gain from the order either (d = 3, F of 4 or 8: 91 against 105 us), and for
+// d = 2 as long as neighbouring lanes have neighbouring points: a workgroup whose first block of points is in no such order
+// (kNear) paces itself all the same, and then looks one level ahead and not three (what the three touch is more than the order keeps).
 constexpr float kNear = 1.0f / 64.0f;
-constexpr int kNetBlock = 512, kPacedBlock = 1024;
+constexpr int kNetBlock = 1024;
 template <int D, int F, bool PACED>
-__global__ __launch_bounds__(PACED ? kPacedBlock : kNetBlock, 4) void encode_network(
+__global__ __launch_bounds__(kNetBlock, 4) void encode_network(
     const LevelTable lv, const bool smooth, const uint32_t B, const NetShape sh, const float* __restrict__ x,
     const _Float16* __restrict__ theta, const _Float16* __restrict__ W1, const _Float16* __restrict__ W2,
     const _Float16* __restrict__ W3, float* __restrict__ out, _Float16* __restrict__ y_out) {
   extern __shared__ _Float16 lds[];
   const int stride = row_stride(sh);
-  const uint32_t block = PACED ? blockDim.x : kNetBlock;
+  const uint32_t block = blockDim.x;
   _Float16* rows = lds + sh.o_end;  // [block][stride]
   _Float16* my_row = rows + (int)threadIdx.x * stride;
-  stage_weights<false>(lds, sh, W1, W2, W3);
-  __syncthreads();
   const uint32_t lane = threadIdx.x & 63, wave0 = threadIdx.x & ~63u;
+  bool near = false;
+  if constexpr (!PACED && D == 2) {
+    const uint64_t i = (uint64_t)blockIdx.x * block + threadIdx.x, j = i + 1 < B ? i + 1 : B - 1;
+    const float* xi = x + (i < B ? i : B - 1) * D;
+    near = fabsf(xi[0] - x[j * D]) < kNear && fabsf(xi[1] - x[j * D + 1]) < kNear;
+  }
+  stage_weights<false>(lds, sh, W1, W2, W3);
+  bool pace = PACED;
+  if constexpr (!PACED && D == 2) pace = __syncthreads_count(near) < (int)block / 2;  // (the barrier behind the staging)
+  else __syncthreads();
   auto walk = [&](auto pace) {
     for (uint64_t p0 = (uint64_t)blockIdx.x * block; p0 < B; p0 += (uint64_t)gridDim.x * block) {
       asm volatile("" ::: "memory");
@@ -242,7 +252,7 @@ __global__ __launch_bounds__(PACED ? kPacedBlock : kNetBlock, 4) void encode_net
       float xp[D];
 #pragma unroll
       for (int i = 0; i < D; ++i) xp[i] = x[(uint64_t)b * D + i];
-      constexpr int kSets = D == 2 && F <= 2 ? 4 : D == 3 && F == 8 ? 1 : 2;  // register sets: kSets - 1 levels are in flight ahead
+      constexpr int kSets = D == 2 && F <= 2 && !decltype(pace)::value ? 4 : D == 3 && F == 8 ? 1 : 2;  // register sets: kSets - 1 levels are in flight ahead
       Vec<_Float16, F> e[kSets][1 << D];
       float wr[kSets][1 << (D - 1)], w0[kSets], u0[kSets];
       auto gather_level = [&](const uint32_t l, const int set) {
@@ -269,7 +279,17 @@ __global__ __launch_bounds__(PACED ? kPacedBlock : kNetBlock, 4) void encode_net
 #pragma unroll
       for (int j = 0; j < kSets - 1; ++j)
         if (j < (int)lv.L) gather_level(j, j);  // uniform, here and below
-      for (uint32_t l0 = 0; l0 < lv.L; l0 += kSets) {
+      uint32_t l0 = 0;
+#pragma unroll 1
+      for (; l0 + 2 * kSets - 1 <= lv.L; l0 += kSets) {
+#pragma unroll
+        for (int j = 0; j < kSets; ++j) {
+          gather_level(l0 + j + kSets - 1, (j + kSets - 1) % kSets);
+          blend_level(l0 + j, j);
+        }
+      }
+#pragma unroll 1
+      for (; l0 < lv.L; l0 += kSets) {
 #pragma unroll
         for (int j = 0; j < kSets; ++j) {
           const uint32_t ahead = l0 + j + kSets - 1;
@@ -302,10 +322,7 @@ __global__ __launch_bounds__(PACED ? kPacedBlock : kNetBlock, 4) void encode_net
   if constexpr (PACED) {
     walk(std::true_type{});
   } else if constexpr (D == 2) {
-    const uint64_t i = (uint64_t)blockIdx.x * block + threadIdx.x, j = i + 1 < B ? i + 1 : B - 1;
-    const float* xi = x + (i < B ? i : B - 1) * D;
-    const bool near = fabsf(xi[0] - x[j * D]) < kNear && fabsf(xi[1] - x[j * D + 1]) < kNear;
-    if (__syncthreads_count(near) < (int)block / 2) walk(std::true_type{});
+    if (pace) walk(std::true_type{});
     else walk(std::false_type{});
   } else {
     walk(std::false_type{});
@@ -447,6 +464,15 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
   }
 }
 
+// Threads of a workgroup where two of half the size fit a compute unit: the batch spread evenly over both, as point_major_block
+// spreads it over one
+static uint32_t half_block(uint32_t B) {
+  constexpr uint64_t kMost = kNetBlock / 2;
+  const uint64_t slots = 2 * cu_count(), rounds = (B + kMost * slots - 1) / (kMost * slots);
+  const uint64_t per_wg = (B + rounds * slots - 1) / (rounds * slots);
+  return (uint32_t)((per_wg + 63) / 64 * 64);
+}
+
 template <int D, int F>
 static hg_status launch_network(const hashgrid* h, uint32_t B, const float* x, const void* params, const void* W1,
                                 const void* W2, const void* W3, uint32_t n_out, float* out, void* y_out, hipStream_t s) {
@@ -456,12 +482,19 @@ static hg_status launch_network(const hashgrid* h, uint32_t B, const float* x, c
   const _Float16 *t = static_cast<const _Float16*>(params), *w1 = static_cast<const _Float16*>(W1),
                  *w2 = static_cast<const _Float16*>(W2), *w3 = static_cast<const _Float16*>(W3);
   _Float16* yo = static_cast<_Float16*>(y_out);
-  // Tables beyond an XCD's L2 and four lines a point and level: the order of the levels counts (see PACED), and the split
-  // kernel, whose waves are at all levels at once, loses to it from some 40 K points on (49 against 40 us at 2^16); else
-  // it holds until the batch gives every thread of the other shape a point (2^17 points of a raster 25 against 24 us).
+  // The split kernel holds until the batch gives every thread of the other shape a point or so.  Its waves are at all levels at
+  // once, so beyond an XCD's L2 it loses to the paced one earlier where the points are in no order, and with more than eight
+  // levels, where a wave has two, earlier still: the line lies where one order wins what the other loses.  Split against not, us,
+  // 16 levels of 2: d = 3, T = 2^19, 30000 points random 28.0 and 28.0, rays 17.6 and 22.4, 40000 points 37.2 and 31.1, 22.7 and
+  // 24.8; T = 2^15, 50000 points 21.9 and 19.0, 14.3 and 16.7; d = 2, T = 2^19, 70000 points random 25.6 and 24.0, raster 12.6 and
+  // 13.1; T = 2^15, 100000 points 17.6 and 18.2, 11.8 and 12.6.  8 levels of 8, d = 3, T = 2^19, 40000 points random 28.1 and 30.8,
+  // rays 17.7 and 23.4; T = 2^15, 100000 points 25.3 and 25.3, 15.5 and 17.0.
   constexpr uint64_t kL2Bytes = 4u << 20;
   const bool large = h->total * F * sizeof(_Float16) > kL2Bytes, paced = D == 3 && (F <= 2 || large);
-  if (B <= (D == 3 && large ? 40000u : 100000u)) {
+  const uint32_t most = h->lv.L <= kSplitWaves ? (D == 3 && large ? 40000u : 100000u)
+                        : D == 3               ? (large ? 32768u : 50000u)
+                                               : (large ? 70000u : 100000u);
+  if (B <= most) {
     const size_t lds = ((size_t)sh.o_end + (kSplitPoints * (n_in + kPad) + 7) / 8 * 8) * sizeof(_Float16);
     const uint32_t blocks = (B + kSplitPoints - 1) / kSplitPoints, slots = 2 * cu_count();
     const dim3 grid(blocks < slots ? blocks : slots), block(64 * kSplitWaves);
@@ -478,11 +511,15 @@ static hg_status launch_network(const hashgrid* h, uint32_t B, const float* x, c
 #undef HG_SPLIT
     return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;
   }
-  const uint32_t block = paced ? point_major_block(B) : kNetBlock;
+  // One workgroup of up to 1024 threads a compute unit where the order of the levels counts, or where two of 512 do not fit (64
+  // features: half the waves otherwise; d = 2, T = 2^19, 16 levels of 4, 2^20 points random 271 us, now 210, raster 92, now 64);
+  // two of 512 else (d = 2, T = 2^15, 16 levels of 2, 2^18 points random 33 us, 35 with one).
+  const bool two_fit = 2 * ((size_t)sh.o_end + (size_t)(kNetBlock / 2) * (n_in + kPad)) * sizeof(_Float16) <= 160 * 1024;
+  const uint32_t block = paced || large || !two_fit ? point_major_block(B) : half_block(B);
   const size_t lds = ((size_t)sh.o_end + (size_t)block * (n_in + kPad)) * sizeof(_Float16);
   static const hipError_t lds_ok = [] {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(encode_network<D, F, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);  // (the vote on the order has some of its own)
     if constexpr (D == 3) {
       if (e == hipSuccess)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(encode_network<D, F, true>),
@@ -492,7 +529,7 @@ static hg_status launch_network(const hashgrid* h, uint32_t B, const float* x, c
   }();
   if (lds_ok != hipSuccess) return HG_ERR_DEVICE;
   const uint32_t blocks = (B + block - 1) / block, per_cu = (uint32_t)(160 * 1024 / lds),
-                 slots = (per_cu < kPacedBlock / block ? per_cu : kPacedBlock / block) * cu_count();
+                 slots = (per_cu < kNetBlock / block ? per_cu : kNetBlock / block) * cu_count();
   const dim3 grid(blocks < slots ? blocks : slots);
   if (paced) {
     if constexpr (D == 3)

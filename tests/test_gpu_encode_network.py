@@ -1,6 +1,7 @@
 """The encoding with the network behind it, at the sizes where its kernels change: batches below and above what the split
-kernel takes (40 000 points, 100 000), paced and free-running workgroups (d = 3 or 2, narrow or wide entries, tables within
-or beyond an L2), points in raster and in random order, one to four levels a wave, ragged last blocks.
+kernel takes (32768 to 100000 points, by d, the number of levels and the size of the tables), paced and free-running
+workgroups (d = 3 or 2, narrow or wide entries, tables within or beyond an L2), points in raster and in random order, one to
+four levels a wave, level counts below and beside what the unconditional loop over levels takes, ragged last blocks.
 
 The fused output must equal the network alone on the features the call keeps, bit for bit (the same instructions on the
 same halves), and the kept features are the encoding's (one rounding to half; ties may fall either way: 2^-10 of the
@@ -25,6 +26,21 @@ def network(n_in, n_out, gen, integers):
 
 @pytest.mark.parametrize("d,L,F,T,N_max,n_out,B,order,interp", [
     (3, 16, 2, 1 << 19, 2048, 3, 1, "random", 0),
+    (3, 16, 2, 1 << 19, 2048, 3, 32768, "random", 0),      # split at the last batch it takes, here and in the next pairs
+    (3, 16, 2, 1 << 19, 2048, 3, 32769, "random", 0),      # paced, workgroups of two waves
+    (3, 16, 4, 1 << 12, 256, 3, 50000, "rays", 0),
+    (3, 16, 4, 1 << 12, 256, 3, 50001, "random", 0),       # free-running, 64 features
+    (2, 16, 2, 1 << 18, 4096, 3, 70000, "random", 0),
+    (2, 16, 2, 1 << 18, 4096, 3, 70001, "random", 0),      # paced by the order of the points, and free-running below
+    (3, 8, 4, 1 << 19, 2048, 3, 40000, "random", 0),
+    (3, 8, 4, 1 << 19, 2048, 3, 40001, "random", 0),
+    (2, 16, 1, 1 << 12, 1024, 3, 100000, "raster", 0),
+    (2, 16, 1, 1 << 12, 1024, 3, 100001, "raster", 0),     # free-running, two workgroups a compute unit
+    (2, 8, 8, 1 << 12, 1024, 3, 100001, "random", 0),      # one workgroup of half the size, paced
+    (2, 4, 2, 1 << 12, 64, 1, 120000, "raster", 0),        # fewer levels than the loop that looks three ahead takes
+    (2, 20, 2, 1 << 12, 300, 1, 150001, "raster", 0),
+    (3, 4, 2, 1 << 12, 64, 1, 60000, "random", 0),
+    (3, 12, 2, 1 << 12, 64, 1, 60000, "random", 1),
     (3, 16, 2, 1 << 19, 2048, 3, 39999, "random", 0),
     (3, 16, 2, 1 << 19, 2048, 4, 40001, "random", 0),      # paced, workgroups of a few waves
     (3, 16, 2, 1 << 14, 512, 1, 300007, "random", 1),      # paced, full workgroups, several blocks each
@@ -32,7 +48,7 @@ def network(n_in, n_out, gen, integers):
     (3, 8, 8, 1 << 18, 512, 32, 70001, "random", 0),       # paced, eight features an entry, 64 features
     (3, 32, 1, 1 << 12, 256, 2, 70003, "random", 0),       # split, four levels a wave
     (3, 32, 2, 1 << 12, 256, 2, 5, "random", 0),
-    (2, 16, 2, 1 << 18, 4096, 3, 100000, "raster", 0),     # split at the last batch it takes
+    (2, 16, 2, 1 << 18, 4096, 3, 100000, "raster", 0),
     (2, 16, 2, 1 << 18, 4096, 3, 262145, "raster", 0),     # free-running
     (2, 16, 2, 1 << 18, 4096, 16, 262145, "random", 1),    # paced by the order of the points
     (2, 12, 2, 1 << 14, 300, 4, 150001, "raster", 1),      # 24 features: a ragged operand
@@ -47,6 +63,8 @@ def test_fused_output_is_the_network_on_the_kept_features(d, L, F, T, N_max, n_o
     if order == "raster":
         i = torch.arange(B, device="cuda")
         x = torch.stack([(i % 640) / 640.0, (i // 640) / (B // 640 + 1.0)], dim=1).contiguous()
+    elif order == "rays":
+        x = (x[:1] + torch.arange(B, device="cuda")[:, None] / B * (x[1:2] - x[:1])).contiguous()
     W = network(L * F, n_out, gen, False)
     y = torch.full((B, L * F), float("nan"), dtype=torch.float16, device="cuda")
     out = grid.encode_mlp_fwd(x, theta, *W, torch.full((B, n_out), float("nan"), device="cuda"), y=y)
