@@ -67,14 +67,18 @@ constexpr int kAccUnroll = 4;                    // record loads in flight per l
 constexpr int kAccPreWords = 24;                 // registers per lane for records requested one item ahead
 constexpr uint32_t kAccWgsPerCu = 1;             // its registers let one accumulate workgroup run per CU
 constexpr uint32_t kTargetRecordsPerAccWg = 16384;
-// Wide entries: a record is 2 F additions in LDS, so 16384 records of 8 features keep a compute unit busy for 30 us, however
-// little the others have to do.  Items of more than kGroupedShare times a compute unit's share of the batch are shared out by
-// features, kGroupFeatures to a work item: every sum is formed from the same records in one place as before, where a finer
-// cut of the records would add partial sums that are rounded (to half, with half-precision gradients).  Each part reads the
-// records again: 30011 points, 8 levels of 8 features, half-precision gradients 48.7 -> 36.0 us; with every item of 8192
-// records or more shared out 71913 points in two dimensions, 16 levels of 4 features, took 98.7 us instead of 96.9 for both passes.
-constexpr int kGroupFeatures = 2;
-constexpr uint32_t kGroupedShare = 2, kShares = 256;  // shares: compute units of the chip
+// Eight features an entry, half-precision gradients: a record is 16 additions in LDS, so 16384 records keep a compute unit busy
+// for 30 us, however little the others have to do.  Items of more than kGroupedHalfShares / 2 times a compute unit's share of the
+// batch are then shared out by features, kGroupFeatures to a work item: every sum is formed from the same records in one
+// place as before, where a finer cut of the records would add partial sums that are rounded to half.  The price is in each part
+// reading the records again and in its sums leaving in requests that a whole item fills, so not from twice the share on (uniform
+// points on equal chunks: 73 -> 81 us for both passes), and not where there are chip-filling numbers of such items already (8
+// levels in one chunk each, 89981 points: 76 -> 90).  Over 180 random configurations, both passes: 0.93 of the time without on
+// average, 0.72 to 1.06; 30011 points, 8 levels on 2^17 entries: 85 -> 72.5 us.  Not for single-precision gradients, whose sums
+// leave one to a lane (a table of 2^14 entries, 91757 points in two dimensions: 86 -> 155 us), nor for four features (1.01 to 1.25 of
+// the time without); and the code is an instance of its own, since merely having it costs the others 5 to 20 %.
+constexpr int kGroupedF = 8, kGroupFeatures = 2;
+constexpr uint32_t kGroupedHalfShares = 5, kShares = 256;  // shares: compute units of the chip
 constexpr uint32_t kMinGroupedAdds = 1u << 15;        // records * F below which an item is short anyway (4 us)
 constexpr uint32_t kMaxParts = 4;                // level parts of the scatter grid (1, 2, 8: slower)
 constexpr uint32_t kCountParts = 2;              // ... of the count grid (its workgroups are lighter)
@@ -112,12 +116,11 @@ static uint32_t tiles_for(const BinPlan& bp, uint32_t B) {
 
 // Slices per bin of each level for a batch of B points: coarse 1:1 levels have
 // few bins and receive B * 2^(d-1) records, so their bins are shared by several
-// accumulate-workgroups.  Levels in group_mask: every share once for each kGroupFeatures features (adam: only where a chunk
-// has several shares, whose sums meet in memory; the owner of a chunk updates whole entries).
-static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool adam) {
-  uint32_t wgs = 0;
+// accumulate-workgroups.  Levels in group_mask: every share once for each kGroupFeatures features.
+static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool half_grad) {
   bp.group_mask = 0;
   const uint64_t share = (uint64_t)B * lv.L * bp.rec_per_point / kShares;
+  uint64_t grouped_items = 0;
   for (uint32_t l = 0; l < lv.L; ++l) {
     const uint32_t nb = bp.bin_base[l + 1] - bp.bin_base[l];
     const uint64_t per_bin = ((uint64_t)B * bp.rec_per_point + nb - 1) / nb;
@@ -125,18 +128,24 @@ static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t 
     if (!((lv.dense_mask >> l) & 1u) && s < 4) s = 1;  // hashed bins are evenly filled
     if (s > 256) s = 256;
     bp.slices[l] = (uint32_t)(s < 1 ? 1 : s);
+    if (F == kGroupedF && half_grad && 2 * per_bin > kGroupedHalfShares * share * bp.slices[l] &&
+        per_bin * F >= (uint64_t)kMinGroupedAdds * bp.slices[l]) {
+      bp.group_mask |= 1u << l;
+      grouped_items += (uint64_t)nb * bp.slices[l] * (F / kGroupFeatures);
+    }
+  }
+  if (grouped_items > kShares) bp.group_mask = 0;
+  uint32_t wgs = 0;
+  for (uint32_t l = 0; l < lv.L; ++l) {
     bp.wg_base[l] = wgs;
-    const bool grouped = F > kGroupFeatures && per_bin > kGroupedShare * share * bp.slices[l] &&
-                         per_bin * F >= (uint64_t)kMinGroupedAdds * bp.slices[l] && (bp.slices[l] > 1 || !adam);
-    if (grouped) bp.group_mask |= 1u << l;
-    wgs += nb * bp.slices[l] * (grouped ? F / kGroupFeatures : 1u);
+    wgs += (bp.bin_base[l + 1] - bp.bin_base[l]) * bp.slices[l] * ((bp.group_mask >> l) & 1u ? F / kGroupFeatures : 1u);
   }
   bp.wg_base[lv.L] = wgs;
 }
 
 static uint64_t max_items(const hashgrid* h, uint32_t B) {
   BinPlan bp = h->bp;
-  plan_slices(bp, h->lv, B, h->cfg.F, false);
+  plan_slices(bp, h->lv, B, h->cfg.F, h->cfg.grad_dtype == HG_F16);
   return bp.wg_base[h->lv.L];
 }
 
@@ -487,8 +496,8 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
   }
   if (e1 > lv.size[l]) e1 = lv.size[l];
   uint32_t groups = 1;
-  if constexpr (F > kGroupFeatures) groups = (bp.group_mask >> l) & 1u ? F / kGroupFeatures : 1u;
-  chunk_open[gb] = per ? (total + per - 1) / per * groups : 1u;
+  if constexpr (F == kGroupedF) groups = (bp.group_mask >> l) & 1u ? F / kGroupFeatures : 1u;
+  chunk_open[gb] = per ? (total + per - 1) / per : 1u;  // (ADAM: never in groups)
   const uint32_t w = (e1 - e0 - 1u) | (l << 12) | (dense ? kItemDense : 0u) | (bin << 20);
   for (uint32_t k = 0; k < n_sl; ++k) {
     const uint32_t r0 = k * per < total ? k * per : total, r1 = r0 + per < total ? r0 + per : total;
@@ -814,11 +823,12 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
 // lanes that have just read them.
 // GT: type of the gradient scalars (float, or _Float16: the sums are still exact fixed point and are
 // rounded to half precision once, where they are added to the gradient).
+// GROUPS: levels in bp.group_mask have work items for some of an entry's features (half-precision gradients).
 //
 // ADAM: a training step has no use for the gradient itself, only for what the optimiser makes of it.  The owner of a
 // chunk then takes its sums straight to Adam on the chunk's entries, instead of writing them for a pass of
 // their own to read back with everything else (the step's largest streams are the two moments and the master copy:
-// 34 bytes a scalar, against 8 for the gradient's round trip), and those streams run beside the
+// 26 bytes a scalar, against 8 for the gradient's round trip), and those streams run beside the
 // LDS work of this kernel.  `grad` is then an array that is zero before and after: the workgroups that share a chunk add their
 // sums into it, and the last one to arrive (chunk_open) takes them out again and applies them, as does the owner of
 // a chunk with what the straddling pairs left there.
@@ -829,7 +839,7 @@ struct AdamOut {
   uint32_t* chunk_open;
   uint32_t cross_mask;  // levels whose straddling pairs were added to grad by the scatter pass
 };
-template <typename IT, int F, bool SMOOTH, typename GT = float, bool ADAM = false>
+template <typename IT, int F, bool SMOOTH, typename GT = float, bool ADAM = false, bool GROUPS = false>
 __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable lv, const BinPlan bp,
                                                               const uint32_t B, const uint32_t n_items,
                                                               const uint4* __restrict__ items,
@@ -910,10 +920,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   // wide entries: the registers do not hold the next item's gradient chunk and several records in
   // flight as well, so the chunk is read when it is flushed and fewer records are unrolled
   constexpr bool kChunkAhead = F <= 2;
-  constexpr bool kGroups = F > kGroupFeatures;
   // is feature f the item's business
   auto takes = [&](const Item& c, const int f) {
-    return !kGroups || !c.grouped || (f >= c.f0 && f < c.f0 + kGroupFeatures);
+    return !GROUPS || !c.grouped || (f >= c.f0 && f < c.f0 + kGroupFeatures);
   };
   constexpr int kUnroll = F <= 2 ? kAccUnroll : 2;
   auto describe = [&](const uint4 d, const bool exists) {
@@ -929,7 +938,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     it.r1 = d.y < n_records ? d.y : n_records;
     it.n_e = (d.w & 0xfffu) + 1u;
     it.gl = grad + (uint64_t)(d.z & 0x3fffffffu) * F;
-    it.grouped = kGroups && ((bp.group_mask >> it.l) & 1u);
+    it.grouped = GROUPS && ((bp.group_mask >> it.l) & 1u);
     it.f0 = it.grouped ? __builtin_amdgcn_readfirstlane((int)(d.z >> 30)) * kGroupFeatures : 0;
     it.orphan = false;
     if constexpr (ADAM) it.orphan = exists && !(d.w & (kItemLive | kItemShared)) && ((ad.cross_mask >> it.l) & 1u);
@@ -1067,7 +1076,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     __syncthreads();
     const uint32_t after_next = s_ticket;  // written before the barrier above, rewritten only after the one below
     if (it.live && finite) {
-      if (kGroups && !ADAM && it.grouped && !it.shared) {
+      if (GROUPS && it.grouped && !it.shared) {
         // the owner of some features of a chunk, each sum put where it belongs as below
 #pragma unroll
         for (int j = 0; j < kPer * kGroupFeatures; ++j) {
@@ -1159,7 +1168,6 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         for (int j = 0; j < F * kPer; ++j) {
           const uint32_t q = threadIdx.x + j * kAccThreads;  // float index in the chunk
           const uint32_t e = q / F;
-          if (!takes(it, (int)(q % F))) continue;
           unsigned long long* slot = &acc[(q % F) * cap + e];
           const long long a = (long long)*slot;
           *slot = 0ull;
@@ -1266,7 +1274,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
   constexpr int DP = CORNERS ? 2 : D;  // (dimension of the kernels that only the pair records use: never D = 1)
   BinPlan bp = h->bp;
-  plan_slices(bp, h->lv, B, F, ba != nullptr);
+  plan_slices(bp, h->lv, B, F, g16);
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const uint32_t n_records = B * h->lv.L * bp.rec_per_point;
   const uint32_t L = h->lv.L, parts = parts_for_batch(bp.scatter_parts, L, ws.n_tiles);
@@ -1308,6 +1316,14 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     if (e == hipSuccess && kAccLds > 48 * 1024)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
+    if constexpr (F == kGroupedF) {
+      if (e == hipSuccess && kAccLds > 48 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, _Float16, false, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
+      if (e == hipSuccess && kAccLds > 48 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16, false, true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
+    }
     if constexpr (kAdam) {
       if (e == hipSuccess && kAccLds > 48 * 1024)
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, float, true>),
@@ -1367,11 +1383,11 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     return (uint32_t)cus * kAccWgsPerCu;
   }();
   const dim3 acc_grid(n_items < acc_slots ? n_items : acc_slots);
-  auto accumulate = [&](auto smooth_t, auto* g) {
+  auto accumulate = [&](auto smooth_t, auto* g, auto groups_t) {
     using GT = typename std::remove_pointer<decltype(g)>::type;
-    hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT>), acc_grid, dim3(kAccThreads), kAccLds, s,
-                       h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts, ws.records,
-                       ws.item_counter, g, overwrite_mask, NoAdam{});
+    hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT, false, decltype(groups_t)::value>), acc_grid,
+                       dim3(kAccThreads), kAccLds, s, h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts,
+                       ws.records, ws.item_counter, g, overwrite_mask, NoAdam{});
   };
   if constexpr (kAdam) {
     if (ba) {
@@ -1389,12 +1405,17 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
       return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;
     }
   }
-  if (g16) {
-    if (smooth) accumulate(std::true_type{}, static_cast<_Float16*>(grad));
-    else accumulate(std::false_type{}, static_cast<_Float16*>(grad));
+  if (g16 && bp.group_mask != 0) {
+    if constexpr (F == kGroupedF) {
+      if (smooth) accumulate(std::true_type{}, static_cast<_Float16*>(grad), std::true_type{});
+      else accumulate(std::false_type{}, static_cast<_Float16*>(grad), std::true_type{});
+    }
+  } else if (g16) {
+    if (smooth) accumulate(std::true_type{}, static_cast<_Float16*>(grad), std::false_type{});
+    else accumulate(std::false_type{}, static_cast<_Float16*>(grad), std::false_type{});
   } else {
-    if (smooth) accumulate(std::true_type{}, static_cast<float*>(grad));
-    else accumulate(std::false_type{}, static_cast<float*>(grad));
+    if (smooth) accumulate(std::true_type{}, static_cast<float*>(grad), std::false_type{});
+    else accumulate(std::false_type{}, static_cast<float*>(grad), std::false_type{});
   }
   if (defer_cross)
     hipLaunchKernelGGL((bin_crossing<DP, IT, F>), dim3((B + kBinThreads - 1) / kBinThreads), dim3(kBinThreads), 0, s,
@@ -1548,11 +1569,11 @@ hg_status hashgrid_encode_bwd_ws(const hashgrid_t* hg, uint32_t B, const float* 
 // HG_STATIC_SCRATCH_BYTES is what counts and records may take; the item list has room of its own behind them.  A level
 // of n chunks has n * ceil(ceil(B R / n) / kTargetRecordsPerAccWg) items at most (plan_slices), which is below
 // n + n / target + B R / target; 32 levels of 4096 chunks and records of 12 bytes and more make that the bound below.
-// Items shared out by features have 4096 records or more and twice the 256th part of all: fewer than 256 of them.
+// Levels whose items are shared out by features have kShares of them at most.
 constexpr uint64_t kMostBins = (uint64_t)HG_MAX_LEVELS * hg::kMaxLevelBins;
 constexpr uint64_t kMostItems = kMostBins + kMostBins / hg::kTargetRecordsPerAccWg + 1 +
                                 HG_STATIC_SCRATCH_BYTES / 12 / hg::kTargetRecordsPerAccWg + 1 +
-                                (8u / hg::kGroupFeatures - 1) * hg::kShares;
+                                hg::kShares;
 constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
