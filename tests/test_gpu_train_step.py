@@ -4,8 +4,9 @@ Where nothing rounds the two must agree bit for bit: small integer tables, point
 0 and 1, or 2^-d with the smoothstep variant's half-voxel shift), sparse integer weights and targets that leave
 dyadic slopes make every half-precision operand and every fp32 sum exact, in any order of summation; the optimiser then
 works on equal gradients.  With random inputs the first moment after one step from zero is (1 - beta1) times the table
-gradient: it is held to the backward bar of the parity suite, 1e-5 of the summand mass (plus the optimiser's own roundings,
-2^-22 of the value), against the plain backward pass on the dL/dy the step itself used.
+gradient: it is held to the backward bar of the parity suite, 1e-5 of the summand mass plus the floor of the fixed-point sums
+(and the optimiser's own roundings, 2^-22 of the value), against the fp64 oracle on the dL/dy the step itself used.  The
+second moments, tables and weights must be what adam_step makes of the gradient in the first moments, to those roundings.
 """
 import ctypes
 
@@ -13,6 +14,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import hashgrid_oracle as orc
 from paper_2201_05989_amd import HashGridError, HashGridModel, adam_step, loss_grad, mlp_bwd
 
 pytestmark = pytest.mark.gpu
@@ -57,6 +59,7 @@ def single_calls(m, x, target):
     (3, 8, 2, 1 << 16, 4, 512, 32, "l2", 0, 100003),     # sorted, owned and shared chunks
     (2, 8, 4, 1 << 15, 64, 8192, 2, "l2", 0, 70001),     # sorted, pairs that straddle two chunks
     (3, 8, 8, 1 << 15, 4, 512, 17, "l2", 1, 30000),      # sorted, eight features (two blocks of inputs), smoothstep
+    (3, 8, 1, 1 << 24, 256, 32768, 1, "l2", 0, 400001),  # sorted, more than 16384 chunks: records written unstaged
 ])
 def test_equals_the_single_calls_where_nothing_rounds(d, L, F, T, N_min, N_max, n_out, loss, interp, B):
     m, gen = exact_model(d, L, F, T, N_min, N_max, n_out, loss, interp, seed=B)
@@ -65,6 +68,7 @@ def test_equals_the_single_calls_where_nothing_rounds(d, L, F, T, N_min, N_max, 
         x[:, 0] = torch.randint(0, 2, (B,), device="cuda", generator=gen) * 0.5 + 0.5 - 1.0 / N_max
         x[:, 0] = torch.where(torch.rand(B, device="cuda", generator=gen) < 0.5, x[:, 0], torch.zeros_like(x[:, 0]))
     x = x.contiguous()
+    assert m.grid.bwd_ws_pays(B) == (B >= 30000)
     p = m.infer(x)
     if loss == "l2":
         target = (p - torch.randint(-4, 5, p.shape, device="cuda", generator=gen) / 8.0).contiguous()
@@ -90,20 +94,36 @@ def test_equals_the_single_calls_where_nothing_rounds(d, L, F, T, N_min, N_max, 
                                                     (2, 16, 2, 1 << 20, 32768, 0, 150001), (3, 8, 4, 1 << 15, 512, 0, 50000)])
 def test_first_moments_are_the_gradient(d, L, F, T, N_max, interp, B):
     m = HashGridModel(d, 2, L=L, F=F, T=T, N_min=16, N_max=N_max, seed=3, interp=interp)
+    cfg = orc.OracleConfig(d, L, F, T, 16, N_max, interp)
     gen = torch.Generator(device="cuda").manual_seed(B)
     x = torch.rand((B, d), device="cuda", generator=gen).clamp_(max=1 - 2.0 ** -24)
+    one_minus = 1 - torch.tensor(0.9, device="cuda")
     for k in range(2):
-        m._tab_m.zero_()
-        m._tab_v.zero_()
-        m.step(x, torch.randn((B, 2), device="cuda", generator=gen))
-        g = m.grid.encode_bwd(x, m._dy, use_workspace=False)
-        mass = m.grid.encode_bwd(x, m._dy.abs(), use_workspace=False)
-        floor = float(m._dy.abs().max()) * 2.0 ** (max(d + int(np.ceil(np.log2(B))), 11) - 54)
+        for t in (m._tab_m, m._tab_v, m._net_m, m._net_v):
+            t.zero_()
+        target = torch.randn((B, 2), device="cuda", generator=gen)
+        tables, weights = m.tables.clone(), m.weights.clone()
+        *_, wm, _, total, dy = single_calls(m, x, target)
+        m.step(x, target)
+        assert torch.equal(m._dy, dy) and abs(float(m._loss_sum - total)) <= 1e-9 * float(total)
+        dy64 = m._dy.cpu().numpy().astype(np.float64)
+        g, mass = orc.encode_bwd(cfg, x.cpu().numpy(), dy64), orc.encode_bwd(cfg, x.cpu().numpy(), np.abs(dy64))
+        floor = np.abs(dy64).max() * 2.0 ** (max(d + int(np.ceil(np.log2(B))), 11) - 54)
         # beta1 m + (1 - beta1) g with m = 0: two roundings, and 0.9 itself is rounded
-        err = (m._tab_m / (1 - torch.tensor(0.9, device="cuda")) - g).abs()
-        assert (err <= 2e-5 * mass + floor + 1e-30).all(), float((err / (mass + 1e-30)).max())
+        table_grad, net_grad = m._tab_m / one_minus, m._net_m / one_minus
+        err = np.abs(table_grad.cpu().numpy().astype(np.float64) - g)
+        assert (err <= 1e-5 * mass + 2.0 ** -22 * np.abs(g) + floor + 1e-30).all(), float((err / (mass + 1e-30)).max())
+        # the weights' gradients: the same products, fp32 sums of 2^18 terms at most in another order
+        assert ((m._net_m - wm).abs() <= 1e-5 * wm.abs().max()).all()
+        for before, grad, moment, v, now, half in ((tables, table_grad, m._tab_m, m._tab_v, m.tables, m.tables_half),
+                                                   (weights, net_grad, m._net_m, m._net_v, m.weights, m.weights_half)):
+            want_m, want_v = torch.zeros_like(before), torch.zeros_like(before)
+            adam_step(before, grad, want_m, want_v, k + 1, lr=m.lr, zero_grad=False)
+            assert torch.allclose(v, want_v, rtol=2.0 ** -20, atol=1e-37)
+            big = grad.abs() > 1e-15  # (beyond 32 bits' reach of the optimiser's eps and of v's smallest values)
+            assert torch.allclose(now[big], before[big], rtol=2.0 ** -22, atol=m.lr * 2.0 ** -18)
+            assert torch.equal(half, now.half()) and torch.equal(now[grad == 0], before[grad == 0])
         assert not m._tab_zeros.any()
-        assert torch.equal(m.tables_half, m.tables.half()) and torch.equal(m.weights_half, m.weights.half())
 
 
 def test_nan_in_the_targets_reaches_the_entries_as_in_the_single_calls():
