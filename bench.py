@@ -358,7 +358,7 @@ def headline_extras(c, ms_fwd, ms_bwd, n, steps, torch):
         # training the whole model: fused forward that keeps y, the loss's gradient (the workload's loss against a
         # synthetic target), backward of the network, sorted backward of the encoding into the tables, optimiser on
         # the tables and on the network's weights
-        from paper_2201_05989_amd import loss_grad, mlp_bwd
+        from paper_2201_05989_amd import HashGridModel, loss_grad, mlp_bwd
         loss_kind = "mape" if w.name.startswith("sdf") else "l2"  # Section 4, "Training"
         target = torch.from_numpy(np.random.default_rng(11).normal(size=(w.B, 1)).astype(np.float32)).cuda()
         dout = torch.empty_like(target)
@@ -367,6 +367,9 @@ def headline_extras(c, ms_fwd, ms_bwd, n, steps, torch):
         dyk = torch.empty_like(yk)
         dWs = views(net_grad)
         grid.encode_mlp_fwd(xd, td, W1, W2, W3, o, y=yk)
+        for _ in range(3):  # untimed: the first launch loads the kernel's code
+            mlp_bwd(yk, W1, W2, W3, o, dyk, *dWs)
+        net_grad.zero_()
         ms_net_bwd = time_launches(lambda: mlp_bwd(yk, W1, W2, W3, o, dyk, *dWs), max(n // 2, 10), torch)
 
         net_counter = [0]
@@ -381,10 +384,19 @@ def headline_extras(c, ms_fwd, ms_bwd, n, steps, torch):
             adam_step(net_master, net_grad, net_m1, net_m2, net_counter[0], lr=1e-4, params_half=net_half, zero_grad=True,
                       l2_reg=1e-6)
 
+        net_grad.zero_()
+        for _ in range(3):
+            model_step()
         ms_model = time_launches(model_step, max(n // 2, 10), torch)
+        # the same iteration behind one call (hashgrid_train_step), on a model of its own
+        model = HashGridModel(w.d, 1, L=w.L, F=w.F, T=w.T, N_min=w.N_min, N_max=w.N_max, loss=loss_kind, lr=1e-4, seed=0)
+        for _ in range(3):
+            model.step(xd, target)
+        ms_one_call = time_launches(lambda: model.step(xd, target), max(n // 2, 10), torch)
         extras["network_training"] = {
             "ms_mlp_bwd": ms_net_bwd, "mlp_bwd_tflop_s": 4.0 * flops / (ms_net_bwd * 1e-3) / 1e12,
             "ms_step": ms_model, "mpoints_s": w.B / (ms_model * 1e-3) / 1e6,
+            "ms_one_call": ms_one_call, "mpoints_s_one_call": w.B / (ms_one_call * 1e-3) / 1e6,
             "loss": loss_kind,
             "step": "encode_mlp_fwd_train + loss_grad + mlp_bwd + encode_bwd_ws (overwrite) + adam_step on the tables + "
                     "adam_step on the network's weights"}
