@@ -1,6 +1,6 @@
 // The optimiser step on one scalar (paper Section 4, "Training"), shared by the kernels that apply it: the streaming
 // one over whole arrays (adam.hip), the accumulate pass that owns a chunk of the gradient (bwd_binned.hip) and the
-// one that visits only what a small batch touched (train.hip).
+// one that visits only what a small batch touched (adam_touched, hashgrid.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -189,9 +189,10 @@ void build_bin_plan(hashgrid* h) {
   const hashgrid_config& c = h->cfg;
   const LevelTable& lv = h->lv;
   bp.chunk_log2 = chunk_log2_of(c.F);
-  // The pairing of the two corners along dimension 0 needs a power-of-two T (after Eq. 4's mod T
-  // with another T the pair's entries are unrelated) and a second dimension to cut 1:1 levels by
-  // grid rows; otherwise every corner gets a record of its own (twice the records).
+  // A pair record gives one corner along dimension 0 and the kernel derives the other, which takes a power-of-two T (with
+  // another T Eq. 4's mod T comes after the XOR, and the upper corner's entry does not follow from the lower one's, though
+  // the two are near: 99.9 % of the pairs of a hashed level in one chunk, T = 1000003) and a second dimension to cut 1:1
+  // levels by grid rows; otherwise every corner gets a record of its own (twice the records).
   bp.corner_records = (c.d < 2 || !lv.T_is_pow2) ? 1u : 0u;
   bp.rec_per_point = bp.corner_records ? 1u << c.d : 1u << (c.d - 1);
   if (c.d < 1 || c.d > 3) return;  // F is 1, 2, 4 or 8 (hashgrid_create)

@@ -2,7 +2,7 @@
 // neurons, ReLU, linear output layer) on the matrix cores: from the encoded features y and the
 // upstream gradient dL/dout to dL/dy (which hashgrid_encode_bwd[_ws] then takes to the tables) and
 // the gradients of the three weight matrices, in one kernel.  Hidden activations are recomputed
-// from y (they never existed in memory: the forward kernel keeps them in LDS), so nothing but y
+// from y (they never existed in memory: the forward kernel keeps them in registers), so nothing but y
 // has to be kept from the forward pass.
 //
 // Work unit: one wave and 32 points.  Activations and gradients of a block never leave the wave's

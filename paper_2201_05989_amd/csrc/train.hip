@@ -1,11 +1,12 @@
 // One training iteration of the whole model (paper Section 4, "Training") behind one call: which kernels a batch
 // takes, and nothing else.
 //
-//   large batches   forward, counting for the sort; network forward + loss + network backward; scan (the network's
+//   large batches   forward, counting for the sort (where the batch does not give every compute unit a full workgroup the plain
+//                   forward and the count pass); network forward + loss + network backward; scan (the network's
 //                   Adam step and the loss sum ride along); scatter; accumulate + Adam on the tables
 //   small batches   forward; network; atomic additions into an array of zeros; Adam on what they touched
 //
-// Five and four launches of dependent kernels, each 2.6 us after the one before at the earliest and 3 us of the
+// Five or six, and four launches of dependent kernels, each 2.6 us after the one before at the earliest and 3 us of the
 // caller's time: one call per pass of the method took eleven and ten, and read and wrote the gradient of every table entry.
 #include <hip/hip_runtime.h>
 #include <math.h>
