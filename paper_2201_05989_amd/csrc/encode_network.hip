@@ -88,18 +88,21 @@ __device__ __forceinline__ void stage_weights(_Float16* lds, const NetShape& sh,
 // Rows of encoded features in LDS: n_in halves and kPad of padding, 8-byte aligned
 __device__ __forceinline__ int row_stride(const NetShape& sh) { return sh.n_in + kPad; }
 
-// A level's features of a point into its row.  A feature is the fp32 sum, rounded to half: the compiler otherwise makes one
+// A level's features of a point into its row.  A feature is the fp32 sum, rounded to half: left alone the compiler makes one
 // instruction with one rounding (v_fma_mixlo_f16) of the last multiply-add and the conversion in some kernels and not in
-// others, and a feature that the forward call keeps is then now and then not the one that the way back has.  (F = 1: it does
-// so in all of them, the forward kernel included.)
-template <int F>
+// others, and a feature that the forward call keeps is then now and then not the one that the way back has.  KEEP holds the
+// sums as they are.  In the split kernel eight features, and two where a wave has four levels, come out so by themselves, and
+// holding them there costs registers that the kernel does not have (77000 points, 8 levels of 8, there and back: 38 us, 63 with what it spills).
+// (F = 1: the one instruction in all of them, the forward kernel included.)
+template <int F, bool KEEP>
 __device__ __forceinline__ void put_features(float (&acc)[F], _Float16* at) {
-  if constexpr (F == 1) {
-    at[0] = (_Float16)acc[0];
+  if constexpr (!KEEP) {
+#pragma unroll
+    for (int f = 0; f < F; ++f) at[f] = (_Float16)acc[f];
   } else {
 #pragma unroll
     for (int f = 0; f < F; ++f) asm("" : "+v"(acc[f]));
-    _Float16* to = static_cast<_Float16*>(__builtin_assume_aligned(at, F == 2 ? 4 : 8));
+    _Float16* to = static_cast<_Float16*>(__builtin_assume_aligned(at, 2 * F));
 #pragma unroll
     for (int f = 0; f < F; f += 2) {
       const half2v h = __builtin_convertvector((float2v{acc[f], acc[f + 1]}), half2v);
@@ -109,9 +112,8 @@ __device__ __forceinline__ void put_features(float (&acc)[F], _Float16* at) {
   }
 }
 
-// A lane's part of the features of 16 points as an operand: `row` is its point's row (lane % 16), in LDS or memory, 8-byte aligned
-__device__ __forceinline__ void load_features(const _Float16* row, const NetShape& sh, half8 (&y)[2]) {
-  const int g = ((int)threadIdx.x & 63) >> 4;
+// A lane's part of the features of 16 points as an operand: `row` is its point's row (lane % 16), in LDS or memory, 8-byte aligned; g = lane / 16
+__device__ __forceinline__ void load_features(const _Float16* row, const NetShape& sh, const int g, half8 (&y)[2]) {
   const half4 zero = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -167,10 +169,10 @@ template <int U>
 __device__ __forceinline__ void network(const _Float16* lds, const NetShape& sh, const _Float16* (&row)[U], const uint64_t p,
                                         const uint32_t B, float* __restrict__ out) {
   half8 y[U][2], h1[U][2], h2[U][2];
-#pragma unroll
-  for (int u = 0; u < U; ++u) load_features(row[u], sh, y[u]);
-  hidden_layers<U, false>(lds, sh, y, h1, h2);
   const int g = ((int)threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int u = 0; u < U; ++u) load_features(row[u], sh, g, y[u]);
+  hidden_layers<U, false>(lds, sh, y, h1, h2);
 #pragma unroll
   for (int T = 0; T < 2; ++T) {
     if (16 * T >= sh.n_out) break;  // uniform
@@ -272,7 +274,7 @@ __global__ __launch_bounds__(kNetBlock, 4) void encode_network(
 #pragma unroll
           for (int f = 0; f < F; ++f) acc[f] = fmaf(wt, (float)e[set][m].v[f], acc[f]);
         }
-        put_features<F>(acc, my_row + l * F);
+        put_features<F, (F > 1)>(acc, my_row + l * F);
         asm volatile("" ::: "memory");  // keep the gathers of one level together
         if constexpr (decltype(pace)::value) __syncthreads();
       };
@@ -391,7 +393,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
 #pragma unroll
         for (int f = 0; f < F; ++f) acc[f] = fmaf(wt, (float)e[q][m].v[f], acc[f]);
       }
-      put_features<F>(acc, rows + lane * stride + l * F);
+      put_features<F, F == 4 || (F == 2 && LPW < 4)>(acc, rows + lane * stride + l * F);
     }
     __syncthreads();  // the rows are complete (and, the first time, the weights)
     if (!GRAD && y_out != nullptr) {
@@ -403,14 +405,16 @@ __global__ __launch_bounds__(64 * kSplitWaves, 4) void encode_network_split(
       }
     }
     if (wave < kSplitPoints / 16) {
-      const int c = lane & 15, g = lane >> 4, r = 16 * wave + c;
+      int at = lane;
+      if constexpr (GRAD) asm volatile("" : "+v"(at));  // what follows from it is not kept in registers from one round to the next
+      const int c = at & 15, g = at >> 4, r = 16 * wave + c;
       const uint64_t p = p0 + r;
       if constexpr (!GRAD) {
         const _Float16* row[1] = {rows + r * stride};
         network<1>(lds, sh, row, p, B, out);
       } else {
         half8 y[1][2], h1[1][2], h2[1][2], z[1][2];
-        load_features(rows + r * stride, sh, y[0]);
+        load_features(rows + r * stride, sh, g, y[0]);
         hidden_layers<1, true>(lds, sh, y, h1, h2);
         // dL/dout, rounded to half as the backward pass of the network rounds it
         const float* d = dout != nullptr ? dout + (p < B ? p : B - 1) * (uint64_t)sh.n_out : nullptr;

@@ -101,7 +101,9 @@ def test_position_gradient_equals_the_three_calls_where_nothing_rounds(d, L, F, 
 
 @pytest.mark.parametrize("d,L,F,T,n_out,B,interp", [(3, 8, 4, 1 << 15, 1, 30001, 1), (3, 16, 2, 1 << 19, 4, 20000, 0), (2, 8, 1, 1 << 12, 8, 777, 0),
                                                     (3, 12, 2, 1 << 14, 17, 5001, 0), (3, 32, 2, 1 << 12, 32, 3001, 0), (2, 8, 8, 1 << 14, 9, 5000, 1),
-                                                    (3, 16, 4, 1 << 14, 16, 2049, 0), (2, 24, 1, 1 << 12, 2, 130, 0)])
+                                                    (3, 16, 4, 1 << 14, 16, 2049, 0), (2, 24, 1, 1 << 12, 2, 130, 0),
+                                                    (3, 8, 8, 1 << 17, 1, 40001, 0), (2, 16, 4, 1 << 14, 1, 30001, 0), (2, 16, 2, 1 << 17, 3, 30001, 1),
+                                                    (2, 32, 2, 1 << 12, 1, 30001, 0), (3, 16, 1, 1 << 14, 1, 30001, 0), (2, 8, 4, 1 << 14, 4, 30001, 1)])
 def test_position_gradient_has_the_bits_of_the_three_calls(d, L, F, T, n_out, B, interp):
     gen = torch.Generator(device="cuda").manual_seed(200 + B)
     grid = HashGrid(d, L, F, T, 16, 512, "f16", "f16", interp)
