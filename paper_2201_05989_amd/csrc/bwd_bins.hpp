@@ -132,7 +132,7 @@ __host__ __device__ __forceinline__ void corner_rows_of(const LevelTable& lv, co
       stride *= verts;
       wt *= ((m >> i) & 1u) ? w[i] : u[i];
     }
-    if (!dense) idx = lv.T_is_pow2 ? idx & (lv.T - 1u) : idx % lv.T;
+    if (!dense) idx = lv.T_is_pow2 ? idx & (lv.T - 1u) : mod_T(idx, lv.T, lv.T_inverse);
     out.bin[m] = gb0 + (idx >> cl);
     if (!COUNT_ONLY) {
       out.la[m] = idx & cmask;

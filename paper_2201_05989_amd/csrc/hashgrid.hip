@@ -55,7 +55,7 @@ __device__ __forceinline__ void corners_of(const LevelTable& lv, uint32_t l, boo
   const CornerTerms<D> ct = corner_terms<D>(c0, dense, lv.verts[l]);
 #pragma unroll
   for (uint32_t m = 0; m < (1u << D); ++m) {
-    out.idx[m] = corner_index<D>(ct, m, dense, lv.T, lv.T_is_pow2 != 0);
+    out.idx[m] = corner_index<D>(ct, m, dense, lv, lv.T_is_pow2 != 0);
     float wt = 1.0f;
 #pragma unroll
     for (int i = 0; i < D; ++i) wt *= ((m >> i) & 1u) ? w[i] : u[i];
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kPmBlock) void bwd_input_point_major(const LevelTab
         } else {
           const CornerTerms<D> ct = corner_terms<D>(c0, false, 0u);
 #pragma unroll
-          for (uint32_t m = 0; m < (1u << D); ++m) idx[m] = corner_index<D>(ct, m, false, lv.T, false);
+          for (uint32_t m = 0; m < (1u << D); ++m) idx[m] = corner_index<D>(ct, m, false, lv, false);
         }
 #pragma unroll
         for (uint32_t m = 0; m < (1u << D); ++m) e[q][m] = tab[idx[m]];
@@ -590,6 +590,7 @@ static hg_status build_levels(const hashgrid_config& c, LevelTable& lv, uint64_t
   lv.L = c.L;
   lv.T = c.T;
   lv.T_is_pow2 = (c.T & (c.T - 1u)) == 0u;
+  lv.T_inverse = lv.T_is_pow2 ? 0u : (uint32_t)((1ull << 32) / c.T);
   uint64_t off = 0;
   for (uint32_t l = 0; l < c.L; ++l) {
     const long double s = (long double)c.N_min * exp2l((long double)l * log2_b);

@@ -22,7 +22,16 @@ struct LevelTable {
   uint32_t L;
   uint32_t T;
   uint32_t T_is_pow2;
+  uint32_t T_inverse;              // floor(2^32 / T), for mod_T (T not a power of two)
 };
+
+// h mod T (Eq. 4) for a T that is no power of two.  inverse = floor(2^32 / T) is short of 2^32 / T by less than 1, so
+// h * inverse / 2^32 is short of h / T by less than h / 2^32 < 1: the quotient is right or one too small, the remainder right
+// or T too large.  Five instructions where a division by a number that the compiler does not know takes twenty.
+__host__ __device__ __forceinline__ uint32_t mod_T(const uint32_t h, const uint32_t T, const uint32_t inverse) {
+  const uint32_t r = h - (uint32_t)(((uint64_t)h * inverse) >> 32) * T;
+  return r < r - T ? r : r - T;  // r - T wraps beyond r where r < T
+}
 
 // Eq. 4: pi_1 = 1, pi_2 = 2654435761, pi_3 = 805459861.
 __host__ __device__ __forceinline__ constexpr uint32_t prime(int i) {
@@ -64,7 +73,7 @@ __device__ __forceinline__ CornerTerms<D> corner_terms(const uint32_t (&c0)[D], 
 }
 
 template <int D>
-__device__ __forceinline__ uint32_t corner_index(const CornerTerms<D>& ct, uint32_t m, bool dense, uint32_t T,
+__device__ __forceinline__ uint32_t corner_index(const CornerTerms<D>& ct, uint32_t m, bool dense, const LevelTable& lv,
                                                  bool pow2) {
   if (dense) {
     uint32_t idx = 0;
@@ -75,7 +84,7 @@ __device__ __forceinline__ uint32_t corner_index(const CornerTerms<D>& ct, uint3
   uint32_t h = 0;
 #pragma unroll
   for (int i = 0; i < D; ++i) h ^= ct.t[i][(m >> i) & 1u];
-  return pow2 ? (h & (T - 1u)) : (h % T);
+  return pow2 ? (h & (lv.T - 1u)) : mod_T(h, lv.T, lv.T_inverse);
 }
 
 // Device-scope atomic add of one scalar of the table gradient.  Half-precision gradients (the
@@ -163,7 +172,7 @@ __device__ __forceinline__ void level_corners(const LevelTable& lv, uint32_t l, 
   } else {
     const CornerTerms<D> ct = corner_terms<D>(c0, false, 0u);
 #pragma unroll
-    for (uint32_t m = 0; m < (1u << D); ++m) idx[m] = corner_index<D>(ct, m, false, lv.T, false);
+    for (uint32_t m = 0; m < (1u << D); ++m) idx[m] = corner_index<D>(ct, m, false, lv, false);
   }
 #pragma unroll
   for (uint32_t r = 0; r < (1u << (D - 1)); ++r) {
