@@ -131,8 +131,8 @@ hg_status hashgrid_encode_bwd(const hashgrid_t* hg, uint32_t B, const float* x, 
  * at most 2^24 (2^23) entries, at most 4096 (2048) vertices per axis on the 1:1 levels of a
  * power-of-two T, and fewer than 2^32 records).  The buffer holds one record of 8 + F *
  * sizeof(dLdy scalar) bytes (rounded up to 4) per pair of corners along dimension 0,
- * B*L*2^(d-1) of them, or per corner, B*L*2^d of them, where the two corners of a pair are not
- * neighbours in memory (T not a power of two: Eq. 4's mod T; d = 1), plus 4 bytes per (tile of
+ * B*L*2^(d-1) of them, with room for one per corner, B*L*2^d of them, where the upper corner does
+ * not follow from the lower one (T not a power of two: Eq. 4's mod T; d = 1), plus 4 bytes per (tile of
  * 512 points, chunk), tiles of 4096 points where there are more than 16384 chunks in all:
  * 195 MiB at Table 1's sizes with 2^18 points, 1.6 GiB at T = 2^24 with 2^21. */
 uint64_t hashgrid_bwd_workspace_bytes(const hashgrid_t* hg, uint32_t B);
@@ -197,7 +197,7 @@ hg_status hashgrid_encode_bwd_static(const hashgrid_t* hg, uint32_t B, const flo
  * and workspace may then pass HG_BWD_COUNTED and skips its own counting pass.  Nothing else may
  * write the workspace in between, and x must be unchanged.
  * Where the counting cannot ride along (batches too small to give every compute unit a full
- * workgroup, configurations whose records are per corner) the call runs hashgrid_encode_fwd and
+ * workgroup, a T that is no power of two, d = 1) the call runs hashgrid_encode_fwd and
  * the counting pass one after the other, with the same result.
  * (What the counting costs this call depends on the order of the points: a few percent of it on
  * batches in random order, against a counting pass of a seventh of it; on batches whose

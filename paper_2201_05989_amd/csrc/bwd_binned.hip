@@ -114,16 +114,20 @@ static uint32_t tiles_for(const BinPlan& bp, uint32_t B) {
   return (uint32_t)(((uint64_t)B + points - 1) / points);
 }
 
+// Records to expect of a point and level: nearly every pair is one record, also where each corner may need its own
+// (rec_per_point then leaves room for that).
+static uint32_t pairs_per_point(const BinPlan& bp) { return bp.corner_records ? bp.rec_per_point / 2 : bp.rec_per_point; }
+
 // Slices per bin of each level for a batch of B points: coarse 1:1 levels have
 // few bins and receive B * 2^(d-1) records, so their bins are shared by several
 // accumulate-workgroups.  Levels in group_mask: every share once for each kGroupFeatures features.
 static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool half_grad) {
   bp.group_mask = 0;
-  const uint64_t share = (uint64_t)B * lv.L * bp.rec_per_point / kShares;
+  const uint64_t share = (uint64_t)B * lv.L * pairs_per_point(bp) / kShares;
   uint64_t grouped_items = 0;
   for (uint32_t l = 0; l < lv.L; ++l) {
     const uint32_t nb = bp.bin_base[l + 1] - bp.bin_base[l];
-    const uint64_t per_bin = ((uint64_t)B * bp.rec_per_point + nb - 1) / nb;
+    const uint64_t per_bin = ((uint64_t)B * pairs_per_point(bp) + nb - 1) / nb;
     uint64_t s = (per_bin + kTargetRecordsPerAccWg - 1) / kTargetRecordsPerAccWg;
     if (!((lv.dense_mask >> l) & 1u) && s < 4) s = 1;  // hashed bins are evenly filled
     if (s > 256) s = 256;
@@ -192,7 +196,9 @@ void build_bin_plan(hashgrid* h) {
   // A pair record gives one corner along dimension 0 and the kernel derives the other, which takes a power-of-two T (with
   // another T Eq. 4's mod T comes after the XOR, and the upper corner's entry does not follow from the lower one's, though
   // the two are near: 99.9 % of the pairs of a hashed level in one chunk, T = 1000003) and a second dimension to cut 1:1
-  // levels by grid rows; otherwise every corner gets a record of its own (twice the records).
+  // levels by grid rows; otherwise the record carries both indices, where it can (NearPair), and the corners get a record
+  // each where it cannot.  100003 points, T = 1000003, fp32 records of 16 bytes, both passes, a record for every corner
+  // against this: 273 against 207 us (a record for every corner writes and reads 205 MB, this 104).
   bp.corner_records = (c.d < 2 || !lv.T_is_pow2) ? 1u : 0u;
   bp.rec_per_point = bp.corner_records ? 1u << c.d : 1u << (c.d - 1);
   if (c.d < 1 || c.d > 3) return;  // F is 1, 2, 4 or 8 (hashgrid_create)
@@ -341,8 +347,10 @@ __global__ __launch_bounds__(kBinThreads) void bin_count(const LevelTable lv, co
         CornerRows<D> cr;
         corner_rows_of<D, true>(lv, bp, l, smooth, xp, cr);
 #pragma unroll
-        for (uint32_t m = 0; m < (1u << D); ++m)
-          count_one(hist, cr.bin[m] - gb_a);
+        for (uint32_t r = 0; r < (1u << (D - 1)); ++r) {
+          count_one(hist, cr.bin[2 * r] - gb_a);
+          if (cr.pair[r].step == NearPair::kNone) count_one(hist, cr.bin[2 * r + 1] - gb_a);
+        }
       } else {
         Rows<D> rw;
         rows_of<D, true>(lv, bp, l, smooth, xp, rw);
@@ -509,6 +517,13 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
   }
 }
 
+// Records of a tile and level that the scatter pass sorts in LDS.  With BinPlan::corner_records some pairs take two records (4 % on
+// a level of resolution 16, 0.5 % on hashed levels): room for an eighth more, what is beyond goes to memory unsorted.
+// Room for two each (74 instead of 41 KB at 16 bytes) would leave two workgroups on a compute unit instead of three.
+__host__ __device__ constexpr uint32_t staged_records(uint32_t pairs, bool corners) {
+  return pairs * kBinThreads + (corners ? pairs * kBinThreads / 8 : 0u);
+}
+
 // scatter: writes every record to its slot.  A bin's first record is the sum of
 // the record counts of all bins before it (every level holds exactly
 // B * rec_per_point records, so this is also level-major); inside a bin the
@@ -521,7 +536,7 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
 // local[nbp + 1] exclusive prefix of this tile's counts (where a bin's records
 // sit in the tile's sorted order), cur[nbp] the same, advanced as records are
 // placed, delta[nbp] = global slot minus tile-local position.
-// CROSS: this pass adds the pairs that straddle two chunks.  CORNERS: one record per corner (BinPlan::corner_records).
+// CROSS: this pass adds the pairs that straddle two chunks.  CORNERS: BinPlan::corner_records.
 template <int D, typename IT, int F, bool CROSS, bool CORNERS = false>
 __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, const BinPlan bp, const bool smooth,
                                                            const uint32_t B, const float* __restrict__ x,
@@ -532,17 +547,18 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
                                                            uint32_t* __restrict__ records, const uint32_t n_bins,
                                                            const uint32_t n_records, const uint32_t n_tiles,
                                                            float* __restrict__ tile_max, void* __restrict__ grad, const bool g16) {
-  constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
+  constexpr uint32_t R = 1u << (D - 1);
   using Rec = Record<IT, F>;
   using Stored = typename Rec::Stored;
   Stored* out = reinterpret_cast<Stored*>(records);
   __shared__ uint32_t scan_tmp[kBinThreads / 64];
-  // dynamic LDS: staging[R * kBinThreads] records, binv[R * kBinThreads] (part-relative bin of each
+  constexpr uint32_t kStage = staged_records(R, CORNERS);
+  // dynamic LDS: staging[kStage] records, binv[kStage] (part-relative bin of each
   // staged record, 16 bits), then the three per-bin arrays
   extern __shared__ uint32_t lds_u32[];
   Stored* staging = reinterpret_cast<Stored*>(lds_u32);
-  uint16_t* binv = reinterpret_cast<uint16_t*>(lds_u32 + R * kBinThreads * Rec::kWords);
-  uint32_t* bins_lds = lds_u32 + R * kBinThreads * Rec::kWords + R * kBinThreads / 2;
+  uint16_t* binv = reinterpret_cast<uint16_t*>(lds_u32 + kStage * Rec::kWords);
+  uint32_t* bins_lds = lds_u32 + kStage * Rec::kWords + kStage / 2;
 
   const uint32_t tile = tile_of_workgroup(blockIdx.x, n_tiles);
   if (tile >= n_tiles) return;  // uniform: a surplus workgroup of the rounded-up grid
@@ -597,7 +613,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   float gmax = 0.0f;  // largest |dL/dy| this workgroup sees (idle lanes shadow point 0)
   for (uint32_t l = l0; l < l1; ++l) {
     const uint32_t rb0 = bp.bin_base[l] - gb_a, rb1 = bp.bin_base[l + 1] - gb_a;
-    const uint32_t level_first = local[rb0], emitted = local[rb1] - level_first;  // <= R * kBinThreads
+    const uint32_t level_first = local[rb0], emitted = local[rb1] - level_first;
     IT g[F];
     if (vec_ok && K > 1) {  // uniform
       if ((l - l0) % K == 0) gv = *reinterpret_cast<const Vec<IT, E>*>(row + (uint64_t)l * F);
@@ -638,17 +654,25 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
     };
     if (valid) {
       if constexpr (CORNERS) {
-        // a corner's record: all of its weight on the "lower" side of a pair whose upper weight is 0
         CornerRows<D> cr;
         corner_rows_of<D, false>(lv, bp, l, smooth, xp, cr);
-#pragma unroll
-        for (uint32_t m = 0; m < R; ++m) {
-          const uint32_t rb = cr.bin[m] - gb_a;
+        auto put = [&](const uint32_t rb, const Stored& rec) {
           const uint32_t pos = take_slot(rb) - level_first;
-          if (pos < R * kBinThreads) {
-            staging[pos] = Rec::make(cr.la[m], 0u, 0.0f, cr.weight[m], g);
+          if (pos < kStage) {
+            staging[pos] = rec;
             binv[pos] = (uint16_t)rb;
+          } else {  // more corners with a record of their own than the staging area has room for
+            const uint32_t d = delta[rb] + level_first + pos;
+            if (d < n_records) out[d] = rec;
           }
+        };
+#pragma unroll
+        for (uint32_t r = 0; r < R; ++r) {
+          const NearPair np = cr.pair[r];
+          const bool near = np.step != NearPair::kNone;
+          put(cr.bin[2 * r] - gb_a, Rec::make_near(cr.la[2 * r], near ? np.step : 0u, near ? np.fraction : 0u,
+                                                   near ? cr.wrow[r] : cr.weight[2 * r], g));
+          if (!near) put(cr.bin[2 * r + 1] - gb_a, Rec::make_near(cr.la[2 * r + 1], 0u, 0u, cr.weight[2 * r + 1], g));
         }
       } else {
         Rows<D> rw;
@@ -658,7 +682,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
         for (uint32_t r = 0; r < R && !rw.cross; ++r) {
           const uint32_t rb = rw.bin[r] - gb_a;
           const uint32_t pos = take_slot(rb) - level_first;
-          if (pos < R * kBinThreads) {  // holds when the count pass saw the same x
+          if (pos < kStage) {  // holds when the count pass saw the same x
             staging[pos] = Rec::make(rw.la[r], rw.k, rw.wf0, rw.wrow[r], g, smooth);
             binv[pos] = (uint16_t)rb;
           }
@@ -666,7 +690,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
       }
     }
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < emitted && j < R * kBinThreads; j += kBinThreads) {
+    for (uint32_t j = threadIdx.x; j < emitted && j < kStage; j += kBinThreads) {
       const uint32_t d = delta[binv[j]] + level_first + j;
       // the count pass saw the same inputs, so d < n_records; the check only keeps a
       // caller who changed x in between from writing out of bounds
@@ -699,7 +723,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
     const IT* __restrict__ dy, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ bin_total,
     uint4* __restrict__ items, uint32_t* __restrict__ chunk_open, uint32_t* __restrict__ records, const uint32_t n_bins, const uint32_t n_records,
     const uint32_t n_tiles, float* __restrict__ tile_max, void* __restrict__ grad, const bool g16) {
-  constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
+  constexpr uint32_t R = 1u << (D - 1);
   using Rec = Record<IT, F>;
   using Stored = typename Rec::Stored;
   Stored* out = reinterpret_cast<Stored*>(records);
@@ -752,11 +776,17 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
       if constexpr (CORNERS) {
         CornerRows<D> cr;
         corner_rows_of<D, false>(lv, bp, l, smooth, xp, cr);
+        auto put = [&](const uint32_t bin, const Stored& rec) {
+          const uint32_t d = __hip_atomic_fetch_add(&slot[bin - gb_a], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (d < n_records) out[d] = rec;
+        };
 #pragma unroll
-        for (uint32_t m = 0; m < R; ++m) {
-          const uint32_t d =
-              __hip_atomic_fetch_add(&slot[cr.bin[m] - gb_a], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (d < n_records) out[d] = Rec::make(cr.la[m], 0u, 0.0f, cr.weight[m], g);
+        for (uint32_t r = 0; r < R; ++r) {
+          const NearPair np = cr.pair[r];
+          const bool near = np.step != NearPair::kNone;
+          put(cr.bin[2 * r], Rec::make_near(cr.la[2 * r], near ? np.step : 0u, near ? np.fraction : 0u,
+                                            near ? cr.wrow[r] : cr.weight[2 * r], g));
+          if (!near) put(cr.bin[2 * r + 1], Rec::make_near(cr.la[2 * r + 1], 0u, 0u, cr.weight[2 * r + 1], g));
         }
       } else {
         Rows<D> rw;
@@ -824,6 +854,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
 // lanes that have just read them.
 // GT: type of the gradient scalars (float, or _Float16: the sums are still exact fixed point and are
 // rounded to half precision once, where they are added to the gradient).
+// NEAR: records of a plan with BinPlan::corner_records (NearPair).
 // GROUPS: levels in bp.group_mask have work items for some of an entry's features (half-precision gradients).
 //
 // ADAM: a training step has no use for the gradient itself, only for what the optimiser makes of it.  The owner of a
@@ -840,7 +871,7 @@ struct AdamOut {
   uint32_t* chunk_open;
   uint32_t cross_mask;  // levels whose straddling pairs were added to grad by the scatter pass
 };
-template <typename IT, int F, bool SMOOTH, typename GT = float, bool ADAM = false, bool GROUPS = false>
+template <typename IT, int F, bool SMOOTH, typename GT = float, bool ADAM = false, bool GROUPS = false, bool NEAR = false>
 __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable lv, const BinPlan bp,
                                                               const uint32_t B, const uint32_t n_items,
                                                               const uint4* __restrict__ items,
@@ -967,6 +998,15 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     }
   };
 
+  auto unpack = [&](const Stored& rec, const Item& c, const double by, uint32_t& la, uint32_t& lb, float& w_lo, float& w_up,
+                    bool& first, double (&G)[F]) {
+    if constexpr (NEAR) {
+      first = false;
+      Rec::unpack_near(rec, cmask, by, la, lb, w_lo, w_up, G);
+    } else {
+      Rec::unpack_scaled(rec, c.dense, cmask, c.n_e - 1u, by, la, lb, w_lo, w_up, first, G);
+    }
+  };
   uint32_t item = blockIdx.x;
   auto item_at = [&](const uint32_t i) { return i < n_items ? items[i] : make_uint4(0u, 0u, 0u, 0u); };  // uniform
   Item it = describe(item_at(item), item < n_items);
@@ -999,13 +1039,14 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         float w_lo, w_up;
         double G[F];
         bool first;
-        Rec::unpack_scaled(Rec::load(records, i), it.dense, cmask, it.n_e - 1u, 1.0, la, lb, w_lo, w_up, first, G);
+        unpack(Rec::load(records, i), it, 1.0, la, lb, w_lo, w_up, first, G);
         const float wu = SMOOTH && !first ? smoothstep(w_up) : w_up, wl = SMOOTH && !first ? smoothstep(w_lo) : w_lo;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
           if (!takes(it, f)) continue;  // uniform
           if (la < it.n_e) grad_atomic_add(it.gl, F * la + f, wl * (float)G[f]);
-          if (lb < it.n_e) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
+          // (a corner's own record has no upper corner: 0 * inf is not to reach another entry)
+          if (lb < it.n_e && !(NEAR && w_up == 0.0f)) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
         }
       }
       it_n = describe(desc_n, next < n_items);
@@ -1020,7 +1061,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         float w_lo, w_up;
         double G[F];
         bool first;
-        Rec::unpack_scaled(rec, it.dense, cmask, it.n_e - 1u, scale, la, lb, w_lo, w_up, first, G);
+        unpack(rec, it, scale, la, lb, w_lo, w_up, first, G);
         const float wu = SMOOTH && !first ? smoothstep(w_up) : w_up, wl = SMOOTH && !first ? smoothstep(w_lo) : w_lo;
 #pragma unroll
         for (int f = 0; f < F; ++f) {
@@ -1272,7 +1313,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
                                const BinnedAdam* ba = nullptr) {
   const bool g16 = h->cfg.grad_dtype == HG_F16;
   using Rec = Record<IT, F>;
-  constexpr uint32_t R = CORNERS ? 1u << D : 1u << (D - 1 > 0 ? D - 1 : 0);
+  constexpr uint32_t R = 1u << (D - 1);
   constexpr int DP = CORNERS ? 2 : D;  // (dimension of the kernels that only the pair records use: never D = 1)
   BinPlan bp = h->bp;
   plan_slices(bp, h->lv, B, F, g16);
@@ -1288,7 +1329,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     return m;
   };
   // scatter: staging area, 16-bit bin of every staged record, three words per bin of the part
-  constexpr size_t kStagingBytes = (size_t)R * kBinThreads * (Rec::kWords * 4 + 2);
+  constexpr size_t kStagingBytes = (size_t)staged_records(R, CORNERS) * (Rec::kWords * 4 + 2);
   constexpr size_t kScatterLdsMax = kStagingBytes + (3 * (size_t)kMaxScatterPartBins + 1) * 4;
   // (eight 40-byte records per point do not fit the 160 KiB of a workgroup: such plans scatter unstaged)
   constexpr bool kStaged = kScatterLdsMax <= 160 * 1024;
@@ -1306,23 +1347,23 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScatterLdsMax);
     }
     if (e == hipSuccess && kAccLds > 48 * 1024)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, float>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, float, false, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
     if (e == hipSuccess && kAccLds > 48 * 1024)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, float>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, float, false, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
     if (e == hipSuccess && kAccLds > 48 * 1024)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, _Float16>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, _Float16, false, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
     if (e == hipSuccess && kAccLds > 48 * 1024)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16>),
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16, false, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
     if constexpr (F == kGroupedF) {
       if (e == hipSuccess && kAccLds > 48 * 1024)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, _Float16, false, true>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, _Float16, false, true, CORNERS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
       if (e == hipSuccess && kAccLds > 48 * 1024)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16, false, true>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, true, _Float16, false, true, CORNERS>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
     }
     if constexpr (kAdam) {
@@ -1386,7 +1427,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const dim3 acc_grid(n_items < acc_slots ? n_items : acc_slots);
   auto accumulate = [&](auto smooth_t, auto* g, auto groups_t) {
     using GT = typename std::remove_pointer<decltype(g)>::type;
-    hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT, false, decltype(groups_t)::value>), acc_grid,
+    hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT, false, decltype(groups_t)::value, CORNERS>), acc_grid,
                        dim3(kAccThreads), kAccLds, s, h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts,
                        ws.records, ws.item_counter, g, overwrite_mask, NoAdam{});
   };
@@ -1489,14 +1530,14 @@ int hashgrid_bwd_ws_pays(const hashgrid_t* hg, uint32_t B) {
   // Both passes in microseconds, from measurements on an MI355X.  Sorted pass: about 16 us of
   // launches, 0.017 us per chunk (every chunk of the gradient is visited and rewritten), then the
   // records, written once and read once: ~300 K records of 12 bytes per us, in proportion for
-  // larger ones (wider entries, fp32 dL/dy) and twice as many where every corner has its own.
+  // larger ones (wider entries, fp32 dL/dy).
   // Atomic pass: ~6 us, then ~14.5 K pairs of corners per us (11 K at F = 4, 9 K at F = 8: their
   // requests are fatter), unless one 64-byte block of the gradient draws so many requests that
   // they queue up behind each other (~0.02 us each): the smallest level decides that, taking the
   // points as spread evenly over its entries.
   const uint32_t F = hg->cfg.F, d = hg->cfg.d;
   const double pairs = (double)B * hg->lv.L * (1u << (d - 1));
-  const double records = (double)B * hg->lv.L * hg->bp.rec_per_point;
+  const double records = (double)B * hg->lv.L * hg::pairs_per_point(hg->bp);
   const double rec_bytes = 8.0 + (F * (hg->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u;
   double per_block = 0.0;
   for (uint32_t l = 0; l < hg->lv.L; ++l) {
@@ -1530,7 +1571,7 @@ hg_status hashgrid_encode_fwd_ws(const hashgrid_t* hg, uint32_t B, const float* 
   // The counting kernel runs full workgroups (they cover whole tiles), which is slow for a batch that
   // cannot give every CU one: there the plain forward in small workgroups plus the count pass is
   // faster and leaves the workspace in the same state.
-  // (So it is for plans with a record per corner, which the counting kernel does not serve.)
+  // (So it is for plans with BinPlan::corner_records, which the counting kernel does not serve.)
   if (hg->bp.corner_records || hg::point_major_block(B) < 1024u) {
     const hg_status st = hashgrid_encode_fwd(hg, B, x, params, y, stream);
     return st != HG_OK ? st : hg::launch_count(hg, B, x, ws, s);

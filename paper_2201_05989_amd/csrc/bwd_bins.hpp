@@ -5,6 +5,7 @@
 
 #include "hashgrid_common.hpp"
 #include "hashgrid_internal.hpp"
+#include "bwd_record.hpp"
 
 namespace hg {
 
@@ -92,15 +93,18 @@ __host__ __device__ __forceinline__ void rows_of(const LevelTable& lv, const Bin
   }
 }
 
-// One record per corner (plans with BinPlan::corner_records: a table size that is not a power of
-// two, where the two corners of a pair land in unrelated chunks after Eq. 4's mod T, and d = 1):
-// every level's slice is cut into aligned blocks of 2^chunk_log2 entries, a corner belongs to the
-// block of its entry.  bin / la as in Rows; weight = the corner's whole interpolation weight.
+// Plans with BinPlan::corner_records (a table size that is not a power of two, where the upper corner of a pair
+// does not follow from the lower one after Eq. 4's mod T, and d = 1): every level's slice is cut into aligned blocks of
+// 2^chunk_log2 entries, a corner belongs to the block of its entry.  bin / la / weight of every corner (weight: its whole
+// interpolation weight); pair[r] of corners 2r and 2r + 1: one record for both where they are near enough (NearPair), with
+// wrow as in Rows, else a record for each.
 template <int D>
 struct CornerRows {
   uint32_t bin[1 << D];
   uint32_t la[1 << D];
   float weight[1 << D];
+  NearPair pair[1 << (D - 1)];
+  float wrow[1 << (D - 1)];
 };
 
 template <int D, bool COUNT_ONLY>
@@ -112,11 +116,12 @@ __host__ __device__ __forceinline__ void corner_rows_of(const LevelTable& lv, co
   const float shift = smooth ? 0.5f : 0.0f;
   const float cmaxf = smooth ? Nf : Nf - 1.0f;
   uint32_t c0[D];
-  float w[D], u[D];
+  float w[D], u[D], wf0 = 0.0f;
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     float wf;
     split(xp[i], Nf, shift, cmaxf, c0[i], wf);
+    if (i == 0) wf0 = wf;
     w[i] = smooth ? smoothstep(wf) : wf;
     u[i] = smooth ? smoothstep(1.0f - wf) : 1.0f - wf;
   }
@@ -134,9 +139,17 @@ __host__ __device__ __forceinline__ void corner_rows_of(const LevelTable& lv, co
     }
     if (!dense) idx = lv.T_is_pow2 ? idx & (lv.T - 1u) : mod_T(idx, lv.T, lv.T_inverse);
     out.bin[m] = gb0 + (idx >> cl);
+    out.la[m] = idx & cmask;
+    if (!COUNT_ONLY) out.weight[m] = wt;
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < (1u << (D - 1)); ++r) {
+    out.pair[r] = near_pair(out.la[2 * r], out.la[2 * r + 1], out.bin[2 * r] == out.bin[2 * r + 1], wf0);
     if (!COUNT_ONLY) {
-      out.la[m] = idx & cmask;
-      out.weight[m] = wt;
+      float wr = 1.0f;
+#pragma unroll
+      for (int i = 1; i < D; ++i) wr *= ((r >> (i - 1)) & 1u) ? w[i] : u[i];
+      out.wrow[r] = wr;
     }
   }
 }

@@ -27,7 +27,38 @@ __host__ __device__ __forceinline__ float unpack_weight(uint32_t c) {
 }
 constexpr uint32_t kFirstVoxel = 15u;  // value of the record's k field for a pair in the first voxel along dimension 0
 
+// The pair of corners of a plan with BinPlan::corner_records (a table size that is no power of two, or d = 1).  Eq. 4's mod T
+// comes after the XOR there, so the upper corner's entry does not follow from the lower one's and the record carries the
+// difference of the two indices: the difference before the mod is +-(an odd number of k + 1 bits), k being the trailing
+// one bits of the lower corner's coordinate c, and it stays that unless one of the two wraps.  The room for it is in the fraction: from c >= 2^k - 1 on
+// the scaled coordinate is a multiple of 2^(k - 24), so the field of 23 bits has k - 1 low bits that are zero.  With
+// |difference| = 2 e + 1 and s = number of bits of e (s <= k), the 4-bit field holds s and the sign, e's bits below its highest
+// lie in the fraction's s - 1 low ones.  What does not fit that form (corners in two chunks, a wrapped index, more than 8 bits, a fraction that
+// is finer than 2^-23 as in the first voxel, or zero) is written as a record for each of the two corners, its whole weight in the
+// weight's field and the fraction 0: as exact as the pair, and no pair has the fraction 0.
+// T = 1000003: 0.4 to 0.6 % of a hashed level's pairs take two records, 4 % at resolution 16, 1 % of all over 16 levels to 2048.
+struct NearPair {
+  uint32_t step;      // s, and 8 for a negative difference; kNone: the corners get a record each
+  uint32_t fraction;  // fractional position along dimension 0 in units of 2^-23, e's lower bits in it
+  static constexpr uint32_t kNone = 16u;
+};
+// local indices la, lb in one chunk (`same`), wf the fractional position along dimension 0
+__host__ __device__ __forceinline__ NearPair near_pair(const uint32_t la, const uint32_t lb, const bool same, const float wf) {
+  const float q = wf * 0x1p23f;  // exact
+  const bool in_field = q > 0.0f && q < 0x1p23f;
+  const uint32_t q0 = in_field ? (uint32_t)q : 0u;
+  const int32_t d = (int32_t)(lb - la);
+  const uint32_t a = (uint32_t)(d < 0 ? -d : d);
+  const uint32_t s = 31u - (uint32_t)__builtin_clz(a | 1u), low = ((1u << s) - 1u) >> 1;
+  const bool fits = same && (a & 1u) && s <= 7u && q0 != 0u && (float)q0 == q && (q0 & low) == 0u;
+  NearPair p;
+  p.step = fits ? s | (d < 0 ? 8u : 0u) : NearPair::kNone;
+  p.fraction = q0 | ((a >> 1) & low);
+  return p;
+}
+
 // One record = one pair of corners that differ along dimension 0, both inside one chunk.
+// (Plans with BinPlan::corner_records use the other form of the header, NearPair below.)
 // Two header words, then the level's F values of dL/dy as they came (fp16 pairs share a word):
 //   bits 0-11   la, chunk-local index of the lower corner;
 //   bits 12-15  k: on a hashed level the upper corner is lb = la ^ (2^(k+1) - 1), k = number of
@@ -82,6 +113,36 @@ struct Record {
     for (uint32_t f = 0; f < kPayloadWords * 4 / sizeof(IT); ++f) pay[f] = f < (uint32_t)F ? g[f] : (IT)0;
     __builtin_memcpy(&r.w[2], pay, kPayloadWords * 4);
     return r;
+  }
+  // NearPair's form; step = fraction = 0 and wrow = the corner's whole weight for a record of one corner
+  static __host__ __device__ __forceinline__ Stored make_near(uint32_t la, uint32_t step, uint32_t fraction, float wrow,
+                                                              const IT (&g)[F]) {
+    const uint64_t p = (uint64_t)(la | (step << 12)) | ((uint64_t)fraction << 16) | ((uint64_t)pack_weight<19, 65>(wrow) << 39);
+    Stored r;
+    r.w[0] = (uint32_t)p;
+    r.w[1] = (uint32_t)(p >> 32);
+    IT pay[kPayloadWords * 4 / sizeof(IT)];
+#pragma unroll
+    for (uint32_t f = 0; f < kPayloadWords * 4 / sizeof(IT); ++f) pay[f] = f < (uint32_t)F ? g[f] : (IT)0;
+    __builtin_memcpy(&r.w[2], pay, kPayloadWords * 4);
+    return r;
+  }
+  // la, lb, weights and totals as unpack_scaled gives them; w_up is 0 exactly where the record is one corner's (lb then names
+  // no entry of its own)
+  static __host__ __device__ __forceinline__ void unpack_near(const Stored& r, uint32_t cmask, double scale, uint32_t& la,
+                                                              uint32_t& lb, float& w_lo, float& w_up, double (&G)[F]) {
+    const uint64_t p = (uint64_t)r.w[0] | ((uint64_t)r.w[1] << 32);
+    la = r.w[0] & 0xfffu & cmask;
+    const uint32_t s = (r.w[0] >> 12) & 7u, q = (uint32_t)(p >> 16) & 0x7fffffu, low = q & (((1u << s) - 1u) >> 1);
+    const uint32_t a = (1u << s) | (low << 1) | 1u;
+    lb = (r.w[0] & 0x8000u ? la - a : la + a) & cmask;
+    w_up = (float)(q - low) * 0x1p-23f;
+    w_lo = 1.0f - w_up;  // exact
+    const double wrow = (double)unpack_weight<19, 65>((uint32_t)(p >> 39)) * scale;
+    IT pay[kPayloadWords * 4 / sizeof(IT)];
+    __builtin_memcpy(pay, &r.w[2], kPayloadWords * 4);
+#pragma unroll
+    for (int f = 0; f < F; ++f) G[f] = wrow * (double)(float)pay[f];
   }
   static __host__ __device__ __forceinline__ Stored load(const uint32_t* base, uint32_t i) {
     const uint32_t* p = base + (uint64_t)i * kWords;
