@@ -214,7 +214,7 @@ void build_bin_plan(hashgrid* h) {
       uint32_t s = 0;
       while (((uint64_t)verts << (s + 1)) <= cap) ++s;
       const uint64_t rows = c.d == 3 ? (uint64_t)verts * verts : verts;
-      bp.row_shift[l] = (uint8_t)s;
+      bp.row_shift[l] = s;
       nb = (uint32_t)((rows + (1ull << s) - 1) >> s);
     } else {
       // The two corners of a pair share the bits above the chunk unless stepping v_0 carries out of
