@@ -21,6 +21,10 @@ HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-munsafe-fp-atomics", "-fno-gpu-flush-denormals-to-zero",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # Without this the compiler drops the end of a divergent branch that ends where the branch around it ends, and its register
+    # allocator may then put copies of live registers between the two, where the lanes that skipped the inner branch are still off:
+    # wrong outputs of the counting forward kernel (d = 3, F = 8, single precision, two points a thread) for such lanes.
+    "-mllvm", "-amdgpu-remove-redundant-endcf=0",
     "-Wall", "-Wno-unused-function",
 ]
 
