@@ -234,6 +234,11 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
       }
     }
   };
+  // Two features and two points a thread: the last multiply-add is rounded to 32 bits before it is to half precision, as in the
+  // other forms of the kernel for two features.  (Where the output and not the sum is due one level later, below, the compiler
+  // folds the two roundings into one for three levels of four.)
+  constexpr bool kLateSums = SB > 1 && F == 2 && std::is_same<IT, _Float16>::value;
+  [[maybe_unused]] float late[SB][F];
   if constexpr (PIPE) gather_level(0, 0);
   for (uint32_t l0 = 0; l0 < lv.L; l0 += G) {
     Vec<IT, F * G> out[SB];
@@ -256,7 +261,14 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
 #pragma unroll
           for (int q = 0; q < SB; ++q) {
 #pragma unroll
-            for (int f = 0; f < F; ++f) asm volatile("" : "+v"(out[q].v[F * (j - 1) + f]));
+            for (int f = 0; f < F; ++f) {
+              if constexpr (kLateSums) {
+                asm volatile("" : "+v"(late[q][f]));
+                out[q].v[F * (j - 1) + f] = (IT)late[q][f];
+              } else {
+                asm volatile("" : "+v"(out[q].v[F * (j - 1) + f]));
+              }
+            }
           }
         }
       }
@@ -275,7 +287,10 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
         // (the compiler folds this conversion into the last multiply-add in some instantiations and
         // not in others - one rounding instead of two - so two variants of the kernel may differ in
         // the last bit of an fp16 output that is an exact tie)
-        for (int f = 0; f < F; ++f) out[q].v[F * j + f] = (IT)acc[f];
+        for (int f = 0; f < F; ++f) {
+          if (kLateSums && j < G - 1) late[q][f] = acc[f];
+          else out[q].v[F * j + f] = (IT)acc[f];
+        }
       }
       asm volatile("" ::: "memory");  // keep the gathers of one level together
       // Pacing only: the barrier keeps the waves of the workgroup on the same level's slice; no data
