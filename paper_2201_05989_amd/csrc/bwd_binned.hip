@@ -670,9 +670,9 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
         for (uint32_t r = 0; r < R; ++r) {
           const NearPair np = cr.pair[r];
           const bool near = np.step != NearPair::kNone;
-          put(cr.bin[2 * r] - gb_a, Rec::make_near(cr.la[2 * r], near ? np.step : 0u, near ? np.fraction : 0u,
+          put(cr.bin[2 * r] - gb_a, Rec::make_near(cr.la[2 * r], near ? np.step : NearPair::kSingle, near ? np.fraction : 0u,
                                                    near ? cr.wrow[r] : cr.weight[2 * r], g));
-          if (!near) put(cr.bin[2 * r + 1] - gb_a, Rec::make_near(cr.la[2 * r + 1], 0u, 0u, cr.weight[2 * r + 1], g));
+          if (!near) put(cr.bin[2 * r + 1] - gb_a, Rec::make_near(cr.la[2 * r + 1], NearPair::kSingle, 0u, cr.weight[2 * r + 1], g));
         }
       } else {
         Rows<D> rw;
@@ -784,9 +784,9 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
         for (uint32_t r = 0; r < R; ++r) {
           const NearPair np = cr.pair[r];
           const bool near = np.step != NearPair::kNone;
-          put(cr.bin[2 * r], Rec::make_near(cr.la[2 * r], near ? np.step : 0u, near ? np.fraction : 0u,
+          put(cr.bin[2 * r], Rec::make_near(cr.la[2 * r], near ? np.step : NearPair::kSingle, near ? np.fraction : 0u,
                                             near ? cr.wrow[r] : cr.weight[2 * r], g));
-          if (!near) put(cr.bin[2 * r + 1], Rec::make_near(cr.la[2 * r + 1], 0u, 0u, cr.weight[2 * r + 1], g));
+          if (!near) put(cr.bin[2 * r + 1], Rec::make_near(cr.la[2 * r + 1], NearPair::kSingle, 0u, cr.weight[2 * r + 1], g));
         }
       } else {
         Rows<D> rw;
@@ -1001,8 +1001,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   auto unpack = [&](const Stored& rec, const Item& c, const double by, uint32_t& la, uint32_t& lb, float& w_lo, float& w_up,
                     bool& first, double (&G)[F]) {
     if constexpr (NEAR) {
-      first = false;
-      Rec::unpack_near(rec, cmask, by, la, lb, w_lo, w_up, G);
+      Rec::unpack_near(rec, cmask, by, la, lb, w_lo, w_up, first, G);  // (one corner's weights, 1 and 0, need no smoothstep)
     } else {
       Rec::unpack_scaled(rec, c.dense, cmask, c.n_e - 1u, by, la, lb, w_lo, w_up, first, G);
     }
@@ -1046,7 +1045,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
           if (!takes(it, f)) continue;  // uniform
           if (la < it.n_e) grad_atomic_add(it.gl, F * la + f, wl * (float)G[f]);
           // (a corner's own record has no upper corner: 0 * inf is not to reach another entry)
-          if (lb < it.n_e && !(NEAR && w_up == 0.0f)) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
+          if (lb < it.n_e && !(NEAR && first)) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
         }
       }
       it_n = describe(desc_n, next < n_items);

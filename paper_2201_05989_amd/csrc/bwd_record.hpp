@@ -33,14 +33,14 @@ constexpr uint32_t kFirstVoxel = 15u;  // value of the record's k field for a pa
 // one bits of the lower corner's coordinate c, and it stays that unless one of the two wraps.  The room for it is in the fraction: from c >= 2^k - 1 on
 // the scaled coordinate is a multiple of 2^(k - 24), so the field of 23 bits has k - 1 low bits that are zero.  With
 // |difference| = 2 e + 1 and s = number of bits of e (s <= k), the 4-bit field holds s and the sign, e's bits below its highest
-// lie in the fraction's s - 1 low ones.  What does not fit that form (corners in two chunks, a wrapped index, more than 8 bits, a fraction that
-// is finer than 2^-23 as in the first voxel, or zero) is written as a record for each of the two corners, its whole weight in the
-// weight's field and the fraction 0: as exact as the pair, and no pair has the fraction 0.
-// T = 1000003: 0.4 to 0.6 % of a hashed level's pairs take two records, 4 % at resolution 16, 1 % of all over 16 levels to 2048.
+// lie in the fraction's s - 1 low ones.  What does not fit that form (corners in two chunks, a wrapped index, more than 8 bits, 8 bits
+// downwards, a fraction that is finer than 2^-23 as in the first voxel) is written as a record for each of the two corners (kSingle), its
+// whole weight in the weight's field and the fraction 0: as exact as the pair.
+// T = 1000003: 0.4 to 0.6 % of a hashed level's pairs take two records, up to 4 % at resolution 16, 1 % of all over 16 levels to 2048.
 struct NearPair {
   uint32_t step;      // s, and 8 for a negative difference; kNone: the corners get a record each
   uint32_t fraction;  // fractional position along dimension 0 in units of 2^-23, e's lower bits in it
-  static constexpr uint32_t kNone = 16u;
+  static constexpr uint32_t kNone = 16u, kSingle = 15u;
 };
 // local indices la, lb in one chunk (`same`), wf the fractional position along dimension 0
 __host__ __device__ __forceinline__ NearPair near_pair(const uint32_t la, const uint32_t lb, const bool same, const float wf) {
@@ -50,9 +50,10 @@ __host__ __device__ __forceinline__ NearPair near_pair(const uint32_t la, const 
   const int32_t d = (int32_t)(lb - la);
   const uint32_t a = (uint32_t)(d < 0 ? -d : d);
   const uint32_t s = 31u - (uint32_t)__builtin_clz(a | 1u), low = ((1u << s) - 1u) >> 1;
-  const bool fits = same && (a & 1u) && s <= 7u && q0 != 0u && (float)q0 == q && (q0 & low) == 0u;
+  const uint32_t step = s | (d < 0 ? 8u : 0u);
+  const bool fits = same && (a & 1u) && s <= 7u && step != NearPair::kSingle && (float)q0 == q && (q0 & low) == 0u;
   NearPair p;
-  p.step = fits ? s | (d < 0 ? 8u : 0u) : NearPair::kNone;
+  p.step = fits ? step : NearPair::kNone;
   p.fraction = q0 | ((a >> 1) & low);
   return p;
 }
@@ -114,7 +115,7 @@ struct Record {
     __builtin_memcpy(&r.w[2], pay, kPayloadWords * 4);
     return r;
   }
-  // NearPair's form; step = fraction = 0 and wrow = the corner's whole weight for a record of one corner
+  // NearPair's form; step = kSingle, fraction = 0 and wrow = the corner's whole weight for a record of one corner
   static __host__ __device__ __forceinline__ Stored make_near(uint32_t la, uint32_t step, uint32_t fraction, float wrow,
                                                               const IT (&g)[F]) {
     const uint64_t p = (uint64_t)(la | (step << 12)) | ((uint64_t)fraction << 16) | ((uint64_t)pack_weight<19, 65>(wrow) << 39);
@@ -127,12 +128,14 @@ struct Record {
     __builtin_memcpy(&r.w[2], pay, kPayloadWords * 4);
     return r;
   }
-  // la, lb, weights and totals as unpack_scaled gives them; w_up is 0 exactly where the record is one corner's (lb then names
-  // no entry of its own)
+  // la, lb, weights and totals as unpack_scaled gives them; single: the record is one corner's (w_up is 0 and lb names no
+  // entry of its own)
   static __host__ __device__ __forceinline__ void unpack_near(const Stored& r, uint32_t cmask, double scale, uint32_t& la,
-                                                              uint32_t& lb, float& w_lo, float& w_up, double (&G)[F]) {
+                                                              uint32_t& lb, float& w_lo, float& w_up, bool& single,
+                                                              double (&G)[F]) {
     const uint64_t p = (uint64_t)r.w[0] | ((uint64_t)r.w[1] << 32);
     la = r.w[0] & 0xfffu & cmask;
+    single = ((r.w[0] >> 12) & 15u) == NearPair::kSingle;
     const uint32_t s = (r.w[0] >> 12) & 7u, q = (uint32_t)(p >> 16) & 0x7fffffu, low = q & (((1u << s) - 1u) >> 1);
     const uint32_t a = (1u << s) | (low << 1) | 1u;
     lb = (r.w[0] & 0x8000u ? la - a : la + a) & cmask;

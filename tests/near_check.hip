@@ -35,21 +35,22 @@ void check(const hashgrid* h, uint32_t B, const float* x, uint64_t* out) {
         out[2] += !near;
         uint32_t la, lb;
         float wl, wu;
+        bool single;
         double G[1];
         if (near) {
-          Rec::unpack_near(Rec::make_near(cr.la[lo], np.step, np.fraction, cr.wrow[r], one), cmask, 1.0, la, lb, wl, wu, G);
+          Rec::unpack_near(Rec::make_near(cr.la[lo], np.step, np.fraction, cr.wrow[r], one), cmask, 1.0, la, lb, wl, wu, single, G);
           if (smooth) {
             wl = hg::smoothstep(wl);
             wu = hg::smoothstep(wu);
           }
           const uint64_t e0 = (uint64_t)(cr.bin[lo] - bp.bin_base[l]) << cl;
           out[0] += cr.bin[lo] != cr.bin[up] || la != cr.la[lo] || lb != cr.la[up] || e0 + la >= lv.size[l] || e0 + lb >= lv.size[l];
-          out[0] += wu == 0.0f;  // only a corner's own record has no upper weight
+          out[0] += single;
           out[0] += fabs(wl * G[0] - cr.weight[lo]) > 0x1p-19 * cr.weight[lo] || fabs(wu * G[0] - cr.weight[up]) > 0x1p-19 * cr.weight[up];
         } else {
           for (uint32_t m = lo; m <= up; ++m) {
-            Rec::unpack_near(Rec::make_near(cr.la[m], 0u, 0u, cr.weight[m], one), cmask, 1.0, la, lb, wl, wu, G);
-            out[0] += la != cr.la[m] || lb > cmask || wu != 0.0f || wl != 1.0f;
+            Rec::unpack_near(Rec::make_near(cr.la[m], hg::NearPair::kSingle, 0u, cr.weight[m], one), cmask, 1.0, la, lb, wl, wu, single, G);
+            out[0] += !single || la != cr.la[m] || lb > cmask || wu != 0.0f || wl != 1.0f;
             out[0] += fabs(G[0] - cr.weight[m]) > 0x1p-19 * cr.weight[m];
           }
         }

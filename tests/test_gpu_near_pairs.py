@@ -47,3 +47,16 @@ def test_non_finite_gradients_reach_the_entries_they_belong_to():
     ok = np.isfinite(want)
     a = orc.encode_bwd(cfg, x, np.abs(np.where(np.isfinite(dy), dy, 0).astype(np.float64)))
     assert (~ok).sum() > 8 and (np.abs(got[ok] - want[ok]) <= 2e-5 * a[ok] + 1e-30).all()
+
+
+def test_non_finite_gradient_at_a_vertex_reaches_both_corners_of_a_pair():
+    """The upper corner's weight is 0 there, and 0 times infinity is not a number: as in the pass of atomic additions."""
+    rng = np.random.default_rng(5)
+    x = (rng.integers(0, 64, (2000, 3)) / 64).astype(np.float32)
+    dy = synth.make_dy(rng, 2000, 2, "f32")
+    dy[100, 0] = np.inf
+    grid = HashGrid(3, 1, 2, 50021, 64, 64, "f32", "f32")
+    got = grid.encode_bwd(dev(x), dev(dy), use_workspace=True).cpu().numpy()
+    want = grid.encode_bwd(dev(x), dev(dy), use_workspace=False).cpu().numpy()
+    np.testing.assert_array_equal(np.isfinite(got), np.isfinite(want))
+    assert (~np.isfinite(want)).sum() == 8

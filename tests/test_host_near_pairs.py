@@ -59,3 +59,13 @@ def test_nearly_every_pair_of_a_hashed_level_is_one_record(near_check):
     bad, pairs, split = near_check(3, 8, 2, 1000003, 256, 2048, 0, x)
     # far steps 2^-8 of the pairs, two chunks and the first voxel less than that
     assert bad == 0 and split < 0.01 * pairs
+
+
+@pytest.mark.parametrize("d,T", [(3, 100003), (2, 1000003), (1, 1 << 16)])
+@pytest.mark.parametrize("interp", [0, 1])
+def test_points_on_vertices_take_one_record_a_pair(near_check, d, T, interp):
+    """Fractions of zero (linear) or a half (smoothstep) on a level of 256 vertices a side.  Two records: chunks' ends, wraps, and the
+    last 8 trailing one bits or so."""
+    x = (np.random.default_rng(d).integers(0, 256, (4000, d)) / 256).astype(np.float32)
+    bad, pairs, split = near_check(d, 1, 2, T, 256, 256, interp, x)
+    assert bad == 0 and split < 0.02 * pairs
