@@ -121,13 +121,14 @@ static uint32_t pairs_per_point(const BinPlan& bp) { return bp.corner_records ? 
 // Slices per bin of each level for a batch of B points: coarse 1:1 levels have
 // few bins and receive B * 2^(d-1) records, so their bins are shared by several
 // accumulate-workgroups.  Levels in group_mask: every share once for each kGroupFeatures features.
-static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool half_grad) {
+// records: of a point and level, to be shared out.
+static void plan_slices_for(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool half_grad, uint64_t records) {
   bp.group_mask = 0;
-  const uint64_t share = (uint64_t)B * lv.L * pairs_per_point(bp) / kShares;
+  const uint64_t share = (uint64_t)B * lv.L * records / kShares;
   uint64_t grouped_items = 0;
   for (uint32_t l = 0; l < lv.L; ++l) {
     const uint32_t nb = bp.bin_base[l + 1] - bp.bin_base[l];
-    const uint64_t per_bin = ((uint64_t)B * pairs_per_point(bp) + nb - 1) / nb;
+    const uint64_t per_bin = ((uint64_t)B * records + nb - 1) / nb;
     uint64_t s = (per_bin + kTargetRecordsPerAccWg - 1) / kTargetRecordsPerAccWg;
     if (!((lv.dense_mask >> l) & 1u) && s < 4) s = 1;  // hashed bins are evenly filled
     if (s > 256) s = 256;
@@ -145,6 +146,19 @@ static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t 
     wgs += (bp.bin_base[l + 1] - bp.bin_base[l]) * bp.slices[l] * ((bp.group_mask >> l) & 1u ? F / kGroupFeatures : 1u);
   }
   bp.wg_base[lv.L] = wgs;
+}
+
+// Plans with BinPlan::corner_records: the items that the pairs ask for, or as many as a record for every corner would (twice as many,
+// half as long) where those leave the chip waiting for a few: in one dimension (neighbours in the batch are on one
+// entry often, and lanes that add to one address wait for each other), for wide entries (2 F additions a record) and where
+// there are fewer items than compute units.  Both passes, us, pairs' items against corners': d = 1, F = 2, points in order 116 -> 94;
+// d = 3, F = 8, T = 524287, uniform 143 -> 127; d = 2, F = 2, N 2 to 3, 64075 points in order 63 -> 46.  Elsewhere the shares' partial sums
+// cost more than that gains (F = 2, T = 1000003, d = 3 129 -> 132, d = 2 106 -> 109).
+static void plan_slices(BinPlan& bp, const LevelTable& lv, uint32_t B, uint32_t F, bool half_grad) {
+  plan_slices_for(bp, lv, B, F, half_grad, pairs_per_point(bp));
+  const bool one_dimension = bp.rec_per_point == 2;
+  if (bp.corner_records && (one_dimension || F >= 4 || bp.wg_base[lv.L] < kShares))
+    plan_slices_for(bp, lv, B, F, half_grad, bp.rec_per_point);
 }
 
 static uint64_t max_items(const hashgrid* h, uint32_t B) {

@@ -21,7 +21,7 @@ def test_points_without_records(d, L, F, T, param, io, interp, B):
     grid = HashGrid(d, L, F, T, 16 if T < 1 << 19 else 128, N, param, io, interp)
     gen = torch.Generator(device="cuda").manual_seed(B + F)
     x = torch.rand(B, d, device="cuda", generator=gen)
-    k = torch.randint(1, 9, (B // 2,), device="cuda", generator=gen) * (N // 8) - 1  # the last voxel of a chunk at F = 8
+    k = torch.randint(1, 5, (B // 2,), device="cuda", generator=gen) * (N // 4) - 1  # the last voxel of a chunk at F = 8
     x[::2, 0] = (k + torch.rand(B // 2, device="cuda", generator=gen) * 0.9 - (0.5 if interp else 0.0)) / N
     x = x.clamp_(max=1 - 2.0 ** -24)
     theta = (torch.rand(grid.n_entries, F, device="cuda", generator=gen) * 2 - 1).to(DT[param])

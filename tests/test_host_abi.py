@@ -214,3 +214,17 @@ def test_largest_batch_of_the_fixed_scratch(d, L, F, T, N_min, N_max, dtype, mos
     taken = [lib.hashgrid_encode_bwd_static(g._h, B, None, None, None, 0, None) != binding.HG_ERR_UNSUPPORTED
              for B in (most, most + 1)]  # (no arrays, perhaps no device: another error, after the size)
     assert taken == [True, False]
+
+
+# work items (16 bytes, last in the workspace) of one 1:1 level, any table size: as many as a record for every corner asks for in one
+# dimension, for four features and more and where there are fewer than compute units, else as a record for every pair does
+@pytest.mark.parametrize("d,F,T,N,B,chunks,items", [
+    (1, 2, 1001, 1000, 1 << 18, 1, 32), (1, 8, 1001, 1000, 1 << 18, 1, 32), (2, 4, 1001, 20, 1 << 18, 1, 64), (3, 8, 1001, 4, 1 << 18, 1, 128),
+    (3, 2, 1001, 4, 1 << 18, 1, 128), (2, 1, 1001, 20, 1 << 18, 1, 64), (2, 2, 1500001, 1100, 1 << 24, 296, 296 * 7),
+    (2, 4, 1500001, 1100, 1 << 23, 296, 296 * 7)])
+def test_work_items_of_a_level_where_pairs_carry_both_indices(d, F, T, N, B, chunks, items):
+    g = binding.HashGrid(d, 1, F, T, N, N, "f16", "f16")
+    pad = lambda n: -(-n // 256) * 256
+    before = (pad((B // 512 + 1) * chunks * 4) + 2 * pad(chunks * 4) + pad(B // 512 * 4) + pad(4) +
+              pad(B * 2 ** d * (8 + max(4, 2 * F))))
+    assert g.bwd_workspace_bytes(B) == before + pad(16 * items)
