@@ -60,3 +60,23 @@ def test_non_finite_gradient_at_a_vertex_reaches_both_corners_of_a_pair():
     want = grid.encode_bwd(dev(x), dev(dy), use_workspace=False).cpu().numpy()
     np.testing.assert_array_equal(np.isfinite(got), np.isfinite(want))
     assert (~np.isfinite(want)).sum() == 8
+
+
+@pytest.mark.parametrize("d,F,iot,interp,T,N_min,N_max,B", [
+    (3, 2, "f16", 0, (1 << 24) - 3, 8192, 65536, 4096 + 513), (2, 1, "f32", 1, (1 << 24) - 3, 8192, 65536, 9000),
+    (1, 2, "f32", 0, 1 << 24, 1 << 23, 1 << 25, 5000)])
+def test_very_many_chunks(d, F, iot, interp, T, N_min, N_max, B):
+    """More than 16384 chunks in all: the scatter pass writes its records unsorted, one or two a pair."""
+    cfg = orc.OracleConfig(d, 5, F, T, N_min, N_max, interp)
+    lv = orc.levels(cfg)
+    assert sum(-(-int(n) // 4096) for n in lv.size) > 16384
+    rng = np.random.default_rng(B)
+    x = synth.points_uniform(rng, B, d)
+    x[: B // 4] = rng.integers(0, N_min, (B // 4, d)) / N_min  # vertices
+    x[B // 4: B // 2, 0] = rng.random(B // 2 - B // 4) / N_min  # first voxel
+    x[B // 2: 3 * B // 4, 0] = (4095.75 + 4096 * rng.integers(0, N_min // 4096, 3 * B // 4 - B // 2)) / N_min  # far steps
+    x = np.clip(x.astype(np.float32), 0, np.float32(1 - 2.0 ** -24))
+    theta = synth.make_tables(rng, lv.total, F, "f16", 1.0)
+    grid = run_case(d, 5, F, T, N_min, N_max, "f16", iot, interp, x, theta, synth.make_dy(rng, B, 5 * F, iot), do_indices=False,
+                    do_dx=False)
+    assert grid.bwd_workspace_bytes(B) > 0

@@ -334,13 +334,13 @@ def test_random_configurations(seed):
     (3, 16, 2, 1000003, 16, 2048, "f16", "f16", 0, 40001),    # the headline shape with T not a power of two
     (3, 8, 2, 524287, 16, 512, "f16", "f32", 1, 20000),       # a prime T (2^19 - 1), smoothstep
     (2, 10, 4, 3 * (1 << 18), 16, 8192, "f32", "f16", 0, 33333),  # 3 * 2^18: resolutions beyond one chunk
-    (3, 6, 8, 100003, 8, 300, "f16", "f32", 0, 9001),         # 40-byte records, eight per point and level: unstaged
+    (3, 6, 8, 100003, 8, 300, "f16", "f32", 0, 9001),         # 40-byte records: the largest staging area
     (1, 12, 2, 1 << 16, 16, 1 << 20, "f16", "f16", 0, 50000),  # one dimension: 1:1 levels longer than a chunk
     (1, 8, 1, 5000, 16, 1 << 18, "f32", "f32", 1, 12345),
 ])
 def test_sorted_backward_with_a_record_per_corner(d, L, F, T, N_min, N_max, pdt, iot, interp, B):
-    # Eq. 4's mod T with a T that is not a power of two, and d = 1: the two corners of a pair are not
-    # neighbours in memory, so the sorted pass gives every corner its own record; batches of many tiles
+    # Eq. 4's mod T with a T that is not a power of two, and d = 1: the upper corner of a pair does not follow
+    # from the lower one, so the sorted pass carries both indices or gives each its own record; batches of many tiles
     # with a ragged last one, every entry point against the oracle
     cfg = orc.OracleConfig(d, L, F, T, N_min, N_max, interp)
     lv = orc.levels(cfg)
