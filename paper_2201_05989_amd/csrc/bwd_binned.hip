@@ -100,7 +100,7 @@ struct Workspace {
   float* tile_max;      // [n_tiles * parts of the scatter grid (at most L)] largest |dL/dy| seen by each scatter workgroup
   uint32_t* item_counter;  // [1] next work item of the accumulate pass
   uint32_t* chunk_open;    // [n_bins] workgroups that have yet to add their share of a chunk (accumulate pass with the optimiser)
-  uint32_t* records;    // [B * L * rec_per_point] records (Record::kWords words each)
+  uint32_t* records;    // room for [B * L * rec_per_point] records (Record::kWords words each)
   uint4* items;         // [accumulate work items] what a workgroup of that pass needs to know of each (write_items)
   uint32_t n_tiles;
   uint32_t n_bins;
@@ -531,16 +531,17 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
   }
 }
 
-// Records of a tile and level that the scatter pass sorts in LDS.  With BinPlan::corner_records some pairs take two records (4 % on
-// a level of resolution 16, 0.5 % on hashed levels): room for an eighth more, what is beyond goes to memory unsorted.
-// Room for two each (74 instead of 41 KB at 16 bytes) would leave two workgroups on a compute unit instead of three.
+// Records of a tile and level that the scatter pass sorts in LDS.  With BinPlan::corner_records some pairs take two records (up to 4 %
+// on a level of resolution 16, 0.5 % on hashed levels): room for an eighth more, what is beyond goes to memory unsorted.  With room for
+// two each (74 instead of 41 KB at 16 bytes, and 12 KB for the bins of a part at T = 1000003) one workgroup would be left on a compute unit
+// instead of three; in one and two dimensions, where it would fit better, random configurations took 1 to 2 % longer.  Most beyond it: points in
+// the first voxel of every level, d = 3, N = 256, F = 2, 100003 of them, both passes 88 us, as with a record for every corner.
 __host__ __device__ constexpr uint32_t staged_records(uint32_t pairs, bool corners) {
   return pairs * kBinThreads + (corners ? pairs * kBinThreads / 8 : 0u);
 }
 
 // scatter: writes every record to its slot.  A bin's first record is the sum of
-// the record counts of all bins before it (every level holds exactly
-// B * rec_per_point records, so this is also level-major); inside a bin the
+// the record counts of all bins before it (so the records are level-major); inside a bin the
 // tiles of 512 points follow each other.  Level by level the workgroup sorts the
 // records of its points by bin in LDS and copies them out bin after bin, so that
 // what reaches memory is runs of whole records that mostly fill whole cache
@@ -1344,21 +1345,21 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   // scatter: staging area, 16-bit bin of every staged record, three words per bin of the part
   constexpr size_t kStagingBytes = (size_t)staged_records(R, CORNERS) * (Rec::kWords * 4 + 2);
   constexpr size_t kScatterLdsMax = kStagingBytes + (3 * (size_t)kMaxScatterPartBins + 1) * 4;
-  // (eight 40-byte records per point do not fit the 160 KiB of a workgroup: such plans scatter unstaged)
-  constexpr bool kStaged = kScatterLdsMax <= 160 * 1024;
+  // The largest (146 KB: d = 3, F = 8, single precision, any table size) leaves one workgroup on a compute unit.  Unstaged such plans
+  // are 3 to 12 % faster on points in no order and up to 1.8 times slower on rays (30000 points, T = 524287, both passes: 98
+  // against 93 us, 108 against 196).
+  static_assert(kScatterLdsMax <= 160 * 1024, "a workgroup's LDS");
   constexpr size_t kAccLds = (size_t)F * 8 << chunk_log2_of(F);
   constexpr bool kAdam = !CORNERS && std::is_same<IT, _Float16>::value;  // what launch_binned_adam serves
   // more dynamic LDS than the default limit of 64 KiB: opt in once per kernel
   static const hipError_t lds_ok = [] {
     hipError_t e = hipSuccess;
-    if constexpr (kStaged) {
-      if (!CORNERS && kScatterLdsMax > 64 * 1024)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<DP, IT, F, true, false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScatterLdsMax);
-      if (e == hipSuccess && kScatterLdsMax > 64 * 1024)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<D, IT, F, false, CORNERS>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScatterLdsMax);
-    }
+    if (!CORNERS && kScatterLdsMax > 64 * 1024)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<DP, IT, F, true, false>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScatterLdsMax);
+    if (e == hipSuccess && kScatterLdsMax > 64 * 1024)
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<D, IT, F, false, CORNERS>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScatterLdsMax);
     if (e == hipSuccess && kAccLds > 48 * 1024)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, float, false, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
@@ -1413,12 +1414,12 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   auto scatter = [&](auto cross) {
     constexpr bool kCross = decltype(cross)::value;
     constexpr int DS = kCross ? DP : D;  // (the straddling pairs exist with pair records only)
-    if (bp.tile_mult > 1 || !kStaged) {
+    if (bp.tile_mult > 1) {
       hipLaunchKernelGGL((bin_scatter_direct<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
                          dim3(kBinThreads), (size_t)max_part_bins(parts) * 4, s, h->lv, bp, smooth, B, x,
                          static_cast<const IT*>(dy), ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins,
                          n_records, ws.n_tiles, ws.tile_max, grad, g16);
-    } else if constexpr (kStaged) {
+    } else {
       hipLaunchKernelGGL((bin_scatter<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
                          dim3(kBinThreads), lds_scatter, s, h->lv, bp, smooth, B, x, static_cast<const IT*>(dy),
                          ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins, n_records, ws.n_tiles,
@@ -1543,7 +1544,8 @@ int hashgrid_bwd_ws_pays(const hashgrid_t* hg, uint32_t B) {
   // Both passes in microseconds, from measurements on an MI355X.  Sorted pass: about 16 us of
   // launches, 0.017 us per chunk (every chunk of the gradient is visited and rewritten), then the
   // records, written once and read once: ~300 K records of 12 bytes per us, in proportion for
-  // larger ones (wider entries, fp32 dL/dy).
+  // larger ones (wider entries, fp32 dL/dy).  (Any table size: priced at a record a pair.  Measured, both passes alone, T = 1000003,
+  // F = 2: d = 3, fp32, 12288 points 66 us sorted and 55 atomic, 24576 70 and 102; d = 2 48 and 40, 50 and 76; the line lies between.)
   // Atomic pass: ~6 us, then ~14.5 K pairs of corners per us (11 K at F = 4, 9 K at F = 8: their
   // requests are fatter), unless one 64-byte block of the gradient draws so many requests that
   // they queue up behind each other (~0.02 us each): the smallest level decides that, taking the

@@ -234,9 +234,9 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
       }
     }
   };
-  // Two features and two points a thread: the last multiply-add is rounded to 32 bits before it is to half precision, as in the
-  // other forms of the kernel for two features.  (Where the output and not the sum is due one level later, below, the compiler
-  // folds the two roundings into one for three levels of four.)
+  // Two features and two points a thread: the last multiply-add is rounded to 32 bits before it is to half precision, plain and
+  // counting alike.  (Where the output and not the sum is due one level later, below, the compiler folds the two roundings into one in
+  // the counting kernel, for three levels of four.)
   constexpr bool kLateSums = SB > 1 && F == 2 && std::is_same<IT, _Float16>::value;
   [[maybe_unused]] float late[SB][F];
   if constexpr (PIPE) gather_level(0, 0);
@@ -254,9 +254,10 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
       if constexpr (SB > 1 && G > 2) {
         // Left alone, the compiler puts off the blends of a piece to its end, keeps the gathered entries of all its levels in registers
         // till then and spills (24 of them counting at d = 3, F = 2 in half precision, each spilled gather waited for by itself; 128 at
-        // F = 1).  The previous level's blend is therefore due here, behind this level's gathers: two levels in flight, no spills.
+        // F = 1).  The previous level's blend is therefore due here, behind this level's gathers: two levels in flight, nothing spilled
+        // there; at d = 3, counting, 42 registers still are at F = 2 with fp32 tables and half outputs (94 before), 2 to 4 at F = 1.
         // Forward and backward of 2^20 points in random order, d = 3, T = 2^19, counting: 912 -> 861 us, on rays 836 -> 798 us (plain
-        // 808 both); F = 1 on rays 939 -> 710 us.  Pieces of two levels have no more in flight to begin with.
+        // 808 both); F = 1 on rays 939 -> 710 us.  Pieces of two levels are left alone; with fp32 tables they spill 32 to 74 at F = 4.
         if (j > 0) {
 #pragma unroll
           for (int q = 0; q < SB; ++q) {
