@@ -199,10 +199,9 @@ hg_status hashgrid_encode_bwd_static(const hashgrid_t* hg, uint32_t B, const flo
  * Where the counting cannot ride along (batches too small to give every compute unit a full
  * workgroup, a T that is no power of two, d = 1) the call runs hashgrid_encode_fwd and
  * the counting pass one after the other, with the same result.
- * (What the counting costs this call depends on the order of the points: a few percent of it on
- * batches in random order, against a counting pass of a seventh of it; on batches whose
- * neighbours share voxels, samples in ray order, the forward waits less for the tables and the
- * counting costs as much as the separate pass: there hashgrid_encode_fwd and no flag is as fast.)
+ * (Both passes, d = 3, L = 16, T = 2^19, half-precision outputs, with hashgrid_encode_fwd and no flag against this call: F = 2,
+ * 2^18 points in random order 232 and 220 us, in ray order 222 and 212; 2^20 points 911 and 900, 819 and 814.  With
+ * fp32 tables and 2^19 points or more the former is the faster pair, 977 against 993.)
  * Returns HG_ERR_UNSUPPORTED when hashgrid_bwd_workspace_bytes is 0, when y or params are not
  * 16-byte / entry aligned, or when the configuration has more than 16384 chunks in all (callers
  * then use hashgrid_encode_fwd and pass no flag); HG_ERR_INVALID_ARG as hashgrid_encode_bwd_ws. */
