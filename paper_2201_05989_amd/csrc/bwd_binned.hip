@@ -508,7 +508,7 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
   uint32_t l = l0;
   while (l + 1 < l1 && gb >= bp.bin_base[l + 1]) ++l;
   const uint32_t bin = gb - bp.bin_base[l], n_sl = bp.slices[l], per = (total + n_sl - 1) / n_sl;
-  const bool dense = ((lv.dense_mask >> l) & 1u) && !bp.corner_records;  // (corner records: every level in aligned blocks)
+  const bool dense = ((lv.dense_mask >> l) & 1u) && !bp.corner_records;  // (BinPlan::corner_records: every level in aligned blocks)
   uint32_t e0, e1;
   if (dense) {
     e0 = (bin << bp.row_shift[l]) * lv.verts[l];

@@ -114,7 +114,7 @@ uint64_t check(const hashgrid* h, uint32_t B, const float* x, uint64_t* crossing
   return bad;
 }
 
-// Plans with one record per corner (BinPlan::corner_records): every corner's bin and chunk-local index
+// Plans with room for one record per corner (BinPlan::corner_records): every corner's bin and chunk-local index
 // must name the entry of Section 3 / Eq. 4, chunks being aligned blocks of the level's slice, and the
 // corners' weights must be the interpolation weights (a partition of unity).
 template <int D>

@@ -76,7 +76,7 @@ def test_sorted_pass_rounds_once_where_a_chunk_has_one_owner(F, iot):
 @pytest.mark.parametrize("d,L,F,T,N_min,N_max,iot,interp,B,points", [
     (3, 16, 2, 1 << 19, 16, 2048, "f16", 0, 40001, "sdf"),       # coarse chunks shared by several workgroups
     (2, 8, 2, 1 << 16, 8192, 32768, "f16", 0, 20000, "uniform"),  # pairs that straddle two chunks: atomics on the side
-    (3, 8, 1, 1000003, 16, 512, "f32", 1, 9000, "uniform"),       # a record per corner, single features, smoothstep
+    (3, 8, 1, 1000003, 16, 512, "f32", 1, 9000, "uniform"),       # pairs that carry both indices, single features, smoothstep
     (1, 10, 4, 1 << 14, 16, 1 << 16, "f16", 0, 30000, "uniform"),
 ])
 def test_sorted_pass_with_shared_chunks_and_atomic_side_paths(d, L, F, T, N_min, N_max, iot, interp, B, points):

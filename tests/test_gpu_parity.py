@@ -700,7 +700,7 @@ def test_workspace_backward_argument_checks():
                                       small.numel(), 0, None) == 2
     assert lib.hashgrid_encode_fwd_ws(g4._h, B, x.data_ptr(), x.data_ptr(), x.data_ptr(), small.data_ptr(),
                                       small.numel(), None) == 2
-    # a table size that is not a power of two: the sorted pass serves it with a record per corner
+    # a table size that is not a power of two: the sorted pass serves it with pairs that carry both indices
     g5 = HashGrid(3, 16, 4, 1000003, 16, 2048)
     assert g5.bwd_workspace_bytes(B) > B * 16 * 8 * 16
 

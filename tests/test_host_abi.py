@@ -165,7 +165,7 @@ def test_choice_between_the_backward_passes_needs_no_device():
     assert table1.bwd_ws_pays(1 << 14) and table1.bwd_ws_pays(1 << 18)
     small_levels = binding.HashGrid(2, 4, 2, 1 << 10, 4, 32, "f32", "f32")  # level 0 has 25 entries
     assert not small_levels.bwd_ws_pays(512) and small_levels.bwd_ws_pays(4096)
-    odd = binding.HashGrid(3, 16, 2, 1000003, 16, 2048)  # T not 2^k: a record per corner, twice as many
+    odd = binding.HashGrid(3, 16, 2, 1000003, 16, 2048)  # T not 2^k: pairs that carry both indices
     assert odd.bwd_ws_pays(1 << 20) and not odd.bwd_ws_pays(4096)
     assert not binding.HashGrid(3, 2, 2, 1 << 25, 16, 2048).bwd_ws_pays(1 << 20)  # not served: too many chunks
     wide = binding.HashGrid(3, 16, 8, 1 << 19, 16, 2048, "f16", "f32")  # 40-byte records: pays later
@@ -193,7 +193,7 @@ def test_workspace_size_of_the_sorted_backward_needs_no_device():
     need = large.bwd_workspace_bytes(1 << 21)
     assert (1 << 21) * 16 * 4 * 12 < need < (1 << 21) * 16 * 4 * 12 + 600 * 50000 * 4
     # not served: one dimension, T not a power of two, T beyond 2^24, too many pairs for 32-bit slots
-    # one record per corner where the pairing along dimension 0 does not hold: d = 1, T not a power of two
+    # room for one record per corner where the upper corner does not follow from the lower one: d = 1, T not a power of two
     assert binding.HashGrid(1, 4, 2, 1 << 10, 4, 64).bwd_workspace_bytes(1000) > 1000 * 4 * 2 * 12
     odd = binding.HashGrid(3, 16, 2, 1000003, 16, 2048).bwd_workspace_bytes(1000)
     assert 1000 * 16 * 8 * 12 < odd < 1000 * 16 * 8 * 12 + (1 << 20)
