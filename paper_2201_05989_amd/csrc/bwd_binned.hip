@@ -63,8 +63,10 @@ namespace hg {
 constexpr int kScanThreads = 1024;
 constexpr int kAccThreads = 1024;                // accumulate workgroup (512 x 2 per CU is slower)
 constexpr uint32_t kFewBins = 32;                 // bins of a level up to which the scatter pass spreads a tile's records (bin_scatter)
-constexpr int kAccUnroll = 4;                    // record loads in flight per lane in the tail of a long item
-constexpr int kAccPreWords = 24;                 // registers per lane for records requested one item ahead
+// Queues of work items: a counter each, a 128-byte line apart.  One counter hands out an item every 13 ns, whoever asks, which is
+// all of the pass where the items are short (table of 2^22 entries in two dimensions: 7600 items of 500 records, 103 us with one
+// queue, 91 with eight); with few items one queue shares them out better.
+constexpr uint32_t kQueues = 8, kQueueStride = 32, kManyItems = 1024;
 constexpr uint32_t kAccWgsPerCu = 1;             // its registers let one accumulate workgroup run per CU
 constexpr uint32_t kTargetRecordsPerAccWg = 16384;
 // Eight features an entry, half-precision gradients: a record is 16 additions in LDS, so 16384 records keep a compute unit busy
@@ -98,7 +100,7 @@ struct Workspace {
   uint32_t* counts;     // [n_tiles + 1][n_bins] counts, then exclusive prefix over tiles (last row: totals)
   uint32_t* bin_total;  // [n_bins] records in the bin
   float* tile_max;      // [n_tiles * parts of the scatter grid (at most L)] largest |dL/dy| seen by each scatter workgroup
-  uint32_t* item_counter;  // [1] next work item of the accumulate pass
+  uint32_t* item_counters;  // [kQueues * kQueueStride] next work item of each queue of the accumulate pass
   uint32_t* chunk_open;    // [n_bins] workgroups that have yet to add their share of a chunk (accumulate pass with the optimiser)
   uint32_t* records;    // room for [B * L * rec_per_point] records (Record::kWords words each)
   uint4* items;         // [accumulate work items] what a workgroup of that pass needs to know of each (write_items)
@@ -167,7 +169,8 @@ static uint64_t max_items(const hashgrid* h, uint32_t B) {
   return bp.wg_base[h->lv.L];
 }
 
-// Bytes of the workspace; before_items: those in front of the item list, which is last.
+// Bytes of the workspace; before_items: those in front of the item list, behind which are the queues' counters only.
+constexpr uint64_t kQueuesBytes = kQueues * kQueueStride * sizeof(uint32_t);
 static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* ws, uint64_t* before_items = nullptr) {
   const uint32_t nt = tiles_for(h->bp, B), nb = h->bp.bin_base[h->lv.L];
   uint64_t off = 0;
@@ -177,16 +180,16 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     return o;
   };
   const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_total = take((uint64_t)nb * 4),
-                 o_max = take((uint64_t)nt * h->lv.L * 4), o_item = take(4), o_open = take((uint64_t)nb * 4),
+                 o_max = take((uint64_t)nt * h->lv.L * 4), o_open = take((uint64_t)nb * 4),
                  o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point *
                               (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u)),
-                 o_items = take(max_items(h, B) * sizeof(uint4));
+                 o_items = take(max_items(h, B) * sizeof(uint4)), o_queues = take(kQueuesBytes);
   if (before_items) *before_items = o_items;
   if (ws) {
     ws->counts = reinterpret_cast<uint32_t*>(base + o_counts);
     ws->bin_total = reinterpret_cast<uint32_t*>(base + o_total);
     ws->tile_max = reinterpret_cast<float*>(base + o_max);
-    ws->item_counter = reinterpret_cast<uint32_t*>(base + o_item);
+    ws->item_counters = reinterpret_cast<uint32_t*>(base + o_queues);
     ws->chunk_open = reinterpret_cast<uint32_t*>(base + o_open);
     ws->records = reinterpret_cast<uint32_t*>(base + o_rec);
     ws->items = reinterpret_cast<uint4*>(base + o_items);
@@ -412,14 +415,14 @@ __device__ __forceinline__ void block_exclusive_scan(uint32_t* a, uint32_t n, ui
 
 // scan: each workgroup takes kScanBins bins and turns their column of
 // counts[tile][bin] into the exclusive prefix over tiles; it also writes the
-// bin's record count.  Workgroup 0 clears the work counter of the accumulate pass.
+// bin's record count.  Workgroup 0 clears the counters of the accumulate pass's queues.
 constexpr int kScanBins = 32;  // 128-byte rows of the count table per load (16, 8: slower; 64: the same)
 // With HG_BWD_OVERWRITE it also clears the gradient of the levels in zero_mask (those that the
 // later passes add into, see launch_binned): it is the first kernel of the call to run.
 __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles, const uint32_t n_bins,
                                                          uint32_t* __restrict__ counts,
                                                          uint32_t* __restrict__ bin_total,
-                                                         uint32_t* __restrict__ item_counter,
+                                                         uint32_t* __restrict__ item_counters,
                                                          const LevelTable lv,
                                                          const uint32_t zero_mask, const uint32_t F,
                                                          void* __restrict__ grad, const bool g16, const SideJob job) {
@@ -430,7 +433,8 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
     run_side_job<kScanThreads>(job, blockIdx.x - scan_wgs, part);
     return;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) item_counter[0] = 0;  // the accumulate pass draws its work items from here
+  // the accumulate pass draws its work items from these
+  if (blockIdx.x == 0 && threadIdx.x < kQueues) item_counters[threadIdx.x * kQueueStride] = 0;
   for (uint32_t l = 0; l < lv.L; ++l) {  // uniform; bounded by L, not by the mask: with level 31 in it the shifts would go on to 32
     if (!((zero_mask >> l) & 1u)) continue;
     const uint64_t first = lv.offset[l] * F, n = (uint64_t)lv.size[l] * F;
@@ -698,7 +702,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
           const uint32_t rb = rw.bin[r] - gb_a;
           const uint32_t pos = take_slot(rb) - level_first;
           if (pos < kStage) {  // holds when the count pass saw the same x
-            staging[pos] = Rec::make(rw.la[r], rw.k, rw.wf0, rw.wrow[r], g, smooth);
+            staging[pos] = Rec::make(rw.la[r], record_k<D>(rw, r, (lv.dense_mask >> l) & 1u), rw.wf0, rw.wrow[r], g, smooth);
             binv[pos] = (uint16_t)rb;
           }
         }
@@ -816,7 +820,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter_direct(
               __hip_atomic_fetch_add(&slot[rw.bin[r] - gb_a], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           // the count pass saw the same inputs, so d < n_records; the check only keeps a caller
           // who changed x in between from writing out of bounds
-          if (d < n_records) out[d] = Rec::make(rw.la[r], rw.k, rw.wf0, rw.wrow[r], g, smooth);
+          if (d < n_records) out[d] = Rec::make(rw.la[r], record_k<D>(rw, r, (lv.dense_mask >> l) & 1u), rw.wf0, rw.wrow[r], g, smooth);
         }
       }
     }
@@ -860,13 +864,19 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
 }
 
 // accumulate: work item = (bin, slice).  The grid is persistent: workgroup w
-// starts with item w and then draws items from a device-wide counter, two items
-// ahead, so that the first records and the count of the next item are fetched
-// while the current one is streamed (the chain "offsets -> records" is paid once
-// per workgroup, not once per bin) and workgroups that drew short items simply
-// draw more of them: items differ in size by a factor of ten on 1:1 levels when
-// the points crowd around a surface.  The LDS accumulators are re-zeroed by the
-// lanes that have just read them.
+// starts with item w and then draws items from its queue's counter, two items
+// ahead, so that the first records of the next item are fetched while the current
+// one is streamed (the chain "offsets -> records" is paid once per workgroup, not
+// once per bin) and workgroups that drew short items simply draw more of them:
+// items differ in size by a factor of ten on 1:1 levels when the points crowd
+// around a surface.  The LDS accumulators are re-zeroed by the lanes that have
+// just read them.
+//
+// What bounds it: the records read and the gradient's old and new values, 293 MB in 58 us at 2^18 points and T = 2^19 (d = 3,
+// F = 2), 57 us without the additions in LDS; in ray order the additions too, where lanes meet in one entry (2^20 points:
+// 267 us with the optimiser, 214 without them).  Times against conditional loads that were waited for all at once, one set of sums,
+// one queue: 72.8 -> 58.3 us; 2^20 points on rays with the optimiser 293 -> 267; d = 2, T = 2^22 107 -> 77; T = 2^24, 2^21 points
+// 847 -> 582.
 // GT: type of the gradient scalars (float, or _Float16: the sums are still exact fixed point and are
 // rounded to half precision once, where they are added to the gradient).
 // NEAR: records of a plan with BinPlan::corner_records (NearPair).
@@ -879,6 +889,9 @@ __global__ __launch_bounds__(kBinThreads) void bin_crossing(const LevelTable lv,
 // LDS work of this kernel.  `grad` is then an array that is zero before and after: the workgroups that share a chunk add their
 // sums into it, and the last one to arrive (chunk_open) takes them out again and applies them, as does the owner of
 // a chunk with what the straddling pairs left there.
+// Sets of sums in LDS.  With two, an item's records are added to one while other waves still empty the other, and one barrier an
+// item is enough: whoever passes it has emptied his part of the other set before.  (2 x 64 KB at F = 2; one for wider entries.)
+__host__ __device__ constexpr uint32_t acc_buffers(uint32_t F) { return F <= 2 ? 2u : 1u; }
 struct NoAdam {};
 struct AdamOut {
   AdamArgs a;
@@ -893,14 +906,15 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
                                                               const float* __restrict__ tile_max,
                                                               const uint32_t n_max,
                                                               const uint32_t* __restrict__ records,
-                                                              uint32_t* __restrict__ item_counter,
+                                                              uint32_t* __restrict__ item_counters, const uint32_t n_queues,
                                                               GT* __restrict__ grad, const uint32_t overwrite_mask,
                                                               const typename std::conditional<ADAM, AdamOut, NoAdam>::type ad) {
   // bit l of overwrite_mask: the owner of a chunk of level l stores its sums (HG_BWD_OVERWRITE, one
   // slice per chunk, no pairs that straddle chunks) instead of adding them to what is there
-  __shared__ uint32_t s_ticket;
-  extern __shared__ unsigned long long acc[];  // [F][2^chunk_log2] fixed point: feature 0 of every entry, then
-                                               // feature 1 ..., so that consecutive entries map to consecutive banks
+  constexpr uint32_t kBuffers = acc_buffers(F);
+  __shared__ uint32_t s_ticket[2];
+  extern __shared__ unsigned long long acc_lds[];  // [kBuffers][F][2^chunk_log2] fixed point: feature 0 of every entry, then
+                                                   // feature 1 ..., so that consecutive entries map to consecutive banks
   // largest |dL/dy| of the call (NaN if any is NaN) from the scatter workgroups' maxima
   __shared__ float red[kAccThreads / 64];
   float m = 0.0f;
@@ -920,9 +934,10 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   if (finite) (void)frexpf(m, &E);
   const int H = 3 + (32 - __builtin_clz(B > 1 ? B - 1 : 1));
   const int S = (62 - H < kFixedBits ? 62 - H : kFixedBits) - E;  // |summand| * 2^S < 2^min(62-H, 51)
-  const double scale = ldexp(1.0, S), inv_scale = ldexp(1.0, -S);
+  const double inv_scale = ldexp(1.0, -S);
   const uint32_t n_records = B * lv.L * bp.rec_per_point;  // < 2^32 (hashgrid_bwd_workspace_bytes)
   constexpr int kPer = (int)cap / kAccThreads;  // entries per lane
+  static_assert(kPer * kAccThreads == (int)cap, "every lane has as many entries of a chunk");
   struct alignas(F * sizeof(GT) > 16 ? 16 : F * sizeof(GT)) Entry {
     GT v[F];
   };
@@ -942,18 +957,23 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     }
   };
 
-  // item_counter starts at 0 (bin_scan clears it); a ticket is the item it stands for
+  // The counters start at 0 (bin_scan clears them).  Item gridDim.x + n_queues t + q is number t of queue q
+  const uint32_t queue = blockIdx.x % n_queues;
+  uint32_t* item_counter = item_counters + queue * kQueueStride;
+  auto item_of = [&](const uint32_t ticket) { return gridDim.x + ticket * n_queues + queue; };
+  // (the empty asm: where the compiler knows that all lanes add to one word it adds up the lanes first and broadcasts the
+  // result at once, which waits for the addition and for every load before it)
   auto draw = [&]() {
-    return gridDim.x + __hip_atomic_fetch_add(item_counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t at = 0;
+    asm volatile("" : "+v"(at));
+    return __hip_atomic_fetch_add(item_counter + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (threadIdx.x == 0) s_ticket = draw();
-  for (uint32_t i = threadIdx.x; i < F * cap; i += kAccThreads) acc[i] = 0ull;
+  if (threadIdx.x == 0) s_ticket[1] = item_of(draw());
+  for (uint32_t i = threadIdx.x; i < kBuffers * F * cap; i += kAccThreads) acc_lds[i] = 0ull;
   __syncthreads();
-  uint32_t next = s_ticket;  // every item number of n_items or more ends the loop, and tickets only grow
+  uint32_t next = __builtin_amdgcn_readfirstlane(s_ticket[1]);  // every item number of n_items or more ends the loop, and tickets only grow
 
-  // Everything an item needs before its records can be used: where they are, which chunk of
-  // the gradient it owns, and (software pipeline) its first kPre records per lane and its
-  // gradient chunk, both requested while the previous item is still being flushed.
+  // An item as the workgroup needs it, all of it uniform (scalar registers)
   struct Item {
     uint32_t l, r0, r1, n_e, bin;
     GT* gl;
@@ -963,15 +983,20 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   };
   using Rec = Record<IT, F>;
   using Stored = typename Rec::Stored;
-  constexpr int kPre = kAccPreWords / (int)Rec::kWords, kHalf = kPre / 2;
-  // wide entries: the registers do not hold the next item's gradient chunk and several records in
-  // flight as well, so the chunk is read when it is flushed and fewer records are unrolled
+  // Records on their way, a ring of kRing rows (a row: a record for every lane).  As soon as a lane has taken one out it requests the
+  // row kRing further on, of the item itself or, in its last round, of the next item: so many loads are in flight at any time,
+  // also while a chunk is flushed.  The loads carry no condition (a buffer's bound makes those beyond the item's end none): behind one
+  // the compiler counts loads in flight as if they were not there, and waits for all of them before it uses the oldest.  Rows of
+  // a short item's ring that hold nothing still take their instructions: 2, 4 and 8 rows are 64, 58 and 59 us at 11 rows an item,
+  // 79, 77 and 88 us at half a row, 612, 582 and 674 us at two.
+  constexpr int kFlushUnroll = F <= 4 ? 8 : 1;
+  constexpr int kRing = F <= 4 ? 4 : 2;
+  // wide entries: the registers do not hold the chunk's old gradient and the ring, so it is read when the chunk is flushed
   constexpr bool kChunkAhead = F <= 2;
   // is feature f the item's business
   auto takes = [&](const Item& c, const int f) {
     return !GROUPS || !c.grouped || (f >= c.f0 && f < c.f0 + kGroupFeatures);
   };
-  constexpr int kUnroll = F <= 2 ? kAccUnroll : 2;
   auto describe = [&](const uint4 d, const bool exists) {
     Item it;
     it.l = (d.w >> 12) & 31u;
@@ -986,30 +1011,27 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     it.n_e = (d.w & 0xfffu) + 1u;
     it.gl = grad + (uint64_t)(d.z & 0x3fffffffu) * F;
     it.grouped = GROUPS && ((bp.group_mask >> it.l) & 1u);
-    it.f0 = it.grouped ? __builtin_amdgcn_readfirstlane((int)(d.z >> 30)) * kGroupFeatures : 0;
+    it.f0 = it.grouped ? (int)(d.z >> 30) * kGroupFeatures : 0;
     it.orphan = false;
     if constexpr (ADAM) it.orphan = exists && !(d.w & (kItemLive | kItemShared)) && ((ad.cross_mask >> it.l) & 1u);
     return it;
   };
-  // records j0..j1-1 of each lane's share of the item
-  auto request_records = [&](const Item& it, Stored (&pre)[kPre], const int j0, const int j1) {
-    if (!it.live || !finite) return;
-#pragma unroll
-    for (int j = 0; j < kPre; ++j) {
-      if (j < j0 || j >= j1) continue;
-      const uint32_t i = it.r0 + threadIdx.x + j * kAccThreads;
-      if (i < it.r1) pre[j] = Rec::load(records, i);
-    }
+  // the ring's loads: row j of those that start at record `first` of the item, nothing beyond its last
+  const uint32_t my_byte = threadIdx.x * (Rec::kWords * 4u);
+  auto window = [&](const Item& it, const uint32_t first) {
+    const bool any = it.live && finite && first < it.r1;
+    const uint32_t at = any ? first : 0u, left = any ? it.r1 - first : 0u;
+    const uint32_t most = (uint32_t)kRing * kAccThreads;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(records) + (uint64_t)at * Rec::kWords, 0,
+                                             (left < most ? left : most) * (Rec::kWords * 4u), kBufferWord3);
   };
   auto overwrites = [&](const Item& it) { return ((overwrite_mask >> it.l) & 1u) != 0; };  // uniform
   auto request_chunk = [&](const Item& it, Entry (&cur)[kPer]) {
-    if (ADAM || !kChunkAhead || !it.live || !finite || overwrites(it)) return;
-    if (!it.shared) {
+    if (ADAM || !kChunkAhead || !it.live || !finite || it.shared || overwrites(it)) return;  // uniform
 #pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        const uint32_t e = threadIdx.x + j * kAccThreads;
-        if (e < it.n_e) cur[j] = reinterpret_cast<const Entry*>(it.gl)[e];
-      }
+    for (int j = 0; j < kPer; ++j) {
+      const uint32_t e = threadIdx.x + j * kAccThreads;
+      if (e < it.n_e) cur[j] = reinterpret_cast<const Entry*>(it.gl)[e];
     }
   };
 
@@ -1024,18 +1046,22 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   uint32_t item = blockIdx.x;
   auto item_at = [&](const uint32_t i) { return i < n_items ? items[i] : make_uint4(0u, 0u, 0u, 0u); };  // uniform
   Item it = describe(item_at(item), item < n_items);
-  Stored pre[kPre];
-  Entry cur[kPer];
-  request_records(it, pre, 0, kPre);
-  request_chunk(it, cur);
+  Stored ring[kRing];
+  {
+    const auto first = window(it, it.r0);
+#pragma unroll
+    for (int j = 0; j < kRing; ++j) ring[j] = Rec::load_from(first, my_byte, j * kAccThreads * (Rec::kWords * 4u));
+  }
+  uint4 desc_n = item_at(next);
+  uint32_t turn = 0;  // 0, 1, 0, ... item after item
   while (item < n_items) {
-    // the item after the next one, and the offsets of the next one: in flight while this one is processed
-    uint32_t ticket = 0;
+    unsigned long long* acc = acc_lds + (kBuffers == 2 ? turn * (F * cap) : 0u);
+    // the item after the next one: on its way while this one is processed
+    uint32_t ticket;
     if (threadIdx.x == 0) ticket = draw();
-    const uint4 desc_n = item_at(next);
-    Item it_n;
-    it_n.live = it_n.orphan = false;
-    Entry cur_n[kPer];
+    const Item it_n = describe(desc_n, next < n_items);
+    Entry cur[kPer];
+    request_chunk(it, cur);
     // HG_BWD_OVERWRITE: a chunk that gets no sums stored below is cleared by its owner
     auto clear_chunk = [&](const Item& c) {
       for (uint32_t q = threadIdx.x; q < c.n_e * F; q += kAccThreads)
@@ -1063,53 +1089,38 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
           if (lb < it.n_e && !(NEAR && first)) grad_atomic_add(it.gl, F * lb + f, wu * (float)G[f]);
         }
       }
-      it_n = describe(desc_n, next < n_items);
     } else if (!it.live) {
       if (overwrites(it)) clear_chunk(it);  // no records for this chunk (item < n_items inside the loop)
-      it_n = describe(desc_n, next < n_items);
-      request_records(it_n, pre, 0, kPre);
-      request_chunk(it_n, cur_n);
-    } else {
+    }
+    {
       auto add_record = [&](const Stored& rec) {
-        uint32_t la, lb;
-        float w_lo, w_up;
-        double G[F];
-        bool first;
-        unpack(rec, it, scale, la, lb, w_lo, w_up, first, G);
-        const float wu = SMOOTH && !first ? smoothstep(w_up) : w_up, wl = SMOOTH && !first ? smoothstep(w_lo) : w_lo;
+        uint32_t la8, lb8;
+        double w_lo, w_up, G[F];
+        Rec::template unpack_products<SMOOTH, NEAR>(rec, it.dense, cmask, it.dense ? cmask : it.n_e - 1u, SMOOTH ? S : S - 23, la8,
+                                                    lb8, w_lo, w_up, G);
 #pragma unroll
         for (int f = 0; f < F; ++f) {
           if (!takes(it, f)) continue;  // uniform
-          __hip_atomic_fetch_add(&acc[f * cap + la], fixed_product(wl, G[f]), __ATOMIC_RELAXED,
+          char* at = reinterpret_cast<char*>(acc + f * cap);
+          __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(at + la8), fixed_product(w_lo, G[f]), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-          __hip_atomic_fetch_add(&acc[f * cap + lb], fixed_product(wu, G[f]), __ATOMIC_RELAXED,
+          __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(at + lb8), fixed_product(w_up, G[f]), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
         }
       };
-      // The records requested ahead of time, in two halves: as soon as the first half has been
-      // consumed its registers take the first half of the next item, so that loads stay in
-      // flight while the LDS atomics of this item run, not only while it is flushed.
+      uint32_t row0 = it.live && finite ? it.r0 : it.r1;  // first record of the ring's oldest row
+      bool last;
+      do {
+        const uint32_t left = it.r1 - row0;
+        last = left <= (uint32_t)kRing * kAccThreads;
+        const auto ahead = last ? window(it_n, it_n.r0) : window(it, row0 + kRing * kAccThreads);
 #pragma unroll
-      for (int j = 0; j < kHalf; ++j)
-        if (it.r0 + threadIdx.x + j * kAccThreads < it.r1) add_record(pre[j]);
-      it_n = describe(desc_n, next < n_items);
-      request_records(it_n, pre, 0, kHalf);
-#pragma unroll
-      for (int j = kHalf; j < kPre; ++j)
-        if (it.r0 + threadIdx.x + j * kAccThreads < it.r1) add_record(pre[j]);
-      // the rest of a long item, kAccUnroll loads in flight per lane
-      uint32_t i = it.r0 + threadIdx.x + kPre * kAccThreads;
-      for (; i + (kUnroll - 1) * kAccThreads < it.r1; i += kUnroll * kAccThreads) {
-        Stored rec[kUnroll];
-#pragma unroll
-        for (int j = 0; j < kUnroll; ++j) rec[j] = Rec::load(records, i + j * kAccThreads);
-#pragma unroll
-        for (int j = 0; j < kUnroll; ++j) add_record(rec[j]);
-      }
-      for (; i < it.r1; i += kAccThreads) add_record(Rec::load(records, i));
-      // request the rest of the next item's records and its gradient chunk, then flush this one under them
-      request_records(it_n, pre, kHalf, kPre);
-      request_chunk(it_n, cur_n);
+        for (int j = 0; j < kRing; ++j) {
+          if (threadIdx.x + j * kAccThreads < left) add_record(ring[j]);
+          ring[j] = Rec::load_from(ahead, my_byte, j * kAccThreads * (Rec::kWords * 4u));
+        }
+        row0 += kRing * kAccThreads;
+      } while (!last);
     }
     // ADAM: the chunk's master values and moments, requested before the barrier that ends the summation.  Where the
     // chunk's records are few most entries get none, and only those that do are read (and below, written).
@@ -1128,15 +1139,18 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         }
       }
     }
-    if (threadIdx.x == 0) s_ticket = ticket;
+    if (threadIdx.x == 0) s_ticket[turn] = item_of(ticket);
     __syncthreads();
-    const uint32_t after_next = s_ticket;  // written before the barrier above, rewritten only after the one below
+    const uint32_t after_next = __builtin_amdgcn_readfirstlane(s_ticket[turn]);  // rewritten two items on, behind the next item's barrier
+    desc_n = item_at(after_next);
     if (it.live && finite) {
+      uint32_t tid = threadIdx.x;
+      if constexpr (F >= 4) asm volatile("" : "+v"(tid));  // (addresses worked out once, ahead of the loop, would not fit the registers)
       if (GROUPS && it.grouped && !it.shared) {
         // the owner of some features of a chunk, each sum put where it belongs as below
-#pragma unroll
+#pragma unroll 1
         for (int j = 0; j < kPer * kGroupFeatures; ++j) {
-          const uint32_t q = threadIdx.x + j * kAccThreads, e = q / kGroupFeatures, f = it.f0 + q % kGroupFeatures;
+          const uint32_t q = tid + j * kAccThreads, e = q / kGroupFeatures, f = it.f0 + q % kGroupFeatures;
           const long long a = (long long)acc[f * cap + e];
           acc[f * cap + e] = 0ull;
           if (e >= it.n_e) continue;
@@ -1147,7 +1161,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
       } else if (!it.shared) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
-          const uint32_t e = threadIdx.x + j * kAccThreads;
+          const uint32_t e = tid + j * kAccThreads;
           long long a[F];
 #pragma unroll
           for (int f = 0; f < F; ++f) {
@@ -1201,9 +1215,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         // served one after the other); the chunk may start on the odd half of a word
         const uint32_t par = (uint32_t)(reinterpret_cast<uintptr_t>(it.gl) >> 1) & 1u;
         const int n_h = (int)(it.n_e * F);
-#pragma unroll
+#pragma unroll kFlushUnroll
         for (int j = 0; j < (F * kPer) / 2 + 1; ++j) {
-          const int p = (int)threadIdx.x + j * kAccThreads;
+          const int p = (int)tid + j * kAccThreads;
           const int q0 = 2 * p - (int)par;
           float v[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -1220,9 +1234,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
       } else {
         // several workgroups share this chunk: fp32 atomics, one lane per float so that the
         // features of an entry and its neighbours travel in the same 64-byte requests
-#pragma unroll
+#pragma unroll kFlushUnroll
         for (int j = 0; j < F * kPer; ++j) {
-          const uint32_t q = threadIdx.x + j * kAccThreads;  // float index in the chunk
+          const uint32_t q = tid + j * kAccThreads;  // float index in the chunk
           const uint32_t e = q / F;
           unsigned long long* slot = &acc[(q % F) * cap + e];
           const long long a = (long long)*slot;
@@ -1262,12 +1276,11 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
         }
       }
     }
-    __syncthreads();
+    if constexpr (kBuffers == 1) __syncthreads();
+    turn ^= 1u;
     item = next;
     next = after_next;
     it = it_n;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) cur[j] = cur_n[j];
   }
 }
 
@@ -1349,7 +1362,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   // are 3 to 12 % faster on points in no order and up to 1.8 times slower on rays (30000 points, T = 524287, both passes: 98
   // against 93 us, 108 against 196).
   static_assert(kScatterLdsMax <= 160 * 1024, "a workgroup's LDS");
-  constexpr size_t kAccLds = (size_t)F * 8 << chunk_log2_of(F);
+  constexpr size_t kAccLds = (size_t)acc_buffers(F) * F * 8 << chunk_log2_of(F);
   constexpr bool kAdam = !CORNERS && std::is_same<IT, _Float16>::value;  // what launch_binned_adam serves
   // more dynamic LDS than the default limit of 64 KiB: opt in once per kernel
   static const hipError_t lds_ok = [] {
@@ -1409,7 +1422,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const bool defer_cross = overwrite && cross_mask != 0;  // those atomic adds then follow the accumulate pass
   const SideJob job = ba ? ba->job : SideJob{};
   hipLaunchKernelGGL(bin_scan, dim3((ws.n_bins + kScanBins - 1) / kScanBins + job.blocks), dim3(kScanThreads), 0, s,
-                     ws.n_tiles, ws.n_bins, ws.counts, ws.bin_total, ws.item_counter, h->lv, zero_mask,
+                     ws.n_tiles, ws.n_bins, ws.counts, ws.bin_total, ws.item_counters, h->lv, zero_mask,
                      (uint32_t)F, grad, g16, job);
   auto scatter = [&](auto cross) {
     constexpr bool kCross = decltype(cross)::value;
@@ -1439,11 +1452,12 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     return (uint32_t)cus * kAccWgsPerCu;
   }();
   const dim3 acc_grid(n_items < acc_slots ? n_items : acc_slots);
+  const uint32_t n_queues = n_items >= kManyItems ? kQueues : 1u;
   auto accumulate = [&](auto smooth_t, auto* g, auto groups_t) {
     using GT = typename std::remove_pointer<decltype(g)>::type;
     hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, GT, false, decltype(groups_t)::value, CORNERS>), acc_grid,
                        dim3(kAccThreads), kAccLds, s, h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts,
-                       ws.records, ws.item_counter, g, overwrite_mask, NoAdam{});
+                       ws.records, ws.item_counters, n_queues, g, overwrite_mask, NoAdam{});
   };
   if constexpr (kAdam) {
     if (ba) {
@@ -1454,7 +1468,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
       out.cross_mask = cross_mask;
       auto accumulate_adam = [&](auto smooth_t) {
         hipLaunchKernelGGL((bin_accumulate<IT, F, decltype(smooth_t)::value, float, true>), acc_grid, dim3(kAccThreads),
-                           kAccLds, s, h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts, ws.records, ws.item_counter, static_cast<float*>(grad), 0u, out);
+                           kAccLds, s, h->lv, bp, B, n_items, ws.items, ws.tile_max, ws.n_tiles * parts, ws.records, ws.item_counters, n_queues, static_cast<float*>(grad), 0u, out);
       };
       if (smooth) accumulate_adam(std::true_type{});
       else accumulate_adam(std::false_type{});
@@ -1631,7 +1645,7 @@ constexpr uint64_t kMostBins = (uint64_t)HG_MAX_LEVELS * hg::kMaxLevelBins;
 constexpr uint64_t kMostItems = kMostBins + kMostBins / hg::kTargetRecordsPerAccWg + 1 +
                                 HG_STATIC_SCRATCH_BYTES / 12 / hg::kTargetRecordsPerAccWg + 1 +
                                 hg::kShares;
-constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256;
+constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256 + hg::kQueuesBytes;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 namespace hg {

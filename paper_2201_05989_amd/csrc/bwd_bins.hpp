@@ -93,6 +93,12 @@ __host__ __device__ __forceinline__ void rows_of(const LevelTable& lv, const Bin
   }
 }
 
+// The record's k field for row r (see bwd_record.hpp): on a 1:1 level the trailing one bits of the local index
+template <int D>
+__host__ __device__ __forceinline__ uint32_t record_k(const Rows<D>& rw, uint32_t r, bool dense) {
+  return dense && rw.k != kFirstVoxel ? (uint32_t)__builtin_ctz(~rw.la[r]) : rw.k;
+}
+
 // Plans with BinPlan::corner_records (a table size that is not a power of two, where the upper corner of a pair
 // does not follow from the lower one after Eq. 4's mod T, and d = 1): every level's slice is cut into aligned blocks of
 // 2^chunk_log2 entries, a corner belongs to the block of its entry.  bin / la / weight of every corner (weight: its whole

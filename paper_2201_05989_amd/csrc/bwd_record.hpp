@@ -8,6 +8,8 @@
 
 namespace hg {
 
+constexpr int kBufferWord3 = 0x00020000;  // last word of a buffer's descriptor: 32-bit elements, no swizzle
+
 // A weight in [0,1] as a small float: `MBITS` mantissa bits under a 6-bit exponent, 0 for weights
 // below 2^(LOW-127) (LOW is the fp32 exponent field that exponent code 1 stands for; such weights,
 // 2^-62 and less, are far below what the fixed-point sums resolve).  The interpolation weights
@@ -65,18 +67,21 @@ __host__ __device__ __forceinline__ NearPair near_pair(const uint32_t la, const 
 //   bits 12-15  k: on a hashed level the upper corner is lb = la ^ (2^(k+1) - 1), k = number of
 //               trailing one bits of the lower corner's coordinate along dimension 0 (pi_1 = 1
 //               in Eq. 4, so stepping that coordinate XORs the index with this mask, cut to the
-//               table size when the table is smaller than a chunk); on a 1:1 level lb = la + 1.
+//               table size when the table is smaller than a chunk); on a 1:1 level lb = la + 1, and k is the
+//               number of trailing one bits of la, which makes it the same XOR.
 //               k = 15 (kFirstVoxel) says that this coordinate is 0 (so k is 0) and that the
 //               next field is in its second form;
-//   bits 16-38  the fractional position wf0 along dimension 0.  Whenever the scaled coordinate is 1
+//   bits 16-40  wrow, product of the weights of the other dimensions, as a small float (19
+//               mantissa bits; 0 and 1 exact);
+//   bits 41-63  the fractional position wf0 along dimension 0.  Whenever the scaled coordinate is 1
 //               or more, its fraction is a multiple of 2^-23 and the field holds it exactly, in
 //               units of 2^-23: both weights of the pair, wf0 and 1 - wf0, are exact.  In the first
 //               voxel (scaled coordinate below 1, k = 15) the fraction can be any float: the field
 //               then holds the smaller of wf0 and 1 - wf0 as a small float (16 mantissa bits) and,
 //               in its top bit, which of the two that is; the other weight is 1 minus it
-//               (for the smoothstep variant: of S(wf0) and S(1 - wf0) = 1 - S(wf0));
-//   bits 39-63  wrow, product of the weights of the other dimensions, as a small float (19
-//               mantissa bits; 0 and 1 exact).
+//               (for the smoothstep variant: of S(wf0) and S(1 - wf0) = 1 - S(wf0)).
+// The reader takes the fields apart in one or two instructions each (unpack_products): the fraction is what a shift leaves of the
+// second word, the weight lies across the two words where one funnel shift puts it into a double's upper half.
 // 12 bytes at F = 2 with fp16 dL/dy.  A corner's summand weight * dL/dy therefore moves by at most
 // 2^-20 of itself through wrow, and by 2^-17 more for a pair in the first voxel: relative
 // precision, inside the 1e-5 the gradient is held to.
@@ -88,6 +93,15 @@ struct Record {
   struct Stored {
     uint32_t w[kWords];
   };
+  static __host__ __device__ __forceinline__ void put_header(Stored& r, uint32_t low16, uint32_t q, float wrow) {
+    const uint64_t p = (uint64_t)low16 | ((uint64_t)pack_weight<19, 65>(wrow) << 16) | ((uint64_t)q << 41);
+    r.w[0] = (uint32_t)p;
+    r.w[1] = (uint32_t)(p >> 32);
+  }
+  // the weight's 25 bits (the bits above them belong to the fraction)
+  static __host__ __device__ __forceinline__ uint32_t weight_code(const Stored& r) {
+    return (uint32_t)(((uint64_t)r.w[0] | ((uint64_t)r.w[1] << 32)) >> 16) & 0x1ffffffu;
+  }
   // `smooth`: the smoothstep variant (Appendix A of the paper).  Only the first-voxel form needs to
   // know: it stores the pair's final weights S(wf0), S(1 - wf0), because S would double the relative
   // error of a rounded small fraction; everywhere else the fraction is exact and S is applied by the reader.
@@ -104,11 +118,8 @@ struct Record {
       q0 = (uint32_t)rintf(wf0 * 0x1p23f);
       q0 = q0 < 0x7fffffu ? q0 : 0x7fffffu;
     }
-    const uint32_t qr = pack_weight<19, 65>(wrow);
-    const uint64_t p = (uint64_t)(la | (k << 12)) | ((uint64_t)q0 << 16) | ((uint64_t)qr << 39);
     Stored r;
-    r.w[0] = (uint32_t)p;
-    r.w[1] = (uint32_t)(p >> 32);
+    put_header(r, la | (k << 12), q0, wrow);
     IT pay[kPayloadWords * 4 / sizeof(IT)];
 #pragma unroll
     for (uint32_t f = 0; f < kPayloadWords * 4 / sizeof(IT); ++f) pay[f] = f < (uint32_t)F ? g[f] : (IT)0;
@@ -118,10 +129,8 @@ struct Record {
   // NearPair's form; step = kSingle, fraction = 0 and wrow = the corner's whole weight for a record of one corner
   static __host__ __device__ __forceinline__ Stored make_near(uint32_t la, uint32_t step, uint32_t fraction, float wrow,
                                                               const IT (&g)[F]) {
-    const uint64_t p = (uint64_t)(la | (step << 12)) | ((uint64_t)fraction << 16) | ((uint64_t)pack_weight<19, 65>(wrow) << 39);
     Stored r;
-    r.w[0] = (uint32_t)p;
-    r.w[1] = (uint32_t)(p >> 32);
+    put_header(r, la | (step << 12), fraction, wrow);
     IT pay[kPayloadWords * 4 / sizeof(IT)];
 #pragma unroll
     for (uint32_t f = 0; f < kPayloadWords * 4 / sizeof(IT); ++f) pay[f] = f < (uint32_t)F ? g[f] : (IT)0;
@@ -133,19 +142,40 @@ struct Record {
   static __host__ __device__ __forceinline__ void unpack_near(const Stored& r, uint32_t cmask, double scale, uint32_t& la,
                                                               uint32_t& lb, float& w_lo, float& w_up, bool& single,
                                                               double (&G)[F]) {
-    const uint64_t p = (uint64_t)r.w[0] | ((uint64_t)r.w[1] << 32);
     la = r.w[0] & 0xfffu & cmask;
     single = ((r.w[0] >> 12) & 15u) == NearPair::kSingle;
-    const uint32_t s = (r.w[0] >> 12) & 7u, q = (uint32_t)(p >> 16) & 0x7fffffu, low = q & (((1u << s) - 1u) >> 1);
+    const uint32_t s = (r.w[0] >> 12) & 7u, q = r.w[1] >> 9, low = q & (((1u << s) - 1u) >> 1);
     const uint32_t a = (1u << s) | (low << 1) | 1u;
     lb = (r.w[0] & 0x8000u ? la - a : la + a) & cmask;
     w_up = (float)(q - low) * 0x1p-23f;
     w_lo = 1.0f - w_up;  // exact
-    const double wrow = (double)unpack_weight<19, 65>((uint32_t)(p >> 39)) * scale;
+    const double wrow = (double)unpack_weight<19, 65>(weight_code(r)) * scale;
     IT pay[kPayloadWords * 4 / sizeof(IT)];
     __builtin_memcpy(pay, &r.w[2], kPayloadWords * 4);
 #pragma unroll
     for (int f = 0; f < F; ++f) G[f] = wrow * (double)(float)pay[f];
+  }
+  // a record at `offset` + `row` bytes of a buffer (row: uniform); zeros beyond its end
+  static __device__ __forceinline__ Stored load_from(__amdgpu_buffer_rsrc_t buffer, uint32_t offset, uint32_t row) {
+    typedef uint32_t words2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t words3 __attribute__((ext_vector_type(3)));
+    typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+    constexpr int kStream = 2;  // read once
+    Stored r;
+    uint32_t q = 0;
+#pragma unroll
+    for (; q + 4 <= kWords; q += 4) {
+      const words4 v = __builtin_amdgcn_raw_buffer_load_b128(buffer, offset + 4 * q, row, kStream);
+      __builtin_memcpy(&r.w[q], &v, 16);
+    }
+    if constexpr (kWords % 4 == 3) {
+      const words3 v = __builtin_amdgcn_raw_buffer_load_b96(buffer, offset + 4 * q, row, kStream);
+      __builtin_memcpy(&r.w[q], &v, 12);
+    } else if constexpr (kWords % 4 == 2) {
+      const words2 v = __builtin_amdgcn_raw_buffer_load_b64(buffer, offset + 4 * q, row, kStream);
+      __builtin_memcpy(&r.w[q], &v, 8);
+    }
+    return r;
   }
   static __host__ __device__ __forceinline__ Stored load(const uint32_t* base, uint32_t i) {
     const uint32_t* p = base + (uint64_t)i * kWords;
@@ -164,10 +194,9 @@ struct Record {
   static __host__ __device__ __forceinline__ void unpack_scaled(const Stored& r, bool dense, uint32_t cmask, uint32_t xmask,
                                                        double scale, uint32_t& la, uint32_t& lb, float& w_lo,
                                                        float& w_up, bool& first, double (&G)[F]) {
-    const uint64_t p = (uint64_t)r.w[0] | ((uint64_t)r.w[1] << 32);
     la = r.w[0] & 0xfffu & cmask;
     uint32_t k = (r.w[0] >> 12) & 0xfu;
-    const uint32_t q0 = (uint32_t)(p >> 16) & 0x7fffffu;
+    const uint32_t q0 = r.w[1] >> 9;
     first = k == kFirstVoxel;
     if (__builtin_expect(first, 0)) {  // rare: one voxel in N_l along dimension 0
       k = 0;
@@ -180,7 +209,53 @@ struct Record {
       w_lo = 1.0f - w_up;  // exact
     }
     lb = dense ? (la + 1u) & cmask : la ^ (((2u << k) - 1u) & xmask);
-    const double wrow = (double)unpack_weight<19, 65>((uint32_t)(p >> 39)) * scale;
+    const double wrow = (double)unpack_weight<19, 65>(weight_code(r)) * scale;
+    IT pay[kPayloadWords * 4 / sizeof(IT)];
+    __builtin_memcpy(pay, &r.w[2], kPayloadWords * 4);
+#pragma unroll
+    for (int f = 0; f < F; ++f) G[f] = wrow * (double)(float)pay[f];
+  }
+  // What the accumulate pass multiplies and where it adds: byte offsets of the two entries' 64-bit sums (la8, lb8) and, as
+  // doubles, the weights along dimension 0 and the totals times a power of two, so that w * G is
+  // weight * wrow * dL/dy * 2^S exactly, as with unpack_scaled.  About 30 vector instructions a record of two features with the
+  // additions, half of what the conversions through single precision and a branch for 1:1 levels came to; the pass
+  // spends more time on them than on the additions in LDS.
+  //   without smoothstep the weights are the fraction's integer and 2^23 minus it, and exponent = S - 23; with it exponent = S;
+  //   the double of wrow is its code with the exponent moved: a code of 0 reads as 2^(S - 63) (or 2^(S - 86)) instead of 0, whose
+  //   products round to 0 (|dL/dy| 2^S <= 2^51);
+  //   xmask: chunk capacity minus 1 on a 1:1 level.
+  template <bool SMOOTH, bool NEAR>
+  static __host__ __device__ __forceinline__ void unpack_products(const Stored& r, bool dense, uint32_t cmask, uint32_t xmask,
+                                                                  int exponent, uint32_t& la8, uint32_t& lb8, double& w_lo,
+                                                                  double& w_up, double (&G)[F]) {
+    const uint32_t w0 = r.w[0], w1 = r.w[1], cmask8 = cmask << 3, xmask8 = xmask << 3;
+    la8 = (w0 << 3) & cmask8;
+    uint32_t q = w1 >> 9;
+    if (NEAR) {
+      const uint32_t s = (w0 >> 12) & 7u, low = q & (((1u << s) - 1u) >> 1);
+      const uint32_t a8 = (8u << s) | (low << 4) | 8u;
+      lb8 = (w0 & 0x8000u ? la8 - a8 : la8 + a8) & cmask8;
+      q -= low;
+    } else {
+      lb8 = la8 ^ (((16u << ((w0 >> 12) & 15u)) - 8u) & xmask8);
+    }
+    if (SMOOTH) {
+      const float up = (float)q * 0x1p-23f, lo = 1.0f - up;
+      w_up = (double)(up * up * (3.0f - 2.0f * up));
+      w_lo = (double)(lo * lo * (3.0f - 2.0f * lo));
+    } else {
+      w_up = (double)q;
+      w_lo = 0x1p23 - w_up;
+    }
+    if (!NEAR && __builtin_expect((w0 & 0xf000u) == kFirstVoxel << 12, 0)) {  // rare: one voxel in N_l along dimension 0
+      lb8 = dense ? (la8 + 8u) & cmask8 : la8 ^ (8u & xmask8);
+      const float small = unpack_weight<16, 64>(q & 0x3fffffu), big = 1.0f - small;
+      const bool upper_small = (q >> 22) == 0u;
+      w_up = (double)(upper_small ? small : big) * (SMOOTH ? 1.0 : 0x1p23);
+      w_lo = (double)(upper_small ? big : small) * (SMOOTH ? 1.0 : 0x1p23);
+    }
+    const uint32_t code2 = (uint32_t)(((uint64_t)w0 | ((uint64_t)w1 << 32)) >> 15) & 0x3fffffeu;  // (19 mantissa bits in a place for 20)
+    const double wrow = __builtin_bit_cast(double, (uint64_t)(code2 + ((uint32_t)(960 + exponent) << 20)) << 32);
     IT pay[kPayloadWords * 4 / sizeof(IT)];
     __builtin_memcpy(pay, &r.w[2], kPayloadWords * 4);
 #pragma unroll
@@ -192,8 +267,8 @@ struct Record {
 // 1.5 * 2^52 leaves the integer, in two's complement, in the low bits of the
 // double.  One rounding, of the exact product.
 constexpr int kFixedBits = 51;
-__host__ __device__ __forceinline__ unsigned long long fixed_product(float w, double G) {
-  const double d = __builtin_fma((double)w, G, 0x1.8p52);
+__host__ __device__ __forceinline__ unsigned long long fixed_product(double w, double G) {
+  const double d = __builtin_fma(w, G, 0x1.8p52);
   return (unsigned long long)(__builtin_bit_cast(long long, d) - __builtin_bit_cast(long long, 0x1.8p52));
 }
 
