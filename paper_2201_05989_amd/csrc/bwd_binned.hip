@@ -63,10 +63,10 @@ namespace hg {
 constexpr int kScanThreads = 1024;
 constexpr int kAccThreads = 1024;                // accumulate workgroup (512 x 2 per CU is slower)
 constexpr uint32_t kFewBins = 32;                 // bins of a level up to which the scatter pass spreads a tile's records (bin_scatter)
-// Queues of work items: a counter each, a 128-byte line apart.  One counter hands out an item every 13 ns, whoever asks, which is
+// Queues of work items: a counter each, 64 bytes apart.  One counter hands out an item every 13 ns, whoever asks, which is
 // all of the pass where the items are short (table of 2^22 entries in two dimensions: 7600 items of 500 records, 103 us with one
-// queue, 91 with eight); with few items one queue shares them out better.
-constexpr uint32_t kQueues = 8, kQueueStride = 32, kManyItems = 1024;
+// queue, 91 with four or eight); with few items one queue shares them out better.
+constexpr uint32_t kQueues = 4, kQueueStride = 16, kManyItems = 1024;
 constexpr uint32_t kAccWgsPerCu = 1;             // its registers let one accumulate workgroup run per CU
 constexpr uint32_t kTargetRecordsPerAccWg = 16384;
 // Eight features an entry, half-precision gradients: a record is 16 additions in LDS, so 16384 records keep a compute unit busy
@@ -169,8 +169,7 @@ static uint64_t max_items(const hashgrid* h, uint32_t B) {
   return bp.wg_base[h->lv.L];
 }
 
-// Bytes of the workspace; before_items: those in front of the item list, behind which are the queues' counters only.
-constexpr uint64_t kQueuesBytes = kQueues * kQueueStride * sizeof(uint32_t);
+// Bytes of the workspace; before_items: those in front of the item list, which is last.
 static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* ws, uint64_t* before_items = nullptr) {
   const uint32_t nt = tiles_for(h->bp, B), nb = h->bp.bin_base[h->lv.L];
   uint64_t off = 0;
@@ -180,10 +179,10 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     return o;
   };
   const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_total = take((uint64_t)nb * 4),
-                 o_max = take((uint64_t)nt * h->lv.L * 4), o_open = take((uint64_t)nb * 4),
+                 o_max = take((uint64_t)nt * h->lv.L * 4), o_queues = take(kQueues * kQueueStride * 4), o_open = take((uint64_t)nb * 4),
                  o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point *
                               (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u)),
-                 o_items = take(max_items(h, B) * sizeof(uint4)), o_queues = take(kQueuesBytes);
+                 o_items = take(max_items(h, B) * sizeof(uint4));
   if (before_items) *before_items = o_items;
   if (ws) {
     ws->counts = reinterpret_cast<uint32_t*>(base + o_counts);
@@ -1645,7 +1644,7 @@ constexpr uint64_t kMostBins = (uint64_t)HG_MAX_LEVELS * hg::kMaxLevelBins;
 constexpr uint64_t kMostItems = kMostBins + kMostBins / hg::kTargetRecordsPerAccWg + 1 +
                                 HG_STATIC_SCRATCH_BYTES / 12 / hg::kTargetRecordsPerAccWg + 1 +
                                 hg::kShares;
-constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256 + hg::kQueuesBytes;
+constexpr uint64_t kStaticBytes = HG_STATIC_SCRATCH_BYTES + (kMostItems * sizeof(uint4) + 255) / 256 * 256;
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
 
 namespace hg {
