@@ -161,7 +161,10 @@ struct CountArgs {
   uint32_t* counts;  // [n_tiles][n_bins]
   uint32_t n_bins, n_tiles;
 };
-struct NoCount {};
+// Without it a workgroup may have some of the levels only (blockIdx.y: which)
+struct LevelParts {
+  uint32_t levels;  // of a part
+};
 
 // SB: points per thread.  A workgroup then walks SB blocks of blockDim.x points level by level,
 // so that a level's slice, once in the XCD's L2, serves SB times the points before the next
@@ -170,7 +173,7 @@ template <int D, int F, typename PT, typename IT, bool POW2, bool COUNT, int SB 
 __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv, const bool smooth, const uint32_t B,
                                                             const float* __restrict__ x,
                                                             const PT* __restrict__ theta, IT* __restrict__ y,
-                                                            const typename std::conditional<COUNT, CountArgs, NoCount>::type ca) {
+                                                            const typename std::conditional<COUNT, CountArgs, LevelParts>::type ca) {
   using Piece = OutPiece<F, IT>;
   constexpr int G = Piece::kLevels;
   constexpr uint32_t kTiles = SB * kPmBlock / kBinThreads;  // tiles of the backward pass per workgroup
@@ -199,6 +202,7 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
   // sets that alternate; the parity of a level inside a piece must be known at compile time).  With
   // the counting on the side the plain order is the faster one: there the counting fills those gaps.
   constexpr bool PIPE = SB == 1 && G % 2 == 0 && !COUNT;
+  constexpr bool PARTS = SB == 1 && !COUNT;
   constexpr int kSets = PIPE ? 2 : 1;
   Vec<PT, F> e[kSets][SB][1 << D];
   float wr[kSets][SB][1 << (D - 1)], w0[kSets][SB], u0[kSets][SB];
@@ -239,15 +243,20 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
   // the counting kernel, for three levels of four.)
   constexpr bool kLateSums = SB > 1 && F == 2 && std::is_same<IT, _Float16>::value;
   [[maybe_unused]] float late[SB][F];
-  if constexpr (PIPE) gather_level(0, 0);
-  for (uint32_t l0 = 0; l0 < lv.L; l0 += G) {
+  uint32_t first = 0, end = lv.L;
+  if constexpr (PARTS) {
+    first = blockIdx.y * ca.levels;
+    end = first + ca.levels < lv.L ? first + ca.levels : lv.L;
+  }
+  if constexpr (PIPE) gather_level(first, 0);
+  for (uint32_t l0 = first; l0 < end; l0 += G) {
     Vec<IT, F * G> out[SB];
 #pragma unroll
     for (int j = 0; j < G; ++j) {
       const uint32_t l = l0 + j;
-      const int set = PIPE ? (j & 1) : 0;  // lv.L is a multiple of G (checked at launch), G even: l and j have the same parity
+      const int set = PIPE ? (j & 1) : 0;  // first and lv.L are multiples of G (checked at launch), G even: l and j have the same parity
       if constexpr (PIPE) {
-        if (l + 1 < lv.L) gather_level(l + 1, set ^ 1);
+        if (l + 1 < end) gather_level(l + 1, set ^ 1);
       } else {
         gather_level(l, 0);
       }
@@ -303,10 +312,11 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
     const uint32_t piece = l0 / G;
 #pragma unroll
     for (int q = 0; q < SB; ++q) {
-      if (Piece::kPair && (piece & 1u) == 0 && l0 + G < lv.L) {
+      const bool odd = (((l0 - first) / G) & 1u) != 0;
+      if (Piece::kPair && !odd && l0 + G < end) {
         held[q] = out[q];  // even piece with a partner: keep it until the partner is ready
       } else if (valid[q]) {
-        if (Piece::kPair && (piece & 1u)) yrow[q][piece - 1] = held[q];
+        if (Piece::kPair && odd) yrow[q][piece - 1] = held[q];
         yrow[q][piece] = out[q];
       }
     }
@@ -654,6 +664,19 @@ static hg_status launched() { return hipGetLastError() == hipSuccess ? HG_OK : H
 // Two points per thread once the batch needs two or more rounds of full workgroups per CU
 static bool fwd_two_points_per_thread(uint32_t B) { return (uint64_t)B >= 2ull * kPmBlock * cu_count(); }
 
+// Levels of a part of the plain forward's grid.  A thread walks its levels one after the other, a gather's latency each, and a batch
+// that leaves compute units with few waves waits for little else: such a batch is cut into parts of whole pieces of 16 bytes,
+// 4 parts up to a wave for every compute unit, then 2 as long as two slices of the tables at a time cost the caches less than
+// the shorter chains save.  d = 3, L = 16, F = 2, T = 2^19, uniform / rays, us with 1, 2 and 4 parts (5.4 us of it the caller's): 2^12 points
+// 12.6 8.0 6.7 / 10.9 6.8 5.6, 2^14 points 17.1 14.9 14.4 / 13.6 10.8 10.4, 2^16 points 36.3 33.3 35.8 / 27.4 24.9 27.5, 2^17 points
+// 54.8 53.6 55.8 / 41.3 40.9 43.0, 200001 points 74.9 79.6 / 56.4 57.7.  Entries of 8 bytes, T = 1000003: 2^16 points 55.1 54.6, 100003
+// points 74.0 77.2; of 16 bytes, T = 2^17: 30011 points 15.2 13.9, 2^16 points 22.3 24.1.
+static uint32_t levels_per_part(uint32_t L, uint32_t G, uint32_t block, uint32_t entry_bytes) {
+  const uint32_t most = entry_bytes <= 4 ? 512 : entry_bytes <= 8 ? 256 : 192;
+  const uint32_t parts = block <= 64 ? 4 : block <= most ? 2 : 1, pieces = L / G;
+  return (pieces + parts - 1) / parts * G;
+}
+
 template <int D, int F, typename PT, typename IT>
 static hg_status launch_fwd(const hashgrid* h, uint32_t B, const float* x, const void* params, void* y,
                             hipStream_t s) {
@@ -661,18 +684,20 @@ static hg_status launch_fwd(const hashgrid* h, uint32_t B, const float* x, const
     constexpr uint32_t G = OutPiece<F, IT>::kLevels;
     if (h->lv.L % G == 0 && !misaligned(y, 16) && !misaligned(params, F * sizeof(PT) > 16 ? 16 : F * sizeof(PT))) {
       const uint32_t block = point_major_block(B);
-      const dim3 grid((B + block - 1) / block);
+      const uint32_t wgs = (B + block - 1) / block;
+      const LevelParts parts{levels_per_part(h->lv.L, G, block, F * (uint32_t)sizeof(PT))};
+      const dim3 grid(wgs, (h->lv.L + parts.levels - 1) / parts.levels);
       const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
       if (h->lv.T_is_pow2 && fwd_two_points_per_thread(B))
         hipLaunchKernelGGL((fwd_point_major<D, F, PT, IT, true, false, 2>), dim3((B + 2 * kPmBlock - 1) / (2 * kPmBlock)),
                            dim3(kPmBlock), 0, s, h->lv, smooth, B, x, static_cast<const PT*>(params),
-                           static_cast<IT*>(y), NoCount{});
+                           static_cast<IT*>(y), parts);
       else if (h->lv.T_is_pow2)
         hipLaunchKernelGGL((fwd_point_major<D, F, PT, IT, true, false>), grid, dim3(block), 0, s, h->lv, smooth, B,
-                           x, static_cast<const PT*>(params), static_cast<IT*>(y), NoCount{});
+                           x, static_cast<const PT*>(params), static_cast<IT*>(y), parts);
       else
         hipLaunchKernelGGL((fwd_point_major<D, F, PT, IT, false, false>), grid, dim3(block), 0, s, h->lv, smooth,
-                           B, x, static_cast<const PT*>(params), static_cast<IT*>(y), NoCount{});
+                           B, x, static_cast<const PT*>(params), static_cast<IT*>(y), parts);
       return launched();
     }
   }
