@@ -412,12 +412,18 @@ __device__ __forceinline__ void block_exclusive_scan(uint32_t* a, uint32_t n, ui
   __syncthreads();
 }
 
-// scan: each workgroup takes kScanBins bins and turns their column of
+// scan: each workgroup takes BINS bins and turns their column of
 // counts[tile][bin] into the exclusive prefix over tiles; it also writes the
 // bin's record count.  Workgroup 0 clears the counters of the accumulate pass's queues.
-constexpr int kScanBins = 32;  // 128-byte rows of the count table per load (16, 8: slower; 64: the same)
+// Bound by the latency of its loads and stores, and by what the stores make of lines: rows start anywhere, so that neighbouring columns
+// share a line in nearly every row, and written from two XCDs it goes out in parts.  Columns dealt out by XCD, and every row of
+// a thread in registers instead of eight at a time and twice: d = 2, T = 2^22, 512 tiles of 7600 bins 18.0 -> 9.6 us (17.3 by the
+// registers alone); T = 2^24, 512 tiles of 49 K bins 90 -> 46; 2048 tiles of 1508 bins 23.1 -> 14.7; 512 of them 7.9 -> 6.1.
 // With HG_BWD_OVERWRITE it also clears the gradient of the levels in zero_mask (those that the
 // later passes add into, see launch_binned): it is the first kernel of the call to run.
+// ROWS: the rows of the table a thread has at most, all of them in registers: every load is in flight at once, and none is made
+// twice.  0: any number, eight at a time and each read again for its prefix.
+template <int ROWS, int BINS>
 __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles, const uint32_t n_bins,
                                                          uint32_t* __restrict__ counts,
                                                          uint32_t* __restrict__ bin_total,
@@ -442,56 +448,72 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan(const uint32_t n_tiles,
       else static_cast<float*>(grad)[first + i] = 0.0f;
     }
   }
-  constexpr uint32_t segs = kScanThreads / kScanBins;
-  const uint32_t bin_in = threadIdx.x % kScanBins, seg = threadIdx.x / kScanBins;
-  const uint32_t gb = blockIdx.x * kScanBins + bin_in;
+  constexpr uint32_t segs = kScanThreads / BINS;
+  const uint32_t bin_in = threadIdx.x % BINS, seg = threadIdx.x / BINS;
+  // Rows do not start on a line: neighbouring columns share one in nearly every row, and go to workgroups of one XCD (as in
+  // tile_of_workgroup) so that it is completed inside one L2
+  const uint32_t gb = tile_of_workgroup(blockIdx.x, (n_bins + BINS - 1) / BINS) * BINS + bin_in;
   const bool active = gb < n_bins;
   const uint32_t tps = (n_tiles + segs - 1) / segs;
   const uint32_t t0 = seg * tps < n_tiles ? seg * tps : n_tiles;
   const uint32_t t1 = t0 + tps < n_tiles ? t0 + tps : n_tiles;
-  uint32_t* col = counts + gb;
-  // the loads of a column are independent: issue them eight at a time
-  uint32_t s = 0;
-  if (active) {
+  uint32_t* col = counts + (active ? gb : 0u);
+  uint32_t sum = 0;
+  uint32_t c[ROWS > 0 ? ROWS : 8];
+  if constexpr (ROWS > 0) {
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) c[k] = col[(uint64_t)(t0 + k < n_tiles ? t0 + k : n_tiles - 1u) * n_bins];
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      c[k] = t0 + k < t1 ? c[k] : 0u;
+      sum += c[k];
+    }
+  } else if (active) {
     uint32_t t = t0;
     for (; t + 8 <= t1; t += 8) {
-      uint32_t c[8];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) c[j] = col[(uint64_t)(t + j) * n_bins];
+      for (int k = 0; k < 8; ++k) c[k] = col[(uint64_t)(t + k) * n_bins];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) s += c[j];
+      for (int k = 0; k < 8; ++k) sum += c[k];
     }
-    for (; t < t1; ++t) s += col[(uint64_t)t * n_bins];
+    for (; t < t1; ++t) sum += col[(uint64_t)t * n_bins];
   }
-  seg_sum[threadIdx.x] = s;
+  seg_sum[threadIdx.x] = sum;
   __syncthreads();
   if (active) {
-    uint32_t pre = 0, total = 0;
+    uint32_t run = 0, total = 0;
+#pragma unroll 32
     for (uint32_t q = 0; q < segs; ++q) {
-      const uint32_t v = seg_sum[q * kScanBins + bin_in];
-      pre += q < seg ? v : 0u;
+      const uint32_t v = seg_sum[q * BINS + bin_in];
+      run += q < seg ? v : 0u;
       total += v;
     }
     if (seg == 0) {
       bin_total[gb] = total;
       col[(uint64_t)n_tiles * n_bins] = total;  // closes the prefix: count of tile t = row t+1 - row t
     }
-    uint32_t run = pre;
-    uint32_t t = t0;
-    for (; t + 8 <= t1; t += 8) {
-      uint32_t c[8];
+    if constexpr (ROWS > 0) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) c[j] = col[(uint64_t)(t + j) * n_bins];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        col[(uint64_t)(t + j) * n_bins] = run;
-        run += c[j];
+      for (int k = 0; k < ROWS; ++k) {
+        if (t0 + k < t1) col[(uint64_t)(t0 + k) * n_bins] = run;
+        run += c[k];
       }
-    }
-    for (; t < t1; ++t) {
-      const uint32_t c = col[(uint64_t)t * n_bins];
-      col[(uint64_t)t * n_bins] = run;
-      run += c;
+    } else {
+      uint32_t t = t0;
+      for (; t + 8 <= t1; t += 8) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) c[k] = col[(uint64_t)(t + k) * n_bins];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          col[(uint64_t)(t + k) * n_bins] = run;
+          run += c[k];
+        }
+      }
+      for (; t < t1; ++t) {
+        const uint32_t v = col[(uint64_t)t * n_bins];
+        col[(uint64_t)t * n_bins] = run;
+        run += v;
+      }
     }
   }
 }
@@ -1326,6 +1348,24 @@ static hg_status launch_count(const hashgrid* h, uint32_t B, const float* x, con
   return hipGetLastError() == hipSuccess ? HG_OK : HG_ERR_DEVICE;
 }
 
+static void launch_scan(const hashgrid* h, const Workspace& ws, uint32_t zero_mask, void* grad, const SideJob& job, hipStream_t s) {
+  auto launch = [&](auto rows, auto bins) {
+    constexpr int kBins = decltype(bins)::value;
+    const dim3 grid((ws.n_bins + kBins * 8 - 1) / (kBins * 8) * 8 + job.blocks);  // see tile_of_workgroup
+    hipLaunchKernelGGL((bin_scan<decltype(rows)::value, kBins>), grid, dim3(kScanThreads), 0, s, ws.n_tiles, ws.n_bins, ws.counts,
+                       ws.bin_total, ws.item_counters, h->lv, zero_mask, h->cfg.F, grad, h->cfg.grad_dtype == HG_F16, job);
+  };
+  auto rows_at = [&](uint32_t bins) { return (ws.n_tiles * bins + kScanThreads - 1) / kScanThreads; };
+  // As wide as the rows a thread then has fit its registers; wider batches than 16 rows of 8 bins (2^20 points) read them twice
+  constexpr std::integral_constant<int, 32> b32{};
+  if (rows_at(32) <= 2) launch(std::integral_constant<int, 2>{}, b32);
+  else if (rows_at(32) <= 8) launch(std::integral_constant<int, 8>{}, b32);
+  else if (rows_at(32) <= 16) launch(std::integral_constant<int, 16>{}, b32);
+  else if (rows_at(16) <= 16) launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 16>{});
+  else if (rows_at(8) <= 16) launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{});
+  else launch(std::integral_constant<int, 0>{}, b32);
+}
+
 // The optimiser's part of a sorted backward pass (launch_binned_adam)
 struct BinnedAdam {
   AdamArgs a;
@@ -1420,9 +1460,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const uint32_t zero_mask = overwrite ? add_mask : 0u, overwrite_mask = overwrite ? all_levels & ~add_mask : 0u;
   const bool defer_cross = overwrite && cross_mask != 0;  // those atomic adds then follow the accumulate pass
   const SideJob job = ba ? ba->job : SideJob{};
-  hipLaunchKernelGGL(bin_scan, dim3((ws.n_bins + kScanBins - 1) / kScanBins + job.blocks), dim3(kScanThreads), 0, s,
-                     ws.n_tiles, ws.n_bins, ws.counts, ws.bin_total, ws.item_counters, h->lv, zero_mask,
-                     (uint32_t)F, grad, g16, job);
+  launch_scan(h, ws, zero_mask, grad, job, s);
   auto scatter = [&](auto cross) {
     constexpr bool kCross = decltype(cross)::value;
     constexpr int DS = kCross ? DP : D;  // (the straddling pairs exist with pair records only)
