@@ -90,6 +90,7 @@ constexpr uint32_t kMaxCountPartBins = 4096, kMaxScatterPartBins = 4096;
 // Beyond this many chunks in all, a tile is kBigTileMult * 512 points and the scatter pass does not
 // stage (bin_scatter_direct, one LDS word per bin of its part).  One level of 4096 chunks per part: the grid runs
 // part after part, so the records in flight then belong to two levels (200 MB at T = 2^24), not four (-3%).
+constexpr uint32_t kWideTilesFrom = 1u << 16, kWideTilesBins = 1024;  // tile_mult_for
 constexpr uint32_t kMaxStagedBins = 16384, kBigTileMult = 8, kMaxDirectPartBins = 4096;
 // A level may have this many chunks (one level is the smallest part): T up to 2^24 at 4096 entries per chunk.
 constexpr uint32_t kMaxLevelBins = 4096;
@@ -110,9 +111,20 @@ struct Workspace {
 
 static inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
+// In two dimensions a tile of 512 points has 1024 records a level, which on a level of 1024 chunks is one to a run: every store a part
+// of a line.  Tiles of 1024 points there, two points a thread, the staging area as large as in three dimensions.  Both passes, us, T =
+// 2^22, uniform points: 2^16 134 -> 125, 2^18 242 -> 229, 2^20 756 -> 685 (scatter at 2^18 67 -> 54, scan 9.6 -> 7.3); smaller
+// batches 94 both.  Levels of 512 chunks lose at some sizes what they gain at others (F = 1, T = 2^21: 100003 points 88 -> 92, 2^20 444 -> 418;
+// F = 8 on chunks of 2048, T = 2^20: 113 -> 118, 624 -> 621), of 32 chunks everywhere (T = 2^17: 100003 points 69 -> 73).
+uint32_t tile_mult_for(const hashgrid* h, uint32_t B) {
+  const BinPlan& bp = h->bp;
+  const uint32_t L = h->lv.L, widest = bp.bin_base[L] - bp.bin_base[L - 1];  // the finest level has the most entries
+  return bp.tile_mult == 1 && h->cfg.d == 2 && !bp.corner_records && widest >= kWideTilesBins && B >= kWideTilesFrom ? 2u : bp.tile_mult;
+}
+
 // one count / scatter workgroup per tile and level part
-static uint32_t tiles_for(const BinPlan& bp, uint32_t B) {
-  const uint32_t points = kBinThreads * bp.tile_mult;
+static uint32_t tiles_for(uint32_t tile_mult, uint32_t B) {
+  const uint32_t points = kBinThreads * tile_mult;
   return (uint32_t)(((uint64_t)B + points - 1) / points);
 }
 
@@ -171,7 +183,8 @@ static uint64_t max_items(const hashgrid* h, uint32_t B) {
 
 // Bytes of the workspace; before_items: those in front of the item list, which is last.
 static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* ws, uint64_t* before_items = nullptr) {
-  const uint32_t nt = tiles_for(h->bp, B), nb = h->bp.bin_base[h->lv.L];
+  const uint32_t nb = h->bp.bin_base[h->lv.L];
+  const uint32_t nt = tiles_for(h->bp.tile_mult, B);  // room for the plan's tiles, where the batch's are twice as large, too
   uint64_t off = 0;
   auto take = [&](uint64_t bytes) {
     uint64_t o = off;
@@ -192,7 +205,7 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
     ws->chunk_open = reinterpret_cast<uint32_t*>(base + o_open);
     ws->records = reinterpret_cast<uint32_t*>(base + o_rec);
     ws->items = reinterpret_cast<uint4*>(base + o_items);
-    ws->n_tiles = nt;
+    ws->n_tiles = tiles_for(tile_mult_for(h, B), B);
     ws->n_bins = nb;
   }
   return off;
@@ -576,8 +589,8 @@ __host__ __device__ constexpr uint32_t staged_records(uint32_t pairs, bool corne
 // local[nbp + 1] exclusive prefix of this tile's counts (where a bin's records
 // sit in the tile's sorted order), cur[nbp] the same, advanced as records are
 // placed, delta[nbp] = global slot minus tile-local position.
-// CROSS: this pass adds the pairs that straddle two chunks.  CORNERS: BinPlan::corner_records.
-template <int D, typename IT, int F, bool CROSS, bool CORNERS = false>
+// CROSS: this pass adds the pairs that straddle two chunks.  CORNERS: BinPlan::corner_records.  PT: points a thread has (BinPlan::tile_mult).
+template <int D, typename IT, int F, bool CROSS, bool CORNERS = false, int PT = 1>
 __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, const BinPlan bp, const bool smooth,
                                                            const uint32_t B, const float* __restrict__ x,
                                                            const IT* __restrict__ dy,
@@ -592,7 +605,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   using Stored = typename Rec::Stored;
   Stored* out = reinterpret_cast<Stored*>(records);
   __shared__ uint32_t scan_tmp[kBinThreads / 64];
-  constexpr uint32_t kStage = staged_records(R, CORNERS);
+  constexpr uint32_t kStage = staged_records(R * PT, CORNERS);
   // dynamic LDS: staging[kStage] records, binv[kStage] (part-relative bin of each
   // staged record, 16 bits), then the three per-bin arrays
   extern __shared__ uint32_t lds_u32[];
@@ -636,52 +649,29 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   }
   __syncthreads();
 
-  const uint64_t b64 = (uint64_t)tile * kBinThreads + threadIdx.x;
-  const bool valid = b64 < B;
-  const uint32_t b = valid ? (uint32_t)b64 : 0u;
-  float xp[D];
-  load_x<D>(x, b, xp);
+  bool valid[PT];
+  float xp[PT][D];
+  const IT* row[PT];
+#pragma unroll
+  for (int p = 0; p < PT; ++p) {
+    const uint64_t b64 = ((uint64_t)tile * PT + p) * kBinThreads + threadIdx.x;
+    valid[p] = b64 < B;
+    const uint32_t b = valid[p] ? (uint32_t)b64 : 0u;
+    load_x<D>(x, b, xp[p]);
+    row[p] = dy + (uint64_t)b * lv.L * F;
+  }
   // dL/dy comes in as 16-byte pieces, K levels each when a level is narrower than that: a narrow
   // read per level with the stride of a row would cost the L1 a line per two lanes, L times over
   constexpr uint32_t kLevelBytes = F * sizeof(IT);
   constexpr uint32_t K = kLevelBytes >= 16 ? 1 : 16 / kLevelBytes;  // levels per piece
   constexpr uint32_t E = 16 / sizeof(IT);                           // scalars per piece
   constexpr uint32_t P = kLevelBytes >= 16 ? kLevelBytes / 16 : 1;  // pieces per level
-  const IT* row = dy + (uint64_t)b * lv.L * F;
   const bool vec_ok = (lv.L % K == 0) && (l0 % K == 0) && ((reinterpret_cast<uintptr_t>(dy) & 15) == 0);
-  Vec<IT, E> gv;
+  Vec<IT, E> gv[PT];
   float gmax = 0.0f;  // largest |dL/dy| this workgroup sees (idle lanes shadow point 0)
   for (uint32_t l = l0; l < l1; ++l) {
     const uint32_t rb0 = bp.bin_base[l] - gb_a, rb1 = bp.bin_base[l + 1] - gb_a;
     const uint32_t level_first = local[rb0], emitted = local[rb1] - level_first;
-    IT g[F];
-    if (vec_ok && K > 1) {  // uniform
-      if ((l - l0) % K == 0) gv = *reinterpret_cast<const Vec<IT, E>*>(row + (uint64_t)l * F);
-      const uint32_t k = (l - l0) % K;
-#pragma unroll
-      for (int f = 0; f < F; ++f) {
-        g[f] = gv.v[f];
-#pragma unroll
-        for (uint32_t q = 1; q < K; ++q) g[f] = k == q ? gv.v[F * q + f] : g[f];
-      }
-    } else if (vec_ok) {
-#pragma unroll
-      for (uint32_t q = 0; q < P; ++q) {
-        const Vec<IT, E> piece = *reinterpret_cast<const Vec<IT, E>*>(row + (uint64_t)l * F + q * E);
-#pragma unroll
-        for (uint32_t e = 0; e < E; ++e)
-          if (q * E + e < (uint32_t)F) g[q * E + e] = piece.v[e];
-      }
-    } else {
-#pragma unroll
-      for (int f = 0; f < F; ++f) g[f] = row[(uint64_t)l * F + f];
-    }
-    float gf[F];
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-      gf[f] = (float)g[f];
-      gmax = nan_max(gmax, fabsf(gf[f]));
-    }
     // Position of a new record of bin rb in the tile's sorted order.  On a level of few bins a wave's
     // lanes crowd into the same counters and a tile's run for a bin is long: there the wave draws
     // its slots with one add per bin (wave_add_one) and the run is filled with a stride
@@ -692,39 +682,70 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
       const uint32_t first = local[rb];
       return first + spread_in_run(wave_add_one<true>(cur, rb) - first, local[rb + 1] - first);
     };
-    if (valid) {
-      if constexpr (CORNERS) {
-        CornerRows<D> cr;
-        corner_rows_of<D, false>(lv, bp, l, smooth, xp, cr);
-        auto put = [&](const uint32_t rb, const Stored& rec) {
-          const uint32_t pos = take_slot(rb) - level_first;
-          if (pos < kStage) {
-            staging[pos] = rec;
-            binv[pos] = (uint16_t)rb;
-          } else {  // more corners with a record of their own than the staging area has room for
-            const uint32_t d = delta[rb] + level_first + pos;
-            if (d < n_records) out[d] = rec;
-          }
-        };
 #pragma unroll
-        for (uint32_t r = 0; r < R; ++r) {
-          const NearPair np = cr.pair[r];
-          const bool near = np.step != NearPair::kNone;
-          put(cr.bin[2 * r] - gb_a, Rec::make_near(cr.la[2 * r], near ? np.step : NearPair::kSingle, near ? np.fraction : 0u,
-                                                   near ? cr.wrow[r] : cr.weight[2 * r], g));
-          if (!near) put(cr.bin[2 * r + 1] - gb_a, Rec::make_near(cr.la[2 * r + 1], NearPair::kSingle, 0u, cr.weight[2 * r + 1], g));
+    for (int p = 0; p < PT; ++p) {
+      IT g[F];
+      if (vec_ok && K > 1) {  // uniform
+        if ((l - l0) % K == 0) gv[p] = *reinterpret_cast<const Vec<IT, E>*>(row[p] + (uint64_t)l * F);
+        const uint32_t k = (l - l0) % K;
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          g[f] = gv[p].v[f];
+#pragma unroll
+          for (uint32_t q = 1; q < K; ++q) g[f] = k == q ? gv[p].v[F * q + f] : g[f];
+        }
+      } else if (vec_ok) {
+#pragma unroll
+        for (uint32_t q = 0; q < P; ++q) {
+          const Vec<IT, E> piece = *reinterpret_cast<const Vec<IT, E>*>(row[p] + (uint64_t)l * F + q * E);
+#pragma unroll
+          for (uint32_t e = 0; e < E; ++e)
+            if (q * E + e < (uint32_t)F) g[q * E + e] = piece.v[e];
         }
       } else {
-        Rows<D> rw;
-        rows_of<D, false>(lv, bp, l, smooth, xp, rw);
-        if (CROSS && rw.cross) add_crossing_pairs<D, F>(lv, l, smooth, xp, gf, grad, g16);
 #pragma unroll
-        for (uint32_t r = 0; r < R && !rw.cross; ++r) {
-          const uint32_t rb = rw.bin[r] - gb_a;
-          const uint32_t pos = take_slot(rb) - level_first;
-          if (pos < kStage) {  // holds when the count pass saw the same x
-            staging[pos] = Rec::make(rw.la[r], record_k<D>(rw, r, (lv.dense_mask >> l) & 1u), rw.wf0, rw.wrow[r], g, smooth);
-            binv[pos] = (uint16_t)rb;
+        for (int f = 0; f < F; ++f) g[f] = row[p][(uint64_t)l * F + f];
+      }
+      float gf[F];
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        gf[f] = (float)g[f];
+        gmax = nan_max(gmax, fabsf(gf[f]));
+      }
+      if (valid[p]) {
+        if constexpr (CORNERS) {
+          CornerRows<D> cr;
+          corner_rows_of<D, false>(lv, bp, l, smooth, xp[p], cr);
+          auto put = [&](const uint32_t rb, const Stored& rec) {
+            const uint32_t pos = take_slot(rb) - level_first;
+            if (pos < kStage) {
+              staging[pos] = rec;
+              binv[pos] = (uint16_t)rb;
+            } else {  // more corners with a record of their own than the staging area has room for
+              const uint32_t d = delta[rb] + level_first + pos;
+              if (d < n_records) out[d] = rec;
+            }
+          };
+#pragma unroll
+          for (uint32_t r = 0; r < R; ++r) {
+            const NearPair np = cr.pair[r];
+            const bool near = np.step != NearPair::kNone;
+            put(cr.bin[2 * r] - gb_a, Rec::make_near(cr.la[2 * r], near ? np.step : NearPair::kSingle, near ? np.fraction : 0u,
+                                                     near ? cr.wrow[r] : cr.weight[2 * r], g));
+            if (!near) put(cr.bin[2 * r + 1] - gb_a, Rec::make_near(cr.la[2 * r + 1], NearPair::kSingle, 0u, cr.weight[2 * r + 1], g));
+          }
+        } else {
+          Rows<D> rw;
+          rows_of<D, false>(lv, bp, l, smooth, xp[p], rw);
+          if (CROSS && rw.cross) add_crossing_pairs<D, F>(lv, l, smooth, xp[p], gf, grad, g16);
+#pragma unroll
+          for (uint32_t r = 0; r < R && !rw.cross; ++r) {
+            const uint32_t rb = rw.bin[r] - gb_a;
+            const uint32_t pos = take_slot(rb) - level_first;
+            if (pos < kStage) {  // holds when the count pass saw the same x
+              staging[pos] = Rec::make(rw.la[r], record_k<D>(rw, r, (lv.dense_mask >> l) & 1u), rw.wf0, rw.wrow[r], g, smooth);
+              binv[pos] = (uint16_t)rb;
+            }
           }
         }
       }
@@ -751,7 +772,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   }
 }
 
-// scatter without staging, for plans of very many bins (BinPlan::tile_mult > 1): a tile is
+// scatter without staging, for plans of very many bins (BinPlan::tile_mult > 2): a tile is
 // tile_mult * 512 points, which the workgroup walks 512 at a time, and every record goes
 // straight to its slot.  The runs a tile writes are a few records long at best, so sorting them
 // in LDS first would not make whole lines of them; what merges partial lines here is the L2,
@@ -1324,7 +1345,8 @@ static uint32_t parts_for_batch(uint32_t plan_parts, uint32_t L, uint32_t n_tile
 
 // The count pass by itself: counts[tile][bin] for the B points (x only).
 static hg_status launch_count(const hashgrid* h, uint32_t B, const float* x, const Workspace& ws, hipStream_t s) {
-  const BinPlan& bp = h->bp;
+  BinPlan bp = h->bp;
+  bp.tile_mult = tile_mult_for(h, B);
   const uint32_t L = h->lv.L, cparts = parts_for_batch(bp.count_parts, L, ws.n_tiles);
   uint32_t max_bins = 0;
   for (uint32_t p = 0; p < cparts; ++p) {
@@ -1382,6 +1404,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   constexpr uint32_t R = 1u << (D - 1);
   constexpr int DP = CORNERS ? 2 : D;  // (dimension of the kernels that only the pair records use: never D = 1)
   BinPlan bp = h->bp;
+  bp.tile_mult = tile_mult_for(h, B);
   plan_slices(bp, h->lv, B, F, g16);
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const uint32_t n_records = B * h->lv.L * bp.rec_per_point;
@@ -1395,12 +1418,16 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     return m;
   };
   // scatter: staging area, 16-bit bin of every staged record, three words per bin of the part
-  constexpr size_t kStagingBytes = (size_t)staged_records(R, CORNERS) * (Rec::kWords * 4 + 2);
+  constexpr size_t kRecordBytes = Rec::kWords * 4 + 2;
+  constexpr size_t kStagingBytes = (size_t)staged_records(R, CORNERS) * kRecordBytes;
+  constexpr bool kWide = D == 2 && !CORNERS;  // (BinPlan::tile_mult of 2)
+  constexpr size_t kWideBytes = (size_t)staged_records(2 * R, CORNERS) * kRecordBytes;
+  constexpr size_t kWideLdsMax = kWideBytes + (3 * (size_t)kMaxScatterPartBins + 1) * 4;
   constexpr size_t kScatterLdsMax = kStagingBytes + (3 * (size_t)kMaxScatterPartBins + 1) * 4;
   // The largest (146 KB: d = 3, F = 8, single precision, any table size) leaves one workgroup on a compute unit.  Unstaged such plans
   // are 3 to 12 % faster on points in no order and up to 1.8 times slower on rays (30000 points, T = 524287, both passes: 98
   // against 93 us, 108 against 196).
-  static_assert(kScatterLdsMax <= 160 * 1024, "a workgroup's LDS");
+  static_assert(kScatterLdsMax <= 160 * 1024 && (!kWide || kWideLdsMax <= 160 * 1024), "a workgroup's LDS");
   constexpr size_t kAccLds = (size_t)acc_buffers(F) * F * 8 << chunk_log2_of(F);
   constexpr bool kAdam = !CORNERS && std::is_same<IT, _Float16>::value;  // what launch_binned_adam serves
   // more dynamic LDS than the default limit of 64 KiB: opt in once per kernel
@@ -1412,6 +1439,14 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     if (e == hipSuccess && kScatterLdsMax > 64 * 1024)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<D, IT, F, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kScatterLdsMax);
+    if constexpr (kWide) {
+      if (e == hipSuccess && kWideLdsMax > 64 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<D, IT, F, true, false, 2>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideLdsMax);
+      if (e == hipSuccess && kWideLdsMax > 64 * 1024)
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_scatter<D, IT, F, false, false, 2>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWideLdsMax);
+    }
     if (e == hipSuccess && kAccLds > 48 * 1024)
       e = hipFuncSetAttribute(reinterpret_cast<const void*>(bin_accumulate<IT, F, false, float, false, false, CORNERS>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kAccLds);
@@ -1443,7 +1478,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     return e;
   }();
   if (lds_ok != hipSuccess) return HG_ERR_DEVICE;
-  const size_t lds_scatter = kStagingBytes + (3 * (size_t)max_part_bins(parts) + 1) * 4;
+  const size_t lds_scatter = (bp.tile_mult == 2 ? kWideBytes : kStagingBytes) + (3 * (size_t)max_part_bins(parts) + 1) * 4;
   const uint32_t tile_wgs = (ws.n_tiles + 7u) / 8u * 8u;  // see tile_of_workgroup
   if (!counted && launch_count(h, B, x, ws, s) != HG_OK) return HG_ERR_DEVICE;
   // HG_BWD_OVERWRITE: the owner of a chunk stores its sums, except on levels whose chunks are summed
@@ -1464,16 +1499,25 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   auto scatter = [&](auto cross) {
     constexpr bool kCross = decltype(cross)::value;
     constexpr int DS = kCross ? DP : D;  // (the straddling pairs exist with pair records only)
-    if (bp.tile_mult > 1) {
+    if (bp.tile_mult > 2) {
       hipLaunchKernelGGL((bin_scatter_direct<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
                          dim3(kBinThreads), (size_t)max_part_bins(parts) * 4, s, h->lv, bp, smooth, B, x,
                          static_cast<const IT*>(dy), ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins,
                          n_records, ws.n_tiles, ws.tile_max, grad, g16);
     } else {
-      hipLaunchKernelGGL((bin_scatter<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
-                         dim3(kBinThreads), lds_scatter, s, h->lv, bp, smooth, B, x, static_cast<const IT*>(dy),
-                         ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins, n_records, ws.n_tiles,
-                         ws.tile_max, grad, g16);
+      auto staged = [&](auto points) {
+        hipLaunchKernelGGL((bin_scatter<DS, IT, F, kCross, CORNERS && !kCross, decltype(points)::value>), dim3(tile_wgs, parts),
+                           dim3(kBinThreads), lds_scatter, s, h->lv, bp, smooth, B, x, static_cast<const IT*>(dy),
+                           ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins, n_records, ws.n_tiles,
+                           ws.tile_max, grad, g16);
+      };
+      if constexpr (kWide) {
+        if (bp.tile_mult == 2) {
+          staged(std::integral_constant<int, 2>{});
+          return;
+        }
+      }
+      staged(std::integral_constant<int, 1>{});
     }
   };
   if (CORNERS || defer_cross || cross_mask == 0)  // no such pairs at these resolutions, or bin_crossing takes them

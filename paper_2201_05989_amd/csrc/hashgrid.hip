@@ -176,11 +176,13 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
                                                             const typename std::conditional<COUNT, CountArgs, LevelParts>::type ca) {
   using Piece = OutPiece<F, IT>;
   constexpr int G = Piece::kLevels;
-  constexpr uint32_t kTiles = SB * kPmBlock / kBinThreads;  // tiles of the backward pass per workgroup
-  static_assert(kPmBlock % kBinThreads == 0, "a forward workgroup covers whole tiles");
-  extern __shared__ uint32_t hist[];  // COUNT: [kTiles][n_bins]
+  static_assert(kPmBlock % (2 * kBinThreads) == 0, "a forward workgroup covers whole tiles");
+  extern __shared__ uint32_t hist[];  // COUNT: [n_hist][n_bins]
+  [[maybe_unused]] uint32_t n_hist = 0, tile_threads = 0;  // tiles of the backward pass per workgroup, threads that share one
   if constexpr (COUNT) {
-    for (uint32_t i = threadIdx.x; i < kTiles * ca.n_bins; i += kPmBlock) hist[i] = 0;
+    tile_threads = kBinThreads * ca.bp.tile_mult;  // (1 or 2)
+    n_hist = SB * kPmBlock / tile_threads;
+    for (uint32_t i = threadIdx.x; i < n_hist * ca.n_bins; i += kPmBlock) hist[i] = 0;
     __syncthreads();
   }
   bool valid[SB];
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
         // entry, a 1:1 level's the group of grid rows of the pair.  (COUNT implies a power-of-two T.)
         if (valid[q]) {
           const uint32_t cl = ca.bp.chunk_log2, gb0 = ca.bp.bin_base[l];
-          uint32_t* h = hist + (q * (kPmBlock / kBinThreads) + threadIdx.x / kBinThreads) * ca.n_bins;
+          uint32_t* h = hist + (ca.bp.tile_mult == 2 ? q : q * (kPmBlock / kBinThreads) + threadIdx.x / kBinThreads) * ca.n_bins;
           if ((lv.dense_mask >> l) & 1u) {  // uniform
             const uint32_t sh = ca.bp.row_shift[l], verts = lv.verts[l];
 #pragma unroll
@@ -323,9 +325,8 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
   }
   if constexpr (COUNT) {
     __syncthreads();  // every wave's LDS atomics have landed: the histograms are complete
-#pragma unroll
-    for (uint32_t t = 0; t < kTiles; ++t) {
-      const uint32_t tile = blockIdx.x * kTiles + t;
+    for (uint32_t t = 0; t < n_hist; ++t) {
+      const uint32_t tile = blockIdx.x * n_hist + t;
       if (tile >= ca.n_tiles) break;
       for (uint32_t i = threadIdx.x; i < ca.n_bins; i += kPmBlock)
         ca.counts[(uint64_t)tile * ca.n_bins + i] = hist[t * ca.n_bins + i];
@@ -763,11 +764,13 @@ template <int D, int F, typename PT, typename IT>
 static hg_status launch_fwd_counting_t(const hashgrid* h, uint32_t B, const float* x, const void* params, void* y,
                                        uint32_t* counts, uint32_t n_bins, uint32_t n_tiles, hipStream_t s) {
   constexpr uint32_t G = OutPiece<F, IT>::kLevels;
-  const bool two = fwd_two_points_per_thread(B) && (size_t)(2 * kPmBlock / kBinThreads) * n_bins * 4 <= 64 * 1024;
-  const size_t lds = (size_t)((two ? 2 : 1) * kPmBlock / kBinThreads) * n_bins * 4;
+  const uint32_t mult = tile_mult_for(h, B);
+  const size_t one_point = (size_t)(kPmBlock / kBinThreads) * n_bins * 4 / (mult == 2 ? 2 : 1);  // histograms, bytes
+  const bool two = fwd_two_points_per_thread(B) && 2 * one_point <= 64 * 1024;
+  const size_t lds = (two ? 2 : 1) * one_point;
   if (h->lv.L % G != 0 || misaligned(y, 16) || misaligned(params, F * sizeof(PT) > 16 ? 16 : F * sizeof(PT)) ||
       !h->lv.T_is_pow2 || h->bp.corner_records || lds > kMaxCountingLds ||
-      h->bp.tile_mult != 1)  // (its tiles are 512 points; it counts pairs of corners)
+      mult > 2)  // (its tiles are 512 or 1024 points; it counts pairs of corners)
     return HG_ERR_UNSUPPORTED;
   if (lds > 64 * 1024) {  // more dynamic LDS than the default limit: opt in once per kernel
     static const hipError_t lds_ok =
@@ -777,6 +780,7 @@ static hg_status launch_fwd_counting_t(const hashgrid* h, uint32_t B, const floa
   }
   CountArgs ca;
   ca.bp = h->bp;
+  ca.bp.tile_mult = mult;
   ca.counts = counts;
   ca.n_bins = n_bins;
   ca.n_tiles = n_tiles;

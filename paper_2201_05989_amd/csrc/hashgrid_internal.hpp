@@ -21,7 +21,8 @@ struct BinPlan {
   uint32_t corner_records;               // 1: every level cut into aligned blocks of 2^chunk_log2 entries, a pair's corners have
                                          // a record each where one cannot name both (T not a power of two, or d = 1); 0: one per pair
   uint32_t count_parts, scatter_parts;   // level parts (gridDim.y) of the count and scatter grids
-  uint32_t tile_mult;                    // a tile of the sort = tile_mult * 512 points; above 1: no staging (bin_scatter_direct)
+  uint32_t tile_mult;                    // a tile of the sort = tile_mult * 512 points (of a batch: tile_mult_for); above 2: no
+                                         // staging (bin_scatter_direct)
   uint32_t supported;                    // 0: configuration not served by the binned path
 };
 
@@ -36,6 +37,8 @@ struct hashgrid {
 
 namespace hg {
 void build_bin_plan(hashgrid* h);
+// bwd_binned.hip: the plan's tile_mult for a batch of B points: 2 where 1 would leave few records to a bin
+uint32_t tile_mult_for(const hashgrid* h, uint32_t B);
 // hashgrid.hip: compute units of the current device at the first call
 uint32_t cu_count();
 // hashgrid.hip: threads (= points) per workgroup of the point-major kernels for a batch of B points

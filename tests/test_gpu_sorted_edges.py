@@ -52,3 +52,26 @@ def test_forward_in_parts_of_the_levels(d, L, F, T, param, io, B):
     check_fwd(y.cpu().numpy()[at], orc.encode_fwd(orc.OracleConfig(d, L, F, T, 8, 128), x[at], theta), 1.0, io)
     if B > 65:  # every row, against calls with another number of parts
         same_forward(y, torch.cat([grid.encode_fwd(dev(x[b:b + 4096]), dev(theta)) for b in range(0, B, 4096)]), io)
+
+
+@pytest.mark.parametrize("F,T,param,io,grad,interp", [
+    (2, 1 << 22, "f16", "f16", "f32", 0), (1, 1 << 22, "f32", "f32", "f32", 1), (4, 1 << 22, "f16", "f32", "f32", 0), (8, 1 << 21, "f16", "f16", "f16", 0)])
+@pytest.mark.parametrize("B", [(1 << 16) - 1, 1 << 16, (1 << 16) + 513, (1 << 18) + 1025])
+def test_tiles_of_twice_the_points(F, T, param, io, grad, interp, B):
+    """d = 2, levels of 1024 chunks: two points a thread of the scatter pass from 2^16 points on, counted by itself and by the forward;
+    resolutions around a chunk's width, so that some pairs straddle two."""
+    L = 8 // F if F < 8 else 2
+    grid = HashGrid(2, L, F, T, 1500, 9000, param, io, interp, grad)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.rand(B, 2, device="cuda", generator=gen).clamp_(max=1 - 2.0 ** -24)
+    theta = torch.randn(grid.n_entries, F, device="cuda", generator=gen, dtype=torch.float32).to(grid.param_dtype)
+    dy = torch.randn(B, L * F, device="cuda", generator=gen).to(grid.io_dtype)
+    want = grid.encode_bwd(x, dy, use_workspace=False).double()  # atomic additions
+    mass = grid.encode_bwd(x, dy.abs(), use_workspace=False).double()
+    # single-precision sums on either side; halves: every summand and running sum of the atomic pass is rounded (at most 64 to an entry here)
+    bar = 2e-5 * mass + 1e-6 if grad == "f32" else 65 * 2.0 ** -11 * mass + 1e-4
+    for count in (False, "always"):
+        grid.encode_fwd(x, theta, count_for_bwd=count)
+        got = torch.zeros_like(want, dtype=grid.grad_dtype)
+        grid.encode_bwd(x, dy, got, use_workspace=True, overwrite=True)
+        assert ((got.double() - want).abs() <= bar).all()
