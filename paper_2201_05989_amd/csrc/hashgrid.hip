@@ -178,10 +178,11 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
   constexpr int G = Piece::kLevels;
   static_assert(kPmBlock % (2 * kBinThreads) == 0, "a forward workgroup covers whole tiles");
   extern __shared__ uint32_t hist[];  // COUNT: [n_hist][n_bins]
-  [[maybe_unused]] uint32_t n_hist = 0, tile_threads = 0;  // tiles of the backward pass per workgroup, threads that share one
+  [[maybe_unused]] uint32_t n_hist = 0;  // tiles of the backward pass per workgroup
+  [[maybe_unused]] bool wide = false;    // they are of 1024 points
   if constexpr (COUNT) {
-    tile_threads = kBinThreads * ca.bp.tile_mult;  // (1 or 2)
-    n_hist = SB * kPmBlock / tile_threads;
+    if constexpr (D == 2) wide = ca.bp.tile_mult == 2;
+    n_hist = SB * kPmBlock / kBinThreads / (wide ? 2 : 1);
     for (uint32_t i = threadIdx.x; i < n_hist * ca.n_bins; i += kPmBlock) hist[i] = 0;
     __syncthreads();
   }
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(kPmBlock) void fwd_point_major(const LevelTable lv,
         // entry, a 1:1 level's the group of grid rows of the pair.  (COUNT implies a power-of-two T.)
         if (valid[q]) {
           const uint32_t cl = ca.bp.chunk_log2, gb0 = ca.bp.bin_base[l];
-          uint32_t* h = hist + (ca.bp.tile_mult == 2 ? q : q * (kPmBlock / kBinThreads) + threadIdx.x / kBinThreads) * ca.n_bins;
+          uint32_t* h = hist + (wide ? q : q * (kPmBlock / kBinThreads) + threadIdx.x / kBinThreads) * ca.n_bins;
           if ((lv.dense_mask >> l) & 1u) {  // uniform
             const uint32_t sh = ca.bp.row_shift[l], verts = lv.verts[l];
 #pragma unroll
