@@ -957,26 +957,8 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   __shared__ uint32_t s_ticket[2];
   extern __shared__ unsigned long long acc_lds[];  // [kBuffers][F][2^chunk_log2] fixed point: feature 0 of every entry, then
                                                    // feature 1 ..., so that consecutive entries map to consecutive banks
-  // largest |dL/dy| of the call (NaN if any is NaN) from the scatter workgroups' maxima
-  __shared__ float red[kAccThreads / 64];
-  float m = 0.0f;
-  for (uint32_t i = threadIdx.x; i < n_max; i += kAccThreads) m = nan_max(m, tile_max[i]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = nan_max(m, __shfl_xor(m, o));
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-  __syncthreads();
-  m = red[0];
-#pragma unroll
-  for (int i = 1; i < kAccThreads / 64; ++i) m = nan_max(m, red[i]);
-  if (m == 0.0f && overwrite_mask == 0) return;  // every summand is zero (uniform: all lanes hold the same m)
-  const bool finite = m < INFINITY;
+  bool finite = true;  // the call's dL/dy (known further down)
   constexpr uint32_t cl = chunk_log2_of(F), cap = 1u << cl, cmask = cap - 1u;
-  // fixed-point scale: |summand| <= m < 2^E, at most 8B summands per entry
-  int E = 0;
-  if (finite) (void)frexpf(m, &E);
-  const int H = 3 + (32 - __builtin_clz(B > 1 ? B - 1 : 1));
-  const int S = (62 - H < kFixedBits ? 62 - H : kFixedBits) - E;  // |summand| * 2^S < 2^min(62-H, 51)
-  const double inv_scale = ldexp(1.0, -S);
   const uint32_t n_records = B * lv.L * bp.rec_per_point;  // < 2^32 (hashgrid_bwd_workspace_bytes)
   constexpr int kPer = (int)cap / kAccThreads;  // entries per lane
   static_assert(kPer * kAccThreads == (int)cap, "every lane has as many entries of a chunk");
@@ -1010,10 +992,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     asm volatile("" : "+v"(at));
     return __hip_atomic_fetch_add(item_counter + at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (threadIdx.x == 0) s_ticket[1] = item_of(draw());
-  for (uint32_t i = threadIdx.x; i < kBuffers * F * cap; i += kAccThreads) acc_lds[i] = 0ull;
-  __syncthreads();
-  uint32_t next = __builtin_amdgcn_readfirstlane(s_ticket[1]);  // every item number of n_items or more ends the loop, and tickets only grow
+  // What the workgroup starts with is asked for all at once: its second item's number, its first item's records, the largest |dL/dy|
+  uint32_t ticket;
+  if (threadIdx.x == 0) ticket = draw();
 
   // An item as the workgroup needs it, all of it uniform (scalar registers)
   struct Item {
@@ -1094,12 +1075,40 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
 #pragma unroll
     for (int j = 0; j < kRing; ++j) ring[j] = Rec::load_from(first, my_byte, j * kAccThreads * (Rec::kWords * 4u));
   }
+  // largest |dL/dy| of the call (NaN if any is NaN) from the scatter workgroups' maxima
+  __shared__ float red[kAccThreads / 64];
+  float m = 0.0f;
+  for (uint32_t i = threadIdx.x; i < n_max; i += 4 * kAccThreads) {
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = tile_max[i + q * kAccThreads < n_max ? i + q * kAccThreads : n_max - 1u];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) m = nan_max(m, v[q]);
+  }
+  for (uint32_t i = threadIdx.x; i < kBuffers * F * cap; i += kAccThreads) acc_lds[i] = 0ull;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = nan_max(m, __shfl_xor(m, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  if (threadIdx.x == 0) s_ticket[1] = item_of(ticket);
+  __syncthreads();
+  uint32_t next = __builtin_amdgcn_readfirstlane(s_ticket[1]);  // every item number of n_items or more ends the loop, and tickets only grow
+  m = red[0];
+#pragma unroll
+  for (int i = 1; i < kAccThreads / 64; ++i) m = nan_max(m, red[i]);
+  m = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, m)));
+  if (m == 0.0f && overwrite_mask == 0) return;  // every summand is zero
+  finite = m < INFINITY;
+  // fixed-point scale: |summand| <= m < 2^E, at most 8B summands per entry
+  int E = 0;
+  if (finite) (void)frexpf(m, &E);
+  const int H = 3 + (32 - __builtin_clz(B > 1 ? B - 1 : 1));
+  const int S = (62 - H < kFixedBits ? 62 - H : kFixedBits) - E;  // |summand| * 2^S < 2^min(62-H, 51)
+  const double inv_scale = ldexp(1.0, -S);
   uint4 desc_n = item_at(next);
   uint32_t turn = 0;  // 0, 1, 0, ... item after item
   while (item < n_items) {
     unsigned long long* acc = acc_lds + (kBuffers == 2 ? turn * (F * cap) : 0u);
     // the item after the next one: on its way while this one is processed
-    uint32_t ticket;
     if (threadIdx.x == 0) ticket = draw();
     const Item it_n = describe(desc_n, next < n_items);
     Entry cur[kPer];
