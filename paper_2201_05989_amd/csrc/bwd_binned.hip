@@ -622,8 +622,21 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   uint32_t* local = bins_lds + nbp;
   uint32_t* cur = bins_lds + 2 * nbp + 1;
 
+  bool valid[PT];
+  float xp[PT][D];
+  const IT* row[PT];
+#pragma unroll
+  for (int p = 0; p < PT; ++p) {
+    const uint64_t b64 = ((uint64_t)tile * PT + p) * kBinThreads + threadIdx.x;
+    valid[p] = b64 < B;
+    const uint32_t b = valid[p] ? (uint32_t)b64 : 0u;
+    load_x<D>(x, b, xp[p]);
+    row[p] = dy + (uint64_t)b * lv.L * F;
+  }
+
   // records of all bins before this part
   uint32_t before = 0;
+#pragma unroll 4
   for (uint32_t i = threadIdx.x; i < gb_a; i += kBinThreads) before += bin_total[i];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o);
@@ -649,17 +662,6 @@ __global__ __launch_bounds__(kBinThreads) void bin_scatter(const LevelTable lv, 
   }
   __syncthreads();
 
-  bool valid[PT];
-  float xp[PT][D];
-  const IT* row[PT];
-#pragma unroll
-  for (int p = 0; p < PT; ++p) {
-    const uint64_t b64 = ((uint64_t)tile * PT + p) * kBinThreads + threadIdx.x;
-    valid[p] = b64 < B;
-    const uint32_t b = valid[p] ? (uint32_t)b64 : 0u;
-    load_x<D>(x, b, xp[p]);
-    row[p] = dy + (uint64_t)b * lv.L * F;
-  }
   // dL/dy comes in as 16-byte pieces, K levels each when a level is narrower than that: a narrow
   // read per level with the stride of a row would cost the L1 a line per two lanes, L times over
   constexpr uint32_t kLevelBytes = F * sizeof(IT);
