@@ -67,7 +67,7 @@ constexpr uint32_t kFewBins = 32;                 // bins of a level up to which
 // all of the pass where the items are short (table of 2^22 entries in two dimensions: 7600 items of 500 records, 103 us with one
 // queue, 91 with four or eight); with few items one queue shares them out better.
 constexpr uint32_t kQueues = 4, kQueueStride = 16, kManyItems = 1024;
-constexpr uint32_t kAccWgsPerCu = 1;             // its registers let one accumulate workgroup run per CU
+constexpr uint32_t kAccWgsPerCu = 1;             // its LDS lets one accumulate workgroup run per CU
 constexpr uint32_t kTargetRecordsPerAccWg = 16384;
 // Eight features an entry, half-precision gradients: a record is 16 additions in LDS, so 16384 records keep a compute unit busy
 // for 30 us, however little the others have to do.  Items of more than kGroupedHalfShares / 2 times a compute unit's share of the
@@ -1536,7 +1536,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   else
     scatter(std::true_type{});
   const uint32_t n_items = bp.wg_base[h->lv.L];
-  static const uint32_t acc_slots = [] {  // its registers let one 1024-thread workgroup run per CU; more would queue
+  static const uint32_t acc_slots = [] {  // its LDS lets one workgroup run per CU; more would queue
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
