@@ -1075,7 +1075,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
   {
     const auto first = window(it, it.r0);
 #pragma unroll
-    for (int j = 0; j < kRing; ++j) ring[j] = Rec::load_from(first, my_byte, j * kAccThreads * (Rec::kWords * 4u));
+    for (int j = 0; j < kRing; ++j) ring[j] = Rec::load_from(first, my_byte + j * kAccThreads * (Rec::kWords * 4u));
   }
   // largest |dL/dy| of the call (NaN if any is NaN) from the scatter workgroups' maxima
   __shared__ float red[kAccThreads / 64];
@@ -1170,7 +1170,7 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
 #pragma unroll
         for (int j = 0; j < kRing; ++j) {
           if (threadIdx.x + j * kAccThreads < left) add_record(ring[j]);
-          ring[j] = Rec::load_from(ahead, my_byte, j * kAccThreads * (Rec::kWords * 4u));
+          ring[j] = Rec::load_from(ahead, my_byte + j * kAccThreads * (Rec::kWords * 4u));
         }
         row0 += kRing * kAccThreads;
       } while (!last);

@@ -155,8 +155,9 @@ struct Record {
 #pragma unroll
     for (int f = 0; f < F; ++f) G[f] = wrow * (double)(float)pay[f];
   }
-  // a record at `offset` + `row` bytes of a buffer (row: uniform); zeros beyond its end
-  static __device__ __forceinline__ Stored load_from(__amdgpu_buffer_rsrc_t buffer, uint32_t offset, uint32_t row) {
+  // a record at `offset` bytes of a buffer; zeros beyond its end.  The whole offset is in the operand that the buffer's bound is sure
+  // to cover: the compiler's documentation leaves the load's scalar offset out of the bounds check.
+  static __device__ __forceinline__ Stored load_from(__amdgpu_buffer_rsrc_t buffer, uint32_t offset) {
     typedef uint32_t words2 __attribute__((ext_vector_type(2)));
     typedef uint32_t words3 __attribute__((ext_vector_type(3)));
     typedef uint32_t words4 __attribute__((ext_vector_type(4)));
@@ -165,14 +166,14 @@ struct Record {
     uint32_t q = 0;
 #pragma unroll
     for (; q + 4 <= kWords; q += 4) {
-      const words4 v = __builtin_amdgcn_raw_buffer_load_b128(buffer, offset + 4 * q, row, kStream);
+      const words4 v = __builtin_amdgcn_raw_buffer_load_b128(buffer, offset + 4 * q, 0, kStream);
       __builtin_memcpy(&r.w[q], &v, 16);
     }
     if constexpr (kWords % 4 == 3) {
-      const words3 v = __builtin_amdgcn_raw_buffer_load_b96(buffer, offset + 4 * q, row, kStream);
+      const words3 v = __builtin_amdgcn_raw_buffer_load_b96(buffer, offset + 4 * q, 0, kStream);
       __builtin_memcpy(&r.w[q], &v, 12);
     } else if constexpr (kWords % 4 == 2) {
-      const words2 v = __builtin_amdgcn_raw_buffer_load_b64(buffer, offset + 4 * q, row, kStream);
+      const words2 v = __builtin_amdgcn_raw_buffer_load_b64(buffer, offset + 4 * q, 0, kStream);
       __builtin_memcpy(&r.w[q], &v, 8);
     }
     return r;
