@@ -1029,10 +1029,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accumulate(const LevelTable l
     it.live = exists && (d.w & kItemLive);
     it.dense = d.w & kItemDense;
     it.shared = d.w & kItemShared;
-    // (within the records for counts that belong to these points; the bound keeps a caller who passed HG_BWD_COUNTED over
-    // the counts of another batch from reading outside them)
-    it.r0 = d.x < n_records ? d.x : n_records;
-    it.r1 = d.y < n_records ? d.y : n_records;
+    const ItemRecords recs = item_records(d.x, d.y, n_records);
+    it.r0 = recs.r0;
+    it.r1 = recs.r1;
     it.n_e = (d.w & 0xfffu) + 1u;
     it.gl = grad + (uint64_t)(d.z & 0x3fffffffu) * F;
     it.grouped = GROUPS && ((bp.group_mask >> it.l) & 1u);

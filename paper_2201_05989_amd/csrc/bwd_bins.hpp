@@ -160,6 +160,20 @@ __host__ __device__ __forceinline__ void corner_rows_of(const LevelTable& lv, co
   }
 }
 
+// The records r0 .. r1 - 1 of a work item of the accumulate pass, from the item's two words.  Within the n_records that there is room
+// for and never the wrong way round, also where a caller passed HG_BWD_COUNTED over counts that are not this batch's (of another one,
+// or scanned twice, whose sums can pass 2^32): that pass walks r1 - r0 records.
+struct ItemRecords {
+  uint32_t r0, r1;
+};
+__host__ __device__ __forceinline__ ItemRecords item_records(const uint32_t first, const uint32_t past_last, const uint32_t n_records) {
+  ItemRecords r;
+  r.r0 = first < n_records ? first : n_records;
+  r.r1 = past_last < n_records ? past_last : n_records;
+  r.r1 = r.r1 > r.r0 ? r.r1 : r.r0;
+  return r;
+}
+
 // Where the k-th record that a tile places into a bin goes inside the tile's run of n records for
 // that bin: k * s mod n for a prime s that does not divide n, a bijection of [0, n).  Points that
 // follow each other in the batch often share a voxel (samples along a ray), their records would

@@ -211,3 +211,21 @@ extern "C" uint32_t spread_check(uint32_t n_max) {
   free(seen);
   return bad;
 }
+
+// item_records over every pair of words around 0, n and 2^32: number of pairs whose records leave [0, n), run backwards, or are not
+// the item's own where those lie inside.
+extern "C" uint32_t item_records_check(uint32_t n) {
+  uint32_t words[64], count = 0, bad = 0;
+  for (uint32_t around : {0u, n / 2u, n, 2u * n, 0x80000000u, 0xffffffffu})
+    for (uint32_t step : {0u, 1u, 2u, 16384u}) {
+      words[count++] = around + step;
+      words[count++] = around - step;
+    }
+  for (uint32_t i = 0; i < count; ++i)
+    for (uint32_t j = 0; j < count; ++j) {
+      const hg::ItemRecords r = hg::item_records(words[i], words[j], n);
+      if (r.r0 > r.r1 || r.r1 > n) ++bad;
+      if (words[i] <= words[j] && words[j] <= n && (r.r0 != words[i] || r.r1 != words[j])) ++bad;
+    }
+  return bad;
+}

@@ -104,3 +104,12 @@ def test_order_of_records_inside_a_run_is_a_permutation(plan_check):
     plan_check.lib.spread_check.restype = ctypes.c_uint32
     plan_check.lib.spread_check.argtypes = [ctypes.c_uint32]
     assert plan_check.lib.spread_check(4096) == 0
+
+
+@pytest.mark.parametrize("n", [1, 4096, 8388608, 2 ** 32 - 1])
+def test_records_of_an_item_never_run_backwards(plan_check, n):
+    """Whatever two words a work item holds (counts of another batch, sums that passed 2^32), the accumulate pass walks forwards over
+    records there is room for."""
+    check = plan_check.lib.item_records_check
+    check.restype, check.argtypes = ctypes.c_uint32, [ctypes.c_uint32]
+    assert check(n) == 0
