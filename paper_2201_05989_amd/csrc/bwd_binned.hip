@@ -90,7 +90,6 @@ constexpr uint32_t kMaxCountPartBins = 4096, kMaxScatterPartBins = 4096;
 // Beyond this many chunks in all, a tile is kBigTileMult * 512 points and the scatter pass does not
 // stage (bin_scatter_direct, one LDS word per bin of its part).  One level of 4096 chunks per part: the grid runs
 // part after part, so the records in flight then belong to two levels (200 MB at T = 2^24), not four (-3%).
-constexpr uint32_t kWideTilesFrom = 1u << 16, kWideTilesBins = 1024;  // tile_mult_for
 constexpr uint32_t kMaxStagedBins = 16384, kBigTileMult = 8, kMaxDirectPartBins = 4096;
 // A level may have this many chunks (one level is the smallest part): T up to 2^24 at 4096 entries per chunk.
 constexpr uint32_t kMaxLevelBins = 4096;
@@ -111,16 +110,18 @@ struct Workspace {
 
 static inline uint64_t align_up(uint64_t v, uint64_t a) { return (v + a - 1) / a * a; }
 
-// In two dimensions a tile of 512 points has 1024 records a level, which on a level of 1024 chunks is one to a run: every store a part
-// of a line.  Tiles of 1024 points there, two points a thread, the staging area as large as in three dimensions.  Both passes, us, T =
-// 2^22, uniform points: 2^16 134 -> 125, 2^18 242 -> 229, 2^20 756 -> 685 (scatter at 2^18 67 -> 54, scan 9.6 -> 7.3); smaller
-// batches 94 both.  Levels of 512 chunks lose at some sizes what they gain at others (F = 1, T = 2^21: 100003 points 88 -> 92, 2^20 444 -> 418;
-// F = 8 on chunks of 2048, T = 2^20: 113 -> 118, 624 -> 621), of 32 chunks everywhere (T = 2^17: 100003 points 69 -> 73).
-uint32_t tile_mult_for(const hashgrid* h, uint32_t B) {
-  const BinPlan& bp = h->bp;
-  const uint32_t L = h->lv.L, widest = bp.bin_base[L] - bp.bin_base[L - 1];  // the finest level has the most entries
-  return bp.tile_mult == 1 && h->cfg.d == 2 && !bp.corner_records && widest >= kWideTilesBins && B >= kWideTilesFrom ? 2u : bp.tile_mult;
+// Chunks of the largest of `parts` level parts
+static uint32_t max_part_bins(const BinPlan& bp, uint32_t L, uint32_t parts) {
+  uint32_t m = 0;
+  for (uint32_t p = 0; p < parts; ++p) {
+    const uint32_t nbp = bp.bin_base[(p + 1) * L / parts] - bp.bin_base[p * L / parts];
+    m = nbp > m ? nbp : m;
+  }
+  return m;
 }
+
+// 32-bit words of a record (Record::kWords)
+static uint32_t record_words(const hashgrid* h) { return 2u + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u; }
 
 // one count / scatter workgroup per tile and level part
 static uint32_t tiles_for(uint32_t tile_mult, uint32_t B) {
@@ -193,8 +194,7 @@ static uint64_t carve(const hashgrid* h, uint32_t B, uint8_t* base, Workspace* w
   };
   const uint64_t o_counts = take((uint64_t)(nt + 1) * nb * 4), o_total = take((uint64_t)nb * 4),
                  o_max = take((uint64_t)nt * h->lv.L * 4), o_queues = take(kQueues * kQueueStride * 4), o_open = take((uint64_t)nb * 4),
-                 o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point *
-                              (8 + (h->cfg.F * (h->cfg.io_dtype == HG_F16 ? 2u : 4u) + 3u) / 4u * 4u)),
+                 o_rec = take((uint64_t)B * h->lv.L * h->bp.rec_per_point * record_words(h) * 4),
                  o_items = take(max_items(h, B) * sizeof(uint4));
   if (before_items) *before_items = o_items;
   if (ws) {
@@ -256,18 +256,10 @@ void build_bin_plan(hashgrid* h) {
     bins += nb;
   }
   bp.bin_base[lv.L] = bins;
-  auto max_part_bins = [&](uint32_t np) {
-    uint32_t m = 0;
-    for (uint32_t p = 0; p < np; ++p) {
-      const uint32_t nbp = bp.bin_base[(p + 1) * lv.L / np] - bp.bin_base[p * lv.L / np];
-      m = nbp > m ? nbp : m;
-    }
-    return m;
-  };
   auto parts_for = [&](uint32_t start, uint32_t limit) {
     uint32_t np = lv.L < start ? lv.L : start;
-    while (max_part_bins(np) > limit && np < lv.L) np = np * 2 < lv.L ? np * 2 : lv.L;
-    return max_part_bins(np) <= limit ? np : 0u;
+    while (max_part_bins(bp, lv.L, np) > limit && np < lv.L) np = np * 2 < lv.L ? np * 2 : lv.L;
+    return max_part_bins(bp, lv.L, np) <= limit ? np : 0u;
   };
   bp.count_parts = parts_for(kCountParts, kMaxCountPartBins);
   // With very many chunks a tile of 512 points leaves less than a record per chunk and level: the
@@ -576,6 +568,11 @@ __device__ __forceinline__ void write_items(const LevelTable& lv, const BinPlan&
 // the first voxel of every level, d = 3, N = 256, F = 2, 100003 of them, both passes 88 us, as with a record for every corner.
 __host__ __device__ constexpr uint32_t staged_records(uint32_t pairs, bool corners) {
   return pairs * kBinThreads + (corners ? pairs * kBinThreads / 8 : 0u);
+}
+
+// Dynamic LDS of a scatter workgroup: staging area, 16-bit bin of every staged record, three words per bin of its part and one more
+constexpr size_t scatter_lds(uint32_t staged, uint32_t words, uint32_t part_bins) {
+  return (size_t)staged * (words * 4 + 2) + (3 * (size_t)part_bins + 1) * 4;
 }
 
 // scatter: writes every record to its slot.  A bin's first record is the sum of
@@ -1353,21 +1350,40 @@ static uint32_t parts_for_batch(uint32_t plan_parts, uint32_t L, uint32_t n_tile
   return parts;
 }
 
+// In two dimensions a tile of 512 points has 1024 records a level, which on a level of 1024 chunks is one to a run: every store a part
+// of a line.  Tiles of 1024 points there, two points a thread, in batches of 2^16 points and more, as long as a compute unit's LDS
+// holds two scatter workgroups with them: the staging area is twice as large, and where that leaves one workgroup it costs what the longer
+// runs save, or more.  Forward and backward, uniform points, us, tiles of 512 / 1024 points, T = 2^22:
+//   two workgroups  F = 2 half 2^16 133 / 125, 2^18 242 / 228, 2^20 756 / 681; F = 1 single 116 / 107, 224 / 209, 738 / 657; F = 4
+//                   half on 8 levels 74 / 73, 138 / 134, 422 / 396, single 92 / 91, 198 / 197, 642 / 631 (200001 points 172 / 174);
+//                   F = 2 single, 2^16 points, which still take 8 parts 152 / 141
+//   one workgroup   F = 2 single 2^17 215 / 218, 2^18 310 / 320, 2^20 1015 / 1010; F = 4 half 275 / 277, 382 / 394, 1098 / 1092;
+//                   F = 8 single, T = 2^21, 2^16 157 / 168, 2^18 340 / 350, 2^20 1001 / 1011
+// Levels of 512 chunks lose at some sizes what they gain at others (F = 1, T = 2^21: 100003 points 88 / 92, 2^20 444 / 418;
+// F = 8 on chunks of 2048, T = 2^20: 113 / 118, 624 / 621), of 32 chunks everywhere (T = 2^17: 100003 points 69 / 73); smaller
+// batches take the same time (94 both).
+constexpr uint32_t kWideTilesFrom = 1u << 16, kWideTilesBins = 1024;
+constexpr size_t kLdsOfUnit = 160 * 1024;
+uint32_t tile_mult_for(const hashgrid* h, uint32_t B) {
+  const BinPlan& bp = h->bp;
+  const uint32_t L = h->lv.L, widest = bp.bin_base[L] - bp.bin_base[L - 1];  // the finest level has the most entries
+  if (bp.tile_mult != 1 || h->cfg.d != 2 || bp.corner_records || widest < kWideTilesBins || B < kWideTilesFrom) return bp.tile_mult;
+  const uint32_t parts = parts_for_batch(bp.scatter_parts, L, tiles_for(2, B));
+  const size_t lds = scatter_lds(staged_records(2 * 2, false), record_words(h), max_part_bins(bp, L, parts)) +
+                     kBinThreads / 64 * sizeof(uint32_t);  // (bin_scatter's scan_tmp)
+  return 2 * lds <= kLdsOfUnit ? 2u : 1u;
+}
+
 // The count pass by itself: counts[tile][bin] for the B points (x only).
 static hg_status launch_count(const hashgrid* h, uint32_t B, const float* x, const Workspace& ws, hipStream_t s) {
   BinPlan bp = h->bp;
   bp.tile_mult = tile_mult_for(h, B);
   const uint32_t L = h->lv.L, cparts = parts_for_batch(bp.count_parts, L, ws.n_tiles);
-  uint32_t max_bins = 0;
-  for (uint32_t p = 0; p < cparts; ++p) {
-    const uint32_t nbp = bp.bin_base[(p + 1) * L / cparts] - bp.bin_base[p * L / cparts];
-    max_bins = nbp > max_bins ? nbp : max_bins;
-  }
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const dim3 grid((ws.n_tiles + 7u) / 8u * 8u, cparts);  // see tile_of_workgroup
 #define HG_COUNT(D, C)                                                                                              \
-  hipLaunchKernelGGL((bin_count<D, C>), grid, dim3(kBinThreads), (size_t)max_bins * 4, s, h->lv, bp, smooth, B, x, \
-                     ws.counts, ws.n_bins, ws.n_tiles)
+  hipLaunchKernelGGL((bin_count<D, C>), grid, dim3(kBinThreads), (size_t)max_part_bins(bp, L, cparts) * 4, s, h->lv, bp, smooth, \
+                     B, x, ws.counts, ws.n_bins, ws.n_tiles)
   if (bp.corner_records) {
     if (h->cfg.d == 3) HG_COUNT(3, true);
     else if (h->cfg.d == 2) HG_COUNT(2, true);
@@ -1419,25 +1435,13 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const uint32_t n_records = B * h->lv.L * bp.rec_per_point;
   const uint32_t L = h->lv.L, parts = parts_for_batch(bp.scatter_parts, L, ws.n_tiles);
-  auto max_part_bins = [&](uint32_t np) {
-    uint32_t m = 0;
-    for (uint32_t p = 0; p < np; ++p) {
-      const uint32_t nbp = bp.bin_base[(p + 1) * L / np] - bp.bin_base[p * L / np];
-      m = nbp > m ? nbp : m;
-    }
-    return m;
-  };
-  // scatter: staging area, 16-bit bin of every staged record, three words per bin of the part
-  constexpr size_t kRecordBytes = Rec::kWords * 4 + 2;
-  constexpr size_t kStagingBytes = (size_t)staged_records(R, CORNERS) * kRecordBytes;
   constexpr bool kWide = D == 2 && !CORNERS;  // (BinPlan::tile_mult of 2)
-  constexpr size_t kWideBytes = (size_t)staged_records(2 * R, CORNERS) * kRecordBytes;
-  constexpr size_t kWideLdsMax = kWideBytes + (3 * (size_t)kMaxScatterPartBins + 1) * 4;
-  constexpr size_t kScatterLdsMax = kStagingBytes + (3 * (size_t)kMaxScatterPartBins + 1) * 4;
+  constexpr size_t kScatterLdsMax = scatter_lds(staged_records(R, CORNERS), Rec::kWords, kMaxScatterPartBins);
+  constexpr size_t kWideLdsMax = scatter_lds(staged_records(2 * R, CORNERS), Rec::kWords, kMaxScatterPartBins);
   // The largest (146 KB: d = 3, F = 8, single precision, any table size) leaves one workgroup on a compute unit.  Unstaged such plans
   // are 3 to 12 % faster on points in no order and up to 1.8 times slower on rays (30000 points, T = 524287, both passes: 98
   // against 93 us, 108 against 196).
-  static_assert(kScatterLdsMax <= 160 * 1024 && (!kWide || kWideLdsMax <= 160 * 1024), "a workgroup's LDS");
+  static_assert(kScatterLdsMax <= kLdsOfUnit && (!kWide || kWideLdsMax <= kLdsOfUnit), "a workgroup's LDS");
   constexpr size_t kAccLds = (size_t)acc_buffers(F) * F * 8 << chunk_log2_of(F);
   constexpr bool kAdam = !CORNERS && std::is_same<IT, _Float16>::value;  // what launch_binned_adam serves
   // more dynamic LDS than the default limit of 64 KiB: opt in once per kernel
@@ -1488,7 +1492,8 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     return e;
   }();
   if (lds_ok != hipSuccess) return HG_ERR_DEVICE;
-  const size_t lds_scatter = (bp.tile_mult == 2 ? kWideBytes : kStagingBytes) + (3 * (size_t)max_part_bins(parts) + 1) * 4;
+  const uint32_t part_bins = max_part_bins(bp, L, parts);
+  const size_t lds_scatter = scatter_lds(staged_records(bp.tile_mult == 2 ? 2 * R : R, CORNERS), Rec::kWords, part_bins);
   const uint32_t tile_wgs = (ws.n_tiles + 7u) / 8u * 8u;  // see tile_of_workgroup
   if (!counted && launch_count(h, B, x, ws, s) != HG_OK) return HG_ERR_DEVICE;
   // HG_BWD_OVERWRITE: the owner of a chunk stores its sums, except on levels whose chunks are summed
@@ -1511,7 +1516,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
     constexpr int DS = kCross ? DP : D;  // (the straddling pairs exist with pair records only)
     if (bp.tile_mult > 2) {
       hipLaunchKernelGGL((bin_scatter_direct<DS, IT, F, kCross, CORNERS && !kCross>), dim3(tile_wgs, parts),
-                         dim3(kBinThreads), (size_t)max_part_bins(parts) * 4, s, h->lv, bp, smooth, B, x,
+                         dim3(kBinThreads), (size_t)part_bins * 4, s, h->lv, bp, smooth, B, x,
                          static_cast<const IT*>(dy), ws.counts, ws.bin_total, ws.items, ws.chunk_open, ws.records, ws.n_bins,
                          n_records, ws.n_tiles, ws.tile_max, grad, g16);
     } else {

@@ -229,3 +229,12 @@ extern "C" uint32_t item_records_check(uint32_t n) {
     }
   return bad;
 }
+
+// Points of a tile of the sort / 512 for a batch of B points (0: the configuration cannot be created or is not served)
+extern "C" uint32_t tile_mult_of(const hashgrid_config* cfg, uint32_t B) {
+  hashgrid_t* h = nullptr;
+  if (hashgrid_create(cfg, &h) != HG_OK) return 0;
+  const uint32_t mult = h->bp.supported ? hg::tile_mult_for(h, B) : 0;
+  hashgrid_destroy(h);
+  return mult;
+}
