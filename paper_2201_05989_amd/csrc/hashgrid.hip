@@ -666,17 +666,37 @@ static hg_status launched() { return hipGetLastError() == hipSuccess ? HG_OK : H
 // Two points per thread once the batch needs two or more rounds of full workgroups per CU
 static bool fwd_two_points_per_thread(uint32_t B) { return (uint64_t)B >= 2ull * kPmBlock * cu_count(); }
 
-// Levels of a part of the plain forward's grid.  A thread walks its levels one after the other, a gather's latency each, and a batch
+// Parts of the levels in the plain forward's grid.  A thread walks its levels one after the other, a gather's latency each, and a batch
 // that leaves compute units with few waves waits for little else: such a batch is cut into parts of whole pieces of 16 bytes,
 // 4 parts up to a wave for every compute unit, then 2 as long as two slices of the tables at a time cost the caches less than
-// the shorter chains save.  d = 3, L = 16, F = 2, T = 2^19, uniform / rays, us with 1, 2 and 4 parts (5.4 us of it the caller's): 2^12 points
-// 12.6 8.0 6.7 / 10.9 6.8 5.6, 2^14 points 17.1 14.9 14.4 / 13.6 10.8 10.4, 2^16 points 36.3 33.3 35.8 / 27.4 24.9 27.5, 2^17 points
-// 54.8 53.6 55.8 / 41.3 40.9 43.0, 200001 points 74.9 79.6 / 56.4 57.7.  Entries of 8 bytes, T = 1000003: 2^16 points 55.1 54.6, 100003
-// points 74.0 77.2; of 16 bytes, T = 2^17: 30011 points 15.2 13.9, 2^16 points 22.3 24.1.
-static uint32_t levels_per_part(uint32_t L, uint32_t G, uint32_t block, uint32_t entry_bytes) {
-  const uint32_t most = entry_bytes <= 4 ? 512 : entry_bytes <= 8 ? 256 : 192;
-  const uint32_t parts = block <= 64 ? 4 : block <= most ? 2 : 1, pieces = L / G;
-  return (pieces + parts - 1) / parts * G;
+// the shorter chains save.  That line lies lower the wider the entries are, and lower in three dimensions, whose points gather twice as
+// many of them.  us with 1 / 2 parts (5.4 of it the caller's), uniform points unless it says rays:
+//   d = 3, F = 2 half, T = 2^19   2^14 points 17.1 / 14.9 (4 parts 14.4), 2^16 36.3 / 33.3, 2^17 54.8 / 53.6, 200001 74.9 / 79.6
+//   4 bytes and less, d = 3       up to 2^16 points 0.66 to 1.0 of the time; 100003 points, F = 1 half: T = 2^19 41.3 / 38.0, 2^21 57.2 / 59.2,
+//                                 2^22 67.0 / 69.9, 2^24 86.3 / 83.5 (an L2 of 4 MB still serves much of one slice there and not of two);
+//                                 d = 2, T = 2^22 31.2 / 28.4
+//   8 bytes                       2^16 points 0.76 to 1.0 of the time, 2^17 about equal
+//   16 bytes, d = 3, T = 2^20     F = 4 single: 20011 points 29.6 / 31.8, 30011 38.0 / 37.6, 34000 1.16 of the time, rays 0.95, 0.93 and
+//                                 1.06; F = 8 half, T = 2^22, 34000 points 1.10.  (20011 points are 157 workgroups, which two parts
+//                                 double on some compute units only; from three quarters of them on two parts gain.)  d = 2: 0.71 to 0.98
+//   32 bytes                      d = 3, T = 2^19, 2^14 points 18.4 / 17.5 (4 parts 20.6), 8192 14.3 / 10.4 (10.4), F = 8 to half-precision
+//                                 outputs, 20011 points 39.3 / 41.6; d = 2, T = 2^20, 30011 points 23.4 / 19.9, 34000 1.03 of the time
+uint32_t level_parts(uint32_t d, uint32_t T, uint32_t entry_bytes, uint32_t B) {
+  const uint32_t block = point_major_block(B), wgs = (B + block - 1) / block, cus = cu_count();
+  if (block <= 64) return d == 3 && entry_bytes > 16 && 2 * wgs > cus ? 2 : 4;
+  uint32_t most;  // threads of a workgroup
+  if (entry_bytes <= 4) {
+    const uint64_t slice = (uint64_t)T * entry_bytes;
+    most = d == 3 && slice > (2u << 20) && slice <= (8u << 20) ? 256 : 512;
+  } else if (entry_bytes <= 8) {
+    most = 256;
+  } else if (entry_bytes <= 16) {
+    most = d == 3 ? 128 : 192;
+    if (d == 3 && 4 * wgs < 3 * cus) return 1;
+  } else {
+    most = d == 1 ? 192 : d == 2 ? 128 : 64;
+  }
+  return block <= most ? 2 : 1;
 }
 
 template <int D, int F, typename PT, typename IT>
@@ -687,7 +707,8 @@ static hg_status launch_fwd(const hashgrid* h, uint32_t B, const float* x, const
     if (h->lv.L % G == 0 && !misaligned(y, 16) && !misaligned(params, F * sizeof(PT) > 16 ? 16 : F * sizeof(PT))) {
       const uint32_t block = point_major_block(B);
       const uint32_t wgs = (B + block - 1) / block;
-      const LevelParts parts{levels_per_part(h->lv.L, G, block, F * (uint32_t)sizeof(PT))};
+      const uint32_t n_parts = level_parts(D, h->lv.T, F * (uint32_t)sizeof(PT), B), pieces = h->lv.L / G;
+      const LevelParts parts{(pieces + n_parts - 1) / n_parts * G};
       const dim3 grid(wgs, (h->lv.L + parts.levels - 1) / parts.levels);
       const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
       if (h->lv.T_is_pow2 && fwd_two_points_per_thread(B))

@@ -43,6 +43,8 @@ uint32_t tile_mult_for(const hashgrid* h, uint32_t B);
 uint32_t cu_count();
 // hashgrid.hip: threads (= points) per workgroup of the point-major kernels for a batch of B points
 uint32_t point_major_block(uint32_t B);
+// hashgrid.hip: parts of the levels that the plain forward's workgroups of a batch of B points are split over
+uint32_t level_parts(uint32_t d, uint32_t T, uint32_t entry_bytes, uint32_t B);
 // hashgrid.hip: forward pass that also fills counts[n_tiles][n_bins] of the binned backward pass
 hg_status launch_fwd_counting(const hashgrid* h, uint32_t B, const float* x, const void* params, void* y,
                               uint32_t* counts, uint32_t n_bins, uint32_t n_tiles, hipStream_t s);

@@ -238,3 +238,6 @@ extern "C" uint32_t tile_mult_of(const hashgrid_config* cfg, uint32_t B) {
   hashgrid_destroy(h);
   return mult;
 }
+
+// Parts of the levels in the plain forward's grid
+extern "C" uint32_t level_parts_of(uint32_t d, uint32_t T, uint32_t entry_bytes, uint32_t B) { return hg::level_parts(d, T, entry_bytes, B); }

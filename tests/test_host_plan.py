@@ -129,3 +129,17 @@ def test_wide_tiles_where_two_scatter_workgroups_fit_a_compute_unit(plan_check, 
     mult_of.restype, mult_of.argtypes = ctypes.c_uint32, [ctypes.POINTER(binding.hashgrid_config), ctypes.c_uint32]
     for B in ((1 << 16) - 1, 1 << 16, 1 << 17, 1 << 20):
         assert mult_of(ctypes.byref(cfg), B) == (8 if wide is None else 2 if B in wide else 1), B
+
+
+@pytest.mark.parametrize("d,T,entry_bytes,parts", [
+    (3, 1 << 19, 4, {1: 4, 1 << 14: 4, (1 << 14) + 1: 2, 1 << 17: 2, (1 << 17) + 1: 1}),
+    (3, 1 << 20, 4, {1 << 14: 4, 1 << 16: 2, (1 << 16) + 1: 1}), (3, 1 << 22, 2, {1 << 16: 2, 100003: 1}), (3, 1 << 24, 2, {100003: 2}),
+    (2, 1 << 22, 2, {100003: 2}), (3, 1 << 19, 8, {1 << 16: 2, (1 << 16) + 1: 1}),
+    (3, 1 << 20, 16, {1 << 14: 4, 20011: 1, 24577: 2, 1 << 15: 2, 34000: 1}), (2, 1 << 20, 16, {20011: 2, 49152: 2, 49153: 1}),
+    (3, 1 << 19, 32, {8192: 4, 8193: 2, 1 << 14: 2, 20011: 1}), (2, 1 << 19, 32, {1 << 14: 4, 1 << 15: 2, 34000: 1}),
+    (1, 1 << 19, 32, {34000: 2, 49153: 1})])
+def test_parts_of_the_levels_in_the_plain_forward(plan_check, d, T, entry_bytes, parts):
+    """Two or four parts only up to the batch at which they stop to pay, by what an entry weighs, d and the table's size."""
+    of = plan_check.lib.level_parts_of
+    of.restype, of.argtypes = ctypes.c_uint32, [ctypes.c_uint32] * 4
+    assert {B: of(d, T, entry_bytes, B) for B in parts} == parts
