@@ -79,14 +79,17 @@ def test_tiles_of_twice_the_points(L, F, T, param, io, grad, interp, B):
     assert n.sum() >= B // 2
     n, want, mass = dev(n), dev(orc.encode_bwd(cfg, x, dy)), dev(orc.encode_bwd(cfg, x, np.abs(dy.astype(np.float64))))
     xd, gd = dev(x), dev(dy)
-    theta = torch.randn(grid.n_entries, F, device="cuda").to(grid.param_dtype)
-    # a rounding where the owner stores, one for every atomic (of a running sum, which the summands' mass bounds)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    theta = torch.randn(grid.n_entries, F, device="cuda", generator=gen).to(grid.param_dtype)
+    # A rounding where the owner stores, one of the running sum for every atomic (what was there and the summands' mass bound it); an
+    # atomic's half-precision summand is itself rounded, at most u times the mass over all of them and the smallest half for each.
     u, sub = (1.001 * 2.0 ** -11, 2.0 ** -25) if grad == "f16" else (1.001 * 2.0 ** -24, 0.0)
-    some = torch.randint(-2, 3, (grid.n_entries, F), device="cuda").to(grid.grad_dtype)
+    summands = (n > 0) * u * mass if grad == "f16" else 0.0
+    some = torch.randint(-2, 3, (grid.n_entries, F), device="cuda", generator=gen).to(grid.grad_dtype)
     for count in (False, "always"):
         for overwrite, before in ((True, torch.full_like(some, 7.0)), (False, torch.zeros_like(some)), (False, some)):
             base = torch.zeros_like(want) if overwrite else before.double()
-            bar = 1e-5 * mass + ws_floor(dy, B) + u * (base + want).abs() + sub + n * (u * (base.abs() + mass) + sub)
+            bar = 1e-5 * mass + ws_floor(dy, B) + u * (base + want).abs() + sub + summands + n * (u * (base.abs() + mass) + sub)
             grid.encode_fwd(xd, theta, count_for_bwd=count)
             got = before.clone()
             grid.encode_bwd(xd, gd, got, use_workspace=True, overwrite=overwrite)
