@@ -133,7 +133,8 @@ hg_status hashgrid_encode_bwd(const hashgrid_t* hg, uint32_t B, const float* x, 
  * sizeof(dLdy scalar) bytes (rounded up to 4) per pair of corners along dimension 0,
  * B*L*2^(d-1) of them, with room for one per corner, B*L*2^d of them, where the upper corner does
  * not follow from the lower one (T not a power of two: Eq. 4's mod T; d = 1), plus 4 bytes per (tile of
- * 512 points, chunk), tiles of 4096 points where there are more than 16384 chunks in all:
+ * 512 points, chunk), tiles of 4096 points where there are more than 16384 chunks in all
+ * (two-dimensional batches that are sorted in tiles of 1024 points use half of that part):
  * 195 MiB at Table 1's sizes with 2^18 points, 1.6 GiB at T = 2^24 with 2^21. */
 uint64_t hashgrid_bwd_workspace_bytes(const hashgrid_t* hg, uint32_t B);
 
@@ -200,8 +201,8 @@ hg_status hashgrid_encode_bwd_static(const hashgrid_t* hg, uint32_t B, const flo
  * workgroup, a T that is no power of two, d = 1) the call runs hashgrid_encode_fwd and
  * the counting pass one after the other, with the same result.
  * (Both passes, d = 3, L = 16, T = 2^19, half-precision outputs, with hashgrid_encode_fwd and no flag against this call: F = 2,
- * 2^18 points in random order 232 and 220 us, in ray order 222 and 212; 2^20 points 911 and 900, 819 and 814.  With
- * fp32 tables and 2^19 points or more the former is the faster pair, 977 against 993.)
+ * 2^18 points in random order 221 and 209 us, in ray order 208 and 196; 2^20 points 836 and 822, 763 and 756.  With
+ * fp32 tables and 2^19 points or more the former is the faster pair, 904 against 916.)
  * Returns HG_ERR_UNSUPPORTED when hashgrid_bwd_workspace_bytes is 0, when y or params are not
  * 16-byte / entry aligned, or when the configuration has more than 16384 chunks in all (callers
  * then use hashgrid_encode_fwd and pass no flag); HG_ERR_INVALID_ARG as hashgrid_encode_bwd_ws. */

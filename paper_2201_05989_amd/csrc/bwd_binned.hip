@@ -36,7 +36,8 @@
 //              two above that largest value (H = ceil(log2(8B))).
 //
 // Variants of the same plan: the forward pass can do the counting (hashgrid.hip,
-// HG_BWD_COUNTED); plans with more than kMaxStagedBins chunks use tiles of
+// HG_BWD_COUNTED); in two dimensions large levels are sorted in tiles of 1024 points
+// (tile_mult_for); plans with more than kMaxStagedBins chunks use tiles of
 // kBigTileMult * 512 points and write their records unstaged (bin_scatter_direct);
 // pairs whose corners lie in two chunks (hashed levels of resolution 2^chunk_log2
 // or more) bypass the sort and are added with device atomics; with
@@ -577,7 +578,7 @@ constexpr size_t scatter_lds(uint32_t staged, uint32_t words, uint32_t part_bins
 
 // scatter: writes every record to its slot.  A bin's first record is the sum of
 // the record counts of all bins before it (so the records are level-major); inside a bin the
-// tiles of 512 points follow each other.  Level by level the workgroup sorts the
+// tiles of 512 or 1024 points (tile_mult_for) follow each other.  Level by level the workgroup sorts the
 // records of its points by bin in LDS and copies them out bin after bin, so that
 // what reaches memory is runs of whole records that mostly fill whole cache
 // lines; 16-byte stores scattered over a thousand open runs leave the L2 as
@@ -1435,7 +1436,8 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const uint32_t n_records = B * h->lv.L * bp.rec_per_point;
   const uint32_t L = h->lv.L, parts = parts_for_batch(bp.scatter_parts, L, ws.n_tiles);
-  constexpr bool kWide = D == 2 && !CORNERS;  // (BinPlan::tile_mult of 2)
+  // (a BinPlan::tile_mult of 2; tile_mult_for gives none for records so large that two workgroups never fit)
+  constexpr bool kWide = D == 2 && !CORNERS && 2 * scatter_lds(staged_records(2 * R, CORNERS), Rec::kWords, kWideTilesBins) <= kLdsOfUnit;
   constexpr size_t kScatterLdsMax = scatter_lds(staged_records(R, CORNERS), Rec::kWords, kMaxScatterPartBins);
   constexpr size_t kWideLdsMax = scatter_lds(staged_records(2 * R, CORNERS), Rec::kWords, kMaxScatterPartBins);
   // The largest (146 KB: d = 3, F = 8, single precision, any table size) leaves one workgroup on a compute unit.  Unstaged such plans
@@ -1654,12 +1656,15 @@ int hashgrid_bwd_ws_pays(const hashgrid_t* hg, uint32_t B) {
   // Both passes in microseconds, from measurements on an MI355X.  Sorted pass: about 16 us of
   // launches, 0.017 us per chunk (every chunk of the gradient is visited and rewritten), then the
   // records, written once and read once: ~300 K records of 12 bytes per us, in proportion for
-  // larger ones (wider entries, fp32 dL/dy).  (Any table size: priced at a record a pair.  Measured, both passes alone, T = 1000003,
-  // F = 2: d = 3, fp32, 12288 points 66 us sorted and 55 atomic, 24576 70 and 102; d = 2 48 and 40, 50 and 76; the line lies between.)
+  // larger ones (wider entries, fp32 dL/dy).  (Any table size: priced at a record a pair.)
   // Atomic pass: ~6 us, then ~14.5 K pairs of corners per us (11 K at F = 4, 9 K at F = 8: their
   // requests are fatter), unless one 64-byte block of the gradient draws so many requests that
   // they queue up behind each other (~0.02 us each): the smallest level decides that, taking the
   // points as spread evenly over its entries.
+  // Measured, sorted / atomic, d = 3, at the last size that takes the atomic pass and the first that takes the sorted one here: F = 2,
+  // T = 2^19 8192 points 40 / 40, 11000 43 / 53; T = 1000003, single precision, 12288 59 / 54, 16384 60 / 69; F = 4, T = 2^17 2048 32 / 20,
+  // 4096 35 / 24 (8192 41 / 41).  The price knows nothing of the longest work item, so that wide entries, whose items are 2 F additions in
+  // LDS a record, change over too early: F = 8 half, T = 2^17, 8 levels 6000 points 35 / 22, 12288 43 / 34, 24576 51 / 59.
   const uint32_t F = hg->cfg.F, d = hg->cfg.d;
   const double pairs = (double)B * hg->lv.L * (1u << (d - 1));
   const double records = (double)B * hg->lv.L * hg::pairs_per_point(hg->bp);
@@ -1779,7 +1784,7 @@ hg_status hashgrid_encode_bwd_static(const hashgrid_t* hg, uint32_t B, const flo
   void* ws = hg::static_scratch_of_current_device();
   if (!ws) return HG_ERR_DEVICE;
   // every word of the scratch that a kernel reads is written earlier in the same call (counts by
-  // bin_count, totals and the work counter by bin_scan, offsets, records and maxima by bin_scatter),
+  // bin_count, totals and the queues' counters by bin_scan, items, records and maxima by bin_scatter),
   // so what the previous call left behind needs no clearing
   return hashgrid_encode_bwd_ws(hg, B, x, dLdy, grad_params, ws, kStaticBytes, flags, stream);
 }

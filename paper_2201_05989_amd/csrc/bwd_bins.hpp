@@ -9,7 +9,7 @@
 
 namespace hg {
 
-constexpr int kBinThreads = 512;      // points of a tile = threads of a count / scatter workgroup (256 and 1024 are slower)
+constexpr int kBinThreads = 512;      // threads of a count / scatter workgroup, and points of a tile but for tile_mult_for (256 and 1024 are slower)
 constexpr uint32_t kChunkLog2 = 12;  // log2 of the entries a chunk can hold, at most
 // The accumulators of a chunk (F 64-bit words per entry) must fit the LDS of a workgroup: 128 KiB at F = 4 and 8.
 __host__ __device__ constexpr uint32_t chunk_log2_of(uint32_t F) { return F <= 4 ? kChunkLog2 : kChunkLog2 - 1; }

@@ -154,7 +154,7 @@ struct OutPiece {
 
 // With COUNT the kernel also fills, for the binned backward pass over the same points, the
 // table that pass would otherwise count in a kernel of its own: counts[tile][bin] = pairs of
-// corners of the tile's kBinThreads points that fall into the bin (bwd_binned.hip).  The
+// corners of the tile's 512 or 1024 points (tile_mult_for) that fall into the bin (bwd_binned.hip).  The
 // gathers leave the vector ALU and the LDS idle, so the counting rides along.
 struct CountArgs {
   BinPlan bp;
