@@ -1352,23 +1352,27 @@ static uint32_t parts_for_batch(uint32_t plan_parts, uint32_t L, uint32_t n_tile
 }
 
 // In two dimensions a tile of 512 points has 1024 records a level, which on a level of 1024 chunks is one to a run: every store a part
-// of a line.  Tiles of 1024 points there, two points a thread, in batches of 2^16 points and more, as long as a compute unit's LDS
-// holds two scatter workgroups with them: the staging area is twice as large, and where that leaves one workgroup it costs what the longer
-// runs save, or more.  Forward and backward, uniform points, us, tiles of 512 / 1024 points, T = 2^22:
-//   two workgroups  F = 2 half 2^16 133 / 125, 2^18 242 / 228, 2^20 756 / 681; F = 1 single 116 / 107, 224 / 209, 738 / 657; F = 4
-//                   half on 8 levels 74 / 73, 138 / 134, 422 / 396, single 92 / 91, 198 / 197, 642 / 631 (200001 points 172 / 174);
-//                   F = 2 single, 2^16 points, which still take 8 parts 152 / 141
+// of a line.  Tiles of 1024 points there, two points a thread, in batches of 2^16 points and more, for records of up to 16 bytes and as
+// long as a compute unit's LDS holds two scatter workgroups with them: the staging area is twice as large, and where that leaves one
+// workgroup it costs what the longer runs save, or more.  Forward and backward, uniform points, us, tiles of 512 / 1024 points, T = 2^22:
+//   two workgroups  F = 2 half 2^16 133 / 125, 100003 162 / 155, 2^18 242 / 228, 2^20 756 / 681; F = 1 single 116 / 107, 140 / 130,
+//                   224 / 209, 738 / 657; F = 4 half on 8 levels 74 / 73, 93 / 91, 138 / 134, 422 / 396; F = 2 single in the batches that still
+//                   take 8 parts 2^16 152 / 141, 100003 195 / 187
 //   one workgroup   F = 2 single 2^17 215 / 218, 2^18 310 / 320, 2^20 1015 / 1010; F = 4 half 275 / 277, 382 / 394, 1098 / 1092;
 //                   F = 8 single, T = 2^21, 2^16 157 / 168, 2^18 340 / 350, 2^20 1001 / 1011
+//   24 bytes, two   F = 4 single on 8 levels 2^16 92 / 91, 80001 97 / 101, 2^17 133 / 127, 200001 172 / 174, 2^18 198 / 197, 2^20 642 / 631;
+//   workgroups      F = 8 half, T = 2^21, 80001 117 / 120, 2^17 140 / 133, 2^18 203 / 201 (three fit with tiles of 512: left at those)
 // Levels of 512 chunks lose at some sizes what they gain at others (F = 1, T = 2^21: 100003 points 88 / 92, 2^20 444 / 418;
 // F = 8 on chunks of 2048, T = 2^20: 113 / 118, 624 / 621), of 32 chunks everywhere (T = 2^17: 100003 points 69 / 73); smaller
 // batches take the same time (94 both).
-constexpr uint32_t kWideTilesFrom = 1u << 16, kWideTilesBins = 1024;
+constexpr uint32_t kWideTilesFrom = 1u << 16, kWideTilesBins = 1024, kWideTilesWords = 4;
 constexpr size_t kLdsOfUnit = 160 * 1024;
 uint32_t tile_mult_for(const hashgrid* h, uint32_t B) {
   const BinPlan& bp = h->bp;
   const uint32_t L = h->lv.L, widest = bp.bin_base[L] - bp.bin_base[L - 1];  // the finest level has the most entries
-  if (bp.tile_mult != 1 || h->cfg.d != 2 || bp.corner_records || widest < kWideTilesBins || B < kWideTilesFrom) return bp.tile_mult;
+  if (bp.tile_mult != 1 || h->cfg.d != 2 || bp.corner_records || widest < kWideTilesBins || B < kWideTilesFrom ||
+      record_words(h) > kWideTilesWords)
+    return bp.tile_mult;
   const uint32_t parts = parts_for_batch(bp.scatter_parts, L, tiles_for(2, B));
   const size_t lds = scatter_lds(staged_records(2 * 2, false), record_words(h), max_part_bins(bp, L, parts)) +
                      kBinThreads / 64 * sizeof(uint32_t);  // (bin_scatter's scan_tmp)
@@ -1436,8 +1440,7 @@ static hg_status launch_binned(const hashgrid* h, uint32_t B, const float* x, co
   const bool smooth = h->cfg.interp == HG_INTERP_SMOOTHSTEP;
   const uint32_t n_records = B * h->lv.L * bp.rec_per_point;
   const uint32_t L = h->lv.L, parts = parts_for_batch(bp.scatter_parts, L, ws.n_tiles);
-  // (a BinPlan::tile_mult of 2; tile_mult_for gives none for records so large that two workgroups never fit)
-  constexpr bool kWide = D == 2 && !CORNERS && 2 * scatter_lds(staged_records(2 * R, CORNERS), Rec::kWords, kWideTilesBins) <= kLdsOfUnit;
+  constexpr bool kWide = D == 2 && !CORNERS && Rec::kWords <= kWideTilesWords;  // (what tile_mult_for may give a tile_mult of 2)
   constexpr size_t kScatterLdsMax = scatter_lds(staged_records(R, CORNERS), Rec::kWords, kMaxScatterPartBins);
   constexpr size_t kWideLdsMax = scatter_lds(staged_records(2 * R, CORNERS), Rec::kWords, kMaxScatterPartBins);
   // The largest (146 KB: d = 3, F = 8, single precision, any table size) leaves one workgroup on a compute unit.  Unstaged such plans

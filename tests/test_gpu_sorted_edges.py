@@ -56,11 +56,11 @@ def test_forward_in_parts_of_the_levels(d, L, F, T, param, io, B):
 
 @pytest.mark.parametrize("L,F,T,param,io,grad,interp", [
     (4, 2, 1 << 22, "f16", "f16", "f32", 0), (4, 2, 1 << 22, "f32", "f32", "f32", 1), (8, 1, 1 << 22, "f32", "f32", "f32", 1),
-    (2, 4, 1 << 22, "f16", "f32", "f32", 0), (2, 4, 1 << 22, "f16", "f16", "f16", 1), (2, 8, 1 << 21, "f16", "f16", "f16", 0)])
+    (2, 4, 1 << 22, "f16", "f16", "f32", 0), (2, 4, 1 << 22, "f16", "f16", "f16", 1), (2, 8, 1 << 21, "f16", "f16", "f16", 0)])
 @pytest.mark.parametrize("B", [1 << 16, (1 << 16) + 513, (1 << 18) + 1025])
 def test_tiles_of_twice_the_points(L, F, T, param, io, grad, interp, B):
-    """d = 2, levels of 1024 chunks, 2^16 points and more: two points a thread of the scatter pass, counted by itself and by the forward,
-    replacing a gradient and adding to one.  One point in eight lies where its pair straddles two chunks of the finest level: those
+    """d = 2, levels of 1024 chunks, 2^16 points and more: two points a thread of the scatter pass (one for the records of eight
+    features), counted by itself and by the forward, replacing a gradient and adding to one.  One point in eight lies where its pair straddles two chunks of the finest level: those
     pairs are added by the scatter pass, or after the owners have stored."""
     cfg = orc.OracleConfig(2, L, F, T, 1500, 9000, interp)
     grid, lv = HashGrid(2, L, F, T, 1500, 9000, param, io, interp, grad), orc.levels(cfg)

@@ -92,7 +92,7 @@ def test_equals_the_single_calls_where_nothing_rounds(d, L, F, T, N_min, N_max, 
 
 @pytest.mark.parametrize("d,L,F,T,N_max,interp,B", [(3, 16, 2, 1 << 19, 2048, 0, 5000), (3, 16, 2, 1 << 17, 2048, 1, 60001),
                                                     (2, 16, 2, 1 << 20, 32768, 0, 150001), (3, 8, 4, 1 << 15, 512, 0, 50000),
-                                                    # levels of 1024 chunks: two points a thread of the scatter pass
+                                                    # levels of 1024 chunks: two points a thread of the scatter pass for records of up to 16 bytes
                                                     (2, 4, 2, 1 << 22, 32768, 0, 150001), (2, 2, 8, 1 << 21, 8192, 1, 150001)])
 def test_first_moments_are_the_gradient(d, L, F, T, N_max, interp, B):
     m = HashGridModel(d, 2, L=L, F=F, T=T, N_min=16, N_max=N_max, seed=3, interp=interp)

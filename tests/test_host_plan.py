@@ -118,11 +118,11 @@ def test_records_of_an_item_never_run_backwards(plan_check, n):
 @pytest.mark.parametrize("L,F,T,N_max,io,wide", [
     (16, 2, 1 << 22, 32768, "f16", (1 << 16, 1 << 17, 1 << 20)), (16, 1, 1 << 22, 32768, "f32", (1 << 16, 1 << 17, 1 << 20)),
     (8, 4, 1 << 22, 4096, "f16", (1 << 16, 1 << 17, 1 << 20)), (16, 2, 1 << 22, 32768, "f32", (1 << 16,)),
-    (16, 4, 1 << 22, 32768, "f16", (1 << 16,)), (8, 8, 1 << 22, 8192, "f16", (1 << 16,)), (8, 8, 1 << 21, 4096, "f32", ()),
+    (16, 4, 1 << 22, 32768, "f16", (1 << 16,)), (8, 4, 1 << 22, 4096, "f32", ()), (8, 8, 1 << 22, 8192, "f16", ()), (8, 8, 1 << 21, 4096, "f32", ()),
     (16, 2, 1 << 21, 32768, "f16", ()), (16, 2, 1 << 24, 1 << 17, "f16", None), (16, 2, 4000003, 32768, "f16", ())])
 def test_wide_tiles_where_two_scatter_workgroups_fit_a_compute_unit(plan_check, L, F, T, N_max, io, wide):
-    """1024 points a tile of the sort where that leaves two workgroups: 2048 records of 8 + F * size bytes and 2 more, three words for each of
-    up to 4096 chunks of a part (2048 where a batch of 2^16 points doubles the parts)."""
+    """1024 points a tile of the sort for records of up to 16 bytes where that leaves two workgroups: 2048 records of 8 + F * size bytes
+    and 2 more, three words for each of up to 4096 chunks of a part (2048 where a batch of 2^16 points doubles the parts)."""
     io = {"f16": binding.HG_F16, "f32": binding.HG_F32}[io]
     cfg = binding.hashgrid_config(2, L, F, T, 16, N_max, io, io, 0, binding.HG_F32)
     mult_of = plan_check.lib.tile_mult_of
